@@ -30,16 +30,16 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, public spec
 
 # algorithmic bytes per grid point of one launch of each PCG-loop kernel (FP64):
 #   row_flux : reads grad_x, grad_y (2 x 8), m (16), r (8); writes F_x, F_y (2 x 8)
-#   col_div  : reads F_x, F_y (16), d, r (16); writes q (8)
-#   col_update: reads x, d, r, q (32); writes x, r, d (24) and grad_x, grad_y (16)
-KERNEL_BYTES_PER_POINT = {"row_flux": 56.0, "col_div": 40.0, "col_update": 72.0}
-KERNEL_IDS = {"row_flux": 0, "col_div": 1, "col_update": 2}
+#   col_update: reads F_x, F_y (16), x, r, d, A d (32); writes x, r, d, A d (32)
+#               and grad_x, grad_y (16)
+KERNEL_BYTES_PER_POINT = {"row_flux": 56.0, "col_update": 96.0}
+KERNEL_IDS = {"row_flux": 0, "col_update": 2}
 # algorithmic bytes per grid point of the passes of one time step outside the
 # PCG loop: gradient of the warm start (24), initial operator apply (56 + 32),
-# first update (32), split: p and gradient (16 + 24), activation/relaxation
+# start of the loop (24), split: p and gradient (16 + 24), activation/relaxation
 # pass (64), heat multiplier (32), final row pass with Delta m (48)
-STEP_BYTES_PER_POINT = 328.0
-KERNEL_SOURCES = ("paper_2606_06720_amd/csrc/nf_kernels.hip", "paper_2606_06720_amd/csrc/nf_fft.hpp",
+STEP_BYTES_PER_POINT = 320.0
+KERNEL_SOURCES = ("paper_2606_06720_amd/csrc/nf_kernels.hip", "paper_2606_06720_amd/csrc/nf_loop.hpp", "paper_2606_06720_amd/csrc/nf_fft.hpp",
                   "paper_2606_06720_amd/csrc/nf_tiles.hpp", "paper_2606_06720_amd/csrc/nf_internal.h")
 
 

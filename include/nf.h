@@ -321,7 +321,7 @@ int nf_gradient(nf_grid *g, const double *f, double *grad);
  *   available).  parts in [1, min(4, count)] fixes it.
  *   NF_EINVAL otherwise.
  * nf_batch_set_graphs: on records each chunk of PCG iterations a partition
- *   launches (the three passes of every iteration for every grid shape) as a
+ *   launches (the two passes of every iteration for every grid shape) as a
  *   HIP graph on first use and replays it afterwards; 0 (the default)
  *   launches the kernels one by one.  The results are the same either way.
  *   NF_EINVAL for a NULL handle.
@@ -344,12 +344,14 @@ const char *nf_batch_last_error(const nf_batch *b);
 
 /*
  * Tile tuning of the PCG loop (2D grids with a side of 256 to 4096, powers of
- * two).  The three passes of a PCG iteration (operator middle: x transforms
- * and the flux (m m^T + r I) grad p; operator end: y transform, divergence and
- * the inner products; update) exist in several tile variants: rows per
- * workgroup of the operator middle, columns and threads per workgroup of the
- * other two, and the order of the radix-8 and radix-4 stages of their
- * transforms.  When
+ * two).  The two passes of a PCG iteration (row pass, the operator middle: x
+ * transforms and the flux (m m^T + r I) grad p; column pass, the operator end
+ * and the update: y transforms, divergence, vector updates and the gradient of
+ * the next preconditioned residual) exist in several tile variants: rows per
+ * workgroup of the row pass, columns and threads per workgroup of the column
+ * pass, and the order of the radix-8 and radix-4 stages of their transforms.
+ * The operator end and the update being one pass, the record below repeats
+ * that pass under both names.  When
  * autotuning is on (the default), the first nf_create_grid of a grid shape
  * and precision in a process times every variant of each pass on the new
  * handle's workspace and keeps the fastest (the default tile unless a variant
@@ -376,10 +378,10 @@ typedef struct {
   int tuned;          /* 1 if the variants were set by the tuner */
   int flux_rows;      /* operator middle: grid rows per workgroup */
   int flux_plan;      /* 0: radix-8 stages first, 1: radix-4 stages first */
-  int div_cols;       /* operator end: spectral columns per workgroup */
+  int div_cols;       /* column pass (operator end): spectral columns per workgroup */
   int div_plan;
   int div_threads;    /* threads per workgroup */
-  int update_cols;    /* update: spectral columns per workgroup */
+  int update_cols;    /* column pass (update): spectral columns per workgroup */
   int update_plan;
   int update_threads;
   int candidates[3];  /* operator middle, operator end, update */
@@ -398,13 +400,15 @@ int nf_tuning(const nf_grid *g, nf_tuning_info *out);
  * where the tile would have 1024 threads), for the operator end and update
  * v / 3 = 2 or 3 the first plan with twice or four times the threads.  Codes:
  * operator middle [0, 8], the others [0, 11]; 1 is the untuned pass, -1 keeps
- * the current one.  NF_EINVAL if a variant does not exist for the grid and
- * precision.
+ * the current one.  update_var is the tile of the column pass, in which the
+ * operator end runs too; div_var is checked and otherwise has no effect.
+ * NF_EINVAL if a variant does not exist for the grid and precision.
  */
 int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
 
 /*
- * Kernel timing: nf_time_kernel(g, k) makes the PCG-loop kernel k (NF_KERNEL_*)
+ * Kernel timing: nf_time_kernel(g, k) makes the PCG-loop kernel k (NF_KERNEL_*;
+ * 2D: COL_DIV and COL_UPDATE are the same pass)
  * stamp, for every loop iteration, the start of its first and the end of its
  * last workgroup on the device wall clock; after each PCG loop the handle adds
  * the spans of the launches that did work (launches queued after the solver

@@ -197,9 +197,8 @@ int init_residual(nf_grid* g, const double* m, const double* r, float* lo = null
     LCHK(g, launch3_zdiv(G, false, 1, g->mix[0], g->mix[1], g->mix[2], g->qh, g->dh, g->rh, g->bh, 0, s));
     return NF_OK;
   }
-  LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, -1, slot_ptr(g->part, SLOT_KBAR), 0.0, s, nullptr, nullptr,
-                          lo));
-  LCHK(g, launch_col_div(G, 1, g->mix[0], g->mix[1], g->qh, g->dh, g->rh, g->bh, 0, row_nwg(G), s));
+  LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, -1, slot_ptr(g->part, SLOT_KBAR), 0.0, s, lo));
+  LCHK(g, launch_col_div(G, 1, g->mix[0], g->mix[1], nullptr, g->rh, g->bh, row_nwg(G), s));
   return NF_OK;
 }
 
@@ -228,8 +227,8 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
     first_chunk = false;
     if (nk > max_iter - it) nk = max_iter - it;
     for (int k = 0; k < nk; ++k) {
-      hipEvent_t e0, e1;
       if (g->dim == 3) {
+        hipEvent_t e0, e1;
         void* const* F = f32 ? g->mix32 : g->mix;
         LCHK(g, launch3_ypass(G, f32, 3, +1, F[0], F[1], F[2], nullptr, it, 1, tol2, -1.0, s));
         if ((rc = timed_events(g, NF_KERNEL_ROW_FLUX, it, &e0, &e1))) return rc;
@@ -245,24 +244,13 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
         ++it;
         continue;
       }
-      if ((rc = timed_events(g, NF_KERNEL_ROW_FLUX, it, &e0, &e1))) return rc;
-      if (f32)
-        LCHK(g, launch_row_flux32(G, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, it, tol2, s, e0, e1));
-      else
-        LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, it, nullptr, tol2, s, e0, e1));
-      if ((rc = timed_events(g, NF_KERNEL_COL_DIV, it, &e0, &e1))) return rc;
-      if (f32)
-        LCHK(g, launch_col_div32(G, g->mix32[0], g->mix32[1], g->q32, g->d32, g->r32, it, s, e0, e1));
-      else
-        LCHK(g, launch_col_div(G, 0, g->mix[0], g->mix[1], g->qh, g->dh, g->rh, g->bh, it, 0, s, e0, e1));
-      // the update of iteration it+1 does work iff the solver had not stopped before it
-      if ((rc = timed_events(g, NF_KERNEL_COL_UPDATE, it, &e0, &e1))) return rc;
-      if (f32)
-        LCHK(g, launch_col_update32(G, g->x32, g->r32, g->d32, g->q32, g->mix32[0], g->mix32[1], it + 1, max_iter,
-                                    tol2, s, e0, e1));
-      else
-        LCHK(g, launch_col_update(G, 0, g->xh, g->rh, g->dh, g->qh, g->mix[0], g->mix[1], it + 1, max_iter, tol2,
-                                  s, e0, e1));
+      if (f32) {
+        LCHK(g, launch_row_flux32(G, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, it, tol2, s));
+        LCHK(g, launch_col_iter32(G, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32, it, max_iter, s));
+      } else {
+        LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, it, nullptr, tol2, s));
+        LCHK(g, launch_col_iter64(G, g->mix[0], g->mix[1], g->xh, g->rh, g->dh, g->qh, it, max_iter, s));
+      }
       ++it;
     }
     if (!g->hst) {
@@ -373,7 +361,7 @@ int pcg_refined(nf_grid* g, const double* m, const double* r, XSource src, const
       LCHK(g, launch3_zrefine_start(g->geo32, g->rh, g->xh, g->x32, g->r32, g->d32, g->mix32[0], g->mix32[1],
                                     g->mix32[2], tol2, g->inner_floor, max_iter, s));
     else
-      LCHK(g, launch_col_refine_start(g->geo32, g->rh, g->xh, g->x32, g->r32, g->d32, g->mix32[0], g->mix32[1],
+      LCHK(g, launch_col_refine_start(g->geo32, g->rh, g->xh, g->x32, g->r32, g->mix32[0], g->mix32[1],
                                       tol2, g->inner_floor, max_iter, s));
     const int slot = outer < 3 ? outer : 3;
     rc = pcg_loop(g, true, m, r, max_iter, 1.0, g->last_inner[slot], &fin);
@@ -414,7 +402,7 @@ int pcg(nf_grid* g, const double* m, const double* r, XSource src, const double*
     LCHK(g, launch3_zupdate(G, false, 1, g->xh, g->rh, g->dh, g->qh, g->mix[0], g->mix[1], g->mix[2], 0, max_iter,
                             tol2, s));
   else
-    LCHK(g, launch_col_update(G, 1, g->xh, g->rh, g->dh, g->qh, g->mix[0], g->mix[1], 0, max_iter, tol2, s));
+    LCHK(g, launch_col_start(G, g->rh, g->xh, g->mix[0], g->mix[1], max_iter, tol2, s));
   DevStatus fin;
   rc = pcg_loop(g, false, m, r, max_iter, tol2, g->last_iters, &fin);
   if (rc) return rc;
@@ -825,6 +813,8 @@ int nf_time_kernel(nf_grid* g, int which) {
     if (khz <= 0) return fail(g, NF_EDEVICE, "device wall-clock rate unavailable");
     g->wall_khz = (double)khz;
   }
+  // 2D: the operator end and the update are one pass
+  if (which == NF_KERNEL_COL_DIV && g->dim == 2) which = NF_KERNEL_COL_UPDATE;
   g->timed = which;
   g->geo.tclk = g->geo32.tclk = which >= 0 ? g->tclk : nullptr;
   g->geo.tkind = g->geo32.tkind = which;
@@ -938,7 +928,7 @@ int nf_apply_operator(nf_grid* g, const double* m, const double* r, const double
   LCHK(g, launch_row_r2c(G, p, g->mix[0], nullptr, s));
   LCHK(g, launch_col_fwd(G, g->mix[0], g->xh, 1, g->mix[0], g->mix[1], s));
   LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, -1, nullptr, 0.0, s));
-  LCHK(g, launch_col_div(G, 0, g->mix[0], g->mix[1], g->qh, g->xh, g->xh, g->bh, 0, 0, s));
+  LCHK(g, launch_col_div(G, 0, g->mix[0], g->mix[1], g->qh, nullptr, nullptr, 0, s));
   LCHK(g, launch_col_grad(G, g->qh, g->mix[0], nullptr, nullptr, s));
   LCHK(g, launch_row_c2r(G, g->mix[0], out, s));
   HIPCHK(g, hipStreamSynchronize(s));

@@ -45,8 +45,8 @@ thread_local std::string batch_create_err;
 // device argument tables of one launch group (k entries each)
 struct Tables {
   FluxArgs *flux_init = nullptr, *flux_init_lo = nullptr, *flux_loop = nullptr, *flux32 = nullptr;
-  DivArgs *div64 = nullptr, *div32 = nullptr;
-  UpdArgs *upd64 = nullptr, *upd32 = nullptr;
+  DivArgs* div_init = nullptr;
+  IterArgs *iter64 = nullptr, *iter32 = nullptr;
   ColGradArgs *grad_x = nullptr, *split_p = nullptr, *split_g = nullptr;
   SplitArgs* split = nullptr;
   HeatArgs* heat = nullptr;
@@ -116,18 +116,18 @@ int bfail(Part* b, int code, const std::string& msg) {
 
 // Offsets of the tables in a group's allocation (256-byte aligned).
 struct Layout {
-  size_t off[18];
+  size_t off[17];
   size_t total;
 };
 Layout layout(int k) {
-  const size_t sz[18] = {sizeof(FluxArgs),    sizeof(FluxArgs),     sizeof(FluxArgs),    sizeof(FluxArgs),
-                         sizeof(DivArgs),     sizeof(DivArgs),      sizeof(UpdArgs),     sizeof(UpdArgs),
+  const size_t sz[17] = {sizeof(FluxArgs),    sizeof(FluxArgs),     sizeof(FluxArgs),    sizeof(FluxArgs),
+                         sizeof(DivArgs),     sizeof(IterArgs),     sizeof(IterArgs),
                          sizeof(ColGradArgs), sizeof(ColGradArgs),  sizeof(ColGradArgs), sizeof(SplitArgs),
                          sizeof(HeatArgs),    sizeof(FinalArgs),    sizeof(RefStartArgs), sizeof(RefAccArgs),
                          sizeof(SumArgs),     sizeof(SumArgs)};
   Layout L;
   size_t o = 0;
-  for (int i = 0; i < 18; ++i) {
+  for (int i = 0; i < 17; ++i) {
     L.off[i] = o;
     o += (sz[i] * k + 255) & ~(size_t)255;
   }
@@ -146,20 +146,19 @@ void bind_tables(Part::Group& G, char* base, const Layout& L) {
   t.flux_init_lo = at<FluxArgs>(base, L.off[1]);
   t.flux_loop = at<FluxArgs>(base, L.off[2]);
   t.flux32 = at<FluxArgs>(base, L.off[3]);
-  t.div64 = at<DivArgs>(base, L.off[4]);
-  t.div32 = at<DivArgs>(base, L.off[5]);
-  t.upd64 = at<UpdArgs>(base, L.off[6]);
-  t.upd32 = at<UpdArgs>(base, L.off[7]);
-  t.grad_x = at<ColGradArgs>(base, L.off[8]);
-  t.split_p = at<ColGradArgs>(base, L.off[9]);
-  t.split_g = at<ColGradArgs>(base, L.off[10]);
-  t.split = at<SplitArgs>(base, L.off[11]);
-  t.heat = at<HeatArgs>(base, L.off[12]);
-  t.fin = at<FinalArgs>(base, L.off[13]);
-  t.rstart = at<RefStartArgs>(base, L.off[14]);
-  t.racc = at<RefAccArgs>(base, L.off[15]);
-  t.sum_rr = at<SumArgs>(base, L.off[16]);
-  t.sum_dm = at<SumArgs>(base, L.off[17]);
+  t.div_init = at<DivArgs>(base, L.off[4]);
+  t.iter64 = at<IterArgs>(base, L.off[5]);
+  t.iter32 = at<IterArgs>(base, L.off[6]);
+  t.grad_x = at<ColGradArgs>(base, L.off[7]);
+  t.split_p = at<ColGradArgs>(base, L.off[8]);
+  t.split_g = at<ColGradArgs>(base, L.off[9]);
+  t.split = at<SplitArgs>(base, L.off[10]);
+  t.heat = at<HeatArgs>(base, L.off[11]);
+  t.fin = at<FinalArgs>(base, L.off[12]);
+  t.rstart = at<RefStartArgs>(base, L.off[13]);
+  t.racc = at<RefAccArgs>(base, L.off[14]);
+  t.sum_rr = at<SumArgs>(base, L.off[15]);
+  t.sum_dm = at<SumArgs>(base, L.off[16]);
 }
 
 // Fill the host image of a group's tables for one run and copy it to the device.
@@ -180,10 +179,9 @@ int upload_tables(Part* b, Part::Group& G, const nf_params* prm, double dt, doub
     H.t.flux_init_lo[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], slot_ptr(g->part, SLOT_KBAR), g->lo};
     H.t.flux_loop[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], nullptr, nullptr};
     H.t.flux32[j] = FluxArgs{g32, g->mix32[0], g->mix32[1], g->lo, g->lo ? g->lo + 2 * n : nullptr, nullptr, nullptr};
-    H.t.div64[j] = DivArgs{g64, g->mix[0], g->mix[1], g->qh, g->dh, g->rh, g->bh};
-    H.t.div32[j] = DivArgs{g32, g->mix32[0], g->mix32[1], g->q32, g->d32, g->r32, nullptr};
-    H.t.upd64[j] = UpdArgs{g64, g->xh, g->rh, g->dh, g->qh, g->mix[0], g->mix[1]};
-    H.t.upd32[j] = UpdArgs{g32, g->x32, g->r32, g->d32, g->q32, g->mix32[0], g->mix32[1]};
+    H.t.div_init[j] = DivArgs{g64, g->mix[0], g->mix[1], g->rh, g->bh};
+    H.t.iter64[j] = IterArgs{g64, g->mix[0], g->mix[1], g->xh, g->rh, g->dh, g->qh};
+    H.t.iter32[j] = IterArgs{g32, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32};
     H.t.grad_x[j] = ColGradArgs{g64, g->xh, nullptr, g->mix[0], g->mix[1]};
     H.t.split_p[j] = ColGradArgs{g64, g->xh, g->mix[0], nullptr, nullptr};
     H.t.split_g[j] = ColGradArgs{g64, g->xh, nullptr, g->mix[1], g->mix[2]};
@@ -191,7 +189,7 @@ int upload_tables(Part* b, Part::Group& G, const nf_params* prm, double dt, doub
                              p[i],       prm[i].c2 * dt, prm[i].gamma, dt, std::exp(-dt)};
     H.t.heat[j] = HeatArgs{g64, g->mix[0], g->mix[1], prm[i].D2 * dt, nullptr};
     H.t.fin[j] = FinalArgs{g64, g->mix[0], g->mix[1], m[i], slot_ptr(g->part, SLOT_DM)};
-    H.t.rstart[j] = RefStartArgs{g32, g->rh, g->xh, g->x32, g->r32, g->d32, g->mix32[0], g->mix32[1]};
+    H.t.rstart[j] = RefStartArgs{g32, g->rh, g->xh, g->x32, g->r32, g->mix32[0], g->mix32[1]};
     H.t.racc[j] = RefAccArgs{g64, g->xh, g->x32, g->mix[0], g->mix[1]};
     H.t.sum_rr[j] = SumArgs{slot_ptr(g->part, SLOT_RR), g->st};
     H.t.sum_dm[j] = SumArgs{slot_ptr(g->part, SLOT_DM), g->st};
@@ -213,9 +211,13 @@ int launch_chunk(Part* b, bool f32, int it0, int nk, int max_iter, double tol2) 
   for (int it = it0; it < it0 + nk; ++it) {
     for (auto& G : b->groups) {
       const int k = (int)G.idx.size();
-      BCHK(b, launchb_row_flux(G.shape, f32, f32 ? G.t.flux32 : G.t.flux_loop, k, it, tol2, s));
-      BCHK(b, launchb_col_div(G.shape, f32, false, f32 ? G.t.div32 : G.t.div64, k, it, s));
-      BCHK(b, launchb_col_update(G.shape, f32, f32 ? G.t.upd32 : G.t.upd64, k, 0, it + 1, max_iter, tol2, s));
+      if (f32) {
+        BCHK(b, launchb_row_flux32(G.shape, G.t.flux32, k, it, tol2, s));
+        BCHK(b, launchb_col_iter32(G.shape, G.t.iter32, k, it, max_iter, s));
+      } else {
+        BCHK(b, launchb_row_flux64(G.shape, G.t.flux_loop, k, it, tol2, s));
+        BCHK(b, launchb_col_iter64(G.shape, G.t.iter64, k, it, max_iter, s));
+      }
     }
   }
   return NF_OK;
@@ -323,9 +325,9 @@ int batch_solve(Part* b, bool first, double* const* p, double rtol, int max_iter
   if (b->dtype == NF_F64) {
     for (auto& G : b->groups) {
       const int k = (int)G.idx.size();
-      BCHK(b, launchb_row_flux(G.shape, false, G.t.flux_init, k, -1, 0.0, s));
-      BCHK(b, launchb_col_div(G.shape, false, true, G.t.div64, k, 0, s));
-      BCHK(b, launchb_col_update(G.shape, false, G.t.upd64, k, 1, 0, max_iter, tol2, s));
+      BCHK(b, launchb_row_flux64(G.shape, G.t.flux_init, k, -1, 0.0, s));
+      BCHK(b, launchb_col_div_init(G.shape, G.t.div_init, k, s));
+      BCHK(b, launchb_col_start(G.shape, G.t.iter64, k, max_iter, tol2, s));
     }
     int rc = batch_loop(b, false, max_iter, tol2, b->last_iters);
     if (rc) return rc;
@@ -358,8 +360,8 @@ int batch_solve(Part* b, bool first, double* const* p, double rtol, int max_iter
   for (int outer = 0;; ++outer) {
     for (auto& G : b->groups) {
       const int k = (int)G.idx.size();
-      BCHK(b, launchb_row_flux(G.shape, false, outer == 0 ? G.t.flux_init_lo : G.t.flux_init, k, -1, 0.0, s));
-      BCHK(b, launchb_col_div(G.shape, false, true, G.t.div64, k, 0, s));
+      BCHK(b, launchb_row_flux64(G.shape, outer == 0 ? G.t.flux_init_lo : G.t.flux_init, k, -1, 0.0, s));
+      BCHK(b, launchb_col_div_init(G.shape, G.t.div_init, k, s));
       BCHK(b, launchb_col_refine_start(G.shape, G.t.rstart, k, tol2, b->inst[G.idx[0]]->inner_floor, max_iter, s));
     }
     const int slot = outer < 3 ? outer : 3;

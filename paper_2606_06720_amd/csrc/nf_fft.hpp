@@ -360,16 +360,58 @@ __device__ __forceinline__ void irfft_pre(cx<T>* buf, const cx<T>* __restrict__ 
 }
 
 // ---------------------------------------------------------------- reductions
-// Deterministic workgroup sum of K doubles per thread: wavefront butterfly via
-// shuffles, then a fixed-order pass over the waves.  Every thread gets the result.
+// A double moved across lanes by a DPP control (all lanes active).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  union {
+    double d;
+    int i[2];
+  } a, b;
+  a.d = v;
+  b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, 0xf, 0xf, true);
+  b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, 0xf, 0xf, true);
+  return b.d;
+}
+// Butterfly sum over the wavefront; every lane gets the result.  The steps
+// within 16 lanes are DPP moves (quad permutes, then the half-row and row
+// mirrors, which pair the same partial sums as exchanges over 4 and 8 lanes
+// once the quads are uniform): a few cycles each, where a shuffle through the
+// LDS crossbar takes about a hundred.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_move<0xB1>(v);   // lanes exchanged in pairs
+  v += dpp_move<0x4E>(v);   // pairs of lanes exchanged
+  v += dpp_move<0x141>(v);  // half-row mirror
+  v += dpp_move<0x140>(v);  // row mirror
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+// A workgroup sum in two phases, for passes that have a barrier between them
+// anyway: every wave leaves its sums of K doubles in red[k * waves + wave]; after
+// a barrier any thread adds the waves in order with waves_total.
+template <int K>
+__device__ __forceinline__ void wave_sums(const double (&v)[K], double* red) {
+  const int nw = blockDim.x >> 6;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const double s = wave_sum(v[k]);
+    if ((threadIdx.x & 63) == 0) red[k * nw + (threadIdx.x >> 6)] = s;
+  }
+}
+template <int NW>
+__device__ __forceinline__ double waves_total(const double* red) {
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) s += red[w];
+  return s;
+}
+// Deterministic workgroup sum of K doubles per thread: wavefront butterfly,
+// then a fixed-order pass over the waves.  Every thread gets the result.
 template <int NT, int K>
 __device__ __forceinline__ void block_sum(double (&v)[K], double* scratch /* >= K*NT/64 */) {
   constexpr int NW = NT / 64;
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-  }
+  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   __syncthreads();
   if (lane == 0) {

@@ -12,7 +12,8 @@ namespace nf {
 struct DevStatus {
   double kbar[8];   // grid mean of K = m m^T + r I: 2D Kxx, Kxy, Kyy; 3D Kxx, Kxy, Kxz, Kyy, Kyz, Kzz
   double bb;        // weighted ||b_hat||^2 of the projected right-hand side
-  double rho[2];    // <r, M^-1 r> by iteration parity (expanded value used for beta)
+  double rho[2];    // <r, M^-1 r> by iteration parity
+  double alpha[2];  // step length by iteration parity (follows rho: the tuner fills both)
   double rr[2];     // rr[0]: ||r||^2 of the residual at which the solve stopped
   double rr0;       // initial ||r||^2
   double orr, obb;  // mixed-precision solve: FP64 ||r||^2 and ||b||^2 at the last correction start
@@ -34,14 +35,14 @@ enum { FLAG_NONFINITE = 1, FLAG_INCOMPAT = 2 };
 // Slots of the partial-sum area; each slot holds up to SLOT_K arrays of
 // MAX_WG doubles.
 enum {
-  SLOT_P3 = 0,      // <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r>
+  SLOT_P3 = 0,      // 2D: <z, A z> of z = M^-1 r; 3D: <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r>
   SLOT_P3INIT = 1,  // <r,M^-1 r>, <r,r>, <b,b>
   SLOT_KBAR = 2,    // sum mx^2, mx my, my^2, r
   SLOT_SCHK = 3,    // sum S, sum |S|
   SLOT_DM = 4,      // sum (m_new - m_old)^2, sum m_old^2
   SLOT_EPT = 5,     // sum r|g|^2, sum (m.g)^2, sum |m|^{2 gamma}
   SLOT_EGM = 6,     // sum w |xi|^2 |m_hat|^2 (both components)
-  SLOT_RR = 7,      // ||r||^2 of the residual written by the last PCG update
+  SLOT_RR = 7,      // ||r||^2 of the residual written by the last PCG update (2D: and <r, M^-1 r>)
   NSLOTS = 8,
   SLOT_K = 8,
   MAX_WG = 4096,
@@ -68,16 +69,17 @@ struct Geo {
   unsigned long long* tclk;
   int tkind;
   // tile variants of the PCG-loop passes chosen by the tuner (index 0: FP64
-  // passes, 1: FP32 passes; VAR_DEFAULT = 1 is the untuned tile): operator
-  // middle (row variant), operator end and update (column variants).  Read by
-  // the launchers only.
+  // passes, 1: FP32 passes; VAR_DEFAULT = 1 is the untuned tile): row pass (row
+  // variant), column pass (column variant var_upd; var_div keeps the code a
+  // caller set for the operator end, which is part of that pass).  Read by the
+  // launchers only.
   int var_flux[2], var_div[2], var_upd[2];
 };
 
-enum { TCLK_CAP = 2048, TCLK_W = 64 };
+enum { TCLK_CAP = 2048, TCLK_W = 64 };  // timed iterations per PCG loop, stamp slots per iteration
 // tile variants of the PCG-loop passes (codes 0 .. NVAR-1, see nf_tiles.hpp);
 // VAR_DEFAULT is the untuned tile
-enum { VAR_DEFAULT = 1, NVAR = 12 };  // timed iterations per PCG loop, stamp slots per iteration
+enum { VAR_DEFAULT = 1, NRV = 12, NCV = 15, NVAR = 15, RV_SMALL = 9, CV_SMALL = 12 };
 
 __host__ __device__ inline double* slot_ptr(double* part, int slot) {
   return part + (size_t)slot * SLOT_K * MAX_WG;
@@ -122,19 +124,17 @@ struct DivArgs {
   Geo g;
   const void* Fx;
   const void* Fy;
-  void* qh;
-  const void* dh;
   void* rh;
   const void* bh;
 };
-struct UpdArgs {
+struct IterArgs {
   Geo g;
+  void* M0;
+  void* M1;
   void* xh;
   void* rh;
   void* dh;
-  const void* qh;
-  void* Gx;
-  void* Gy;
+  void* sh;
 };
 struct SplitArgs {
   Geo g;
@@ -165,7 +165,6 @@ struct RefStartArgs {
   void* x64;
   void* x32;
   void* r32;
-  void* d32;
   void* Gx;
   void* Gy;
 };
@@ -258,14 +257,14 @@ hipError_t launch_zero_spec(const Geo& g, void* xh, hipStream_t s);
 // row passes (physical <-> mixed)
 int row_nwg(const Geo& g);
 int col_nwg(const Geo& g);
-// workgroups of the row variant rv of the operator middle / column variant cv
-// of the operator end and update
+// workgroups of the row variant rv of the row pass / column variant cv of the
+// column pass
 int row_nwg_var(const Geo& g, int rv);
 int col_nwg_var(const Geo& g, int cv);
 // whether a variant exists for the grid of g and the real type (f32) and can run
 bool flux_var_valid(const Geo& g, bool f32, int rv);
 bool div_var_valid(const Geo& g, bool f32, int cv);
-// partial sums of ||r||^2 written by the update of the PCG loop
+// workgroups of the column pass of the loop (the partials of ||r||^2 and <r, M^-1 r>)
 int rr_nwg(const Geo& g, bool f32);
 // rows per workgroup of row variant rv, columns per workgroup of column variant cv
 int flux_var_rows(const Geo& g, int rv);
@@ -273,17 +272,18 @@ int flux_var_threads(const Geo& g, int rv);
 int flux_var_plan(int rv);
 int div_var_cols(const Geo& g, int cv);
 int div_var_threads(const Geo& g, int cv);
+// variants in use by the loop (it >= 0), the column pass
+int use_rv(const Geo& g, bool f32, int it);
+int use_cv(const Geo& g, bool f32);
 // whether the grid sizes have tuned variants at all
 bool var_grid(const Geo& g);
 // fill n doubles with a value (a kernel, so that no memset node is recorded)
 hipError_t launch_fill_doubles(double* p, size_t n, double v, hipStream_t s);
 hipError_t launch_row_r2c(const Geo& g, const double* f, void* out_mixed, double* schk_slot, hipStream_t s);
 hipError_t launch_row_c2r(const Geo& g, const void* in_mixed, double* f, hipStream_t s);
-// e0/e1: optional start/stop events timestamped by the dispatch (nullptr = none)
 // lo: optional FP32 copies of m then r (3n floats), written when non-null
 hipError_t launch_row_flux(const Geo& g, void* G0, void* G1, const double* m, const double* r, int it,
-                           double* kbar_slot, double tol2, hipStream_t s, hipEvent_t e0 = nullptr,
-                           hipEvent_t e1 = nullptr, float* lo = nullptr);
+                           double* kbar_slot, double tol2, hipStream_t s, float* lo = nullptr);
 hipError_t launch_row_split(const Geo& g, void* P, void* Gx, void* Gy, const double* m, double* p_out,
                             double c2dt, double gamma, double dt, double relax_gamma1, hipStream_t s);
 hipError_t launch_row_final(const Geo& g, const void* Mx, const void* My, double* m, double* dm_slot,
@@ -294,23 +294,21 @@ hipError_t launch_row_energy(const Geo& g, const void* Gx, const void* Gy, const
 hipError_t launch_col_fwd(const Geo& g, void* in_mixed, void* out_spec, int with_grad, void* Gx, void* Gy,
                           hipStream_t s);
 hipError_t launch_col_grad(const Geo& g, const void* xh, void* P, void* Gx, void* Gy, hipStream_t s);
-hipError_t launch_col_div(const Geo& g, int init, const void* Fx, const void* Fy, void* qh, const void* dh,
-                          void* rh, const void* bh, int it, int nwg_row, hipStream_t s, hipEvent_t e0 = nullptr,
-                          hipEvent_t e1 = nullptr);
-hipError_t launch_col_update(const Geo& g, int first, void* xh, void* rh, void* dh, const void* qh, void* Gx,
-                             void* Gy, int it, int max_iter, double tol2, hipStream_t s, hipEvent_t e0 = nullptr,
-                             hipEvent_t e1 = nullptr);
+hipError_t launch_col_div(const Geo& g, int init, const void* Fx, const void* Fy, void* qh, void* rh, const void* bh,
+                          int nwg_row, hipStream_t s);
+hipError_t launch_col_start(const Geo& g, const void* rh, void* xh, void* Gx, void* Gy, int max_iter, double tol2,
+                            hipStream_t s);
+// column pass of the PCG loop (M0, M1: fluxes in, gradient out; sh: A d)
+hipError_t launch_col_iter64(const Geo& g, void* M0, void* M1, void* xh, void* rh, void* dh, void* sh, int it,
+                             int max_iter, hipStream_t s);
 // FP32 instantiations of the PCG-loop passes (g.tw points at the FP32 table;
 // m32/r32 are the FP32 copies written by launch_row_flux)
 hipError_t launch_row_flux32(const Geo& g, void* G0, void* G1, const float* m32, const float* r32, int it,
-                             double tol2, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-hipError_t launch_col_div32(const Geo& g, const void* Fx, const void* Fy, void* qh, const void* dh, void* rh, int it,
-                            hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-hipError_t launch_col_update32(const Geo& g, void* xh, void* rh, void* dh, const void* qh, void* Gx, void* Gy, int it,
-                               int max_iter, double tol2, hipStream_t s, hipEvent_t e0 = nullptr,
-                               hipEvent_t e1 = nullptr);
+                             double tol2, hipStream_t s);
+hipError_t launch_col_iter32(const Geo& g, void* M0, void* M1, void* xh, void* rh, void* dh, void* sh, int it,
+                             int max_iter, hipStream_t s);
 // mixed-precision correction start / accumulation (g32: FP32 twiddles)
-hipError_t launch_col_refine_start(const Geo& g32, const void* r64, void* x64, void* x32, void* r32, void* d32,
+hipError_t launch_col_refine_start(const Geo& g32, const void* r64, void* x64, void* x32, void* r32,
                                    void* Gx32, void* Gy32, double tol2, double floor_in, int max_iter, hipStream_t s);
 hipError_t launch_col_refine_acc(const Geo& g, void* x64, const void* x32, void* Gx, void* Gy, hipStream_t s);
 hipError_t launch_col_heat(const Geo& g, void* Mx, void* My, double D2dt, double* egm_slot, hipStream_t s);
@@ -336,12 +334,13 @@ hipError_t launchb_sum_slot(const SumArgs* A, int count, int K, int n, int o, hi
 hipError_t launchb_row_r2c(const Geo& shape, const RowR2cArgs* A, int count, hipStream_t s);
 hipError_t launchb_col_fwd(const Geo& shape, const ColFwdArgs* A, int count, int mode, hipStream_t s);
 hipError_t launchb_col_grad(const Geo& shape, const ColGradArgs* A, int count, bool grad, hipStream_t s);
-hipError_t launchb_row_flux(const Geo& shape, bool f32, const FluxArgs* A, int count, int it, double tol2,
-                            hipStream_t s);
-hipError_t launchb_col_div(const Geo& shape, bool f32, bool init, const DivArgs* A, int count, int it,
-                           hipStream_t s);
-hipError_t launchb_col_update(const Geo& shape, bool f32, const UpdArgs* A, int count, int first, int it,
-                              int max_iter, double tol2, hipStream_t s);
+hipError_t launchb_row_flux64(const Geo& shape, const FluxArgs* A, int count, int it, double tol2, hipStream_t s);
+hipError_t launchb_row_flux32(const Geo& shape, const FluxArgs* A, int count, int it, double tol2, hipStream_t s);
+hipError_t launchb_col_div_init(const Geo& shape, const DivArgs* A, int count, hipStream_t s);
+hipError_t launchb_col_start(const Geo& shape, const IterArgs* A, int count, int max_iter, double tol2,
+                             hipStream_t s);
+hipError_t launchb_col_iter64(const Geo& shape, const IterArgs* A, int count, int it, int max_iter, hipStream_t s);
+hipError_t launchb_col_iter32(const Geo& shape, const IterArgs* A, int count, int it, int max_iter, hipStream_t s);
 hipError_t launchb_row_split(const Geo& shape, const SplitArgs* A, int count, hipStream_t s);
 hipError_t launchb_col_heat(const Geo& shape, const HeatArgs* A, int count, hipStream_t s);
 hipError_t launchb_row_final(const Geo& shape, const FinalArgs* A, int count, hipStream_t s);

@@ -19,7 +19,7 @@
 // Spectral vectors hold the unnormalised DFT of the physical field.  Inner
 // products are sum_k w_k Re(a conj b) with w = 1 on the packed column and 2
 // elsewhere, which is n times the physical Euclidean product (Parseval).
-#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
 
 #include <climits>
 
@@ -36,6 +36,7 @@ __device__ __forceinline__ void k_status_reset_one(DevStatus* st, int full) {
     for (int i = 0; i < 8; ++i) st->kbar[i] = 0.0;
     st->bb = 0.0;
     st->rho[0] = st->rho[1] = 0.0;
+    st->alpha[0] = st->alpha[1] = 0.0;
     st->rr[0] = st->rr[1] = 0.0;
     st->rr0 = 0.0;
     st->orr = st->obb = st->rscale = 0.0;
@@ -151,136 +152,6 @@ template <int NX>
 __global__ void __launch_bounds__((Row2D<NX, 1>::NT)) kb_row_split_p(const SplitArgs* __restrict__ A) {
   const SplitArgs& a = A[blockIdx.y];
   row_c2r_body<NX>(a.g, (const cd*)a.P, (double*)a.p_out);
-}
-
-// Operator middle: gradient fields (mixed) -> physical g -> flux K g -> mixed,
-// both components in one batched transform each way.  In place: G0/G1 hold
-// grad_x/grad_y on entry and F_x/F_y on exit.  Optional partials: sum mx^2,
-// mx my, my^2, r (the preconditioner's Kbar).  Optional lo: FP32 copies of
-// m (2n values) followed by r (n values) for the single-precision inner solve.
-// In the PCG loop (it >= 1) the pass first takes the stopping decision for the
-// residual r_it left by k_col_update: ||r_it||^2 (reduced directly from that
-// kernel's partials) <= tol2 * status.bb ends the solve at iteration it.
-// T is the arithmetic and storage type of the transforms and fields; the
-// reductions are FP64 in both instantiations.
-template <int NX, typename T, int RV>
-__device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
-                                                  const T* __restrict__ r, int it, double* kslot, int nwg_col,
-                                                  double tol2, float* lo) {
-  using C = FluxCfg<NX, RV>;
-  using V = cx<T>;
-  using P = typename vec2<T>::type;
-  if (it >= 0 ? g.st->conv_at <= it : g.st->outer_done != 0) return;
-  tclk_start(g, 0, it);
-  __shared__ V buf[C::NB * C::LS];
-  __shared__ double red[4 * (C::NT / 64)];
-  const V* tw = (const V*)g.tw;
-  const int y0 = xcd_block() * C::R;
-  const int nrow = min(C::R, g.ny - y0);
-  const size_t n = (size_t)g.nx * g.ny;
-  // Tiles of fewer than 1024 threads load the pairs (k, H - k) of each line, so
-  // that the pre-processing of the inverse real transform happens on the way
-  // into LDS; 1024-thread tiles (at most 128 registers per thread) load the
-  // plain transposed image and pre-process in LDS, since the paired form
-  // spills there.
-  constexpr bool PAIRS = C::NT < 1024;
-  constexpr int NA = PAIRS ? RowPairs<C>::ETP : C::ET, NBP = PAIRS ? RowPairs<C>::ETP : 1;
-  V ta[NA], tb[NBP];
-  if constexpr (PAIRS)
-    rowTP_gload<C>(ta, tb, G0, G1, nullptr, g.ny, y0, nrow);
-  else
-    rowT_gload<C>(ta, G0, G1, nullptr, g.ny, y0, nrow);
-  if (it >= 1) {
-    double rr[1];
-    sum_partials<C::NT, 1>(slot_ptr(g.part, SLOT_RR), nwg_col, MAX_WG, rr, red);
-    const double bb = g.st->bb;
-    const bool bad = !isfinite(rr[0]);
-    if (bad || rr[0] <= tol2 * bb) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        g.st->rr[0] = rr[0];
-        g.st->converged = bad ? 0 : 1;
-        if (bad) g.st->flags |= FLAG_NONFINITE;
-        g.st->conv_at = it;
-      }
-      return;
-    }
-  }
-  if constexpr (PAIRS) {
-    rowTP_put_pre<C>(buf, ta, tb, tw, g.twn);
-    __syncthreads();
-  } else {
-    rowT_put<C>(buf, ta);
-    __syncthreads();
-    irfft_pre<T, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
-  }
-  lds_fft<T, +1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
-  // m and r are loaded only now: held across the transform they would cost
-  // about 48 registers, and a workgroup with fewer registers shares a compute
-  // unit more easily with the passes of concurrent solves
-  P mx[C::EP], my[C::EP], rv[C::EP];
-  rowP_gload<C>(mx, m, y0, nrow);
-  rowP_gload<C>(my, m + n, y0, nrow);
-  rowP_gload<C>(rv, r, y0, nrow);
-  if (lo) {
-#pragma unroll
-    for (int i = 0; i < C::EP; ++i) {
-      const int p = threadIdx.x + i * C::NT;
-      const int rr = p / C::H, j = p % C::H;
-      if (p < C::RH && rr < nrow) {
-        const size_t o = (size_t)(y0 + rr) * NX + 2 * j;
-        *(float2*)(lo + o) = make_float2((float)mx[i].x, (float)mx[i].y);
-        *(float2*)(lo + n + o) = make_float2((float)my[i].x, (float)my[i].y);
-        *(float2*)(lo + 2 * n + o) = make_float2((float)rv[i].x, (float)rv[i].y);
-      }
-    }
-  }
-  double ks[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int i = 0; i < C::EP; ++i) {
-    const int p = threadIdx.x + i * C::NT;
-    const int rr = p / C::H, j = p % C::H;
-    if (p < C::RH && rr < nrow) {
-      V* px = buf + rr * C::LS + j;
-      V* py = buf + (C::R + rr) * C::LS + j;
-      const V gx = *px, gy = *py;
-      // K g = (m.g) m + r g at the two grid points packed in this element
-      const T a0 = mx[i].x * gx.x + my[i].x * gy.x;
-      const T a1 = mx[i].y * gx.y + my[i].y * gy.y;
-      *px = mk<T>(fma(a0, mx[i].x, rv[i].x * gx.x), fma(a1, mx[i].y, rv[i].y * gx.y));
-      *py = mk<T>(fma(a0, my[i].x, rv[i].x * gy.x), fma(a1, my[i].y, rv[i].y * gy.y));
-      if (kslot) {
-        ks[0] += (double)mx[i].x * mx[i].x + (double)mx[i].y * mx[i].y;
-        ks[1] += (double)mx[i].x * my[i].x + (double)mx[i].y * my[i].y;
-        ks[2] += (double)my[i].x * my[i].x + (double)my[i].y * my[i].y;
-        ks[3] += (double)rv[i].x + (double)rv[i].y;
-      }
-    }
-  }
-  __syncthreads();
-  lds_fft<T, -1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
-  // post-processing of the forward real transform on the way out
-  if constexpr (PAIRS) {
-    rowTP_store_post<C, 2>(buf, G0, G1, nullptr, tw, g.twn, g.ny, y0, nrow);
-  } else {
-    rfft_post<T, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
-    rowT_store<C, 2>(buf, G0, G1, nullptr, g.ny, y0, nrow);
-  }
-  if (kslot) {
-    block_sum<C::NT, 4>(ks, red);
-    write_partials<C::NT>(kslot, ks, 4);
-  }
-  tclk_end(g, 0, it);
-}
-template <int NX, typename T, int RV>
-__global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) k_row_flux(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
-                                                  const T* __restrict__ r, int it, double* kslot, int nwg_col,
-                                                  double tol2, float* lo) {
-  row_flux_body<NX, T, RV>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo);
-}
-template <int NX, typename T, int RV>
-__global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) kb_row_flux(const FluxArgs* __restrict__ A, int it, int nwg_col, double tol2) {
-  const FluxArgs& a = A[blockIdx.y];
-  row_flux_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, (double*)a.kslot, nwg_col, tol2, (float*)a.lo);
 }
 
 // Split update, pointwise part: p = F^-1 x_hat (written out), g = grad p,
@@ -751,29 +622,21 @@ __global__ void __launch_bounds__((ColCfg<NY, GRAD ? 2 : 1>::NT)) kb_col_grad(co
 }
 
 
-// Operator end: forward y transform of the fluxes, q_hat = -i xi . F_hat.
+// Operator end outside the loop: forward y transform of the fluxes, q_hat = -i xi . F_hat.
 // INIT: r_hat = b_hat - q_hat (stored), partials <r,M^-1 r>, <r,r>, <b,b>;
 //       also reduces the Kbar and compatibility partials of the row pass.
-// else: q_hat stored, partials <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r> (the
-//       inner products the update's alpha and beta need).
-// INIT exists for T = double only (the residual of the refinement is FP64).
-template <int NY, bool INIT, typename T, int CV>
-__device__ __forceinline__ void col_div_body(Geo g, const cx<T>* __restrict__ Fx,
-                                                 const cx<T>* __restrict__ Fy, cx<T>* __restrict__ qh,
-                                                 const cx<T>* __restrict__ dh, cx<T>* rh,
-                                                 const cx<T>* __restrict__ bh, int it, int nwg_row) {
-  using C = DivCfg<NY, CV>;
-  static_assert(!INIT || CV == VAR_DEFAULT, "the INIT pass uses the default tile");
-  using V = cx<T>;
-  static_assert(!INIT || sizeof(T) == sizeof(double), "INIT pass is FP64");
-  if (INIT ? g.st->outer_done != 0 : g.st->conv_at <= it) return;
-  if (!INIT) tclk_start(g, 1, it);
-  __shared__ V buf[C::NB * C::LS];
+// else: q_hat stored (operator apply).
+template <int NY, bool INIT>
+__device__ __forceinline__ void col_div_body(Geo g, const cd* __restrict__ Fx, const cd* __restrict__ Fy,
+                                             cd* __restrict__ qh, cd* rh, const cd* __restrict__ bh, int nwg_row) {
+  using C = ColCfg<NY, 2>;
+  if (INIT && g.st->outer_done != 0) return;
+  __shared__ cd buf[C::NB * C::LS];
   __shared__ double red[4 * (C::NT / 64)];
   __shared__ double Ks[4];
-  const V* tw = (const V*)g.tw;
+  const cd* tw = (const cd*)g.tw;
   const int kx0 = blockIdx.x * C::C;
-  V tv[C::ET];
+  cd tv[C::ET];
   colT_gload<C, 2>(tv, Fx, Fy, kx0, g.h);
   if (INIT) {
     double kb[4], sc[2];
@@ -789,214 +652,123 @@ __device__ __forceinline__ void col_div_body(Geo g, const cx<T>* __restrict__ Fx
         if (fabs(sc[0]) > 1e-12 * sc[1]) atomicOr(&g.st->flags, (int)FLAG_INCOMPAT);
       }
     }
-  } else if (threadIdx.x < 4) {
-    Ks[threadIdx.x] = g.st->kbar[threadIdx.x];
   }
   colT_put<C, 2>(buf, tv);
   __syncthreads();
-  lds_fft<T, -1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
-  // the vectors of the dot products are loaded after the transform (fewer
-  // registers held across it)
-  V av[C::EP], bv[C::EP];
-  if (INIT) {
-    colP_gload<C>(av, bh, kx0, g.h);
-  } else {
-    colP_gload<C>(av, dh, kx0, g.h);
-    colP_gload<C>(bv, rh, kx0, g.h);
-  }
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  lds_fft<double, -1, NY, C::NB, C::LS, C::NT>(buf, tw, g.twn);
+  // b is loaded after the transform (fewer registers held across it)
+  cd bv[C::EP];
+  if (INIT) colP_gload<C>(bv, bh, kx0, g.h);
+  double s[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
     const int c = p / NY, ky = p % NY;
     const int kx = kx0 + c;
     if (p < C::CN && kx < g.h) {
-      const V fx = buf[c * C::LS + ky], fy = buf[(C::C + c) * C::LS + ky];
+      const cd fx = buf[c * C::LS + ky], fy = buf[(C::C + c) * C::LS + ky];
       const double xx = xi_col(kx, g.lx);
       const double yy = xi_tilde(ky, NY, g.ly);
       // q = -i (xx Fx + yy Fy)
-      const T ax = (T)xx * fx.x + (T)yy * fy.x, ay = (T)xx * fx.y + (T)yy * fy.y;
-      const V q = mk<T>(ay, -ax);
-      const double w = kx == 0 ? 1.0 : 2.0;
-      const double sig = precond_symbol_inv(Ks, xx, yy);
+      const double ax = xx * fx.x + yy * fy.x, ay = xx * fx.y + yy * fy.y;
+      const cd q = mk<double>(ay, -ax);
       const size_t idx = (size_t)kx * NY + ky;
-      const double qx = q.x, qy = q.y;
       if (INIT) {
-        const V b = av[i];
-        const V rn = sub(b, q);
+        const double w = kx == 0 ? 1.0 : 2.0;
+        const cd b = bv[i];
+        const cd rn = sub(b, q);
         rh[idx] = rn;
-        const double rr = (double)rn.x * rn.x + (double)rn.y * rn.y;
-        s[0] += w * sig * rr;
+        const double rr = rn.x * rn.x + rn.y * rn.y;
+        s[0] += w * precond_symbol_inv(Ks, xx, yy) * rr;
         s[1] += w * rr;
-        s[2] += w * ((double)b.x * b.x + (double)b.y * b.y);
+        s[2] += w * (b.x * b.x + b.y * b.y);
       } else {
         qh[idx] = q;
-        const double dx = av[i].x, dy = av[i].y, rx = bv[i].x, ry = bv[i].y;
-        const double qq = qx * qx + qy * qy;
-        const double rq = rx * qx + ry * qy;
-        s[0] += w * (dx * qx + dy * qy);
-        s[1] += w * sig * rq;
-        s[2] += w * sig * qq;
-        s[3] += w * sig * (rx * rx + ry * ry);
       }
     }
   }
   if (INIT) {
-    double s3[3] = {s[0], s[1], s[2]};
-    block_sum<C::NT, 3>(s3, red);
-    write_partials<C::NT>(slot_ptr(g.part, SLOT_P3INIT), s3, 3);
-  } else {
-    block_sum<C::NT, 4>(s, red);
-    write_partials<C::NT>(slot_ptr(g.part, SLOT_P3), s, 4);
+    block_sum<C::NT, 3>(s, red);
+    write_partials<C::NT>(slot_ptr(g.part, SLOT_P3INIT), s, 3);
   }
-  if (!INIT) tclk_end(g, 1, it);
 }
-template <int NY, bool INIT, typename T, int CV>
-__global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) k_col_div(Geo g, const cx<T>* __restrict__ Fx,
-                                                 const cx<T>* __restrict__ Fy, cx<T>* __restrict__ qh,
-                                                 const cx<T>* __restrict__ dh, cx<T>* rh,
-                                                 const cx<T>* __restrict__ bh, int it, int nwg_row) {
-  col_div_body<NY, INIT, T, CV>(g, Fx, Fy, qh, dh, rh, bh, it, nwg_row);
+template <int NY, bool INIT>
+__global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) k_col_div(Geo g, const cd* __restrict__ Fx, const cd* __restrict__ Fy,
+                                                 cd* __restrict__ qh, cd* rh, const cd* __restrict__ bh, int nwg_row) {
+  col_div_body<NY, INIT>(g, Fx, Fy, qh, rh, bh, nwg_row);
 }
-template <int NY, bool INIT, typename T, int CV>
-__global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_div(const DivArgs* __restrict__ A, int it, int nwg_row) {
+template <int NY>
+__global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) kb_col_div(const DivArgs* __restrict__ A, int nwg_row) {
   const DivArgs& a = A[blockIdx.y];
-  col_div_body<NY, INIT, T, CV>(a.g, (const cx<T>*)a.Fx, (const cx<T>*)a.Fy, (cx<T>*)a.qh, (const cx<T>*)a.dh, (cx<T>*)a.rh, (const cx<T>*)a.bh, it, nwg_row);
+  col_div_body<NY, true>(a.g, (const cd*)a.Fx, (const cd*)a.Fy, nullptr, (cd*)a.rh, (const cd*)a.bh, nwg_row);
 }
 
-// PCG scalar step + vector update + next direction + its gradient (mixed).
-// first: d = M^-1 r.  else: alpha, beta from the partials of k_col_div (the
-// new <r,M^-1 r> follows from the expansion of <r - alpha q, M^-1 (r - alpha q)>
-// around the directly computed old value; it is used for beta only), then
-// x += alpha d, r -= alpha q, d = M^-1 r + beta d.  The stopping test on the
-// new residual is taken by the next pass from its direct norm (SLOT_RR).
-// The scalars are FP64; the vector updates run in T.  `first` exists for
-// T = double only (the single-precision solve starts in k_col_refine_start).
-template <int NY, typename T, int CV>
-__device__ __forceinline__ void col_update_body(Geo g, int first, cx<T>* xh, cx<T>* rh, cx<T>* dh,
-                                                    const cx<T>* __restrict__ qh, cx<T>* Gx, cx<T>* Gy, int it,
-                                                    int max_iter, double tol2, int nwg_col) {
-  using C = DivCfg<NY, CV>;
-  using V = cx<T>;
+// Start of the FP64 loop: <r,M^-1 r>, ||r||^2 and ||b||^2 from the partials of the
+// INIT pass, the stopping test on the initial residual, and the gradient of
+// z = M^-1 r in the mixed buffers for the first row pass.
+template <int NY>
+__device__ __forceinline__ void col_start_body(Geo g, const cd* __restrict__ rh, cd* xh, cd* Gx, cd* Gy, int max_iter,
+                                               double tol2, int nwg_col) {
+  using C = ColCfg<NY, 2>;
   DevStatus* st = g.st;
-  if (st->conv_at < it) return;
-  const int tit = first ? -1 : it;  // timing slot (the first update is not a loop pass)
-  tclk_start(g, 2, tit);
-  __shared__ V buf[C::NB * C::LS];
-  __shared__ double red[7 * (C::NT / 64)];
-  const V* tw = (const V*)g.tw;
+  __shared__ cd buf[C::NB * C::LS];
+  __shared__ double red[3 * (C::NT / 64)];
+  const cd* tw = (const cd*)g.tw;
   const int kx0 = blockIdx.x * C::C;
-  const bool lead = (blockIdx.x == 0 && threadIdx.x == 0);
   double K[4];
   for (int i = 0; i < 4; ++i) K[i] = st->kbar[i];
-  // vectors of the block, loaded before the scalar reduction so that both
-  // latencies overlap
-  V xv[C::EP], rv0[C::EP], dv0[C::EP], qv[C::EP];
-  colP_gload<C>(rv0, rh, kx0, g.h);
-  if (!first) {
-    colP_gload<C>(xv, xh, kx0, g.h);
-    colP_gload<C>(dv0, dh, kx0, g.h);
-    colP_gload<C>(qv, qh, kx0, g.h);
-  }
-  double alpha = 0.0, beta = 0.0;
-  bool stop = false, zero_x = false;
-  if (first) {
-    double s[3];
-    sum_partials<C::NT, 3>(slot_ptr(g.part, SLOT_P3INIT), nwg_col, MAX_WG, s, red);
-    const double rho = s[0], rr = s[1], bb = s[2];
-    const bool incompat = (st->flags & FLAG_INCOMPAT) != 0;
-    zero_x = (bb == 0.0);
-    const bool bad = !isfinite(rr) || !isfinite(bb);
-    const bool conv = !bad && (incompat || zero_x || rr <= tol2 * bb);
-    if (bad) zero_x = false;
-    if (lead) {
-      st->rho[0] = rho;
-      st->rr[0] = zero_x ? 0.0 : rr;
-      st->rr0 = rr;
-      st->bb = bb;
-      st->iters = 0;
-      if (bad) st->flags |= FLAG_NONFINITE;
-      if (conv || bad || max_iter <= 0) {
-        st->conv_at = 0;
-        st->converged = conv ? 1 : 0;
-      }
-    }
-    if (!zero_x && (conv || bad || max_iter <= 0)) return;
-    stop = zero_x;
-  } else {
-    // rho = <r,M^-1 r> of the residual the last operator pass read, computed
-    // directly from it
-    double s[4];
-    sum_partials<C::NT, 4>(slot_ptr(g.part, SLOT_P3), nwg_col, MAX_WG, s, red);
-    const double rho = s[3];
-    alpha = rho / s[0];
-    const double rhon = rho - 2.0 * alpha * s[1] + alpha * alpha * s[2];
-    beta = rhon / rho;
-    const bool bad = !isfinite(rhon) || !isfinite(alpha);
-    stop = bad || it >= max_iter || it >= st->budget;
-    if (lead) {
-      if (bad) st->flags |= FLAG_NONFINITE;
-      st->rho[it & 1] = rhon;
-      st->iters = it;
-      if (stop) {
-        st->conv_at = it;
-        st->converged = 0;
-      }
+  cd rv[C::EP];
+  colP_gload<C>(rv, rh, kx0, g.h);
+  double s[3];
+  sum_partials<C::NT, 3>(slot_ptr(g.part, SLOT_P3INIT), nwg_col, MAX_WG, s, red);
+  const double rho = s[0], rr = s[1], bb = s[2];
+  const bool incompat = (st->flags & FLAG_INCOMPAT) != 0;
+  bool zero_x = (bb == 0.0);
+  const bool bad = !isfinite(rr) || !isfinite(bb);
+  const bool conv = !bad && (incompat || zero_x || rr <= tol2 * bb);
+  if (bad) zero_x = false;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rho[0] = rho;
+    st->rr[0] = zero_x ? 0.0 : rr;
+    st->rr0 = rr;
+    st->bb = bb;
+    st->iters = 0;
+    if (bad) st->flags |= FLAG_NONFINITE;
+    if (conv || bad || max_iter <= 0) {
+      st->conv_at = 0;
+      st->converged = conv ? 1 : 0;
     }
   }
-  const T a = (T)alpha, bt = (T)beta;
-  double rrp[1] = {0.0};
+  if (zero_x) {
+#pragma unroll
+    for (int i = 0; i < C::EP; ++i) {
+      const int p = threadIdx.x + i * C::NT;
+      const int kx = kx0 + p / NY;
+      if (p < C::CN && kx < g.h) xh[(size_t)kx * NY + p % NY] = vzero<cd>();
+    }
+  }
+  if (conv || bad || max_iter <= 0) return;
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
     const int c = p / NY, ky = p % NY;
     const int kx = kx0 + c;
-    V d = vzero<V>();
-    if (p < C::CN && kx < g.h) {
-      const size_t idx = (size_t)kx * NY + ky;
-      if (zero_x) {
-        xh[idx] = vzero<V>();
-      } else {
-        V rv = rv0[i];
-        if (!first) {
-          d = dv0[i];
-          xh[idx] = add(xv[i], scl(d, a));
-          rv = sub(rv, scl(qv[i], a));
-          rh[idx] = rv;
-          rrp[0] += (kx == 0 ? 1.0 : 2.0) * ((double)rv.x * rv.x + (double)rv.y * rv.y);
-        }
-        if (!stop) {
-          const T sig = (T)precond_symbol_inv(K, xi_col(kx, g.lx), xi_tilde(ky, NY, g.ly));
-          d = add(scl(rv, sig), scl(d, bt));
-          dh[idx] = d;
-        }
-      }
-    }
-    if (!stop && p < C::CN) put_grad<C>(buf, c, ky, kx, d, g);
-  }
-  if (!first && !zero_x) {
-    block_sum<C::NT, 1>(rrp, red);
-    write_partials<C::NT>(slot_ptr(g.part, SLOT_RR), rrp, 1);
-  }
-  if (stop) {
-    tclk_end(g, 2, tit);
-    return;
+    if (p < C::CN)
+      put_grad<C>(buf, c, ky, kx, scl(rv[i], precond_symbol_inv(K, xi_col(kx, g.lx), xi_tilde(ky, NY, g.ly))), g);
   }
   __syncthreads();
-  lds_fft<T, +1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+  lds_fft<double, +1, NY, C::NB, C::LS, C::NT>(buf, tw, g.twn);
   colT_store<C, 2>(buf, Gx, Gy, kx0, g.h);
-  tclk_end(g, 2, tit);
 }
-template <int NY, typename T, int CV>
-__global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) k_col_update(Geo g, int first, cx<T>* xh, cx<T>* rh, cx<T>* dh,
-                                                    const cx<T>* __restrict__ qh, cx<T>* Gx, cx<T>* Gy, int it,
+template <int NY>
+__global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) k_col_start(Geo g, const cd* __restrict__ rh, cd* xh, cd* Gx, cd* Gy,
                                                     int max_iter, double tol2, int nwg_col) {
-  col_update_body<NY, T, CV>(g, first, xh, rh, dh, qh, Gx, Gy, it, max_iter, tol2, nwg_col);
+  col_start_body<NY>(g, rh, xh, Gx, Gy, max_iter, tol2, nwg_col);
 }
-template <int NY, typename T, int CV>
-__global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_update(const UpdArgs* __restrict__ A, int first, int it, int max_iter, double tol2, int nwg_col) {
-  const UpdArgs& a = A[blockIdx.y];
-  col_update_body<NY, T, CV>(a.g, first, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (const cx<T>*)a.qh, (cx<T>*)a.Gx, (cx<T>*)a.Gy, it, max_iter, tol2, nwg_col);
+template <int NY>
+__global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) kb_col_start(const IterArgs* __restrict__ A, int max_iter, double tol2, int nwg_col) {
+  const IterArgs& a = A[blockIdx.y];
+  col_start_body<NY>(a.g, (const cd*)a.rh, (cd*)a.xh, (cd*)a.M0, (cd*)a.M1, max_iter, tol2, nwg_col);
 }
 
 // Start of one correction of the mixed-precision solve (iterative refinement
@@ -1006,8 +778,8 @@ __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_update(const UpdA
 // or S is incompatible, or the values are not finite) the solve is over: the
 // status records the outcome and every later inner launch is a no-op.
 // Otherwise the inner right-hand side is r / ||r|| in FP32, the inner
-// iterate starts at 0, its first direction is M^-1 r with the gradient of it
-// in the FP32 mixed buffers, and the inner stopping threshold (a relative
+// iterate starts at 0, the gradient of M^-1 r goes to the FP32 mixed buffers
+// for the first row pass, and the inner stopping threshold (a relative
 // residual of tol_in on the unit right-hand side, kept in status.bb for the
 // passes' test with tol2 = 1) asks for the reduction that reaches tol2 with a
 // margin of 2, but no less than `floor_in`.  A residual no smaller than the
@@ -1018,7 +790,7 @@ __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_update(const UpdA
 // Status fields read here are written only by other launches.
 template <int NY>
 __device__ __forceinline__ void col_refine_start_body(Geo g, const cd* __restrict__ r64, cd* x64,
-                                                          cx<float>* x32, cx<float>* r32, cx<float>* d32,
+                                                          cx<float>* x32, cx<float>* r32,
                                                           cx<float>* Gx, cx<float>* Gy, double tol2,
                                                           double floor_in, int max_iter, int nwg_col) {
   using C = ColCfg<NY, 2>;
@@ -1092,7 +864,6 @@ __device__ __forceinline__ void col_refine_start_body(Geo g, const cd* __restric
       const double ux = rv[i].x * scale, uy = rv[i].y * scale;
       r32[idx] = mk<float>((float)ux, (float)uy);
       d = mk<float>((float)(sig * ux), (float)(sig * uy));
-      d32[idx] = d;
       x32[idx] = vzero<V>();
     }
     if (p < C::CN) put_grad<C>(buf, c, ky, kx, d, g);
@@ -1103,15 +874,15 @@ __device__ __forceinline__ void col_refine_start_body(Geo g, const cd* __restric
 }
 template <int NY>
 __global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) k_col_refine_start(Geo g, const cd* __restrict__ r64, cd* x64,
-                                                          cx<float>* x32, cx<float>* r32, cx<float>* d32,
+                                                          cx<float>* x32, cx<float>* r32,
                                                           cx<float>* Gx, cx<float>* Gy, double tol2,
                                                           double floor_in, int max_iter, int nwg_col) {
-  col_refine_start_body<NY>(g, r64, x64, x32, r32, d32, Gx, Gy, tol2, floor_in, max_iter, nwg_col);
+  col_refine_start_body<NY>(g, r64, x64, x32, r32, Gx, Gy, tol2, floor_in, max_iter, nwg_col);
 }
 template <int NY>
 __global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) kb_col_refine_start(const RefStartArgs* __restrict__ A, double tol2, double floor_in, int max_iter, int nwg_col) {
   const RefStartArgs& a = A[blockIdx.y];
-  col_refine_start_body<NY>(a.g, (const cd*)a.r64, (cd*)a.x64, (cx<float>*)a.x32, (cx<float>*)a.r32, (cx<float>*)a.d32, (cx<float>*)a.Gx, (cx<float>*)a.Gy, tol2, floor_in, max_iter, nwg_col);
+  col_refine_start_body<NY>(a.g, (const cd*)a.r64, (cd*)a.x64, (cx<float>*)a.x32, (cx<float>*)a.r32, (cx<float>*)a.Gx, (cx<float>*)a.Gy, tol2, floor_in, max_iter, nwg_col);
 }
 
 // End of one correction: x64 += ||r|| e32 (status.rscale), then the gradient
@@ -1299,36 +1070,6 @@ __global__ void __launch_bounds__((ColCfg<NY, 2>::NT)) k_col_gradnorm(Geo g, con
   write_partials<C::NT>(eslot, s, 1);
 }
 
-// ================================================================ launchers
-#define NF_DISPATCH(N, MACRO)                \
-  switch (N) {                               \
-    case 8: MACRO(8); break;                 \
-    case 16: MACRO(16); break;               \
-    case 32: MACRO(32); break;               \
-    case 64: MACRO(64); break;               \
-    case 128: MACRO(128); break;             \
-    case 256: MACRO(256); break;             \
-    case 512: MACRO(512); break;             \
-    case 1024: MACRO(1024); break;           \
-    case 2048: MACRO(2048); break;           \
-    case 4096: MACRO(4096); break;           \
-    case 50: MACRO(50); break;               \
-    case 100: MACRO(100); break;             \
-    case 200: MACRO(200); break;             \
-    case 400: MACRO(400); break;             \
-    case 800: MACRO(800); break;             \
-    case 1600: MACRO(1600); break;           \
-    default: return hipErrorInvalidValue;    \
-  }
-
-// Launch through hipExtLaunchKernelGGL when a start/stop event pair is given
-// (the events are then timestamped by the dispatch itself).
-#define NF_LAUNCH(K, GRID, BLK, S, E0, E1, ...)                                   \
-  do {                                                                             \
-    if (E0) hipExtLaunchKernelGGL(K, GRID, BLK, 0, S, E0, E1, 0, __VA_ARGS__);     \
-    else hipLaunchKernelGGL(K, GRID, BLK, 0, S, __VA_ARGS__);                      \
-  } while (0)
-
 static int row_threads(int nx, int nf) {
   const int t = row_tile(nx, nf) / 8 * nf;
   return t > 1024 ? 1024 : t;
@@ -1359,11 +1100,13 @@ int col_nwg_var(const Geo& g, int cv) {
 }
 bool flux_var_valid(const Geo& g, bool f32, int rv) {
   if (rv == VAR_DEFAULT) return true;
+  if (rv >= RV_SMALL) return rv < NRV && small_ok(rv_rows(g.nx, rv), g.nx / 2) && g.nz == 1;
   const int es = f32 ? 8 : 16;
   return var_size(g.nx) && g.nz == 1 && rv_ok(g.nx, g.ny, rv, es);
 }
 bool div_var_valid(const Geo& g, bool f32, int cv) {
   if (cv == VAR_DEFAULT) return true;
+  if (cv >= CV_SMALL) return cv < NCV && small_ok(cv_cols(g.ny, cv), g.ny) && g.nz == 1;
   const int es = f32 ? 8 : 16;
   return var_size(g.ny) && g.nz == 1 && cv_ok(g.ny, g.h, cv, es);
 }
@@ -1376,168 +1119,31 @@ hipError_t launch_fill_doubles(double* p, size_t n, double v, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Variant dispatch of the PCG-loop passes: a switch over the variant code that
-// instantiates only the variants that exist for the size and real type.
-template <int NX, typename T, int RV>
-static hipError_t flux_go(const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const T* r, int it, double* kslot,
-                          int nwg_col, double tol2, float* lo, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if constexpr (flux_var_exists<NX, RV, (int)sizeof(cx<T>)>()) {
-    const dim3 grid(row_nwg_var(g, RV)), blk(FluxCfg<NX, RV>::NT);
-    NF_LAUNCH((k_row_flux<NX, T, RV>), grid, blk, s, e0, e1, g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
-}
-template <int NX, typename T>
-static hipError_t flux_var(int rv, const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const T* r, int it,
-                           double* kslot, int nwg_col, double tol2, float* lo, hipStream_t s, hipEvent_t e0,
-                           hipEvent_t e1) {
-  switch (rv) {
-#define V_(K) \
-  case K: return flux_go<NX, T, K>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo, s, e0, e1);
-    V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11)
-#undef V_
-    default: return hipErrorInvalidValue;
-  }
-}
-template <int NX, typename T, int RV>
-static hipError_t fluxb_go(const Geo& g, const FluxArgs* A, int count, int it, int nwg_col, double tol2,
-                           hipStream_t s) {
-  if constexpr (flux_var_exists<NX, RV, (int)sizeof(cx<T>)>()) {
-    const dim3 grid(row_nwg_var(g, RV), count), blk(FluxCfg<NX, RV>::NT);
-    hipLaunchKernelGGL((kb_row_flux<NX, T, RV>), grid, blk, 0, s, A, it, nwg_col, tol2);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
-}
-template <int NX, typename T>
-static hipError_t fluxb_var(int rv, const Geo& g, const FluxArgs* A, int count, int it, int nwg_col, double tol2,
-                            hipStream_t s) {
-  switch (rv) {
-#define V_(K) \
-  case K: return fluxb_go<NX, T, K>(g, A, count, it, nwg_col, tol2, s);
-    V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11)
-#undef V_
-    default: return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T, int CV>
-static hipError_t div_go(const Geo& g, const cx<T>* Fx, const cx<T>* Fy, cx<T>* qh, const cx<T>* dh, cx<T>* rh,
-                         int it, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if constexpr (div_var_exists<NY, CV, (int)sizeof(cx<T>)>()) {
-    const dim3 grid(col_nwg_var(g, CV)), blk(DivCfg<NY, CV>::NT);
-    NF_LAUNCH((k_col_div<NY, false, T, CV>), grid, blk, s, e0, e1, g, Fx, Fy, qh, dh, rh, (const cx<T>*)nullptr, it,
-              0);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T>
-static hipError_t div_var(int cv, const Geo& g, const cx<T>* Fx, const cx<T>* Fy, cx<T>* qh, const cx<T>* dh,
-                          cx<T>* rh, int it, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (cv) {
-#define V_(K) \
-  case K: return div_go<NY, T, K>(g, Fx, Fy, qh, dh, rh, it, s, e0, e1);
-    V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11)
-#undef V_
-    default: return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T, int CV>
-static hipError_t divb_go(const Geo& g, const DivArgs* A, int count, int it, hipStream_t s) {
-  if constexpr (div_var_exists<NY, CV, (int)sizeof(cx<T>)>()) {
-    const dim3 grid(col_nwg_var(g, CV), count), blk(DivCfg<NY, CV>::NT);
-    hipLaunchKernelGGL((kb_col_div<NY, false, T, CV>), grid, blk, 0, s, A, it, 0);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T>
-static hipError_t divb_var(int cv, const Geo& g, const DivArgs* A, int count, int it, hipStream_t s) {
-  switch (cv) {
-#define V_(K) \
-  case K: return divb_go<NY, T, K>(g, A, count, it, s);
-    V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11)
-#undef V_
-    default: return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T, int CV>
-static hipError_t upd_go(const Geo& g, int first, cx<T>* xh, cx<T>* rh, cx<T>* dh, const cx<T>* qh, cx<T>* Gx,
-                         cx<T>* Gy, int it, int max_iter, double tol2, int nwg, hipStream_t s, hipEvent_t e0,
-                         hipEvent_t e1) {
-  if constexpr (div_var_exists<NY, CV, (int)sizeof(cx<T>)>()) {
-    const dim3 grid(col_nwg_var(g, CV)), blk(DivCfg<NY, CV>::NT);
-    NF_LAUNCH((k_col_update<NY, T, CV>), grid, blk, s, e0, e1, g, first, xh, rh, dh, qh, Gx, Gy, it, max_iter, tol2,
-              nwg);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T>
-static hipError_t upd_var(int cv, const Geo& g, int first, cx<T>* xh, cx<T>* rh, cx<T>* dh, const cx<T>* qh,
-                          cx<T>* Gx, cx<T>* Gy, int it, int max_iter, double tol2, int nwg, hipStream_t s,
-                          hipEvent_t e0, hipEvent_t e1) {
-  switch (cv) {
-#define V_(K) \
-  case K: return upd_go<NY, T, K>(g, first, xh, rh, dh, qh, Gx, Gy, it, max_iter, tol2, nwg, s, e0, e1);
-    V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11)
-#undef V_
-    default: return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T, int CV>
-static hipError_t updb_go(const Geo& g, const UpdArgs* A, int count, int first, int it, int max_iter, double tol2,
-                          int nwg, hipStream_t s) {
-  if constexpr (div_var_exists<NY, CV, (int)sizeof(cx<T>)>()) {
-    const dim3 grid(col_nwg_var(g, CV), count), blk(DivCfg<NY, CV>::NT);
-    hipLaunchKernelGGL((kb_col_update<NY, T, CV>), grid, blk, 0, s, A, first, it, max_iter, tol2, nwg);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
-}
-template <int NY, typename T>
-static hipError_t updb_var(int cv, const Geo& g, const UpdArgs* A, int count, int first, int it, int max_iter,
-                           double tol2, int nwg, hipStream_t s) {
-  switch (cv) {
-#define V_(K) \
-  case K: return updb_go<NY, T, K>(g, A, count, first, it, max_iter, tol2, nwg, s);
-    V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11)
-#undef V_
-    default: return hipErrorInvalidValue;
-  }
-}
 // variant codes in use (a variant that cannot run on this grid falls back to the default)
-static int use_rv(const Geo& g, bool f32, int it) {
+int use_rv(const Geo& g, bool f32, int it) {
   const int rv = it >= 0 ? g.var_flux[f32 ? 1 : 0] : VAR_DEFAULT;
   return flux_var_valid(g, f32, rv) ? rv : VAR_DEFAULT;
 }
-static int use_cvd(const Geo& g, bool f32) {
-  const int cv = g.var_div[f32 ? 1 : 0];
-  return div_var_valid(g, f32, cv) ? cv : VAR_DEFAULT;
-}
-static int use_cvu(const Geo& g, bool f32) {
+int use_cv(const Geo& g, bool f32) {
   const int cv = g.var_upd[f32 ? 1 : 0];
   return div_var_valid(g, f32, cv) ? cv : VAR_DEFAULT;
 }
-int rr_nwg(const Geo& g, bool f32) { return col_nwg_var(g, use_cvu(g, f32)); }
+int rr_nwg(const Geo& g, bool f32) { return col_nwg_var(g, use_cv(g, f32)); }
 int flux_var_rows(const Geo& g, int rv) {
   return rv == VAR_DEFAULT ? tile_rows(g.nx / 2, row_tile(g.nx, 2)) : rv_rows(g.nx, rv);
 }
-int flux_var_plan(int rv) { return rv_plan(rv); }
+int flux_var_plan(int rv) { return rv >= RV_SMALL ? 0 : rv_plan(rv); }
 int flux_var_threads(const Geo& g, int rv) {
   const int rt = rv == VAR_DEFAULT ? row_tile(g.nx, 2) : rv_rows(g.nx, rv) * (g.nx / 2);
+  if (rv >= RV_SMALL) return small_threads(rv_rows(g.nx, rv), g.nx / 2);
   const int nt = (rt / 8) * 2 > 1024 ? 1024 : (rt / 8) * 2;
   return nt / (rv == VAR_DEFAULT ? 1 : rv_td(rv));
 }
 int div_var_cols(const Geo& g, int cv) { return cv == VAR_DEFAULT ? col_cols(g.ny) : cv_cols(g.ny, cv); }
-int div_var_threads(const Geo& g, int cv) { return cv == VAR_DEFAULT ? col_threads(g.ny, 2) : 2 * TPF * cv_tm(cv); }
+int div_var_threads(const Geo& g, int cv) {
+  if (cv >= CV_SMALL) return small_threads(cv_cols(g.ny, cv), g.ny);
+  return cv == VAR_DEFAULT ? col_threads(g.ny, 2) : 2 * TPF * cv_tm(cv);
+}
 bool var_grid(const Geo& g) { return g.nz == 1 && (var_size(g.nx) || var_size(g.ny)); }
 
 hipError_t launch_status_reset(const Geo& g, int full, hipStream_t s) {
@@ -1567,30 +1173,6 @@ hipError_t launch_row_c2r(const Geo& g, const void* in, double* f, hipStream_t s
   NF_DISPATCH(g.nx, L_)
 #undef L_
   return hipGetLastError();
-}
-// The operator middle: the initial pass (it < 0, which may write the Kbar
-// partials read with the default workgroup count) uses the default tile, the
-// loop passes the tuned variant; the stopping test of the loop reads the
-// partials of the update's variant.
-hipError_t launch_row_flux(const Geo& g, void* G0, void* G1, const double* m, const double* r, int it,
-                           double* kslot, double tol2, hipStream_t s, hipEvent_t e0, hipEvent_t e1, float* lo) {
-  const int rv = use_rv(g, false, it);
-  const int nwg_col = rr_nwg(g, false);
-#define L_(N) return flux_var<N, double>(rv, g, (cd*)G0, (cd*)G1, m, r, it, kslot, nwg_col, tol2, lo, s, e0, e1)
-  NF_DISPATCH(g.nx, L_)
-#undef L_
-  return hipErrorInvalidValue;
-}
-hipError_t launch_row_flux32(const Geo& g, void* G0, void* G1, const float* m32, const float* r32, int it,
-                             double tol2, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const int rv = use_rv(g, true, it);
-  const int nwg_col = rr_nwg(g, true);
-#define L_(N)                                                                                                  \
-  return flux_var<N, float>(rv, g, (cx<float>*)G0, (cx<float>*)G1, m32, r32, it, (double*)nullptr, nwg_col,    \
-                            tol2, (float*)nullptr, s, e0, e1)
-  NF_DISPATCH(g.nx, L_)
-#undef L_
-  return hipErrorInvalidValue;
 }
 // Split update, pointwise part.  Where the three-field tile holds one row per
 // workgroup (rows of 2048 and more), p is written by a one-field pass first and
@@ -1656,71 +1238,44 @@ hipError_t launch_col_grad(const Geo& g, const void* xh, void* P, void* Gx, void
   }
   return hipGetLastError();
 }
-// The operator end: the initial (INIT) pass uses the default tile, the loop
-// passes the tuned variant.
-hipError_t launch_col_div(const Geo& g, int init, const void* Fx, const void* Fy, void* qh, const void* dh,
-                          void* rh, const void* bh, int it, int nwg_row, hipStream_t s, hipEvent_t e0,
-                          hipEvent_t e1) {
+// The operator end outside the loop (default tile): the residual of the
+// initial iterate (init) or the plain operator apply.
+hipError_t launch_col_div(const Geo& g, int init, const void* Fx, const void* Fy, void* qh, void* rh, const void* bh,
+                          int nwg_row, hipStream_t s) {
+  const dim3 grid(col_nwg(g)), blk(col_threads(g.ny, 2));
   if (init) {
-    const dim3 grid(col_nwg(g)), blk(col_threads(g.ny, 2));
-#define L_(N)                                                                                                  \
-  NF_LAUNCH((k_col_div<N, true, double, VAR_DEFAULT>), grid, blk, s, e0, e1, g, (const cd*)Fx, (const cd*)Fy,  \
-            (cd*)qh, (const cd*)dh, (cd*)rh, (const cd*)bh, it, nwg_row)
+#define L_(N)                                                                                               \
+  hipLaunchKernelGGL((k_col_div<N, true>), grid, blk, 0, s, g, (const cd*)Fx, (const cd*)Fy, (cd*)qh, (cd*)rh, \
+                     (const cd*)bh, nwg_row)
     NF_DISPATCH(g.ny, L_)
 #undef L_
-    return hipGetLastError();
+  } else {
+#define L_(N)                                                                                                \
+  hipLaunchKernelGGL((k_col_div<N, false>), grid, blk, 0, s, g, (const cd*)Fx, (const cd*)Fy, (cd*)qh, (cd*)rh, \
+                     (const cd*)bh, nwg_row)
+    NF_DISPATCH(g.ny, L_)
+#undef L_
   }
-  const int cv = use_cvd(g, false);
+  return hipGetLastError();
+}
+hipError_t launch_col_start(const Geo& g, const void* rh, void* xh, void* Gx, void* Gy, int max_iter, double tol2,
+                            hipStream_t s) {
+  const dim3 grid(col_nwg(g)), blk(col_threads(g.ny, 2));
+  const int nwg = col_nwg(g);
 #define L_(N) \
-  return div_var<N, double>(cv, g, (const cd*)Fx, (const cd*)Fy, (cd*)qh, (const cd*)dh, (cd*)rh, it, s, e0, e1)
+  hipLaunchKernelGGL(k_col_start<N>, grid, blk, 0, s, g, (const cd*)rh, (cd*)xh, (cd*)Gx, (cd*)Gy, max_iter, tol2, nwg)
   NF_DISPATCH(g.ny, L_)
 #undef L_
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
-hipError_t launch_col_div32(const Geo& g, const void* Fx, const void* Fy, void* qh, const void* dh, void* rh, int it,
-                            hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  typedef cx<float> cf;
-  const int cv = use_cvd(g, true);
-#define L_(N) \
-  return div_var<N, float>(cv, g, (const cf*)Fx, (const cf*)Fy, (cf*)qh, (const cf*)dh, (cf*)rh, it, s, e0, e1)
-  NF_DISPATCH(g.ny, L_)
-#undef L_
-  return hipErrorInvalidValue;
-}
-// The update: the first one reads the partials of the INIT pass (default
-// tile), the others those of the operator end's variant.
-hipError_t launch_col_update(const Geo& g, int first, void* xh, void* rh, void* dh, const void* qh, void* Gx,
-                             void* Gy, int it, int max_iter, double tol2, hipStream_t s, hipEvent_t e0,
-                             hipEvent_t e1) {
-  const int cv = use_cvu(g, false);
-  const int nwg = first ? col_nwg(g) : col_nwg_var(g, use_cvd(g, false));
-#define L_(N)                                                                                                    \
-  return upd_var<N, double>(cv, g, first, (cd*)xh, (cd*)rh, (cd*)dh, (const cd*)qh, (cd*)Gx, (cd*)Gy, it,        \
-                            max_iter, tol2, nwg, s, e0, e1)
-  NF_DISPATCH(g.ny, L_)
-#undef L_
-  return hipErrorInvalidValue;
-}
-hipError_t launch_col_update32(const Geo& g, void* xh, void* rh, void* dh, const void* qh, void* Gx, void* Gy, int it,
-                               int max_iter, double tol2, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  typedef cx<float> cf;
-  const int cv = use_cvu(g, true);
-  const int nwg = col_nwg_var(g, use_cvd(g, true));
-#define L_(N)                                                                                                    \
-  return upd_var<N, float>(cv, g, 0, (cf*)xh, (cf*)rh, (cf*)dh, (const cf*)qh, (cf*)Gx, (cf*)Gy, it, max_iter,  \
-                           tol2, nwg, s, e0, e1)
-  NF_DISPATCH(g.ny, L_)
-#undef L_
-  return hipErrorInvalidValue;
-}
-hipError_t launch_col_refine_start(const Geo& g, const void* r64, void* x64, void* x32, void* r32, void* d32,
+hipError_t launch_col_refine_start(const Geo& g, const void* r64, void* x64, void* x32, void* r32,
                                    void* Gx, void* Gy, double tol2, double floor_in, int max_iter, hipStream_t s) {
   typedef cx<float> cf;
   const dim3 grid(col_nwg(g)), blk(col_threads(g.ny, 2));
   const int nwg = col_nwg(g);
 #define L_(N)                                                                                                 \
   hipLaunchKernelGGL(k_col_refine_start<N>, grid, blk, 0, s, g, (const cd*)r64, (cd*)x64, (cf*)x32, (cf*)r32,  \
-                     (cf*)d32, (cf*)Gx, (cf*)Gy, tol2, floor_in, max_iter, nwg)
+                     (cf*)Gx, (cf*)Gy, tol2, floor_in, max_iter, nwg)
   NF_DISPATCH(g.ny, L_)
 #undef L_
   return hipGetLastError();
@@ -1784,56 +1339,21 @@ hipError_t launchb_col_grad(const Geo& g, const ColGradArgs* A, int count, bool 
   }
   return hipGetLastError();
 }
-hipError_t launchb_row_flux(const Geo& g, bool f32, const FluxArgs* A, int count, int it, double tol2,
-                            hipStream_t s) {
-  const int rv = use_rv(g, f32, it);
-  const int nwg_col = rr_nwg(g, f32);
-  if (f32) {
-#define L_(N) return fluxb_var<N, float>(rv, g, A, count, it, nwg_col, tol2, s)
-    NF_DISPATCH(g.nx, L_)
+hipError_t launchb_col_div_init(const Geo& g, const DivArgs* A, int count, hipStream_t s) {
+  const dim3 grid(col_nwg(g), count), blk(col_threads(g.ny, 2));
+  const int nwg_row = row_nwg(g);
+#define L_(N) hipLaunchKernelGGL(kb_col_div<N>, grid, blk, 0, s, A, nwg_row)
+  NF_DISPATCH(g.ny, L_)
 #undef L_
-  } else {
-#define L_(N) return fluxb_var<N, double>(rv, g, A, count, it, nwg_col, tol2, s)
-    NF_DISPATCH(g.nx, L_)
-#undef L_
-  }
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
-hipError_t launchb_col_div(const Geo& g, bool f32, bool init, const DivArgs* A, int count, int it, hipStream_t s) {
-  if (init) {
-    const dim3 grid(col_nwg(g), count), blk(col_threads(g.ny, 2));
-    const int nwg_row = row_nwg(g);
-#define L_(N) hipLaunchKernelGGL((kb_col_div<N, true, double, VAR_DEFAULT>), grid, blk, 0, s, A, it, nwg_row)
-    NF_DISPATCH(g.ny, L_)
+hipError_t launchb_col_start(const Geo& g, const IterArgs* A, int count, int max_iter, double tol2, hipStream_t s) {
+  const dim3 grid(col_nwg(g), count), blk(col_threads(g.ny, 2));
+  const int nwg = col_nwg(g);
+#define L_(N) hipLaunchKernelGGL(kb_col_start<N>, grid, blk, 0, s, A, max_iter, tol2, nwg)
+  NF_DISPATCH(g.ny, L_)
 #undef L_
-    return hipGetLastError();
-  }
-  const int cv = use_cvd(g, f32);
-  if (f32) {
-#define L_(N) return divb_var<N, float>(cv, g, A, count, it, s)
-    NF_DISPATCH(g.ny, L_)
-#undef L_
-  } else {
-#define L_(N) return divb_var<N, double>(cv, g, A, count, it, s)
-    NF_DISPATCH(g.ny, L_)
-#undef L_
-  }
-  return hipErrorInvalidValue;
-}
-hipError_t launchb_col_update(const Geo& g, bool f32, const UpdArgs* A, int count, int first, int it, int max_iter,
-                              double tol2, hipStream_t s) {
-  const int cv = use_cvu(g, f32);
-  const int nwg = (first && !f32) ? col_nwg(g) : col_nwg_var(g, use_cvd(g, f32));
-  if (f32) {
-#define L_(N) return updb_var<N, float>(cv, g, A, count, 0, it, max_iter, tol2, nwg, s)
-    NF_DISPATCH(g.ny, L_)
-#undef L_
-  } else {
-#define L_(N) return updb_var<N, double>(cv, g, A, count, first, it, max_iter, tol2, nwg, s)
-    NF_DISPATCH(g.ny, L_)
-#undef L_
-  }
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 template <int NX>
 static hipError_t splitb_go(const Geo& g, const SplitArgs* A, int count, hipStream_t s) {

@@ -37,6 +37,8 @@ __host__ __device__ constexpr int tile_rows(int h, int t) { return t / h < 1 ? 1
 // passes over three and four fields keep TILE.
 __host__ __device__ constexpr int row_tile(int nx, int nf) { return (nf <= 2 && nx >= 4096) ? nx : TILE; }
 
+// threads rounded up to whole wavefronts
+__host__ __device__ constexpr int waves_of(int t) { return (t + 63) / 64 * 64; }
 template <int NX, int NF, int RT = TILE, int PL = 0, int TD = 1>
 struct RowCfg {
   static constexpr int H = NX / 2;
@@ -46,7 +48,7 @@ struct RowCfg {
   // one radix-8 butterfly per thread, at most 1024 threads (wider tiles give
   // each thread several butterflies per stage); TD divides the thread count
   // (each thread then runs TD times the butterflies)
-  static constexpr int NT = ((RT / 8) * NF > 1024 ? 1024 : (RT / 8) * NF) / TD;
+  static constexpr int NT = ((RT / 8) * NF > 1024 ? 1024 : waves_of((RT / 8) * NF)) / TD;
   // LDS line stride: room for the FFT's padded layout, rounded so that the R
   // rows a group of 8 lanes touches in the row-interleaved phases (transposed
   // and paired loads and stores, consecutive lanes running over the rows of
@@ -70,14 +72,15 @@ using Row2D = RowCfg<NX, NF, row_tile(NX, NF)>;
 // rather than 4.
 __host__ __device__ constexpr int col_tm_default(int ny) { return ny >= 4096 ? 2 : 1; }
 __host__ __device__ constexpr int col_threads(int ny, int nf) { return TPF * nf * col_tm_default(ny); }
-template <int NY, int NF, int CT = TILE, int PL = 0, int TM = 0>
+template <int NY, int NF, int CT = TILE, int PL = 0, int TM = 0, int NTV = 0>
 struct ColCfg {
   static constexpr int C0 = CT / NY;
   static constexpr int C = C0 < 1 ? 1 : (C0 > 64 ? 64 : C0);   // columns per workgroup
   static constexpr int PLAN = PL;                               // radix plan of the y transforms
   static constexpr int NYv = NY;
-  // TM: thread multiple of the tile (0: the default of the column length)
-  static constexpr int NT = TPF * NF * (TM > 0 ? TM : col_tm_default(NY));
+  // TM: thread multiple of the tile (0: the default of the column length);
+  // NTV: thread count, if not that of the default tile
+  static constexpr int NT = NTV > 0 ? NTV : TPF * NF * (TM > 0 ? TM : col_tm_default(NY));
   static constexpr int LS = lpad_use(NY) ? lpad_len(NY) : NY;   // room for the FFT's padded layout
   static constexpr int CN = C * NY;                             // elements per field in the block
   static constexpr int NB = NF * C;                             // LDS lines
@@ -86,13 +89,13 @@ struct ColCfg {
 };
 
 // ---------------------------------------------------------------- tuned variants
-// The PCG-loop passes (operator middle, operator end, update) come in variants
-// that a run-time tuner chooses between per grid shape and real type:
-//   row variant rv (operator middle): rows per workgroup RD/2, RD or 2 RD for
+// The PCG-loop passes (row pass, column pass) come in variants that a run-time
+// tuner chooses between per grid shape and real type:
+//   row variant rv (row pass): rows per workgroup RD/2, RD or 2 RD for
 //     rv % 3 = 0, 1, 2 (RD the default rows of Row2D<NX, 2>); rv / 3 = 0: radix
 //     plan 0, 1: plan 1, 2: plan 0 with half the threads, for tiles that would
 //     have 1024 threads (whose 128-register limit per thread makes them spill);
-//   column variant cv (operator end, update): columns per workgroup CD/2, CD or
+//   column variant cv (column pass): columns per workgroup CD/2, CD or
 //     2 CD for cv % 3 = 0, 1, 2 (CD the default of ColCfg<NY, 2>); cv / 3 = 0:
 //     radix plan 0, 1: plan 1, 2 and 3: plan 0 with twice and four times the
 //     threads (long columns, where each thread of the default tile would
@@ -100,20 +103,28 @@ struct ColCfg {
 // Variant 1 (default tile, plan 0) is the untuned pass.  Variants that would
 // repeat another (a radix plan without an alternative), fall below one row or
 // column, leave threads without a radix-8 butterfly, or exceed the LDS of a
-// workgroup do not exist.  Row variants use the codes below 9 only.
-enum { LDS_LIMIT = 160 * 1024 };  // VAR_DEFAULT, NVAR: nf_internal.h
+// workgroup do not exist.
+// Small tiles, with the threads that fit them (one radix-8 butterfly each): row
+// variants 9, 10, 11 hold RD/2, RD/4, RD/8 rows, column variants 12, 13, 14
+// CD/2, CD/4, CD/8 columns.  They exist for every size and are not part of the
+// public codes.
+enum { LDS_LIMIT = 160 * 1024 };  // VAR_DEFAULT, NVAR, RV_SMALL, CV_SMALL: nf_internal.h
+// threads of a small tile of `lines` lines of h elements over two fields
+__host__ __device__ constexpr int small_threads(int lines, int h) { return waves_of(lines * h / 8 * 2); }
 
 __host__ __device__ constexpr int rv_rows(int nx, int rv) {
   const int rd = tile_rows(nx / 2, row_tile(nx, 2));
+  if (rv >= RV_SMALL) return rd >> (rv - RV_SMALL + 1);
   return rv % 3 == 0 ? rd / 2 : (rv % 3 == 1 ? rd : 2 * rd);
 }
 __host__ __device__ constexpr int cv_cols_default(int ny) {
   return TILE / ny < 1 ? 1 : (TILE / ny > 64 ? 64 : TILE / ny);
 }
 __host__ __device__ constexpr int cv_cols(int ny, int cv) {
+  if (cv >= CV_SMALL) return cv_cols_default(ny) >> (cv - CV_SMALL + 1);
   return cv % 3 == 0 ? cv_cols_default(ny) / 2 : (cv % 3 == 1 ? cv_cols_default(ny) : 2 * cv_cols_default(ny));
 }
-// LDS bytes of the operator-middle and operator-end passes for element size es
+// LDS bytes of the row and column passes for element size es
 __host__ __device__ constexpr int flux_lds(int nx, int rows, int es) {
   return 2 * rows * ((lpad_use(nx / 2) ? lpad_len(nx / 2) + 1 : nx / 2 + 2) + 7) * es;
 }
@@ -124,14 +135,16 @@ __host__ __device__ constexpr int cv_plan(int cv) { return cv / 3 == 1 ? 1 : 0; 
 __host__ __device__ constexpr int cv_tm(int cv) { return cv / 3 == 2 ? 2 : (cv / 3 == 3 ? 4 : 1); }
 __host__ __device__ constexpr int rv_plan(int rv) { return rv / 3 == 1 ? 1 : 0; }
 __host__ __device__ constexpr int rv_td(int rv) { return rv / 3 == 2 ? 2 : 1; }
+// small tiles: at least one line, and at least half a wavefront of butterflies
+__host__ __device__ constexpr bool small_ok(int lines, int h) { return lines >= 1 && lines * h / 8 * 2 >= 32; }
 __host__ __device__ constexpr bool rv_ok(int nx, int ny, int rv, int es) {
-  return rv >= 0 && rv < 9 && (rv / 3 != 1 || plan_has_alt(ilog2(nx / 2))) && rv_rows(nx, rv) >= 1 &&
+  return rv >= 0 && rv < RV_SMALL && (rv / 3 != 1 || plan_has_alt(ilog2(nx / 2))) && rv_rows(nx, rv) >= 1 &&
          rv_rows(nx, rv) <= 64 && (rv % 3 != 2 || rv_rows(nx, rv) <= ny) &&
          (rv / 3 != 2 || rv_rows(nx, rv) * (nx / 2) / 8 * 2 >= 1024) &&
          flux_lds(nx, rv_rows(nx, rv), es) + 4096 <= LDS_LIMIT;
 }
 __host__ __device__ constexpr bool cv_ok(int ny, int h, int cv, int es) {
-  return cv >= 0 && cv < NVAR && (cv / 3 != 1 || plan_has_alt(ilog2(ny))) && cv_cols(ny, cv) >= 1 &&
+  return cv >= 0 && cv < CV_SMALL && (cv / 3 != 1 || plan_has_alt(ilog2(ny))) && cv_cols(ny, cv) >= 1 &&
          cv_cols(ny, cv) <= 64 && (cv % 3 != 2 || cv_cols(ny, cv) <= h) &&
          cv_cols(ny, cv) * ny >= cv_tm(cv) * TILE && div_lds(ny, cv_cols(ny, cv), es) + 4096 <= LDS_LIMIT;
 }
@@ -140,18 +153,24 @@ __host__ __device__ constexpr bool var_size(int n) { return n >= 256 && n <= 409
 // configurations of the variants (the default is exactly the untuned tile)
 template <int NX, int RV>
 using FluxCfg = typename std::conditional<RV == VAR_DEFAULT, Row2D<NX, 2>,
-                                          RowCfg<NX, 2, rv_rows(NX, RV) * (NX / 2), rv_plan(RV), rv_td(RV)>>::type;
+                                          RowCfg<NX, 2, rv_rows(NX, RV) * (NX / 2), RV >= RV_SMALL ? 0 : rv_plan(RV),
+                                                 RV >= RV_SMALL ? 1 : rv_td(RV)>>::type;
 template <int NY, int CV>
-using DivCfg = typename std::conditional<CV == VAR_DEFAULT, ColCfg<NY, 2>,
-                                         ColCfg<NY, 2, cv_cols(NY, CV) * NY, cv_plan(CV), cv_tm(CV)>>::type;
+using DivCfg = typename std::conditional<
+    CV == VAR_DEFAULT, ColCfg<NY, 2>,
+    typename std::conditional<(CV >= CV_SMALL),
+                              ColCfg<NY, 2, cv_cols(NY, CV) * NY, 0, 1, small_threads(cv_cols(NY, CV), NY)>,
+                              ColCfg<NY, 2, cv_cols(NY, CV) * NY, cv_plan(CV), cv_tm(CV)>>::type>::type;
 // variants that can be built for a size (the row count against Ny is checked at run time)
 template <int NX, int RV, int ES>
 constexpr bool flux_var_exists() {
-  return RV == VAR_DEFAULT || (var_size(NX) && rv_ok(NX, 1 << 20, RV, ES));
+  return RV == VAR_DEFAULT || (RV >= RV_SMALL ? RV < NRV && small_ok(rv_rows(NX, RV), NX / 2)
+                                              : var_size(NX) && rv_ok(NX, 1 << 20, RV, ES));
 }
 template <int NY, int CV, int ES>
 constexpr bool div_var_exists() {
-  return CV == VAR_DEFAULT || (var_size(NY) && cv_ok(NY, 1 << 20, CV, ES));
+  return CV == VAR_DEFAULT || (CV >= CV_SMALL ? CV < NCV && small_ok(cv_cols(NY, CV), NY)
+                                              : var_size(NY) && cv_ok(NY, 1 << 20, CV, ES));
 }
 
 // first-derivative wavenumber (Nyquist zeroed) and full wavenumber
@@ -429,5 +448,28 @@ __device__ __forceinline__ double precond_symbol_inv(const double* K, double xx,
   const double s = K[0] * xx * xx + 2.0 * K[1] * xx * yy + K[2] * yy * yy;
   return s > 0.0 ? 1.0 / s : 0.0;
 }
+
+// Switch over the transform lengths of the 2D passes.
+#define NF_DISPATCH(N, MACRO)                \
+  switch (N) {                               \
+    case 8: MACRO(8); break;                 \
+    case 16: MACRO(16); break;               \
+    case 32: MACRO(32); break;               \
+    case 64: MACRO(64); break;               \
+    case 128: MACRO(128); break;             \
+    case 256: MACRO(256); break;             \
+    case 512: MACRO(512); break;             \
+    case 1024: MACRO(1024); break;           \
+    case 2048: MACRO(2048); break;           \
+    case 4096: MACRO(4096); break;           \
+    case 50: MACRO(50); break;               \
+    case 100: MACRO(100); break;             \
+    case 200: MACRO(200); break;             \
+    case 400: MACRO(400); break;             \
+    case 800: MACRO(800); break;             \
+    case 1600: MACRO(1600); break;           \
+    default: return hipErrorInvalidValue;    \
+  }
+
 
 }  // namespace nf

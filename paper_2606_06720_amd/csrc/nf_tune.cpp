@@ -1,10 +1,10 @@
 // Run-time tuner of the tile variants of the PCG-loop passes (2D grids).
 //
 // For a grid shape and the real type of its inner solve, every variant of the
-// operator middle (rows per workgroup, radix plan of the x transforms) and of
-// the operator end and update (columns per workgroup, radix plan of the y
-// transforms) that exists for the shape is timed on the new handle's own
-// buffers, and the fastest of each pass is kept.  The default tile stays unless
+// row pass (rows per workgroup, radix plan of the x transforms) and of the
+// column pass (columns per workgroup, radix plan of the y transforms) that
+// exists for the shape is timed on the new handle's own buffers, and the
+// fastest of each pass is kept.  The default tile stays unless
 // a variant is more than 3% faster.  By default each candidate is timed with
 // three concurrent launches, each on its own copy of the buffers, so that the
 // choice holds for solves that share the GPU (ensembles, concurrent
@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <climits>
+#include <cstddef>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -192,12 +193,12 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
   // a running solver state for the loop passes: no stop recorded
   TCHK(launch_status_reset(G, 1, s));
   TCHK(hipStreamSynchronize(s));
-  for (int pass = 0; pass < 3; ++pass) {
-    if (pass == 2) {
-      // partial sums of the operator end that give the update finite,
-      // non-stopping PCG scalars (the timed operator end overwrote them)
-      TCHK(launch_fill_doubles(slot_ptr(g->part, SLOT_P3), (size_t)SLOT_K * MAX_WG, 1.0, s));
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1) {
+      // totals that give the column pass finite, non-stopping PCG scalars
+      TCHK(launch_fill_doubles(slot_ptr(g->part, SLOT_P3), (size_t)MAX_WG, 1.0, s));
       TCHK(launch_status_reset(G, 1, s));
+      TCHK(launch_fill_doubles((double*)((char*)g->st + offsetof(DevStatus, rho)), 4, 1.0, s));
       TCHK(hipStreamSynchronize(s));
     }
     double best[NVAR];
@@ -218,19 +219,12 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
                        : launch_row_flux(G, b.M0, b.M1, (const double*)b.mr, (const double*)b.mr + 2 * n, 0,
                                          nullptr, 0.0, ss[k]);
           }, &ms, clear, nclear));
-        } else if (pass == 1) {
-          G.var_div[k32] = v;
-          TCHK(time_pass(ss, e0, e1, ej, [&](int k) {
-            const TuneBufs& b = bufs[k];
-            return f32 ? launch_col_div32(G, b.M0, b.M1, b.Q, b.D, b.R, 0, ss[k])
-                       : launch_col_div(G, 0, b.M0, b.M1, b.Q, b.D, b.R, g->bh, 0, 0, ss[k]);
-          }, &ms, clear, nclear));
         } else {
           G.var_upd[k32] = v;
           TCHK(time_pass(ss, e0, e1, ej, [&](int k) {
             const TuneBufs& b = bufs[k];
-            return f32 ? launch_col_update32(G, b.X, b.R, b.D, b.Q, b.M0, b.M1, 1, INT_MAX, 0.0, ss[k])
-                       : launch_col_update(G, 0, b.X, b.R, b.D, b.Q, b.M0, b.M1, 1, INT_MAX, 0.0, ss[k]);
+            return f32 ? launch_col_iter32(G, b.M0, b.M1, b.X, b.R, b.D, b.Q, 1, INT_MAX, ss[k])
+                       : launch_col_iter64(G, b.M0, b.M1, b.X, b.R, b.D, b.Q, 1, INT_MAX, ss[k]);
           }, &ms, clear, nclear));
         }
         if (best[v] < 0.0 || ms < best[v]) best[v] = ms;
@@ -246,13 +240,15 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
         arg = v;
       }
     const int pick = bmin < 0.97 * best[VAR_DEFAULT] ? arg : VAR_DEFAULT;
-    out->var[pass] = pick;
-    out->ncand[pass] = nc;
-    out->us[pass] = 1e3 * best[pick];
-    out->us_default[pass] = 1e3 * best[VAR_DEFAULT];
+    // the column pass is both the operator end (1) and the update (2) of the record
+    for (int q = pass; q < (pass == 0 ? 1 : 3); ++q) {
+      out->var[q] = pick;
+      out->ncand[q] = nc;
+      out->us[q] = 1e3 * best[pick];
+      out->us_default[q] = 1e3 * best[VAR_DEFAULT];
+    }
     if (pass == 0) G.var_flux[k32] = pick;
-    if (pass == 1) G.var_div[k32] = pick;
-    if (pass == 2) G.var_upd[k32] = pick;
+    if (pass == 1) G.var_div[k32] = G.var_upd[k32] = pick;
   }
   // leave the handle as a fresh one: status, partial sums and iterate cleared
   TCHK(launch_status_reset(G, 1, s));
@@ -319,7 +315,10 @@ int nf_set_tiles(nf_grid* g, int flux_var, int div_var, int update_var) {
   nf::Geo& G = f32 ? g->geo32 : g->geo;
   const int v[3] = {flux_var < 0 ? G.var_flux[k] : flux_var, div_var < 0 ? G.var_div[k] : div_var,
                     update_var < 0 ? G.var_upd[k] : update_var};
-  if (!nf::flux_var_valid(G, f32, v[0]) || !nf::div_var_valid(G, f32, v[1]) || !nf::div_var_valid(G, f32, v[2])) {
+  // the public codes; the small tiles beyond them are set by the tuner only
+  const bool coded = flux_var < nf::RV_SMALL && div_var < nf::CV_SMALL && update_var < nf::CV_SMALL;
+  if (!coded || !nf::flux_var_valid(G, f32, v[0]) || !nf::div_var_valid(G, f32, v[1]) ||
+      !nf::div_var_valid(G, f32, v[2])) {
     g->err = "tile variant does not exist for this grid and precision";
     return NF_EINVAL;
   }

@@ -1,0 +1,54 @@
+"""The two-pass PCG loop against the oracle's textbook PCG, iterate by iterate.
+
+The loop takes its step lengths from the single-reduction recurrences, so the
+first iterations (which start the recurrences) and the last ones (far below the
+tolerances in use, where rounding decides) are the places where it could leave
+the textbook iterates.  Iterates after one to four iterations are compared at
+1e-10 relative L2 (the FP64 bound of the pressure), on grids whose row and column
+tiles have remainders, a single line, or several small lines."""
+
+import numpy as np
+import pytest
+
+import oracle as O
+
+pytestmark = [pytest.mark.gpu, pytest.mark.filterwarnings("ignore::RuntimeWarning")]
+
+TOL = 1e-10
+
+SHAPES = [((8, 8), (1.0, 1.0)), ((50, 16), (1.0, 0.5)), ((64, 64), (1.0, 1.0)), ((200, 128), (1.0, 1.0)),
+          ((256, 512), (1.0, 2.0)), ((800, 32), (1.0, 0.04)), ((16, 2048), (1.0 / 128, 1.0))]
+
+
+def rel(a, b):
+    return float(np.linalg.norm(np.ravel(a - b)) / np.linalg.norm(np.ravel(b)))
+
+
+@pytest.mark.parametrize("n,L", SHAPES)
+def test_first_iterates_and_attainable_accuracy(n, L):
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    rng = np.random.default_rng(41)
+    shape = n[::-1]
+    m = rng.uniform(-1.0, 1.0, (2,) + shape)
+    r = rng.uniform(0.05, 0.15, shape)
+    S = rng.standard_normal(shape)
+    S -= S.mean()
+    p0 = rng.standard_normal(shape)
+    with NF.Grid(n, L) as g:
+        for k in (1, 2, 3, 4):
+            want, io = O.pressure_pcg(m, r, S, p0, 1e-13, k, L)
+            p = T(p0)
+            rc, info = g.pressure_solve(T(m), T(r), T(S), p, rtol=1e-13, max_iter=k, allow_notconv=True)
+            assert info.iters == io.iters
+            assert rel(p.cpu().numpy(), want) <= TOL, k
+            assert abs(info.rel_res - io.rel_res) <= 1e-9 * io.rel_res
+        # a tolerance below the attainable accuracy: the recurrence residual still reaches it
+        want, _ = O.pressure_pcg(m, r, S, None, 1e-13, 4000, L)
+        p = T(np.zeros(shape))
+        rc, info = g.pressure_solve(T(m), T(r), T(S), p, rtol=1e-15, max_iter=4000)
+        assert info.converged and info.true_rel_res <= 1e-11
+        assert rel(p.cpu().numpy(), want) <= TOL
