@@ -360,11 +360,12 @@ const char *nf_batch_last_error(const nf_batch *b);
  * The variants change the work split and the rounding of the transforms and
  * inner products only.
  * nf_set_autotune: 2 (the default) times each candidate's throughput with three
- *   concurrent launches on separate buffers on grids of at most 2^21 points
+ *   concurrent launches on separate buffers on grids of 2^17 to 2^21 points
  *   (the choice for solves that share the GPU, as ensemble partitions and
  *   concurrent handles do; the tuning then allocates two scratch copies of the
- *   loop's buffers, freed before nf_create_grid returns) and alone on larger
- *   grids, which fill the GPU by themselves, each timed launch after an
+ *   loop's buffers, freed before nf_create_grid returns) and alone on the
+ *   others: smaller grids, whose passes are bound by latency, and larger ones,
+ *   which fill the GPU by themselves, there each timed launch after an
  *   untimed fill of a 320 MiB scratch buffer (freed likewise) that clears the
  *   Infinity Cache as the loop's other passes do; 1 times each candidate alone
  *   on every grid; 0 turns tuning off

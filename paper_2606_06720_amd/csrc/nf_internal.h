@@ -275,7 +275,8 @@ int div_var_threads(const Geo& g, int cv);
 // variants in use by the loop (it >= 0), the column pass
 int use_rv(const Geo& g, bool f32, int it);
 int use_cv(const Geo& g, bool f32);
-// whether the grid sizes have tuned variants at all
+// whether an axis length has tuned variants; whether the grid has any
+bool tuned_length(int n);
 bool var_grid(const Geo& g);
 // fill n doubles with a value (a kernel, so that no memset node is recorded)
 hipError_t launch_fill_doubles(double* p, size_t n, double v, hipStream_t s);

@@ -1144,6 +1144,7 @@ int div_var_threads(const Geo& g, int cv) {
   if (cv >= CV_SMALL) return small_threads(cv_cols(g.ny, cv), g.ny);
   return cv == VAR_DEFAULT ? col_threads(g.ny, 2) : 2 * TPF * cv_tm(cv);
 }
+bool tuned_length(int n) { return var_size(n); }
 bool var_grid(const Geo& g) { return g.nz == 1 && (var_size(g.nx) || var_size(g.ny)); }
 
 hipError_t launch_status_reset(const Geo& g, int full, hipStream_t s) {
