@@ -409,7 +409,7 @@ int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
 
 /*
  * Kernel timing: nf_time_kernel(g, k) makes the PCG-loop kernel k (NF_KERNEL_*;
- * 2D: COL_DIV and COL_UPDATE are the same pass)
+ * COL_DIV and COL_UPDATE are the same pass)
  * stamp, for every loop iteration, the start of its first and the end of its
  * last workgroup on the device wall clock; after each PCG loop the handle adds
  * the spans of the launches that did work (launches queued after the solver

@@ -113,7 +113,7 @@ int compute_rhs(nf_grid* g, const double* S) {
   const Geo& G = g->geo;
   if (g->dim == 3) {
     LCHK(g, launch3_row_r2c(G, S, g->mix[0], 1, g->stream));
-    LCHK(g, launch3_ypass(G, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, g->stream));
+    LCHK(g, launch3_ypass(G, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, -1.0, g->stream));
     LCHK(g, launch3_zfwd(G, g->mix[0], g->bh, 1, g->stream));
     return NF_OK;
   }
@@ -130,14 +130,7 @@ enum XSource { X_FROM_P = 0, X_FROM_XH = 1, X_ZERO = 2 };
 // each PCG loop and copied out after it without waiting (pinned buffer, event);
 // the host adds them up before the next copy or when the totals are read, so
 // timing adds no synchronisation to the loop.  Launches queued after the
-// solver stopped (no-ops) are discarded.  The launch events are no longer used.
-int timed_events(nf_grid* g, int which, int it, hipEvent_t* e0, hipEvent_t* e1) {
-  (void)g;
-  (void)which;
-  (void)it;
-  *e0 = *e1 = nullptr;
-  return NF_OK;
-}
+// solver stopped (no-ops) are discarded.
 int timed_reset(nf_grid* g) {
   if (g->timed < 0) return NF_OK;
   LCHK(g, launch_tclk_reset(g->tclk, g->stream));
@@ -192,9 +185,9 @@ int init_residual(nf_grid* g, const double* m, const double* r, float* lo = null
   const Geo& G = g->geo;
   hipStream_t s = g->stream;
   if (g->dim == 3) {
-    LCHK(g, launch3_row_flux(G, false, g->mix[0], g->mix[1], g->mix[2], m, r, -1, 1, lo, s));
-    LCHK(g, launch3_ypass(G, false, 3, -1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, 0.0, -1.0, s));
-    LCHK(g, launch3_zdiv(G, false, 1, g->mix[0], g->mix[1], g->mix[2], g->qh, g->dh, g->rh, g->bh, 0, s));
+    LCHK(g, launch3_row_flux(G, false, g->mix[0], g->mix[1], g->mix[2], m, r, -1, 1, lo, 0.0, s));
+    LCHK(g, launch3_ypass(G, false, 3, -1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, -1.0, s));
+    LCHK(g, launch3_zdiv(G, 1, g->mix[0], g->mix[1], g->mix[2], nullptr, g->rh, g->bh, s));
     return NF_OK;
   }
   LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, -1, slot_ptr(g->part, SLOT_KBAR), 0.0, s, lo));
@@ -228,19 +221,13 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
     if (nk > max_iter - it) nk = max_iter - it;
     for (int k = 0; k < nk; ++k) {
       if (g->dim == 3) {
-        hipEvent_t e0, e1;
         void* const* F = f32 ? g->mix32 : g->mix;
-        LCHK(g, launch3_ypass(G, f32, 3, +1, F[0], F[1], F[2], nullptr, it, 1, tol2, -1.0, s));
-        if ((rc = timed_events(g, NF_KERNEL_ROW_FLUX, it, &e0, &e1))) return rc;
+        LCHK(g, launch3_ypass(G, f32, 3, +1, F[0], F[1], F[2], nullptr, it, it > 0 ? nwg3_ziter(G, f32) : 0, -1.0, s));
         LCHK(g, launch3_row_flux(G, f32, F[0], F[1], F[2], f32 ? (const void*)g->lo : (const void*)m,
-                                 f32 ? (const void*)(g->lo + 3 * n) : (const void*)r, it, 0, nullptr, s, e0, e1));
-        LCHK(g, launch3_ypass(G, f32, 3, -1, F[0], F[1], F[2], nullptr, it, 0, 0.0, -1.0, s));
-        if ((rc = timed_events(g, NF_KERNEL_COL_DIV, it, &e0, &e1))) return rc;
-        LCHK(g, launch3_zdiv(G, f32, 0, F[0], F[1], F[2], f32 ? g->q32 : g->qh, f32 ? g->d32 : g->dh,
-                             f32 ? g->r32 : g->rh, g->bh, it, s, e0, e1));
-        if ((rc = timed_events(g, NF_KERNEL_COL_UPDATE, it, &e0, &e1))) return rc;
-        LCHK(g, launch3_zupdate(G, f32, 0, f32 ? g->x32 : g->xh, f32 ? g->r32 : g->rh, f32 ? g->d32 : g->dh,
-                                f32 ? g->q32 : g->qh, F[0], F[1], F[2], it + 1, max_iter, tol2, s, e0, e1));
+                                 f32 ? (const void*)(g->lo + 3 * n) : (const void*)r, it, 0, nullptr, tol2, s));
+        LCHK(g, launch3_ypass(G, f32, 3, -1, F[0], F[1], F[2], nullptr, it, nwg3_flux(G, f32), -1.0, s));
+        LCHK(g, launch3_ziter(G, f32, F[0], F[1], F[2], f32 ? g->x32 : g->xh, f32 ? g->r32 : g->rh,
+                              f32 ? g->d32 : g->dh, f32 ? g->q32 : g->qh, it, max_iter, s));
         ++it;
         continue;
       }
@@ -291,7 +278,7 @@ int grad_to_mixed3(nf_grid* g) {
   const Geo& G = g->geo;
   hipStream_t s = g->stream;
   LCHK(g, launch3_zinv(G, 2, g->xh, nullptr, g->mix[0], g->mix[1], g->mix[2], s));
-  LCHK(g, launch3_ypass(G, false, 3, +1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 3, +1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, -1.0, s));
   return NF_OK;
 }
 
@@ -301,7 +288,7 @@ int write_p(nf_grid* g, double* p) {
   hipStream_t s = g->stream;
   if (g->dim == 3) {
     LCHK(g, launch3_zinv(G, 1, g->xh, g->mix[0], nullptr, nullptr, nullptr, s));
-    LCHK(g, launch3_ypass(G, false, 1, +1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+    LCHK(g, launch3_ypass(G, false, 1, +1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_row_c2r(G, g->mix[0], p, s));
     return NF_OK;
   }
@@ -318,7 +305,7 @@ int prepare_iterate(nf_grid* g, XSource src, const double* p) {
   if (g->dim == 3) {
     if (src == X_FROM_P) {
       LCHK(g, launch3_row_r2c(G, p, g->mix[0], 0, s));
-      LCHK(g, launch3_ypass(G, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+      LCHK(g, launch3_ypass(G, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
       LCHK(g, launch3_zfwd(G, g->mix[0], g->xh, 1, s));
     } else if (src == X_ZERO) {
       LCHK(g, launch_zero_spec(G, g->xh, s));
@@ -358,7 +345,7 @@ int pcg_refined(nf_grid* g, const double* m, const double* r, XSource src, const
     rc = init_residual(g, m, r, outer == 0 ? g->lo : nullptr);
     if (rc) return rc;
     if (g->dim == 3)
-      LCHK(g, launch3_zrefine_start(g->geo32, g->rh, g->xh, g->x32, g->r32, g->d32, g->mix32[0], g->mix32[1],
+      LCHK(g, launch3_zrefine_start(g->geo32, g->rh, g->xh, g->x32, g->r32, g->mix32[0], g->mix32[1],
                                     g->mix32[2], tol2, g->inner_floor, max_iter, s));
     else
       LCHK(g, launch_col_refine_start(g->geo32, g->rh, g->xh, g->x32, g->r32, g->mix32[0], g->mix32[1],
@@ -371,7 +358,7 @@ int pcg_refined(nf_grid* g, const double* m, const double* r, XSource src, const
     // x += ||r|| e and the gradient of the new x for the next residual
     if (g->dim == 3) {
       LCHK(g, launch3_zrefine_acc(G, g->xh, g->x32, g->mix[0], g->mix[1], g->mix[2], s));
-      LCHK(g, launch3_ypass(G, false, 3, +1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, 0.0, -1.0, s));
+      LCHK(g, launch3_ypass(G, false, 3, +1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, -1.0, s));
     } else {
       LCHK(g, launch_col_refine_acc(G, g->xh, g->x32, g->mix[0], g->mix[1], s));
     }
@@ -399,8 +386,7 @@ int pcg(nf_grid* g, const double* m, const double* r, XSource src, const double*
   if (rc) return rc;
   const double tol2 = rtol * rtol;
   if (g->dim == 3)
-    LCHK(g, launch3_zupdate(G, false, 1, g->xh, g->rh, g->dh, g->qh, g->mix[0], g->mix[1], g->mix[2], 0, max_iter,
-                            tol2, s));
+    LCHK(g, launch3_zstart(G, g->rh, g->xh, g->mix[0], g->mix[1], g->mix[2], max_iter, tol2, s));
   else
     LCHK(g, launch_col_start(G, g->rh, g->xh, g->mix[0], g->mix[1], max_iter, tol2, s));
   DevStatus fin;
@@ -408,9 +394,10 @@ int pcg(nf_grid* g, const double* m, const double* r, XSource src, const double*
   if (rc) return rc;
   if (!fin.converged && fin.conv_at == max_iter && max_iter > 0 && !(fin.flags & (FLAG_NONFINITE | FLAG_INCOMPAT))) {
     // stopped by max_iter: take the stopping test on the final residual here
-    if (g->dim == 3)
+    if (g->dim == 3) {
+      LCHK(g, launch3_sum_tot(G, SLOT_RR, 1, nwg3_ziter(G, false), s));
       LCHK(g, launch3_copy_tot(G, SLOT_RR, 1, 11, s));
-    else
+    } else
       LCHK(g, launch_sum_slot(G, slot_ptr(g->part, SLOT_RR), 1, rr_nwg(G, false), 11, s));
     rc = read_status(g, &fin);
     if (rc) return rc;
@@ -478,11 +465,11 @@ int split_update(nf_grid* g, const nf_params* prm, double dt, double* m, double*
     void* const* M = g->mix;
     const double D2dt = prm->D2 * dt;
     LCHK(g, launch3_zinv(G, 3, g->xh, M[0], M[1], M[2], M[3], s));
-    LCHK(g, launch3_ypass(G, false, 4, +1, M[0], M[1], M[2], M[3], -1, 0, 0.0, -1.0, s));
+    LCHK(g, launch3_ypass(G, false, 4, +1, M[0], M[1], M[2], M[3], -1, 0, -1.0, s));
     LCHK(g, launch3_row_split(G, M[0], M[1], M[2], M[3], m, p, prm->c2 * dt, prm->gamma, dt, std::exp(-dt), D2dt, s));
-    LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, D2dt, s));
+    LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, D2dt, s));
     LCHK(g, launch3_zheat(G, M[0], M[1], M[2], D2dt, s));
-    LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, -1.0, s));
+    LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_row_final(G, M[0], M[1], M[2], m, s));
     return NF_OK;
   }
@@ -543,13 +530,13 @@ int energy3(nf_grid* g, const nf_params* prm, const double* m, const double* r, 
   double* P[3] = {(double*)g->rh, (double*)g->dh, (double*)g->qh};
   void* const* M = g->mix;
   LCHK(g, launch3_zinv(G, 2, g->xh, nullptr, M[0], M[1], M[2], s));
-  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
   for (int c = 0; c < 3; ++c) LCHK(g, launch3_row_c2r(G, M[c], P[c], s));
   LCHK(g, launch3_energy_pt(G, m, r, P[0], P[1], P[2], prm->gamma, s));
   LCHK(g, launch3_copy_tot(G, SLOT_EPT, 3, 4, s));
   for (int c = 0; c < 3; ++c) {
     LCHK(g, launch3_row_r2c(G, m + c * n, M[0], 0, s));
-    LCHK(g, launch3_ypass(G, false, 1, -1, M[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+    LCHK(g, launch3_ypass(G, false, 1, -1, M[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_zfwd(G, M[0], P[c], 0, s));
   }
   LCHK(g, launch3_spec_gradnorm(G, P[0], P[1], P[2], s));
@@ -586,10 +573,10 @@ int grad_phys3(nf_grid* g, const double* f, void* spec, double* const* out) {
   hipStream_t s = g->stream;
   void* const* M = g->mix;
   LCHK(g, launch3_row_r2c(G, f, M[0], 0, s));
-  LCHK(g, launch3_ypass(G, false, 1, -1, M[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 1, -1, M[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
   LCHK(g, launch3_zfwd(G, M[0], spec, 0, s));
   LCHK(g, launch3_zinv(G, 2, spec, nullptr, M[0], M[1], M[2], s));
-  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
   for (int c = 0; c < 3; ++c) LCHK(g, launch3_row_c2r(G, M[c], out[c], s));
   return NF_OK;
 }
@@ -611,11 +598,11 @@ int step_adjoint3(nf_grid* g, const nf_params* prm, double dt, const double* m, 
     HIPCHK(g, hipMemcpyAsync(lam_k, lam_next, 3 * n * sizeof(double), hipMemcpyDeviceToDevice, s));
   LCHK(g, launch_zero_doubles((double*)g->xh, n, s));
   LCHK(g, launch3_zinv(G, 3, g->xh, M[0], M[1], M[2], M[3], s));
-  LCHK(g, launch3_ypass(G, false, 4, +1, M[0], M[1], M[2], M[3], -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 4, +1, M[0], M[1], M[2], M[3], -1, 0, -1.0, s));
   LCHK(g, launch3_row_split(G, M[0], M[1], M[2], M[3], lam_k, (double*)g->qh, 0.0, 1.0, dt, 1.0, D2dt, s));
-  LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, D2dt, s));
+  LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, D2dt, s));
   LCHK(g, launch3_zheat(G, M[0], M[1], M[2], D2dt, s));
-  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
   LCHK(g, launch3_row_final(G, M[0], M[1], M[2], lam_k, s));
   // grad p^k, then the reverse of relaxation and activation: lam_k <- lam_m, Gp <- lam_g
   double* Gp[3] = {(double*)g->rh, (double*)g->dh, (double*)g->qh};
@@ -626,7 +613,7 @@ int step_adjoint3(nf_grid* g, const nf_params* prm, double dt, const double* m, 
   void* F[3] = {g->xh, M[1], M[2]};
   for (int c = 0; c < 3; ++c) {
     LCHK(g, launch3_row_r2c(G, Gp[c], M[0], 0, s));
-    LCHK(g, launch3_ypass(G, false, 1, -1, M[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+    LCHK(g, launch3_ypass(G, false, 1, -1, M[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_zfwd(G, M[0], F[c], 0, s));
   }
   LCHK(g, launch3_spec_divrhs(G, F[0], F[1], F[2], g->bh, s));
@@ -638,7 +625,7 @@ int step_adjoint3(nf_grid* g, const nf_params* prm, double dt, const double* m, 
   rc = write_p(g, mu);
   if (rc) return rc;
   LCHK(g, launch3_zinv(G, 2, g->xh, nullptr, M[0], M[1], M[2], s));
-  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, -1.0, s));
+  LCHK(g, launch3_ypass(G, false, 3, +1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
   double* U[3] = {(double*)g->rh, (double*)g->dh, (double*)g->qh};
   for (int c = 0; c < 3; ++c) LCHK(g, launch3_row_c2r(G, M[c], U[c], s));
   double* P[3] = {(double*)g->xh, (double*)M[3], (double*)g->bh};
@@ -725,8 +712,11 @@ int nf_create_grid(nf_grid** out, int ndim, const int64_t n[3], const double L[3
     tmp.nz = g->nz;
     tmp.h = g->h;
     pstride = nwg3_row(tmp);
-    if (nwg3_y(tmp) > pstride) pstride = nwg3_y(tmp);
     if (nwg3_z(tmp) > pstride) pstride = nwg3_z(tmp);
+    for (bool f32 : {false, true}) {
+      if (nwg3_flux(tmp, f32) > pstride) pstride = nwg3_flux(tmp, f32);
+      if (nwg3_ziter(tmp, f32) > pstride) pstride = nwg3_ziter(tmp, f32);
+    }
   }
   const size_t part_doubles = (size_t)NSLOTS * SLOT_K * pstride + NSLOTS * SLOT_K;
   CREATE_CHK(hipMalloc((void**)&g->part, part_doubles * sizeof(double)), NF_ENOMEM);
@@ -813,8 +803,8 @@ int nf_time_kernel(nf_grid* g, int which) {
     if (khz <= 0) return fail(g, NF_EDEVICE, "device wall-clock rate unavailable");
     g->wall_khz = (double)khz;
   }
-  // 2D: the operator end and the update are one pass
-  if (which == NF_KERNEL_COL_DIV && g->dim == 2) which = NF_KERNEL_COL_UPDATE;
+  // the operator end and the update are one pass
+  if (which == NF_KERNEL_COL_DIV) which = NF_KERNEL_COL_UPDATE;
   g->timed = which;
   g->geo.tclk = g->geo32.tclk = which >= 0 ? g->tclk : nullptr;
   g->geo.tkind = g->geo32.tkind = which;
@@ -858,7 +848,7 @@ int nf_transform_forward(nf_grid* g, const double* f, double* out) {
   if (rc) return rc;
   if (g->dim == 3) {
     LCHK(g, launch3_row_r2c(g->geo, f, g->mix[0], 0, g->stream));
-    LCHK(g, launch3_ypass(g->geo, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, g->stream));
+    LCHK(g, launch3_ypass(g->geo, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, -1.0, g->stream));
     LCHK(g, launch3_zfwd(g->geo, g->mix[0], out, 0, g->stream));
     HIPCHK(g, hipStreamSynchronize(g->stream));
     return NF_OK;
@@ -876,7 +866,7 @@ int nf_transform_inverse(nf_grid* g, const double* spec, double* f) {
   if (rc) return rc;
   if (g->dim == 3) {
     LCHK(g, launch3_zinv(g->geo, 1, spec, g->mix[0], nullptr, nullptr, nullptr, g->stream));
-    LCHK(g, launch3_ypass(g->geo, false, 1, +1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, g->stream));
+    LCHK(g, launch3_ypass(g->geo, false, 1, +1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, -1.0, g->stream));
     LCHK(g, launch3_row_c2r(g->geo, g->mix[0], f, g->stream));
     HIPCHK(g, hipStreamSynchronize(g->stream));
     return NF_OK;
@@ -916,11 +906,11 @@ int nf_apply_operator(nf_grid* g, const double* m, const double* r, const double
     rc = prepare_iterate(g, X_FROM_P, p);
     if (rc) return rc;
     void* const* M = g->mix;
-    LCHK(g, launch3_row_flux(G, false, M[0], M[1], M[2], m, r, -1, 0, nullptr, s));
-    LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, 0.0, -1.0, s));
-    LCHK(g, launch3_zdiv(G, false, 0, M[0], M[1], M[2], g->qh, g->xh, g->xh, g->bh, 0, s));
+    LCHK(g, launch3_row_flux(G, false, M[0], M[1], M[2], m, r, -1, 0, nullptr, 0.0, s));
+    LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
+    LCHK(g, launch3_zdiv(G, 0, M[0], M[1], M[2], g->qh, nullptr, nullptr, s));
     LCHK(g, launch3_zinv(G, 1, g->qh, M[0], nullptr, nullptr, nullptr, s));
-    LCHK(g, launch3_ypass(G, false, 1, +1, M[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+    LCHK(g, launch3_ypass(G, false, 1, +1, M[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_row_c2r(G, M[0], out, s));
     HIPCHK(g, hipStreamSynchronize(s));
     return NF_OK;
@@ -1176,7 +1166,7 @@ int nf_energy(nf_grid* g, const nf_params* prm, const double* m, const double* p
   if (p) {
     if (g->dim == 3) {
       LCHK(g, launch3_row_r2c(G, p, g->mix[0], 0, s));
-      LCHK(g, launch3_ypass(G, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, 0.0, -1.0, s));
+      LCHK(g, launch3_ypass(G, false, 1, -1, g->mix[0], nullptr, nullptr, nullptr, -1, 0, -1.0, s));
       LCHK(g, launch3_zfwd(G, g->mix[0], g->xh, 0, s));
     } else {
       LCHK(g, launch_row_r2c(G, p, g->mix[0], nullptr, s));

@@ -202,32 +202,34 @@ hipError_t launch_status_reset(const Geo& g, int full, hipStream_t s);
 // Mixed buffers hold [kx][z][y] (after x) or, in place, [kx][z][ky] (after
 // x and y); spectral buffers hold [kx][ky][kz].
 int nwg3_row(const Geo& g);
-int nwg3_y(const Geo& g);
-int nwg3_z(const Geo& g, bool f32 = false);  // workgroups of the z passes (FP32 loop passes: f32)
+int nwg3_z(const Geo& g);
+int nwg3_flux(const Geo& g, bool f32);   // operator middle
+int nwg3_ziter(const Geo& g, bool f32);  // z pass of the PCG loop
 hipError_t launch3_row_r2c(const Geo& g, const double* f, void* out, int schk, hipStream_t s);
 hipError_t launch3_row_c2r(const Geo& g, const void* in, double* f, hipStream_t s);
-// lo: FP32 copies of m (3n) then r (n), written when non-null; kbar: write the Kbar partials
+// lo: FP32 copies of m (3n) then r (n), written when non-null; kbar: write the Kbar partials;
+// tol2: stopping test of the loop (it >= 1)
 hipError_t launch3_row_flux(const Geo& g, bool f32, void* G0, void* G1, void* G2, const void* m, const void* r, int it,
-                            int kbar, float* lo, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+                            int kbar, float* lo, double tol2, hipStream_t s);
 hipError_t launch3_row_split(const Geo& g, void* P, void* G0, void* G1, void* G2, const double* m, double* p_out,
                              double c2dt, double gamma, double dt, double relax1, double D2dt, hipStream_t s);
 hipError_t launch3_row_final(const Geo& g, const void* M0, const void* M1, const void* M2, double* m, hipStream_t s);
-// y passes over nf fields (1..4) in place; dir -1 forward, +1 inverse; stop_test: PCG
-// stopping decision of iteration it (it >= 1); heat_D2dt >= 0: multiply by exp(-D2dt xi_y^2)
+// y passes over nf fields (1..4) in place; dir -1 forward, +1 inverse; nsum > 0: also add up the
+// nsum partials of the pass before (PCG loop, 3 fields); heat_D2dt >= 0: multiply by exp(-D2dt xi_y^2)
 hipError_t launch3_ypass(const Geo& g, bool f32, int nf, int dir, void* F0, void* F1, void* F2, void* F3, int it,
-                         int stop_test, double tol2, double heat_D2dt, hipStream_t s);
+                         int nsum, double heat_D2dt, hipStream_t s);
 // z passes
 hipError_t launch3_zfwd(const Geo& g, const void* in, void* out, int project, hipStream_t s);
 // mode 1: P = x/n; 2: gradient (G0..G2); 3: both
 hipError_t launch3_zinv(const Geo& g, int mode, const void* xh, void* P, void* G0, void* G1, void* G2, hipStream_t s);
-hipError_t launch3_zdiv(const Geo& g, bool f32, int init, const void* F0, const void* F1, const void* F2, void* qh,
-                        const void* dh, void* rh, const void* bh, int it, hipStream_t s, hipEvent_t e0 = nullptr,
-                        hipEvent_t e1 = nullptr);
-hipError_t launch3_zupdate(const Geo& g, bool f32, int first, void* xh, void* rh, void* dh, const void* qh, void* G0,
-                           void* G1, void* G2, int it, int max_iter, double tol2, hipStream_t s,
-                           hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+hipError_t launch3_zdiv(const Geo& g, int init, const void* F0, const void* F1, const void* F2, void* qh, void* rh,
+                        const void* bh, hipStream_t s);
+hipError_t launch3_zstart(const Geo& g, const void* rh, void* xh, void* G0, void* G1, void* G2, int max_iter,
+                          double tol2, hipStream_t s);
+hipError_t launch3_ziter(const Geo& g, bool f32, void* M0, void* M1, void* M2, void* xh, void* rh, void* dh, void* sh,
+                         int it, int max_iter, hipStream_t s);
 hipError_t launch3_zheat(const Geo& g, void* M0, void* M1, void* M2, double D2dt, hipStream_t s);
-hipError_t launch3_zrefine_start(const Geo& g32, const void* r64, void* x64, void* x32, void* r32, void* d32,
+hipError_t launch3_zrefine_start(const Geo& g32, const void* r64, void* x64, void* x32, void* r32,
                                  void* G0, void* G1, void* G2, double tol2, double floor_in, int max_iter,
                                  hipStream_t s);
 hipError_t launch3_zrefine_acc(const Geo& g, void* x64, const void* x32, void* G0, void* G1, void* G2,
@@ -251,7 +253,7 @@ hipError_t launch3_adj2(const Geo& g, const double* m, const double* mu, const d
                         const double* U2, const double* P0, const double* P1, const double* P2, double* lam,
                         double* grad_r, double* grad_S, hipStream_t s);
 // g.tot of a slot from the n partials the passes of the PCG loop store (one
-// workgroup; K = 1 or 7 arrays)
+// workgroup; K = 1, 2, 3 or 7 arrays)
 hipError_t launch3_sum_tot(const Geo& g, int slot, int K, int n, hipStream_t s);
 hipError_t launch_zero_spec(const Geo& g, void* xh, hipStream_t s);
 // row passes (physical <-> mixed)

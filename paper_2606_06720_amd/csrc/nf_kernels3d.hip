@@ -19,7 +19,7 @@
 // Reductions: every workgroup stores its block sums as partials and a
 // one-workgroup pass launched right after the producing pass adds them in
 // index order (deterministic) into the totals (see store_partials).
-#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
 
 #include <climits>
 
@@ -53,9 +53,6 @@ __device__ __forceinline__ double precond3_inv(const double* K, double a, double
 // ---------------------------------------------------------------- z tiles
 // A z tile holds 2 * TILE elements per field: at Nz = 256 that is 8 lines, so
 // the strided gathers and scatters move 128-byte runs (full cache lines).
-// Tiles of 8-byte elements (ES = 8, the FP32 loop passes) hold twice the lines
-// with twice the threads, so that their runs stay 128 bytes long for the same
-// LDS and the same registers per thread.
 template <int NZ, int NF, int ES = 16, int TW = 1>
 struct ZCfg {
   static constexpr int W = ES == 8 ? 2 : 1;
@@ -206,26 +203,63 @@ __global__ void __launch_bounds__(TPF) k3_row_c2r(Geo g, const cd* __restrict__ 
   }
 }
 
-// Operator middle: gradient (mixed, 3 fields) -> physical g -> K g -> mixed,
-// in place.  K = m m^T + r I.  it >= 0: no-op once the solve has stopped.
+// Tile of the operator middle: 128-byte runs through the mixed layout (8 rows of
+// FP64 values, 16 of FP32), with at least 512 and at most TILE (FP64) or
+// 2 TILE (FP32) elements per field, i.e. the same LDS in both precisions.  With
+// TILE elements in both, the FP32 pass moved 64-byte runs at Nx = 256 and took
+// 123 us at 256 x 256 x 128 instead of 113 us.
 template <int NX, typename T>
-__global__ void __launch_bounds__(3 * TPF) k3_row_flux(Geo g, cx<T>* G0, cx<T>* G1, cx<T>* G2,
+struct Flux3 {
+  static constexpr int H = NX / 2;
+  static constexpr int R0 = sizeof(T) == 4 ? 16 : 8;
+  static constexpr int R1 = R0 * H < 512 ? 512 / H : R0;
+  static constexpr int RM = (sizeof(T) == 4 ? 2 : 1) * TILE / H;
+  static constexpr int R2 = R1 < RM ? R1 : RM;
+  static constexpr int R = R2 < 1 ? 1 : (R2 > 64 ? 64 : R2);
+  using C = RowCfg<NX, 3, R * H>;
+};
+template <int NX, typename T>
+using Flux3Cfg = typename Flux3<NX, T>::C;
+
+// Operator middle: gradient (mixed, 3 fields) -> physical g -> K g -> mixed,
+// in place.  K = m m^T + r I.  In the PCG loop (it >= 0) the pass leaves the
+// partials of delta = n sum g . K g in SLOT_P3 and (it >= 1) takes the stopping
+// decision for the residual of the last z pass (its total was added up by the
+// inverse y pass).
+template <int NX, typename T>
+__global__ void __launch_bounds__((Flux3Cfg<NX, T>::NT)) k3_row_flux(Geo g, cx<T>* G0, cx<T>* G1, cx<T>* G2,
                                                      const T* __restrict__ m, const T* __restrict__ r, int it,
-                                                     int kbar, float* lo) {
-  using C = RowCfg<NX, 3>;
+                                                     int kbar, float* lo, double tol2) {
+  using C = Flux3Cfg<NX, T>;
   using V = cx<T>;
   using P = typename vec2<T>::type;
+  constexpr int NW = C::NT / 64;
   if (it >= 0 ? g.st->conv_at <= it : g.st->outer_done != 0) return;
   tclk_start(g, 0, it);
   __shared__ V buf[C::NB * C::LS];
-  __shared__ double red[7 * (C::NT / 64)];
+  __shared__ double red[7 * NW];
+  __shared__ double redd[NW];
   const V* tw = (const V*)g.tw;
   const int rows = g.ny * g.nz;
   const int y0 = xcd_block() * C::R;
   const int nrow = min(C::R, rows - y0);
   const size_t n = (size_t)g.nx * rows;
-  V tv[C::ET];
-  rowT_gload<C>(tv, G0, G1, G2, rows, y0, nrow);
+  V ta[RowPairs<C>::ETP], tb[RowPairs<C>::ETP];
+  rowTP_gload<C>(ta, tb, G0, G1, G2, rows, y0, nrow);
+  if (it >= 1) {
+    const double rr = g.tot[SLOT_RR * SLOT_K];
+    const double bb = g.st->bb;
+    const bool bad = !isfinite(rr);
+    if (bad || rr <= tol2 * bb) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        g.st->rr[0] = rr;
+        g.st->converged = bad ? 0 : 1;
+        if (bad) g.st->flags |= FLAG_NONFINITE;
+        g.st->conv_at = it;
+      }
+      return;
+    }
+  }
   P mx[C::EP], my[C::EP], mz[C::EP], rv[C::EP];
   rowP_gload<C>(mx, m, y0, nrow);
   rowP_gload<C>(my, m + n, y0, nrow);
@@ -245,11 +279,11 @@ __global__ void __launch_bounds__(3 * TPF) k3_row_flux(Geo g, cx<T>* G0, cx<T>* 
       }
     }
   }
-  rowT_put<C>(buf, tv);
+  rowTP_put_pre<C>(buf, ta, tb, tw, g.twn);
   __syncthreads();
-  irfft_pre<T, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
   lds_fft<T, +1, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
   double ks[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  double de[1] = {0.0};
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
@@ -261,9 +295,14 @@ __global__ void __launch_bounds__(3 * TPF) k3_row_flux(Geo g, cx<T>* G0, cx<T>* 
       const V gx = *px, gy = *py, gz = *pz;
       const T a0 = mx[i].x * gx.x + my[i].x * gy.x + mz[i].x * gz.x;
       const T a1 = mx[i].y * gx.y + my[i].y * gy.y + mz[i].y * gz.y;
-      *px = mk<T>(fma(a0, mx[i].x, rv[i].x * gx.x), fma(a1, mx[i].y, rv[i].y * gx.y));
-      *py = mk<T>(fma(a0, my[i].x, rv[i].x * gy.x), fma(a1, my[i].y, rv[i].y * gy.y));
-      *pz = mk<T>(fma(a0, mz[i].x, rv[i].x * gz.x), fma(a1, mz[i].y, rv[i].y * gz.y));
+      const V fx = mk<T>(fma(a0, mx[i].x, rv[i].x * gx.x), fma(a1, mx[i].y, rv[i].y * gx.y));
+      const V fy = mk<T>(fma(a0, my[i].x, rv[i].x * gy.x), fma(a1, my[i].y, rv[i].y * gy.y));
+      const V fz = mk<T>(fma(a0, mz[i].x, rv[i].x * gz.x), fma(a1, mz[i].y, rv[i].y * gz.y));
+      *px = fx;
+      *py = fy;
+      *pz = fz;
+      de[0] += (double)gx.x * fx.x + (double)gx.y * fx.y + (double)gy.x * fy.x + (double)gy.y * fy.y +
+               (double)gz.x * fz.x + (double)gz.y * fz.y;
       if (kbar) {
         const double ax[2] = {mx[i].x, mx[i].y}, ay[2] = {my[i].x, my[i].y}, az[2] = {mz[i].x, mz[i].y};
 #pragma unroll
@@ -279,10 +318,12 @@ __global__ void __launch_bounds__(3 * TPF) k3_row_flux(Geo g, cx<T>* G0, cx<T>* 
       }
     }
   }
+  wave_sums<1>(de, redd);
   __syncthreads();
   lds_fft<T, -1, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
-  rfft_post<T, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
-  rowT_store<C, 3>(buf, G0, G1, G2, rows, y0, nrow);
+  if (it >= 0 && threadIdx.x == 0)
+    g.part[(size_t)SLOT_P3 * SLOT_K * g.pstride + blockIdx.x] = waves_total<NW>(redd) * (double)n;
+  rowTP_store_post<C, 3>(buf, G0, G1, G2, tw, g.twn, rows, y0, nrow);
   if (kbar) store_partials<C::NT, 7>(ks, g, SLOT_KBAR, red);
   tclk_end(g, 0, it);
 }
@@ -434,14 +475,33 @@ __global__ void __launch_bounds__(3 * TPF) k3_row_final(Geo g, const cd* __restr
 }
 
 // ================================================================ y passes
+// Tile of the y passes: 512 FP64 or 256 FP32 elements per field (at least one
+// line).  The lines are contiguous, so a small tile costs no run length, and
+// several workgroups per compute unit drift apart in their load, transform and
+// store phases (1024 -> 512 elements, three FP64 fields of 128 x 128 x 64: 16.3
+// -> 12.4 us; 1024 -> 256, FP32 at 256 x 256 x 128: 38.8 -> 36.4 us).
+template <typename T>
+constexpr int y_tile() { return sizeof(T) == 4 ? 256 : 512; }
+template <int NY, int NF, typename T>
+struct YCfg0 {
+  static constexpr int C0 = y_tile<T>() / NY;
+  static constexpr int C = C0 < 1 ? 1 : (C0 > 64 ? 64 : C0);
+  using type = ColCfg<NY, NF, C * NY, 0, 1, waves_of(NF * C * NY / 8)>;
+};
+template <int NY, int NF, typename T>
+using YCfg = typename YCfg0<NY, NF, T>::type;
+
 // NF fields, lines (kx, z) of length NY, transformed in place (DIR -1 forward,
-// +1 inverse).  stop_test: take the PCG stopping decision of iteration it
-// (it >= 1) from the totals of the last update.  heat_D2dt >= 0: multiply by
-// the y factor exp(-D2dt xi_y^2) of the heat kernel after the transform.
+// +1 inverse).  heat_D2dt >= 0: multiply by the y factor exp(-D2dt xi_y^2) of
+// the heat kernel after the transform.  nsum > 0 (PCG loop): block 0 also adds
+// up the nsum partials the pass before it left, in index order: for DIR > 0
+// ||r||^2 and <r, M^-1 r> of the z pass, for DIR < 0 delta of the row pass.
+// The sums ride on passes that follow their producers anyway, beside their
+// other workgroups; passes of their own took 4.7 us each.
 template <int NY, int NF, int DIR, typename T>
-__global__ void __launch_bounds__(NF * TPF) k3_ypass(Geo g, cx<T>* F0, cx<T>* F1, cx<T>* F2, cx<T>* F3, int it,
-                                                   int stop_test, double tol2, double heat_D2dt) {
-  using C = ColCfg<NY, NF>;
+__global__ void __launch_bounds__((YCfg<NY, NF, T>::NT)) k3_ypass(Geo g, cx<T>* F0, cx<T>* F1, cx<T>* F2, cx<T>* F3, int it,
+                                                   int nsum, double heat_D2dt) {
+  using C = YCfg<NY, NF, T>;
   using V = cx<T>;
   if (it >= 0 && g.st->conv_at <= it) return;
   __shared__ V buf[C::NB * C::LS];
@@ -455,20 +515,6 @@ __global__ void __launch_bounds__(NF * TPF) k3_ypass(Geo g, cx<T>* F0, cx<T>* F1
     const int f = e / C::CN, ee = e % C::CN;
     const int c = ee / NY, ky = ee % NY;
     tv[i] = (e < NF * C::CN && l0 + c < nl) ? pick4<V>(f, F0, F1, F2, F3)[(size_t)(l0 + c) * NY + ky] : vzero<V>();
-  }
-  if (stop_test && it >= 1) {
-    const double rr = g.tot[SLOT_RR * SLOT_K];
-    const double bb = g.st->bb;
-    const bool bad = !isfinite(rr);
-    if (bad || rr <= tol2 * bb) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        g.st->rr[0] = rr;
-        g.st->converged = bad ? 0 : 1;
-        if (bad) g.st->flags |= FLAG_NONFINITE;
-        g.st->conv_at = it;
-      }
-      return;
-    }
   }
 #pragma unroll
   for (int i = 0; i < C::ET; ++i) {
@@ -487,6 +533,23 @@ __global__ void __launch_bounds__(NF * TPF) k3_ypass(Geo g, cx<T>* F0, cx<T>* F1
         v = scl(v, (T)exp(-heat_D2dt * yk * yk));
       }
       pick4w<V>(f, F0, F1, F2, F3)[(size_t)(l0 + c) * NY + ky] = v;
+    }
+  }
+  if (NF == 3 && nsum > 0 && blockIdx.x == 0) {
+    constexpr int KS = DIR > 0 ? 2 : 1;
+    __shared__ double red[KS * (C::NT / 64)];
+    const int slot = DIR > 0 ? SLOT_RR : SLOT_P3;
+    const double* part = g.part + (size_t)slot * SLOT_K * g.pstride;
+    double sv[KS] = {};
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nsum; i += C::NT) {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) sv[k] += part[(size_t)k * g.pstride + i];
+    }
+    block_sum<C::NT, KS>(sv, red);
+    if (threadIdx.x == 0) {
+      for (int k = 0; k < KS; ++k) g.tot[slot * SLOT_K + k] = sv[k];
+      if (DIR > 0) g.st->rho[it & 1] = sv[KS - 1];
     }
   }
 }
@@ -553,42 +616,31 @@ __global__ void __launch_bounds__((MODE == 1 ? 1 : (MODE == 2 ? 3 : 4)) * TPF)
   if (MODE == 3) zT_store<NZ, NF, 4>(buf, P, G0, G1, G2, lam0, nlam, g.ny);
 }
 
-// Operator end: forward z transform of the three fluxes, q = -i xi . F.
-// INIT (FP64 only): r = b - q (stored); totals <r,M^-1 r>, <r,r>, <b,b>;
-//   also turns the Kbar and compatibility totals of the row passes into
-//   status.kbar and the incompatibility flag.
-// else: q stored; totals <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,q>, <q,q>,
-//   <r,M^-1 r>, <r,r>.
-// z tile of the loop passes: 128-byte runs in both precisions (section of
-// ZCfg); FP64 with twice the threads (the tile's 111 KB of LDS admit one
-// workgroup per compute unit: 12 waves rather than 6)
-template <typename T>
-constexpr int z_tw() { return sizeof(T) == sizeof(double) ? 2 : 1; }
-template <int NZ, bool INIT, typename T>
-__global__ void __launch_bounds__((ZCfg<NZ, 3, sizeof(cx<T>), z_tw<T>()>::NT))
-    k3_zdiv(Geo g, const cx<T>* F0, const cx<T>* F1, const cx<T>* F2, cx<T>* __restrict__ qh,
-            const cx<T>* __restrict__ dh, cx<T>* rh, const cx<T>* __restrict__ bh, int it) {
-  constexpr int ES = sizeof(cx<T>), TW = z_tw<T>();
+// Operator end outside the loop (FP64): forward z transform of the three fluxes,
+// q = -i xi . F.
+// INIT: r = b - q (stored); totals <r,M^-1 r>, <r,r>, <b,b>; also turns the Kbar
+//   and compatibility totals of the row passes into status.kbar and the
+//   incompatibility flag.
+// else: q stored (operator apply).
+// Twice the threads of the tile (its 111 KB of LDS at Nz = 256 admit one
+// workgroup per compute unit: 12 waves rather than 6).
+template <int NZ, bool INIT>
+__global__ void __launch_bounds__((ZCfg<NZ, 3, 16, 2>::NT))
+    k3_zdiv(Geo g, const cd* F0, const cd* F1, const cd* F2, cd* __restrict__ qh, cd* rh, const cd* __restrict__ bh) {
+  constexpr int ES = 16, TW = 2;
   using C = ZCfg<NZ, 3, ES, TW>;
-  using V = cx<T>;
-  static_assert(!INIT || sizeof(T) == sizeof(double), "INIT pass is FP64");
-  if (INIT ? g.st->outer_done != 0 : g.st->conv_at <= it) return;
-  if (!INIT) tclk_start(g, 1, it);
+  using V = cd;
+  if (INIT && g.st->outer_done != 0) return;
   __shared__ V buf[C::NB * C::LS];
-  __shared__ double red[7 * (C::NT / 64)];
+  __shared__ double red[3 * (C::NT / 64)];
   __shared__ double Ks[6];
   const V* tw = (const V*)g.tw;
   const int nlam = g.h * g.ny;
   const int lam0 = xcd_block() * C::C;
-  V tv[C::ET], av[C::EP], bv[C::EP];
+  V tv[C::ET], av[C::EP];
   zT_gload<NZ, 3, 3, V, ES, TW>(tv, F0, F1, F2, nullptr, lam0, nlam, g.ny);
   if (INIT) {
     zP_gload<NZ, 3, V, ES, TW>(av, bh, lam0, nlam);
-  } else {
-    zP_gload<NZ, 3, V, ES, TW>(av, dh, lam0, nlam);
-    zP_gload<NZ, 3, V, ES, TW>(bv, rh, lam0, nlam);
-  }
-  if (INIT) {
     if (threadIdx.x == 0) {
       const double* kb = g.tot + SLOT_KBAR * SLOT_K;
       const double* sc = g.tot + SLOT_SCHK * SLOT_K;
@@ -604,14 +656,11 @@ __global__ void __launch_bounds__((ZCfg<NZ, 3, sizeof(cx<T>), z_tw<T>()>::NT))
         if (fabs(sc[0]) > 1e-12 * sc[1]) atomicOr(&g.st->flags, (int)FLAG_INCOMPAT);
       }
     }
-  } else if (threadIdx.x < 6) {
-    Ks[threadIdx.x] = g.st->kbar[threadIdx.x];
   }
   zT_put<NZ, 3, 3, V, ES, TW>(buf, tv);
   __syncthreads();
-  lds_fft<T, -1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
-  constexpr int KP = INIT ? 3 : 4;  // partial sums stored (see below)
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  lds_fft<double, -1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
+  double s[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
@@ -622,153 +671,241 @@ __global__ void __launch_bounds__((ZCfg<NZ, 3, sizeof(cx<T>), z_tw<T>()>::NT))
       double xx, yy;
       line_xi(g, lam, xx, yy);
       const double zz = xi_tilde(kz, NZ, g.lz);
-      const T ax = (T)xx * fx.x + (T)yy * fy.x + (T)zz * fz.x;
-      const T ay = (T)xx * fx.y + (T)yy * fy.y + (T)zz * fz.y;
-      const V q = mk<T>(ay, -ax);
-      const double w = lam < g.ny ? 1.0 : 2.0;  // slot kx = 0 <=> lam < Ny
-      const double sig = precond3_inv(Ks, xx, yy, zz);
+      const double ax = xx * fx.x + yy * fy.x + zz * fz.x;
+      const double ay = xx * fx.y + yy * fy.y + zz * fz.y;
+      const V q = mk<double>(ay, -ax);
       const size_t idx = (size_t)lam * NZ + kz;
-      const double qx = q.x, qy = q.y;
       if (INIT) {
+        const double w = lam < g.ny ? 1.0 : 2.0;  // slot kx = 0 <=> lam < Ny
         const V b = av[i];
         const V rn = sub(b, q);
         rh[idx] = rn;
-        const double rr = (double)rn.x * rn.x + (double)rn.y * rn.y;
-        s[0] += w * sig * rr;
+        const double rr = rn.x * rn.x + rn.y * rn.y;
+        s[0] += w * precond3_inv(Ks, xx, yy, zz) * rr;
         s[1] += w * rr;
-        s[2] += w * ((double)b.x * b.x + (double)b.y * b.y);
+        s[2] += w * (b.x * b.x + b.y * b.y);
       } else {
         qh[idx] = q;
-        const double dx = av[i].x, dy = av[i].y, rx = bv[i].x, ry = bv[i].y;
-        const double qq = qx * qx + qy * qy;
-        const double rq = rx * qx + ry * qy;
-        s[0] += w * (dx * qx + dy * qy);
-        s[1] += w * sig * rq;
-        s[2] += w * sig * qq;
-        s[3] += w * sig * (rx * rx + ry * ry);
       }
     }
   }
-  // INIT: <r,M^-1 r>, <r,r>, <b,b>; else <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r>
-  double sk[KP];
-#pragma unroll
-  for (int k = 0; k < KP; ++k) sk[k] = s[k];
-  store_partials<C::NT, KP>(sk, g, INIT ? SLOT_P3INIT : SLOT_P3, red);
-  if (!INIT) tclk_end(g, 1, it);
+  if (INIT) store_partials<C::NT, 3>(s, g, SLOT_P3INIT, red);
 }
 
-// PCG scalar step + vector update + next direction + its gradient through the
-// inverse z transform (the 2D column update with three gradient fields).
-template <int NZ, typename T>
-__global__ void __launch_bounds__((ZCfg<NZ, 3, sizeof(cx<T>), z_tw<T>()>::NT))
-    k3_zupdate(Geo g, int first, cx<T>* xh, cx<T>* rh, cx<T>* dh, const cx<T>* __restrict__ qh, cx<T>* G0,
-               cx<T>* G1, cx<T>* G2, int it, int max_iter, double tol2) {
-  constexpr int ES = sizeof(cx<T>), TW = z_tw<T>();
-  using C = ZCfg<NZ, 3, ES, TW>;
-  using V = cx<T>;
+// Start of the FP64 loop: the stopping test on the initial residual and the
+// gradient of z = M^-1 r through the inverse z transform.
+template <int NZ>
+__global__ void __launch_bounds__(3 * TPF) k3_zstart(Geo g, const cd* __restrict__ rh, cd* xh, cd* G0, cd* G1, cd* G2,
+                                                     int max_iter, double tol2) {
+  using C = ZCfg<NZ, 3>;
   DevStatus* st = g.st;
-  if (st->conv_at < it) return;
-  const int tit = first ? -1 : it;  // timing slot (the first update is not a loop pass)
-  tclk_start(g, 2, tit);
-  __shared__ V buf[C::NB * C::LS];
-  __shared__ double red[7 * (C::NT / 64)];
-  const V* tw = (const V*)g.tw;
+  __shared__ cd buf[C::NB * C::LS];
+  const cd* tw = (const cd*)g.tw;
   const int nlam = g.h * g.ny;
   const int lam0 = xcd_block() * C::C;
-  const bool lead = (blockIdx.x == 0 && threadIdx.x == 0);
   double K[6];
   for (int i = 0; i < 6; ++i) K[i] = st->kbar[i];
-  V xv[C::EP], rv0[C::EP], dv0[C::EP], qv[C::EP];
-  zP_gload<NZ, 3, V, ES, TW>(rv0, rh, lam0, nlam);
-  if (!first) {
-    zP_gload<NZ, 3, V, ES, TW>(xv, xh, lam0, nlam);
-    zP_gload<NZ, 3, V, ES, TW>(dv0, dh, lam0, nlam);
-    zP_gload<NZ, 3, V, ES, TW>(qv, qh, lam0, nlam);
-  }
-  double alpha = 0.0, beta = 0.0;
-  bool stop = false, zero_x = false;
-  if (first) {
-    const double* s = g.tot + SLOT_P3INIT * SLOT_K;
-    const double rho = s[0], rr = s[1], bb = s[2];
-    const bool incompat = (st->flags & FLAG_INCOMPAT) != 0;
-    zero_x = (bb == 0.0);
-    const bool bad = !isfinite(rr) || !isfinite(bb);
-    const bool conv = !bad && (incompat || zero_x || rr <= tol2 * bb);
-    if (bad) zero_x = false;
-    if (lead) {
-      st->rho[0] = rho;
-      st->rr[0] = zero_x ? 0.0 : rr;
-      st->rr0 = rr;
-      st->bb = bb;
-      st->iters = 0;
-      if (bad) st->flags |= FLAG_NONFINITE;
-      if (conv || bad || max_iter <= 0) {
-        st->conv_at = 0;
-        st->converged = conv ? 1 : 0;
-      }
-    }
-    if (!zero_x && (conv || bad || max_iter <= 0)) return;
-    stop = zero_x;
-  } else {
-    const double* s = g.tot + SLOT_P3 * SLOT_K;
-    const double rho = s[3];
-    alpha = rho / s[0];
-    const double rhon = rho - 2.0 * alpha * s[1] + alpha * alpha * s[2];
-    beta = rhon / rho;
-    const bool bad = !isfinite(rhon) || !isfinite(alpha);
-    stop = bad || it >= max_iter || it >= st->budget;
-    if (lead) {
-      if (bad) st->flags |= FLAG_NONFINITE;
-      st->rho[it & 1] = rhon;
-      st->iters = it;
-      if (stop) {
-        st->conv_at = it;
-        st->converged = 0;
-      }
+  cd rv[C::EP];
+  zP_gload<NZ, 3>(rv, rh, lam0, nlam);
+  const double* s = g.tot + SLOT_P3INIT * SLOT_K;
+  const double rho = s[0], rr = s[1], bb = s[2];
+  const bool incompat = (st->flags & FLAG_INCOMPAT) != 0;
+  bool zero_x = (bb == 0.0);
+  const bool bad = !isfinite(rr) || !isfinite(bb);
+  const bool conv = !bad && (incompat || zero_x || rr <= tol2 * bb);
+  if (bad) zero_x = false;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rho[0] = rho;
+    st->rr[0] = zero_x ? 0.0 : rr;
+    st->rr0 = rr;
+    st->bb = bb;
+    st->iters = 0;
+    if (bad) st->flags |= FLAG_NONFINITE;
+    if (conv || bad || max_iter <= 0) {
+      st->conv_at = 0;
+      st->converged = conv ? 1 : 0;
     }
   }
-  const T a = (T)alpha, bt = (T)beta;
-  double rrp[1] = {0.0};
+  if (zero_x) {
+#pragma unroll
+    for (int i = 0; i < C::EP; ++i) {
+      const int p = threadIdx.x + i * C::NT;
+      const int lam = lam0 + p / NZ;
+      if (p < C::CN && lam < nlam) xh[(size_t)lam * NZ + p % NZ] = vzero<cd>();
+    }
+  }
+  if (conv || bad || max_iter <= 0) return;
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
     const int c = p / NZ, kz = p % NZ;
     const int lam = lam0 + c;
-    V d = vzero<V>();
-    double xx = 0.0, yy = 0.0;
-    const double zz = xi_tilde(kz, NZ, g.lz);
-    if (p < C::CN && lam < nlam) {
-      line_xi(g, lam, xx, yy);
-      const size_t idx = (size_t)lam * NZ + kz;
-      if (zero_x) {
-        xh[idx] = vzero<V>();
-      } else {
-        V rv = rv0[i];
-        if (!first) {
-          d = dv0[i];
-          xh[idx] = add(xv[i], scl(d, a));
-          rv = sub(rv, scl(qv[i], a));
-          rh[idx] = rv;
-          rrp[0] += (lam < g.ny ? 1.0 : 2.0) * ((double)rv.x * rv.x + (double)rv.y * rv.y);
-        }
-        if (!stop) {
-          const T sig = (T)precond3_inv(K, xx, yy, zz);
-          d = add(scl(rv, sig), scl(d, bt));
-          dh[idx] = d;
-        }
-      }
+    if (p < C::CN) {
+      double xx = 0.0, yy = 0.0;
+      const double zz = xi_tilde(kz, NZ, g.lz);
+      if (lam < nlam) line_xi(g, lam, xx, yy);
+      put_grad3<NZ, 3, double>(buf, 0, c, kz, scl(rv[i], precond3_inv(K, xx, yy, zz)), xx, yy, zz, g.inv_n);
     }
-    if (!stop && p < C::CN) put_grad3<NZ, 3, T, ES, TW>(buf, 0, c, kz, d, xx, yy, zz, g.inv_n);
-  }
-  if (!first && !zero_x) store_partials<C::NT, 1>(rrp, g, SLOT_RR, red);
-  if (stop) {
-    tclk_end(g, 2, tit);
-    return;
   }
   __syncthreads();
-  lds_fft<T, +1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
-  zT_store<NZ, 3, 3, V, ES, TW>(buf, G0, G1, G2, nullptr, lam0, nlam, g.ny);
-  tclk_end(g, 2, tit);
+  lds_fft<double, +1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
+  zT_store<NZ, 3, 3>(buf, G0, G1, G2, nullptr, lam0, nlam, g.ny);
+}
+
+// Tile of the z pass of the loop: 128-byte runs in the gathers and scatters (8
+// FP64 lines, 16 FP32 lines), at least 512 elements per field, and at most
+// 2 TILE (FP64) or 4 TILE (FP32), whose three fields take 111 KB of LDS.  Up to
+// Nz = 128 two or more workgroups share a compute unit, so that one's
+// transform overlaps another's memory phase.
+template <int NZ, int ES>
+struct ZIter {
+  static constexpr int CA = ES == 8 ? 16 : 8;
+  static constexpr int CB = CA * NZ < 512 ? 512 / NZ : CA;
+  static constexpr int CM = (ES == 8 ? 4 : 2) * TILE / NZ;
+  static constexpr int C = CB < CM ? CB : CM;  // lines (kx, ky) per workgroup
+  static constexpr int NFB = 3 * C * NZ / 8;   // radix-8 butterflies per stage
+  static constexpr int NT = NFB > 768 ? 768 : waves_of(NFB);
+  static constexpr int LS = lpad_use(NZ) ? lpad_len(NZ) : NZ + 1;
+  static constexpr int CN = C * NZ;
+  static constexpr int NB = 3 * C;
+  static constexpr int ET = (3 * CN + NT - 1) / NT;
+  static constexpr int EP = (CN + NT - 1) / NT;
+};
+
+// Iteration it of the PCG loop on one block of (kx, ky) lines: forward z
+// transform of the fluxes, w = -i xi . F = A z, the scalars (gamma in
+// status.rho, delta in the SLOT_P3 total), the vector updates of the
+// single-reduction recurrences (nf_loop.hpp), z = M^-1 r of the new residual and
+// its gradient through the inverse z transform, in place.  Partials ||r||^2 and
+// <r, M^-1 r> in SLOT_RR.  Bytes per point (FP64): 112, where the operator end
+// and the update of the textbook recurrence moved 48 + 80.
+template <int NZ, typename T>
+__global__ void __launch_bounds__((ZIter<NZ, sizeof(cx<T>)>::NT))
+    k3_ziter(Geo g, cx<T>* M0, cx<T>* M1, cx<T>* M2, cx<T>* __restrict__ xh, cx<T>* __restrict__ rh,
+             cx<T>* __restrict__ dh, cx<T>* __restrict__ sh, int it, int max_iter) {
+  using C = ZIter<NZ, sizeof(cx<T>)>;
+  using V = cx<T>;
+  constexpr int NW = C::NT / 64;
+  DevStatus* st = g.st;
+  if (st->conv_at <= it) return;
+  tclk_start(g, 2, it + 1);
+  __shared__ V buf[C::NB * C::LS];
+  __shared__ double red[2 * NW];
+  const V* tw = (const V*)g.tw;
+  const int nlam = g.h * g.ny;
+  const int lam0 = xcd_block() * C::C;
+  const bool first = it == 0;
+  // gathered image: consecutive threads read consecutive ky of one z
+  V tv[C::ET];
+#pragma unroll
+  for (int i = 0; i < C::ET; ++i) {
+    const int e = threadIdx.x + i * C::NT;
+    const int f = e / C::CN, ee = e % C::CN;
+    const int z = ee / C::C, lam = lam0 + ee % C::C;
+    const int kx = lam / g.ny, ky = lam - kx * g.ny;
+    tv[i] = (e < 3 * C::CN && lam < nlam) ? pick<V>(f, M0, M1, M2)[((size_t)kx * NZ + z) * g.ny + ky] : vzero<V>();
+  }
+  double K[6];
+  for (int i = 0; i < 6; ++i) K[i] = st->kbar[i];
+  const double ga = st->rho[it & 1], ga_prev = st->rho[(it + 1) & 1], al_prev = st->alpha[(it + 1) & 1];
+  const double de = g.tot[SLOT_P3 * SLOT_K];
+  const int budget = st->budget;
+#pragma unroll
+  for (int i = 0; i < C::ET; ++i) {
+    const int e = threadIdx.x + i * C::NT;
+    const int f = e / C::CN, ee = e % C::CN;
+    if (e < 3 * C::CN) buf[(f * C::C + ee % C::C) * C::LS + ee / C::C] = tv[i];
+  }
+  __syncthreads();
+  lds_fft<T, -1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
+  // the vectors are loaded after the transform (fewer registers held across it)
+  V rv[C::EP], xv[C::EP], dv[C::EP], sv[C::EP];
+#pragma unroll
+  for (int i = 0; i < C::EP; ++i) {
+    const int p = threadIdx.x + i * C::NT;
+    const bool ok = p < C::CN && lam0 + p / NZ < nlam;
+    const size_t idx = (size_t)lam0 * NZ + p;
+    rv[i] = ok ? rh[idx] : vzero<V>();
+    xv[i] = ok ? xh[idx] : vzero<V>();
+    dv[i] = ok && !first ? dh[idx] : vzero<V>();
+    sv[i] = ok && !first ? sh[idx] : vzero<V>();
+  }
+  double beta = first ? 0.0 : ga / ga_prev;
+  double den = first ? de : de - beta * (ga / al_prev);
+  if (!first && den <= 0.0) {
+    beta = 0.0;
+    den = de;
+  }
+  const double alpha = ga / den;
+  const bool bad = !isfinite(ga) || !isfinite(alpha);
+  const bool stop = bad || it + 1 >= max_iter || it + 1 >= budget;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->alpha[it & 1] = alpha;
+    st->iters = it + 1;
+    if (bad) st->flags |= FLAG_NONFINITE;
+    if (stop) {
+      st->conv_at = it + 1;
+      st->converged = 0;
+    }
+  }
+  const T a = (T)alpha, bt = (T)beta;
+  double ps[2] = {0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < C::EP; ++i) {
+    const int p = threadIdx.x + i * C::NT;
+    const int c = p / NZ, kz = p % NZ;
+    const int lam = lam0 + c;
+    if (p >= C::CN) continue;
+    V* p0 = buf + c * C::LS + kz;
+    V* p1 = buf + (C::C + c) * C::LS + kz;
+    V* p2 = buf + (2 * C::C + c) * C::LS + kz;
+    V z = vzero<V>();
+    double xx = 0.0, yy = 0.0;
+    const double zz = xi_tilde(kz, NZ, g.lz);
+    if (lam < nlam) {
+      line_xi(g, lam, xx, yy);
+      const V fx = *p0, fy = *p1, fz = *p2;
+      const T ax = (T)xx * fx.x + (T)yy * fy.x + (T)zz * fz.x;
+      const T ay = (T)xx * fx.y + (T)yy * fy.y + (T)zz * fz.y;
+      const V w = mk<T>(ay, -ax);
+      const T sig = (T)precond3_inv(K, xx, yy, zz);
+      V rn = rv[i];
+      const V zo = scl(rn, sig);
+      const V d = first ? zo : add(zo, scl(dv[i], bt));
+      const V s = first ? w : add(w, scl(sv[i], bt));
+      const size_t idx = (size_t)lam0 * NZ + p;
+      xh[idx] = add(xv[i], scl(d, a));
+      rn = sub(rn, scl(s, a));
+      rh[idx] = rn;
+      dh[idx] = d;
+      sh[idx] = s;
+      const double wr = (lam < g.ny ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
+      ps[0] += wr;
+      ps[1] += (double)sig * wr;
+      z = scl(rn, sig);
+    }
+    // the gradient of z takes the places of the flux values this thread read
+    const T sx = (T)(xx * g.inv_n), sy = (T)(yy * g.inv_n), sz = (T)(zz * g.inv_n);
+    *p0 = mk<T>(-sx * z.y, sx * z.x);
+    *p1 = mk<T>(-sy * z.y, sy * z.x);
+    *p2 = mk<T>(-sz * z.y, sz * z.x);
+  }
+  wave_sums<2>(ps, red);
+  __syncthreads();
+  if (!stop) {
+    lds_fft<T, +1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
+    for (int e = threadIdx.x; e < 3 * C::CN; e += C::NT) {
+      const int f = e / C::CN, ee = e % C::CN;
+      const int c = ee % C::C, z = ee / C::C, lam = lam0 + c;
+      if (lam < nlam) {
+        const int kx = lam / g.ny, ky = lam - kx * g.ny;
+        pickw<V>(f, M0, M1, M2)[((size_t)kx * NZ + z) * g.ny + ky] = buf[(f * C::C + c) * C::LS + z];
+      }
+    }
+  }
+  if (threadIdx.x < 2)
+    g.part[((size_t)SLOT_RR * SLOT_K + threadIdx.x) * g.pstride + blockIdx.x] = waves_total<NW>(red + threadIdx.x * NW);
+  tclk_end(g, 2, it + 1);
 }
 
 // Diffusion, z part: forward z transform of the three components, multiply by
@@ -800,7 +937,7 @@ __global__ void __launch_bounds__(3 * TPF) k3_zheat(Geo g, cd* M0, cd* M1, cd* M
 // kernels with the z transform and three gradient fields).
 template <int NZ>
 __global__ void __launch_bounds__(3 * TPF) k3_zrefine_start(Geo g, const cd* __restrict__ r64, cd* x64,
-                                                          cx<float>* x32, cx<float>* r32, cx<float>* d32,
+                                                          cx<float>* x32, cx<float>* r32,
                                                           cx<float>* G0, cx<float>* G1, cx<float>* G2, double tol2,
                                                           double floor_in, int max_iter) {
   using C = ZCfg<NZ, 3>;
@@ -876,7 +1013,6 @@ __global__ void __launch_bounds__(3 * TPF) k3_zrefine_start(Geo g, const cd* __r
       const double ux = rv[i].x * scale, uy = rv[i].y * scale;
       r32[idx] = mk<float>((float)ux, (float)uy);
       d = mk<float>((float)(sig * ux), (float)(sig * uy));
-      d32[idx] = d;
       x32[idx] = vzero<V>();
     }
     if (p < C::CN) put_grad3<NZ, 3, float>(buf, 0, c, kz, d, xx, yy, zz, g.inv_n);
@@ -1127,12 +1263,6 @@ __global__ void __launch_bounds__(256) k3_sum_tot(Geo g, int slot, int n) {
     default: return hipErrorInvalidValue; \
   }
 
-#define NF3_LAUNCH(K, GRID, BLK, S, E0, E1, ...)                               \
-  do {                                                                         \
-    if (E0) hipExtLaunchKernelGGL(K, GRID, BLK, 0, S, E0, E1, 0, __VA_ARGS__); \
-    else hipLaunchKernelGGL(K, GRID, BLK, 0, S, __VA_ARGS__);                  \
-  } while (0)
-
 static int clamp_tile(int n) {
   const int c = TILE / n;
   return c < 1 ? 1 : (c > 64 ? 64 : c);
@@ -1141,14 +1271,55 @@ int nwg3_row(const Geo& g) {
   const int R = clamp_tile(g.nx / 2);
   return (g.ny * g.nz + R - 1) / R;
 }
-int nwg3_y(const Geo& g) {
-  const int C = clamp_tile(g.ny);
+static int nwg3_y(const Geo& g, int tile) {
+  int C = tile / g.ny;
+  C = C < 1 ? 1 : (C > 64 ? 64 : C);
   return (g.h * g.nz + C - 1) / C;
 }
-int nwg3_z(const Geo& g, bool f32) {
-  // lines per workgroup of ZCfg: 2 TILE / Nz (FP64), 4 TILE / Nz (FP32 loop passes), in [1, 64]
-  const int c0 = (f32 ? 4 : 2) * TILE / g.nz;
+int nwg3_z(const Geo& g) {
+  // lines per workgroup of ZCfg: 2 TILE / Nz, in [1, 64]
+  const int c0 = 2 * TILE / g.nz;
   const int C = c0 < 1 ? 1 : (c0 > 64 ? 64 : c0);
+  return (g.h * g.ny + C - 1) / C;
+}
+
+// workgroups of the operator middle and of the z pass of the loop
+template <typename T>
+static int flux3_rows(int nx) {
+#define L_(N) return Flux3<N, T>::R
+  switch (nx) {
+    case 8: L_(8);
+    case 16: L_(16);
+    case 32: L_(32);
+    case 64: L_(64);
+    case 128: L_(128);
+    case 256: L_(256);
+    case 512: L_(512);
+    default: L_(1024);
+  }
+#undef L_
+}
+template <int ES>
+static int ziter_lines(int nz) {
+#define L_(N) return ZIter<N, ES>::C
+  switch (nz) {
+    case 8: L_(8);
+    case 16: L_(16);
+    case 32: L_(32);
+    case 64: L_(64);
+    case 128: L_(128);
+    case 256: L_(256);
+    case 512: L_(512);
+    default: L_(1024);
+  }
+#undef L_
+}
+int nwg3_flux(const Geo& g, bool f32) {
+  const int R = f32 ? flux3_rows<float>(g.nx) : flux3_rows<double>(g.nx);
+  return (g.ny * g.nz + R - 1) / R;
+}
+int nwg3_ziter(const Geo& g, bool f32) {
+  const int C = f32 ? ziter_lines<8>(g.nz) : ziter_lines<16>(g.nz);
   return (g.h * g.ny + C - 1) / C;
 }
 
@@ -1171,25 +1342,25 @@ hipError_t launch3_row_c2r(const Geo& g, const void* in, double* f, hipStream_t 
   return hipGetLastError();
 }
 hipError_t launch3_row_flux(const Geo& g, bool f32, void* G0, void* G1, void* G2, const void* m, const void* r, int it,
-                            int kbar, float* lo, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const dim3 grid(nwg3_row(g)), blk(3 * TPF);
+                            int kbar, float* lo, double tol2, hipStream_t s) {
+  const dim3 grid(nwg3_flux(g, f32));
   if (f32) {
     typedef cx<float> cf;
-#define L_(N)                                                                                                   \
-  NF3_LAUNCH((k3_row_flux<N, float>), grid, blk, s, e0, e1, g, (cf*)G0, (cf*)G1, (cf*)G2, (const float*)m,     \
-             (const float*)r, it, kbar, (float*)nullptr)
+#define L_(N)                                                                                                     \
+  hipLaunchKernelGGL((k3_row_flux<N, float>), grid, dim3(Flux3Cfg<N, float>::NT), 0, s, g, (cf*)G0, (cf*)G1,      \
+                     (cf*)G2, (const float*)m, (const float*)r, it, kbar, (float*)nullptr, tol2)
     NF3_DISPATCH(g.nx, L_)
 #undef L_
   } else {
-#define L_(N)                                                                                                   \
-  NF3_LAUNCH((k3_row_flux<N, double>), grid, blk, s, e0, e1, g, (cd*)G0, (cd*)G1, (cd*)G2, (const double*)m,    \
-             (const double*)r, it, kbar, lo)
+#define L_(N)                                                                                                     \
+  hipLaunchKernelGGL((k3_row_flux<N, double>), grid, dim3(Flux3Cfg<N, double>::NT), 0, s, g, (cd*)G0, (cd*)G1,    \
+                     (cd*)G2, (const double*)m, (const double*)r, it, kbar, lo, tol2)
     NF3_DISPATCH(g.nx, L_)
 #undef L_
   }
   if (kbar) {
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch3_sum_tot(g, SLOT_KBAR, 7, nwg3_row(g), s);
+    return e != hipSuccess ? e : launch3_sum_tot(g, SLOT_KBAR, 7, nwg3_flux(g, f32), s);
   }
   return hipGetLastError();
 }
@@ -1213,22 +1384,22 @@ hipError_t launch3_row_final(const Geo& g, const void* M0, const void* M1, const
 }
 
 template <int NF, int DIR, typename T>
-static hipError_t ypass_t(const Geo& g, void* F0, void* F1, void* F2, void* F3, int it, int stop_test, double tol2,
-                          double heat, hipStream_t s) {
+static hipError_t ypass_t(const Geo& g, void* F0, void* F1, void* F2, void* F3, int it, int nsum, double heat,
+                          hipStream_t s) {
   typedef cx<T> cv;
-  const dim3 grid(nwg3_y(g)), blk(NF * TPF);
+  const dim3 grid(nwg3_y(g, y_tile<T>()));
 #define L_(N)                                                                                                   \
-  hipLaunchKernelGGL((k3_ypass<N, NF, DIR, T>), grid, blk, 0, s, g, (cv*)F0, (cv*)F1, (cv*)F2, (cv*)F3, it,     \
-                     stop_test, tol2, heat)
+  hipLaunchKernelGGL((k3_ypass<N, NF, DIR, T>), grid, dim3(YCfg<N, NF, T>::NT), 0, s, g, (cv*)F0, (cv*)F1, (cv*)F2, (cv*)F3, it,     \
+                     nsum, heat)
   NF3_DISPATCH(g.ny, L_)
 #undef L_
   return hipGetLastError();
 }
 hipError_t launch3_ypass(const Geo& g, bool f32, int nf, int dir, void* F0, void* F1, void* F2, void* F3, int it,
-                         int stop_test, double tol2, double heat_D2dt, hipStream_t s) {
+                         int nsum, double heat_D2dt, hipStream_t s) {
 #define Y_(NFv, D)                                                                                 \
-  return f32 ? ypass_t<NFv, D, float>(g, F0, F1, F2, F3, it, stop_test, tol2, heat_D2dt, s)       \
-             : ypass_t<NFv, D, double>(g, F0, F1, F2, F3, it, stop_test, tol2, heat_D2dt, s)
+  return f32 ? ypass_t<NFv, D, float>(g, F0, F1, F2, F3, it, nsum, heat_D2dt, s)                  \
+             : ypass_t<NFv, D, double>(g, F0, F1, F2, F3, it, nsum, heat_D2dt, s)
   if (dir < 0) {
     if (nf == 1) Y_(1, -1);
     if (nf == 3) Y_(3, -1);
@@ -1268,55 +1439,53 @@ hipError_t launch3_zinv(const Geo& g, int mode, const void* xh, void* P, void* G
   }
   return hipGetLastError();
 }
-hipError_t launch3_zdiv(const Geo& g, bool f32, int init, const void* F0, const void* F1, const void* F2, void* qh,
-                        const void* dh, void* rh, const void* bh, int it, hipStream_t s, hipEvent_t e0,
-                        hipEvent_t e1) {
-  const bool lo = f32 && !init;
-  const dim3 grid(nwg3_z(g, lo)), blk(6 * TPF);  // FP32: twice the lines, FP64: twice the threads
+hipError_t launch3_zdiv(const Geo& g, int init, const void* F0, const void* F1, const void* F2, void* qh, void* rh,
+                        const void* bh, hipStream_t s) {
+  const dim3 grid(nwg3_z(g)), blk(6 * TPF);  // twice the threads of the tile
   if (init) {
-#define L_(N)                                                                                                  \
-  NF3_LAUNCH((k3_zdiv<N, true, double>), grid, blk, s, e0, e1, g, (const cd*)F0, (const cd*)F1, (const cd*)F2, \
-             (cd*)qh, (const cd*)dh, (cd*)rh, (const cd*)bh, it)
+#define L_(N)                                                                                                     \
+  hipLaunchKernelGGL((k3_zdiv<N, true>), grid, blk, 0, s, g, (const cd*)F0, (const cd*)F1, (const cd*)F2, (cd*)qh, \
+                     (cd*)rh, (const cd*)bh)
     NF3_DISPATCH(g.nz, L_)
 #undef L_
-  } else if (f32) {
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch3_sum_tot(g, SLOT_P3INIT, 3, nwg3_z(g), s);
+  }
+#define L_(N)                                                                                                      \
+  hipLaunchKernelGGL((k3_zdiv<N, false>), grid, blk, 0, s, g, (const cd*)F0, (const cd*)F1, (const cd*)F2, (cd*)qh, \
+                     (cd*)rh, (const cd*)bh)
+  NF3_DISPATCH(g.nz, L_)
+#undef L_
+  return hipGetLastError();
+}
+hipError_t launch3_zstart(const Geo& g, const void* rh, void* xh, void* G0, void* G1, void* G2, int max_iter,
+                          double tol2, hipStream_t s) {
+  const dim3 grid(nwg3_z(g)), blk(3 * TPF);
+#define L_(N)                                                                                               \
+  hipLaunchKernelGGL(k3_zstart<N>, grid, blk, 0, s, g, (const cd*)rh, (cd*)xh, (cd*)G0, (cd*)G1, (cd*)G2,    \
+                     max_iter, tol2)
+  NF3_DISPATCH(g.nz, L_)
+#undef L_
+  return hipGetLastError();
+}
+hipError_t launch3_ziter(const Geo& g, bool f32, void* M0, void* M1, void* M2, void* xh, void* rh, void* dh, void* sh,
+                         int it, int max_iter, hipStream_t s) {
+  const dim3 grid(nwg3_ziter(g, f32));
+  if (f32) {
     typedef cx<float> cf;
-#define L_(N)                                                                                                    \
-  NF3_LAUNCH((k3_zdiv<N, false, float>), grid, blk, s, e0, e1, g, (const cf*)F0, (const cf*)F1, (const cf*)F2,   \
-             (cf*)qh, (const cf*)dh, (cf*)rh, (const cf*)nullptr, it)
+#define L_(N)                                                                                                   \
+  hipLaunchKernelGGL((k3_ziter<N, float>), grid, dim3(ZIter<N, 8>::NT), 0, s, g, (cf*)M0, (cf*)M1, (cf*)M2,     \
+                     (cf*)xh, (cf*)rh, (cf*)dh, (cf*)sh, it, max_iter)
     NF3_DISPATCH(g.nz, L_)
 #undef L_
   } else {
 #define L_(N)                                                                                                   \
-  NF3_LAUNCH((k3_zdiv<N, false, double>), grid, blk, s, e0, e1, g, (const cd*)F0, (const cd*)F1, (const cd*)F2, \
-             (cd*)qh, (const cd*)dh, (cd*)rh, (const cd*)bh, it)
+  hipLaunchKernelGGL((k3_ziter<N, double>), grid, dim3(ZIter<N, 16>::NT), 0, s, g, (cd*)M0, (cd*)M1, (cd*)M2,   \
+                     (cd*)xh, (cd*)rh, (cd*)dh, (cd*)sh, it, max_iter)
     NF3_DISPATCH(g.nz, L_)
 #undef L_
   }
-  const hipError_t e = hipGetLastError();
-  return e != hipSuccess ? e : launch3_sum_tot(g, init ? SLOT_P3INIT : SLOT_P3, init ? 3 : 4, nwg3_z(g, lo), s);
-}
-hipError_t launch3_zupdate(const Geo& g, bool f32, int first, void* xh, void* rh, void* dh, const void* qh, void* G0,
-                           void* G1, void* G2, int it, int max_iter, double tol2, hipStream_t s, hipEvent_t e0,
-                           hipEvent_t e1) {
-  const dim3 grid(nwg3_z(g, f32)), blk(6 * TPF);  // FP32: twice the lines, FP64: twice the threads
-  if (f32) {
-    typedef cx<float> cf;
-#define L_(N)                                                                                               \
-  NF3_LAUNCH((k3_zupdate<N, float>), grid, blk, s, e0, e1, g, 0, (cf*)xh, (cf*)rh, (cf*)dh, (const cf*)qh,  \
-             (cf*)G0, (cf*)G1, (cf*)G2, it, max_iter, tol2)
-    NF3_DISPATCH(g.nz, L_)
-#undef L_
-  } else {
-#define L_(N)                                                                                                 \
-  NF3_LAUNCH((k3_zupdate<N, double>), grid, blk, s, e0, e1, g, first, (cd*)xh, (cd*)rh, (cd*)dh, (const cd*)qh, \
-             (cd*)G0, (cd*)G1, (cd*)G2, it, max_iter, tol2)
-    NF3_DISPATCH(g.nz, L_)
-#undef L_
-  }
-  const hipError_t e = hipGetLastError();
-  // the first update writes no residual norm
-  return e != hipSuccess || first ? e : launch3_sum_tot(g, SLOT_RR, 1, nwg3_z(g, f32), s);
+  return hipGetLastError();
 }
 hipError_t launch3_zheat(const Geo& g, void* M0, void* M1, void* M2, double D2dt, hipStream_t s) {
   const dim3 grid(nwg3_z(g)), blk(3 * TPF);
@@ -1325,13 +1494,13 @@ hipError_t launch3_zheat(const Geo& g, void* M0, void* M1, void* M2, double D2dt
 #undef L_
   return hipGetLastError();
 }
-hipError_t launch3_zrefine_start(const Geo& g, const void* r64, void* x64, void* x32, void* r32, void* d32, void* G0,
+hipError_t launch3_zrefine_start(const Geo& g, const void* r64, void* x64, void* x32, void* r32, void* G0,
                                  void* G1, void* G2, double tol2, double floor_in, int max_iter, hipStream_t s) {
   typedef cx<float> cf;
   const dim3 grid(nwg3_z(g)), blk(3 * TPF);
 #define L_(N)                                                                                                    \
   hipLaunchKernelGGL(k3_zrefine_start<N>, grid, blk, 0, s, g, (const cd*)r64, (cd*)x64, (cf*)x32, (cf*)r32,       \
-                     (cf*)d32, (cf*)G0, (cf*)G1, (cf*)G2, tol2, floor_in, max_iter)
+                     (cf*)G0, (cf*)G1, (cf*)G2, tol2, floor_in, max_iter)
   NF3_DISPATCH(g.nz, L_)
 #undef L_
   return hipGetLastError();
@@ -1394,7 +1563,6 @@ hipError_t launch3_sum_tot(const Geo& g, int slot, int K, int n, hipStream_t s) 
     case 1: hipLaunchKernelGGL(k3_sum_tot<1>, dim3(1), dim3(256), 0, s, g, slot, n); break;
     case 2: hipLaunchKernelGGL(k3_sum_tot<2>, dim3(1), dim3(256), 0, s, g, slot, n); break;
     case 3: hipLaunchKernelGGL(k3_sum_tot<3>, dim3(1), dim3(256), 0, s, g, slot, n); break;
-    case 4: hipLaunchKernelGGL(k3_sum_tot<4>, dim3(1), dim3(256), 0, s, g, slot, n); break;
     case 7: hipLaunchKernelGGL(k3_sum_tot<7>, dim3(1), dim3(256), 0, s, g, slot, n); break;
     default: return hipErrorInvalidValue;
   }

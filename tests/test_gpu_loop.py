@@ -17,7 +17,10 @@ pytestmark = [pytest.mark.gpu, pytest.mark.filterwarnings("ignore::RuntimeWarnin
 TOL = 1e-10
 
 SHAPES = [((8, 8), (1.0, 1.0)), ((50, 16), (1.0, 0.5)), ((64, 64), (1.0, 1.0)), ((200, 128), (1.0, 1.0)),
-          ((256, 512), (1.0, 2.0)), ((800, 32), (1.0, 0.04)), ((16, 2048), (1.0 / 128, 1.0))]
+          ((256, 512), (1.0, 2.0)), ((800, 32), (1.0, 0.04)), ((16, 2048), (1.0 / 128, 1.0)),
+          # 3D: the smallest tiles, z tiles of one and of several lines, a long row
+          ((8, 8, 8), (1.0, 1.0, 1.0)), ((16, 8, 512), (1.0, 0.5, 32.0)), ((64, 32, 16), (1.0, 0.5, 0.25)),
+          ((512, 8, 16), (32.0, 0.5, 1.0))]
 
 
 def rel(a, b):
@@ -33,7 +36,7 @@ def test_first_iterates_and_attainable_accuracy(n, L):
     T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
     rng = np.random.default_rng(41)
     shape = n[::-1]
-    m = rng.uniform(-1.0, 1.0, (2,) + shape)
+    m = rng.uniform(-1.0, 1.0, (len(n),) + shape)
     r = rng.uniform(0.05, 0.15, shape)
     S = rng.standard_normal(shape)
     S -= S.mean()
