@@ -360,7 +360,7 @@ const char *nf_batch_last_error(const nf_batch *b);
  * The variants change the work split and the rounding of the transforms and
  * inner products only.
  * nf_set_autotune: 2 (the default) times each candidate's throughput with three
- *   concurrent launches on separate buffers on grids of 2^17 to 2^21 points
+ *   concurrent launches on separate buffers on grids of 2^19 to 2^21 points
  *   (the choice for solves that share the GPU, as ensemble partitions and
  *   concurrent handles do; the tuning then allocates two scratch copies of the
  *   loop's buffers, freed before nf_create_grid returns) and alone on the

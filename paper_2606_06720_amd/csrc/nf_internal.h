@@ -79,7 +79,7 @@ struct Geo {
 enum { TCLK_CAP = 2048, TCLK_W = 64 };  // timed iterations per PCG loop, stamp slots per iteration
 // tile variants of the PCG-loop passes (codes 0 .. NVAR-1, see nf_tiles.hpp);
 // VAR_DEFAULT is the untuned tile
-enum { VAR_DEFAULT = 1, NRV = 12, NCV = 15, NVAR = 15, RV_SMALL = 9, CV_SMALL = 12 };
+enum { VAR_DEFAULT = 1, RV_SMALL = 9, RV_SEQ = 12, NRV = 15, CV_SMALL = 12, CV_SEQ = 15, NCV = 17, NVAR = 17 };
 
 __host__ __device__ inline double* slot_ptr(double* part, int slot) {
   return part + (size_t)slot * SLOT_K * MAX_WG;

@@ -1100,13 +1100,15 @@ int col_nwg_var(const Geo& g, int cv) {
 }
 bool flux_var_valid(const Geo& g, bool f32, int rv) {
   if (rv == VAR_DEFAULT) return true;
-  if (rv >= RV_SMALL) return rv < NRV && small_ok(rv_rows(g.nx, rv), g.nx / 2) && g.nz == 1;
   const int es = f32 ? 8 : 16;
+  if (rv >= RV_SEQ) return rv_seq_ok(g.nx, rv, es) && rv_rows(g.nx, rv) <= g.ny && g.nz == 1;
+  if (rv >= RV_SMALL) return small_ok(rv_rows(g.nx, rv), g.nx / 2) && g.nz == 1;
   return var_size(g.nx) && g.nz == 1 && rv_ok(g.nx, g.ny, rv, es);
 }
 bool div_var_valid(const Geo& g, bool f32, int cv) {
   if (cv == VAR_DEFAULT) return true;
-  if (cv >= CV_SMALL) return cv < NCV && small_ok(cv_cols(g.ny, cv), g.ny) && g.nz == 1;
+  if (cv >= CV_SEQ) return cv_seq_ok(g.ny, cv) && g.nz == 1;
+  if (cv >= CV_SMALL) return small_ok(cv_cols(g.ny, cv), g.ny) && g.nz == 1;
   const int es = f32 ? 8 : 16;
   return var_size(g.ny) && g.nz == 1 && cv_ok(g.ny, g.h, cv, es);
 }
@@ -1135,13 +1137,14 @@ int flux_var_rows(const Geo& g, int rv) {
 int flux_var_plan(int rv) { return rv >= RV_SMALL ? 0 : rv_plan(rv); }
 int flux_var_threads(const Geo& g, int rv) {
   const int rt = rv == VAR_DEFAULT ? row_tile(g.nx, 2) : rv_rows(g.nx, rv) * (g.nx / 2);
+  if (rv >= RV_SEQ) return rv_rows(g.nx, rv) * (g.nx / 2) / 8;
   if (rv >= RV_SMALL) return small_threads(rv_rows(g.nx, rv), g.nx / 2);
   const int nt = (rt / 8) * 2 > 1024 ? 1024 : (rt / 8) * 2;
   return nt / (rv == VAR_DEFAULT ? 1 : rv_td(rv));
 }
 int div_var_cols(const Geo& g, int cv) { return cv == VAR_DEFAULT ? col_cols(g.ny) : cv_cols(g.ny, cv); }
 int div_var_threads(const Geo& g, int cv) {
-  if (cv >= CV_SMALL) return small_threads(cv_cols(g.ny, cv), g.ny);
+  if (cv >= CV_SMALL) return wide_threads(g.ny, cv);
   return cv == VAR_DEFAULT ? col_threads(g.ny, 2) : 2 * TPF * cv_tm(cv);
 }
 bool tuned_length(int n) { return var_size(n); }

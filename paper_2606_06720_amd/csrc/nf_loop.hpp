@@ -177,16 +177,131 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
   }
   tclk_end(g, 0, it);
 }
+// The loop's row pass with the two fields one after the other through one field's
+// LDS (row variants RV_SEQ and up, rows of 2048 and more): grad_x waits in
+// registers while grad_y is transformed, F_x while F_y is.  For the same rows
+// the tile takes half the LDS and half the threads, so twice the workgroups
+// share a compute unit and one's transforms overlap the others' memory phases
+// (the two-field tile of 2048 keeps a compute unit's vector units 20%, its LDS
+// 21% and HBM 50% busy, one phase after the other).
+template <int NX, typename T, int RV>
+__device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
+                                                  const T* __restrict__ r, int it, int nwg_col, double tol2) {
+  using C = FluxCfg<NX, RV>;
+  using V = cx<T>;
+  using P = typename vec2<T>::type;
+  constexpr int NW = C::NT / 64;
+  if (g.st->conv_at <= it) return;
+  tclk_start(g, 0, it);
+  __shared__ V buf[C::NB * C::LS];
+  __shared__ double red[2 * NW];
+  __shared__ double redd[NW];
+  const V* tw = (const V*)g.tw;
+  const int y0 = xcd_block() * C::R;
+  const int nrow = min(C::R, g.ny - y0);
+  const size_t n = (size_t)g.nx * g.ny;
+  V ta[RowPairs<C>::ETP], tb[RowPairs<C>::ETP];
+  rowTP_gload<C>(ta, tb, G0, nullptr, nullptr, g.ny, y0, nrow);
+  if (it >= 1) {
+    const double* part = slot_ptr(g.part, SLOT_RR);
+    double s[1] = {0.0};
+    for (int i = threadIdx.x; i < nwg_col; i += C::NT) s[0] += part[i];
+    wave_sums<1>(s, red);
+    if (blockIdx.x == 0) {
+      double z[1] = {0.0};
+      for (int i = threadIdx.x; i < nwg_col; i += C::NT) z[0] += part[MAX_WG + i];
+      wave_sums<1>(z, red + NW);
+    }
+  }
+  rowTP_put_pre<C>(buf, ta, tb, tw, g.twn);
+  __syncthreads();
+  if (it >= 1) {
+    const double rr = waves_total<NW>(red);
+    const bool bad = !isfinite(rr);
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    if (bad || rr <= tol2 * g.st->bb) {
+      if (lead) {
+        g.st->rr[0] = rr;
+        g.st->converged = bad ? 0 : 1;
+        if (bad) g.st->flags |= FLAG_NONFINITE;
+        g.st->conv_at = it;
+      }
+      return;
+    }
+    if (lead) g.st->rho[it & 1] = waves_total<NW>(red + NW);
+  }
+  rowTP_gload<C>(ta, tb, G1, nullptr, nullptr, g.ny, y0, nrow);
+  lds_fft<T, +1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+  V gx[C::EP];
+#pragma unroll
+  for (int i = 0; i < C::EP; ++i) {
+    const int p = threadIdx.x + i * C::NT;
+    if (p < C::RH) gx[i] = buf[(p / C::H) * C::LS + p % C::H];
+  }
+  __syncthreads();
+  rowTP_put_pre<C>(buf, ta, tb, tw, g.twn);
+  __syncthreads();
+  lds_fft<T, +1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+  double de[1] = {0.0};
+  // half of the points at a time: the loads of m and r of one half are in
+  // flight together
+  constexpr int HE = C::EP > 4 ? 4 : C::EP;
+#pragma unroll
+  for (int i0 = 0; i0 < C::EP; i0 += HE) {
+    P mx[HE], my[HE], rv[HE];
+#pragma unroll
+    for (int q = 0; q < HE; ++q) {
+      const int p = threadIdx.x + (i0 + q) * C::NT;
+      const int rr = p / C::H, j = p % C::H;
+      const size_t o = (size_t)(y0 + rr) * NX + 2 * j;
+      const bool ok = p < C::RH && rr < nrow;
+      mx[q] = ok ? *(const P*)(m + o) : vzero<P>();
+      my[q] = ok ? *(const P*)(m + n + o) : vzero<P>();
+      rv[q] = ok ? *(const P*)(r + o) : vzero<P>();
+    }
+#pragma unroll
+    for (int q = 0; q < HE; ++q) {
+      const int p = threadIdx.x + (i0 + q) * C::NT;
+      if (p >= C::RH) continue;
+      V* py = buf + (p / C::H) * C::LS + p % C::H;
+      const V gxv = gx[i0 + q], gyv = *py;
+      const T a0 = mx[q].x * gxv.x + my[q].x * gyv.x;
+      const T a1 = mx[q].y * gxv.y + my[q].y * gyv.y;
+      const V fx = mk<T>(fma(a0, mx[q].x, rv[q].x * gxv.x), fma(a1, mx[q].y, rv[q].y * gxv.y));
+      const V fy = mk<T>(fma(a0, my[q].x, rv[q].x * gyv.x), fma(a1, my[q].y, rv[q].y * gyv.y));
+      gx[i0 + q] = fx;
+      *py = fy;
+      de[0] += (double)gxv.x * fx.x + (double)gxv.y * fx.y + (double)gyv.x * fy.x + (double)gyv.y * fy.y;
+    }
+  }
+  wave_sums<1>(de, redd);
+  __syncthreads();
+  lds_fft<T, -1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+  if (threadIdx.x == 0) slot_ptr(g.part, SLOT_P3)[blockIdx.x] = waves_total<NW>(redd) * (double)n;
+  rowTP_store_post<C, 1>(buf, G1, nullptr, nullptr, tw, g.twn, g.ny, y0, nrow);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < C::EP; ++i) {
+    const int p = threadIdx.x + i * C::NT;
+    if (p < C::RH) buf[(p / C::H) * C::LS + p % C::H] = gx[i];
+  }
+  __syncthreads();
+  lds_fft<T, -1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+  rowTP_store_post<C, 1>(buf, G0, nullptr, nullptr, tw, g.twn, g.ny, y0, nrow);
+  tclk_end(g, 0, it);
+}
 template <int NX, typename T, int RV>
 __global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) k_row_flux(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
                                                   const T* __restrict__ r, int it, double* kslot, int nwg_col,
                                                   double tol2, float* lo) {
-  row_flux_body<NX, T, RV>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo);
+  if constexpr (RV >= RV_SEQ) row_flux_seq_body<NX, T, RV>(g, G0, G1, m, r, it, nwg_col, tol2);
+  else row_flux_body<NX, T, RV>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo);
 }
 template <int NX, typename T, int RV>
 __global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) kb_row_flux(const FluxArgs* __restrict__ A, int it, int nwg_col, double tol2) {
   const FluxArgs& a = A[blockIdx.y];
-  row_flux_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, (double*)a.kslot, nwg_col, tol2, (float*)a.lo);
+  if constexpr (RV >= RV_SEQ) row_flux_seq_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, nwg_col, tol2);
+  else row_flux_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, (double*)a.kslot, nwg_col, tol2, (float*)a.lo);
 }
 
 // ---------------------------------------------------------------- column pass
@@ -313,21 +428,170 @@ __device__ __forceinline__ void col_iter_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>
   if (threadIdx.x < 2) slot_ptr(g.part, SLOT_RR)[threadIdx.x * MAX_WG + blockIdx.x] = waves_total<NW>(red2 + threadIdx.x * NW);
   tclk_end(g, 2, it + 1);
 }
+// The column pass with one field at a time through one field's LDS (column
+// variants CV_SEQ and up): w is summed up in registers, grad_x leaves before
+// grad_y is formed.  Half the LDS and, for the same elements per thread, half
+// the threads per workgroup, so twice the workgroups share a compute unit.
+template <int NY, typename T, int CV>
+__device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>* __restrict__ xh,
+                                                  cx<T>* __restrict__ rh, cx<T>* __restrict__ dh,
+                                                  cx<T>* __restrict__ sh, int it, int max_iter, int nwg_row) {
+  using C = DivCfg<NY, CV>;
+  using V = cx<T>;
+  constexpr int NW = C::NT / 64;
+  DevStatus* st = g.st;
+  if (st->conv_at <= it) return;
+  tclk_start(g, 2, it + 1);
+  __shared__ V buf[C::NB * C::LS];
+  __shared__ double red[NW];
+  __shared__ double red2[2 * NW];
+  const V* tw = (const V*)g.tw;
+  const int kx0 = blockIdx.x * C::C;
+  const bool first = it == 0;
+  V tv[C::EP], w[C::EP];
+  colP_gload<C>(tv, M0, kx0, g.h);
+  double K[4];
+  for (int i = 0; i < 3; ++i) K[i] = st->kbar[i];
+  const double ga = st->rho[it & 1], ga_prev = st->rho[(it + 1) & 1], al_prev = st->alpha[(it + 1) & 1];
+  const int budget = st->budget;
+  {
+    const double* part = slot_ptr(g.part, SLOT_P3);
+    double s[1] = {0.0};
+    for (int i = threadIdx.x; i < nwg_row; i += C::NT) s[0] += part[i];
+    wave_sums<1>(s, red);
+  }
+  auto put = [&]() {
+#pragma unroll
+    for (int i = 0; i < C::EP; ++i) {
+      const int p = threadIdx.x + i * C::NT;
+      if (p < C::CN) buf[(p / NY) * C::LS + p % NY] = tv[i];
+    }
+    __syncthreads();
+  };
+  put();
+  colP_gload<C>(tv, M1, kx0, g.h);
+  lds_fft<T, -1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+#pragma unroll
+  for (int i = 0; i < C::EP; ++i) {
+    const int p = threadIdx.x + i * C::NT;
+    if (p >= C::CN) continue;
+    const T xx = (T)xi_col(kx0 + p / NY, g.lx);
+    const V f = buf[(p / NY) * C::LS + p % NY];
+    w[i] = mk<T>(xx * f.y, -xx * f.x);
+  }
+  __syncthreads();
+  put();
+  lds_fft<T, -1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+  const double de = waves_total<NW>(red);
+  double beta = first ? 0.0 : ga / ga_prev;
+  double den = first ? de : de - beta * (ga / al_prev);
+  if (!first && den <= 0.0) {
+    beta = 0.0;
+    den = de;
+  }
+  const double alpha = ga / den;
+  const bool bad = !isfinite(ga) || !isfinite(alpha);
+  const bool stop = bad || it + 1 >= max_iter || it + 1 >= budget;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->alpha[it & 1] = alpha;
+    st->iters = it + 1;
+    if (bad) st->flags |= FLAG_NONFINITE;
+    if (stop) {
+      st->conv_at = it + 1;
+      st->converged = 0;
+    }
+  }
+  const T a = (T)alpha, bt = (T)beta;
+  double ps[2] = {0.0, 0.0};
+  // w becomes z = M^-1 r of the new residual; a few elements at a time, their
+  // vector loads in flight together
+  constexpr int HE = C::EP > 4 ? 4 : C::EP;
+#pragma unroll
+  for (int i0 = 0; i0 < C::EP; i0 += HE) {
+    V rv[HE], xv[HE], dv[HE], sv[HE];
+#pragma unroll
+    for (int q = 0; q < HE; ++q) {
+      const int p = threadIdx.x + (i0 + q) * C::NT;
+      const bool ok = p < C::CN && kx0 + p / NY < g.h;
+      const size_t idx = (size_t)kx0 * NY + p;
+      rv[q] = ok ? rh[idx] : vzero<V>();
+      dv[q] = ok && !first ? dh[idx] : vzero<V>();
+      sv[q] = ok && !first ? sh[idx] : vzero<V>();
+      xv[q] = ok ? xh[idx] : vzero<V>();
+    }
+#pragma unroll
+    for (int q = 0; q < HE; ++q) {
+      const int p = threadIdx.x + (i0 + q) * C::NT;
+      if (p >= C::CN) continue;
+      const int kx = kx0 + p / NY, ky = p % NY;
+      V z = vzero<V>();
+      if (kx < g.h) {
+        const double xx = xi_col(kx, g.lx), yy = xi_tilde(ky, NY, g.ly);
+        const V fy = buf[(p / NY) * C::LS + ky];
+        const V wv = mk<T>(w[i0 + q].x + (T)yy * fy.y, w[i0 + q].y - (T)yy * fy.x);
+        const T sig = (T)precond_symbol_inv(K, xx, yy);
+        V rn = rv[q];
+        const V zo = scl(rn, sig);
+        const V d = first ? zo : add(zo, scl(dv[q], bt));
+        const V s = first ? wv : add(wv, scl(sv[q], bt));
+        const size_t idx = (size_t)kx0 * NY + p;
+        xh[idx] = add(xv[q], scl(d, a));
+        rn = sub(rn, scl(s, a));
+        rh[idx] = rn;
+        dh[idx] = d;
+        sh[idx] = s;
+        const double wr = (kx == 0 ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
+        ps[0] += wr;
+        ps[1] += (double)sig * wr;
+        z = scl(rn, sig);
+      }
+      w[i0 + q] = z;
+    }
+  }
+  wave_sums<2>(ps, red2);
+  if (!stop) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+#pragma unroll
+      for (int i = 0; i < C::EP; ++i) {
+        const int p = threadIdx.x + i * C::NT;
+        if (p >= C::CN) continue;
+        const int ky = p % NY;
+        const T sc = (T)((f == 0 ? xi_col(kx0 + p / NY, g.lx) : xi_tilde(ky, NY, g.ly)) * g.inv_n);
+        buf[(p / NY) * C::LS + ky] = mk<T>(-sc * w[i].y, sc * w[i].x);
+      }
+      __syncthreads();
+      lds_fft<T, +1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
+      V* dst = f == 0 ? M0 : M1;
+#pragma unroll
+      for (int i = 0; i < C::EP; ++i) {
+        const int p = threadIdx.x + i * C::NT;
+        if (p < C::CN && kx0 + p / NY < g.h) dst[(size_t)kx0 * NY + p] = buf[(p / NY) * C::LS + p % NY];
+      }
+      if (f == 0) __syncthreads();
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) slot_ptr(g.part, SLOT_RR)[threadIdx.x * MAX_WG + blockIdx.x] = waves_total<NW>(red2 + threadIdx.x * NW);
+  tclk_end(g, 2, it + 1);
+}
 template <int NY, typename T, int CV>
 __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) k_col_iter(Geo g, cx<T>* M0, cx<T>* M1, cx<T>* xh, cx<T>* rh,
                                                     cx<T>* dh, cx<T>* sh, int it, int max_iter, int nwg_row) {
-  col_iter_body<NY, T, CV>(g, M0, M1, xh, rh, dh, sh, it, max_iter, nwg_row);
+  if constexpr (CV >= CV_SEQ) col_iter_seq_body<NY, T, CV>(g, M0, M1, xh, rh, dh, sh, it, max_iter, nwg_row);
+  else col_iter_body<NY, T, CV>(g, M0, M1, xh, rh, dh, sh, it, max_iter, nwg_row);
 }
 template <int NY, typename T, int CV>
 __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_iter(const IterArgs* __restrict__ A, int it, int max_iter, int nwg_row) {
   const IterArgs& a = A[blockIdx.y];
-  col_iter_body<NY, T, CV>(a.g, (cx<T>*)a.M0, (cx<T>*)a.M1, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (cx<T>*)a.sh, it, max_iter, nwg_row);
+  if constexpr (CV >= CV_SEQ) col_iter_seq_body<NY, T, CV>(a.g, (cx<T>*)a.M0, (cx<T>*)a.M1, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (cx<T>*)a.sh, it, max_iter, nwg_row);
+  else col_iter_body<NY, T, CV>(a.g, (cx<T>*)a.M0, (cx<T>*)a.M1, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (cx<T>*)a.sh, it, max_iter, nwg_row);
 }
 
 // ---------------------------------------------------------------- dispatch
 // A switch over the variant code that instantiates only the variants that exist
 // for the size and real type.
-#define NF_VARIANTS(V_) V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11) V_(12) V_(13) V_(14)
+#define NF_VARIANTS(V_) V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11) V_(12) V_(13) V_(14) V_(15) V_(16)
 
 template <int NX, typename T, int RV>
 static hipError_t flux_go(const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const T* r, int it, double* kslot,

@@ -108,12 +108,16 @@ struct ColCfg {
 // variants 9, 10, 11 hold RD/2, RD/4, RD/8 rows, column variants 12, 13, 14
 // CD/2, CD/4, CD/8 columns.  They exist for every size and are not part of the
 // public codes.
+// Sequential fields (one field of the tile in LDS at a time), for lengths from
+// 2048 on: row variants 12, 13, 14 hold 1, 2, 4 rows, column variants 15, 16 one
+// column with one and two radix-8 butterflies per thread and stage.
 enum { LDS_LIMIT = 160 * 1024 };  // VAR_DEFAULT, NVAR, RV_SMALL, CV_SMALL: nf_internal.h
 // threads of a small tile of `lines` lines of h elements over two fields
 __host__ __device__ constexpr int small_threads(int lines, int h) { return waves_of(lines * h / 8 * 2); }
 
 __host__ __device__ constexpr int rv_rows(int nx, int rv) {
   const int rd = tile_rows(nx / 2, row_tile(nx, 2));
+  if (rv >= RV_SEQ) return 1 << (rv - RV_SEQ);
   if (rv >= RV_SMALL) return rd >> (rv - RV_SMALL + 1);
   return rv % 3 == 0 ? rd / 2 : (rv % 3 == 1 ? rd : 2 * rd);
 }
@@ -121,6 +125,7 @@ __host__ __device__ constexpr int cv_cols_default(int ny) {
   return TILE / ny < 1 ? 1 : (TILE / ny > 64 ? 64 : TILE / ny);
 }
 __host__ __device__ constexpr int cv_cols(int ny, int cv) {
+  if (cv >= CV_SEQ) return 1;
   if (cv >= CV_SMALL) return cv_cols_default(ny) >> (cv - CV_SMALL + 1);
   return cv % 3 == 0 ? cv_cols_default(ny) / 2 : (cv % 3 == 1 ? cv_cols_default(ny) : 2 * cv_cols_default(ny));
 }
@@ -135,6 +140,16 @@ __host__ __device__ constexpr int cv_plan(int cv) { return cv / 3 == 1 ? 1 : 0; 
 __host__ __device__ constexpr int cv_tm(int cv) { return cv / 3 == 2 ? 2 : (cv / 3 == 3 ? 4 : 1); }
 __host__ __device__ constexpr int rv_plan(int rv) { return rv / 3 == 1 ? 1 : 0; }
 __host__ __device__ constexpr int rv_td(int rv) { return rv / 3 == 2 ? 2 : 1; }
+// threads of the column variants beyond the public codes
+__host__ __device__ constexpr int wide_threads(int ny, int cv) {
+  return cv >= CV_SEQ ? ny / 8 / (cv - CV_SEQ + 1) : small_threads(cv_cols(ny, cv), ny);
+}
+// sequential fields: whether one field of the tile fits a workgroup's LDS
+__host__ __device__ constexpr bool rv_seq_ok(int nx, int rv, int es) {
+  return nx >= 2048 && rv < NRV && rv_rows(nx, rv) * (nx / 2 + 10) * es + 4096 <= LDS_LIMIT &&
+         rv_rows(nx, rv) * (nx / 2) / 8 <= 1024;
+}
+__host__ __device__ constexpr bool cv_seq_ok(int ny, int cv) { return ny >= 2048 && cv < NCV; }
 // small tiles: at least one line, and at least half a wavefront of butterflies
 __host__ __device__ constexpr bool small_ok(int lines, int h) { return lines >= 1 && lines * h / 8 * 2 >= 32; }
 __host__ __device__ constexpr bool rv_ok(int nx, int ny, int rv, int es) {
@@ -152,24 +167,28 @@ __host__ __device__ constexpr bool cv_ok(int ny, int h, int cv, int es) {
 __host__ __device__ constexpr bool var_size(int n) { return n >= 256 && n <= 4096 && (n & (n - 1)) == 0; }
 // configurations of the variants (the default is exactly the untuned tile)
 template <int NX, int RV>
-using FluxCfg = typename std::conditional<RV == VAR_DEFAULT, Row2D<NX, 2>,
-                                          RowCfg<NX, 2, rv_rows(NX, RV) * (NX / 2), RV >= RV_SMALL ? 0 : rv_plan(RV),
-                                                 RV >= RV_SMALL ? 1 : rv_td(RV)>>::type;
+using FluxCfg = typename std::conditional<
+    RV == VAR_DEFAULT, Row2D<NX, 2>,
+    typename std::conditional<(RV >= RV_SEQ), RowCfg<NX, 1, rv_rows(NX, RV) * (NX / 2)>,
+                              RowCfg<NX, 2, rv_rows(NX, RV) * (NX / 2), RV >= RV_SMALL ? 0 : rv_plan(RV),
+                                     RV >= RV_SMALL ? 1 : rv_td(RV)>>::type>::type;
 template <int NY, int CV>
 using DivCfg = typename std::conditional<
     CV == VAR_DEFAULT, ColCfg<NY, 2>,
     typename std::conditional<(CV >= CV_SMALL),
-                              ColCfg<NY, 2, cv_cols(NY, CV) * NY, 0, 1, small_threads(cv_cols(NY, CV), NY)>,
+                              ColCfg<NY, CV >= CV_SEQ ? 1 : 2, cv_cols(NY, CV) * NY, 0, 1, wide_threads(NY, CV)>,
                               ColCfg<NY, 2, cv_cols(NY, CV) * NY, cv_plan(CV), cv_tm(CV)>>::type>::type;
 // variants that can be built for a size (the row count against Ny is checked at run time)
 template <int NX, int RV, int ES>
 constexpr bool flux_var_exists() {
-  return RV == VAR_DEFAULT || (RV >= RV_SMALL ? RV < NRV && small_ok(rv_rows(NX, RV), NX / 2)
+  if (RV >= RV_SEQ) return rv_seq_ok(NX, RV, ES);
+  return RV == VAR_DEFAULT || (RV >= RV_SMALL ? small_ok(rv_rows(NX, RV), NX / 2)
                                               : var_size(NX) && rv_ok(NX, 1 << 20, RV, ES));
 }
 template <int NY, int CV, int ES>
 constexpr bool div_var_exists() {
-  return CV == VAR_DEFAULT || (CV >= CV_SMALL ? CV < NCV && small_ok(cv_cols(NY, CV), NY)
+  if (CV >= CV_SEQ) return cv_seq_ok(NY, CV);
+  return CV == VAR_DEFAULT || (CV >= CV_SMALL ? small_ok(cv_cols(NY, CV), NY)
                                               : var_size(NY) && cv_ok(NY, 1 << 20, CV, ES));
 }
 

@@ -9,7 +9,7 @@
 // three concurrent launches, each on its own copy of the buffers, so that the
 // choice holds for solves that share the GPU (ensembles, concurrent
 // instances); a variant that is faster alone but takes more of a compute
-// unit's resources can lose there.  Grids above 2^21 or below 2^17 points are
+// unit's resources can lose there.  Grids above 2^21 or below 2^19 points are
 // timed alone.  The choice is made once per process for
 // each (Nx, Ny, real type) and cached, so every handle, ensemble and
 // allocation-free solve of that shape runs the same kernels (their results then
@@ -48,10 +48,11 @@ std::map<std::tuple<int, int, int, int>, Choice> cache;  // (device, nx, ny, f32
 // alone in practice
 int autotune_mode = 2;
 constexpr long long CONTEND_MAX_POINTS = 1LL << 21;
-// below this a pass is a few microseconds of latency and three streams only
+// below this a pass is a few microseconds of latency and three streams mostly
 // measure the rate of the launches (256^2: every row tile 5.7 us per launch,
-// alone 5.9 to 9.1 us): such grids are timed alone as well
-constexpr long long CONTEND_MIN_POINTS = 1LL << 17;
+// alone 5.9 to 9.1 us; 512^2 the choice changed from run to run): such grids
+// are timed alone as well
+constexpr long long CONTEND_MIN_POINTS = 1LL << 19;
 
 void apply(nf_grid* g, bool f32, const Choice& c, int tuned) {
   const int k = f32 ? 1 : 0;
@@ -271,13 +272,18 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
 // of one workgroup, which a smaller tile shortens (per iteration: 200^2 with 2
 // rows and 1 column instead of 10 and 5, 26.9 -> 20.2 us; 128^2 18.1 -> 12.2
 // us); beyond 256 workgroups the shorter runs cost more than they gain (800
-// wide rows, one instead of two: +3 us).
-void untuned_tiles(const Geo& G, int var[3]) {
+// wide rows, one instead of two: +3 us).  Rows of 2048 and more take two rows
+// with one field at a time in LDS (2048^2 row pass, FP64: 133 us with the
+// default tile, 84 us with two rows and two fields, 72 us with one field at a
+// time), FP32 columns of 4096 one column likewise.
+void untuned_tiles(const Geo& G, bool f32, int var[3]) {
   var[0] = var[1] = var[2] = VAR_DEFAULT;
   if (!tuned_length(G.nx))
-    for (int v = RV_SMALL; v < NRV && flux_var_valid(G, false, v) && row_nwg_var(G, v) <= 256; ++v) var[0] = v;
+    for (int v = RV_SMALL; v < RV_SEQ && flux_var_valid(G, false, v) && row_nwg_var(G, v) <= 256; ++v) var[0] = v;
+  if (flux_var_valid(G, f32, RV_SEQ + 1)) var[0] = RV_SEQ + 1;
+  if (f32 && G.ny >= 4096 && div_var_valid(G, f32, CV_SEQ + 1)) var[1] = var[2] = CV_SEQ + 1;
   if (!tuned_length(G.ny))
-    for (int v = CV_SMALL; v < NCV && div_var_valid(G, false, v) && col_nwg_var(G, v) <= 256; ++v) var[1] = var[2] = v;
+    for (int v = CV_SMALL; v < CV_SEQ && div_var_valid(G, false, v) && col_nwg_var(G, v) <= 256; ++v) var[1] = var[2] = v;
 }
 
 }  // namespace
@@ -286,7 +292,7 @@ int tune_handle(nf_grid* g) {
   const bool f32 = g->dtype == NF_F32_REFINED;
   Choice c;
   std::lock_guard<std::mutex> lock(cache_mu);
-  if (g->dim == 2) untuned_tiles(g->geo, c.var);
+  if (g->dim == 2) untuned_tiles(g->geo, f32, c.var);
   if (g->dim != 2 || !autotune_mode || !var_grid(g->geo)) {
     apply(g, f32, c, 0);
     return NF_OK;
@@ -316,7 +322,7 @@ bool tune_lookup(int device, int nx, int ny, bool f32, int var[3]) {
   shape.ny = ny;
   shape.h = nx / 2;
   shape.nz = 1;
-  untuned_tiles(shape, var);
+  untuned_tiles(shape, f32, var);
   if (!autotune_mode) return false;
   auto it = cache.find(std::make_tuple(device, nx, ny, f32 ? 1 : 0));
   if (it == cache.end()) return false;

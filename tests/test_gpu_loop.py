@@ -55,3 +55,34 @@ def test_first_iterates_and_attainable_accuracy(n, L):
         rc, info = g.pressure_solve(T(m), T(r), T(S), p, rtol=1e-15, max_iter=4000)
         assert info.converged and info.true_rel_res <= 1e-11
         assert rel(p.cpu().numpy(), want) <= TOL
+
+
+@pytest.mark.parametrize("n,L", [((2048, 8), (1.0, 1.0 / 256)), ((4096, 50), (1.0, 1.0 / 80)),
+                                 ((16, 4096), (1.0 / 256, 1.0))])
+def test_sequential_field_tiles_match_oracle(n, L):
+    """Rows of 2048 and more (and FP32 columns of 4096) with one field at a time in
+    LDS: the tiles a handle takes when the tuner is off."""
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    rng = np.random.default_rng(43)
+    shape = n[::-1]
+    m = rng.uniform(-1.0, 1.0, (2,) + shape)
+    r = rng.uniform(0.05, 0.15, shape)
+    S = rng.standard_normal(shape)
+    S -= S.mean()
+    want, io = O.pressure_pcg(m, r, S, None, 1e-12, 4000, L)
+    NF.nf_set_autotune(0)
+    try:
+        for dtype in (NF.NF_F64, NF.NF_F32_REFINED):
+            with NF.Grid(n, L, dtype=dtype) as g:
+                p = T(np.zeros(shape))
+                rc, info = g.pressure_solve(T(m), T(r), T(S), p, rtol=1e-12, max_iter=4000)
+                assert info.converged
+                if dtype == NF.NF_F64:
+                    assert abs(info.iters - io.iters) <= 1
+                assert rel(p.cpu().numpy(), want) <= TOL
+    finally:
+        NF.nf_set_autotune(2)
