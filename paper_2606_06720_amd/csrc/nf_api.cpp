@@ -3,6 +3,7 @@
 // stopping criteria (Algorithm 1, Sec. 2.5) and the discrete energy.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <chrono>
 #include <climits>
 #include <cmath>
@@ -89,6 +90,16 @@ void make_twiddles(int N, T* out /* 2N */) {
     out[2 * u] = (T)c;
     out[2 * u + 1] = (T)(-s);
   }
+}
+
+// The handle's small-grid team.  Successive handles take successive XCDs, so
+// that teams that run at the same time have compute units of their own.
+constexpr size_t TEAM_DOUBLES = (sizeof(TeamCtl) + sizeof(double) - 1) / sizeof(double);
+std::atomic<unsigned> next_xcc{0};
+void team_init(nf_grid* g) {
+  g->team_on = g->team_loop = team_shape(g->geo, &g->team_shape);
+  g->team_shape.xcc = (int)(next_xcc.fetch_add(1) % 8);
+  g->team_shape.epoch = 0;
 }
 
 int check_launch(nf_grid* g, hipError_t e, const char* what) {
@@ -195,6 +206,55 @@ int init_residual(nf_grid* g, const double* m, const double* r, float* lo = null
   return NF_OK;
 }
 
+TeamGo team_args(const nf_grid* g, bool f32, const double* m, const double* r, int max_iter, double tol2) {
+  TeamGo go{};
+  const size_t n = (size_t)g->nx * g->ny;
+  go.ts = g->team_shape;
+  go.max_iter = max_iter;
+  go.tol2 = tol2;
+  if (f32) {
+    go.f = FluxArgs{g->geo32, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, nullptr, nullptr};
+    go.a = IterArgs{g->geo32, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32};
+  } else {
+    go.f = FluxArgs{g->geo, g->mix[0], g->mix[1], m, r, nullptr, nullptr};
+    go.a = IterArgs{g->geo, g->mix[0], g->mix[1], g->xh, g->rh, g->dh, g->qh};
+  }
+  return go;
+}
+
+// The loop as launches of the small-grid team.  *done: the solve has stopped and
+// *fin is its status; otherwise a team did not form and the loop of launches
+// goes on from iteration *it.
+int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_iter, double tol2, DevStatus* fin,
+              int* it, bool* done) {
+  hipStream_t s = g->stream;
+  TeamGo go = team_args(g, f32, m, r, max_iter, tol2);
+  go.what = TeamGo::LOOP;
+  *done = false;
+  while (*it < max_iter) {
+    go.it = *it;
+    go.nk = max_iter - *it < TEAM_CHUNK ? max_iter - *it : TEAM_CHUNK;
+    go.ts.epoch = g->team_shape.epoch;
+    if (*it > 0) LCHK(g, launch_team_reset(go.a.g, s));
+    LCHK(g, launch_team(f32, go, s));
+    g->team_shape.epoch += 2 * (unsigned)go.nk + 2;
+    int rc = read_status(g, fin);
+    if (rc) return rc;
+    if (fin->conv_at != INT_MAX) {
+      *done = true;
+      return NF_OK;
+    }
+    if (fin->team == TEAM_LOST) return fail(g, NF_EDEVICE, "a member of the small-grid team was lost");
+    if (fin->team != TEAM_MORE) {
+      if (++g->team_missed >= 2) g->team_loop = false;
+      return NF_OK;
+    }
+    g->team_missed = 0;
+    *it += go.nk;
+  }
+  return NF_OK;
+}
+
 // Iterations it = 0, 1, ... of the PCG loop after its first update, queued in
 // chunks; after each chunk the status is copied to pinned memory, and the host
 // waits on the copy of the PREVIOUS chunk, so the GPU always has queued work.
@@ -209,6 +269,13 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
   int rc = timed_reset(g);
   if (rc) return rc;
   int it = 0;
+  TeamGo go{};
+  if (g->team_on) go = team_args(g, f32, m, r, max_iter, tol2);
+  if (g->team_loop && g->timed < 0) {
+    bool done = false;
+    rc = team_loop(g, f32, m, r, max_iter, tol2, fin, &it, &done);
+    if (rc || done) return rc;
+  }
   int slot = 0, pending = -1;
   bool first_chunk = true, stopped = false;
   while (it < max_iter) {
@@ -231,7 +298,13 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
         ++it;
         continue;
       }
-      if (f32) {
+      if (g->team_on) {
+        go.it = it;
+        go.what = TeamGo::ROW;
+        LCHK(g, launch_team(f32, go, s));
+        go.what = TeamGo::COL;
+        LCHK(g, launch_team(f32, go, s));
+      } else if (f32) {
         LCHK(g, launch_row_flux32(G, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, it, tol2, s));
         LCHK(g, launch_col_iter32(G, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32, it, max_iter, s));
       } else {
@@ -392,13 +465,16 @@ int pcg(nf_grid* g, const double* m, const double* r, XSource src, const double*
   DevStatus fin;
   rc = pcg_loop(g, false, m, r, max_iter, tol2, g->last_iters, &fin);
   if (rc) return rc;
-  if (!fin.converged && fin.conv_at == max_iter && max_iter > 0 && !(fin.flags & (FLAG_NONFINITE | FLAG_INCOMPAT))) {
+  if (!fin.converged && fin.team != TEAM_STOP && fin.conv_at == max_iter && max_iter > 0 && !(fin.flags & (FLAG_NONFINITE | FLAG_INCOMPAT))) {
     // stopped by max_iter: take the stopping test on the final residual here
     if (g->dim == 3) {
       LCHK(g, launch3_sum_tot(G, SLOT_RR, 1, nwg3_ziter(G, false), s));
       LCHK(g, launch3_copy_tot(G, SLOT_RR, 1, 11, s));
-    } else
+    } else if (g->team_on) {
+      LCHK(g, launch_team_rr(G, g->team_shape, s));
+    } else {
       LCHK(g, launch_sum_slot(G, slot_ptr(g->part, SLOT_RR), 1, rr_nwg(G, false), 11, s));
+    }
     rc = read_status(g, &fin);
     if (rc) return rc;
     fin.rr[0] = fin.out[11];
@@ -718,7 +794,7 @@ int nf_create_grid(nf_grid** out, int ndim, const int64_t n[3], const double L[3
       if (nwg3_ziter(tmp, f32) > pstride) pstride = nwg3_ziter(tmp, f32);
     }
   }
-  const size_t part_doubles = (size_t)NSLOTS * SLOT_K * pstride + NSLOTS * SLOT_K;
+  const size_t part_doubles = (size_t)NSLOTS * SLOT_K * pstride + NSLOTS * SLOT_K + TEAM_DOUBLES;
   CREATE_CHK(hipMalloc((void**)&g->part, part_doubles * sizeof(double)), NF_ENOMEM);
   CREATE_CHK(hipMalloc((void**)&g->st, sizeof(DevStatus)), NF_ENOMEM);
   g->st_own = g->st;
@@ -765,9 +841,11 @@ int nf_create_grid(nf_grid** out, int ndim, const int64_t n[3], const double L[3
   G.tot = g->part + (size_t)NSLOTS * SLOT_K * pstride;
   G.tclk = nullptr;
   G.tkind = -1;
+  G.team = ndim == 2 ? G.tot + NSLOTS * SLOT_K : nullptr;
   for (int k = 0; k < 2; ++k) G.var_flux[k] = G.var_div[k] = G.var_upd[k] = VAR_DEFAULT;
   g->geo32 = G;
   g->geo32.tw = g->tw32;
+  team_init(g);
   // tile variants of the PCG loop for this grid shape (tuned once per process)
   rc = nf::tune_handle(g);
   if (rc != NF_OK) {
@@ -998,7 +1076,7 @@ int nf_pressure_solve_noalloc(const int64_t n[2], const double L[2], void* strea
   const size_t spec_bytes = (size_t)g->h * g->ny * 2 * sizeof(double);
   void** spec[] = {&g->xh, &g->rh, &g->dh, &g->qh, &g->bh, &g->mix[0], &g->mix[1], &g->mix[2]};
   for (void** b : spec) *b = carve(spec_bytes);
-  const size_t part_doubles = (size_t)NSLOTS * SLOT_K * MAX_WG + NSLOTS * SLOT_K;
+  const size_t part_doubles = (size_t)NSLOTS * SLOT_K * MAX_WG + NSLOTS * SLOT_K + TEAM_DOUBLES;
   g->part = (double*)carve(part_doubles * sizeof(double));
   g->st = (DevStatus*)carve(sizeof(DevStatus));
   g->tw = carve((size_t)g->twn * 2 * sizeof(double));
@@ -1028,6 +1106,7 @@ int nf_pressure_solve_noalloc(const int64_t n[2], const double L[2], void* strea
   Gg.tot = g->part + (size_t)NSLOTS * SLOT_K * MAX_WG;
   Gg.tclk = nullptr;
   Gg.tkind = -1;
+  Gg.team = Gg.tot + NSLOTS * SLOT_K;
   // the tile variants tuned for this shape by an earlier nf_create_grid, if any
   int var[3] = {VAR_DEFAULT, VAR_DEFAULT, VAR_DEFAULT};
   (void)nf::tune_lookup(g->device, g->nx, g->ny, false, var);
@@ -1036,6 +1115,7 @@ int nf_pressure_solve_noalloc(const int64_t n[2], const double L[2], void* strea
     Gg.var_div[k] = var[1];
     Gg.var_upd[k] = var[2];
   }
+  team_init(g);
   // the array keeps the previous call's contents: clear the partial sums (a
   // fill kernel, no memset node) before the solve resets the status
   int rc = check_launch(g, launch_zero_doubles(g->part, part_doubles, g->stream), "clear workspace");

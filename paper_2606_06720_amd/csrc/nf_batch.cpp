@@ -69,6 +69,8 @@ struct Part {
   struct Group {
     std::vector<int> idx;
     Geo shape;
+    bool team = false;  // the shape's loop runs the small-grid team's passes
+    TeamShape ts{};
     char* dev = nullptr;
     size_t bytes = 0;
     std::vector<char> host;
@@ -211,7 +213,22 @@ int launch_chunk(Part* b, bool f32, int it0, int nk, int max_iter, double tol2) 
   for (int it = it0; it < it0 + nk; ++it) {
     for (auto& G : b->groups) {
       const int k = (int)G.idx.size();
-      if (f32) {
+      if (G.team) {
+        // the passes of the small-grid team, which a handle of its own runs in
+        // one launch: same results
+        TeamGo go{};
+        go.ts = G.ts;
+        go.it = it;
+        go.max_iter = max_iter;
+        go.tol2 = tol2;
+        go.count = k;
+        go.fb = f32 ? G.t.flux32 : G.t.flux_loop;
+        go.ab = f32 ? G.t.iter32 : G.t.iter64;
+        go.what = TeamGo::ROWS;
+        BCHK(b, launch_team(f32, go, s));
+        go.what = TeamGo::COLS;
+        BCHK(b, launch_team(f32, go, s));
+      } else if (f32) {
         BCHK(b, launchb_row_flux32(G.shape, G.t.flux32, k, it, tol2, s));
         BCHK(b, launchb_col_iter32(G.shape, G.t.iter32, k, it, max_iter, s));
       } else {
@@ -339,8 +356,13 @@ int batch_solve(Part* b, bool first, double* const* p, double rtol, int max_iter
                           !(f.flags & (FLAG_NONFINITE | FLAG_INCOMPAT)));
     }
     if (capped) {
-      for (auto& G : b->groups)
-        BCHK(b, launchb_sum_slot(G.t.sum_rr, (int)G.idx.size(), 1, rr_nwg(G.shape, false), 11, s));
+      for (auto& G : b->groups) {
+        if (G.team) {
+          for (int i : G.idx) BCHK(b, launch_team_rr(b->inst[i]->geo, G.ts, s));
+        } else {
+          BCHK(b, launchb_sum_slot(G.t.sum_rr, (int)G.idx.size(), 1, rr_nwg(G.shape, false), 11, s));
+        }
+      }
       rc = read_all(b);
       if (rc) return rc;
     }
@@ -577,6 +599,8 @@ int part_create(nf_batch* top, const std::vector<int>& idx, Part** out, std::str
       q->groups.emplace_back();
       grp = &q->groups.back();
       grp->shape = g->geo;
+      grp->team = g->team_on;
+      grp->ts = g->team_shape;
     }
     grp->idx.push_back(i);
   }

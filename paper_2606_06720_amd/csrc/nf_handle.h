@@ -63,6 +63,11 @@ struct nf_grid {
   int tune_ncand[3] = {1, 1, 1};
   double tune_us[3] = {0.0, 0.0, 0.0};
   double tune_us_default[3] = {0.0, 0.0, 0.0};
+  // small-grid team (nf_team.hpp): its split, whether the grid uses its passes,
+  // whether as one launch (two launches that did not form switch to passes)
+  nf::TeamShape team_shape{};
+  bool team_on = false, team_loop = false;
+  int team_missed = 0;
 };
 
 namespace nf {

@@ -28,6 +28,32 @@ struct DevStatus {
   int outer_done;   // mixed-precision solve: 1 once the FP64 residual test has ended it
   int itot;         // mixed-precision solve: FP32 iterations of the finished corrections
   int budget;       // iteration limit of the current (inner) PCG run, INT_MAX when unused
+  int team;         // outcome of the last team launch (TEAM_*), TEAM_NONE if no team ran
+};
+// what a team launch left (DevStatus::team): more iterations to do, stopped by
+// max_iter, stopped by the residual test, a member was lost
+enum { TEAM_NONE = 0, TEAM_MORE = 1, TEAM_STOP = 2, TEAM_CONV = 3, TEAM_LOST = 4 };
+// formation of a team (TeamCtl::state)
+enum { TEAM_OPEN = 0, TEAM_GO = 1, TEAM_ABORT = 2 };
+enum {
+  TEAM_MAX = 32,      // members at most: the compute units of an XCD
+  TEAM_CHUNK = 4096,  // iterations per team launch at most
+};
+// Device memory of a handle's team: formation and the barrier's slots, two sets
+// of two 16-byte entries (partial sum, epoch) per member.
+struct TeamCtl {
+  unsigned tickets, state;
+  unsigned pad[14];
+  double slots[2 * TEAM_MAX * 2 * 2];
+};
+// Split of a grid over a team: members, columns and 2^lr rows per member,
+// threads per member, the XCD it runs on, and the epoch its barriers count from.
+// complex elements of a member's transform buffer: two fields of at most 2 nt
+// elements in padded lines, with room for short lines
+constexpr int team_lds(int nt) { return nt == 64 ? 672 : (nt == 128 ? 1120 : (nt == 256 ? 1664 : 2688)); }
+struct TeamShape {
+  int G, C, lr, nt, xcc;
+  unsigned epoch;
 };
 
 enum { FLAG_NONFINITE = 1, FLAG_INCOMPAT = 2 };
@@ -68,6 +94,7 @@ struct Geo {
   // tclk[2 (it TCLK_W + (block mod TCLK_W))]; the host reduces them
   unsigned long long* tclk;
   int tkind;
+  void* team;         // TeamCtl of the handle (2D)
   // tile variants of the PCG-loop passes chosen by the tuner (index 0: FP64
   // passes, 1: FP32 passes; VAR_DEFAULT = 1 is the untuned tile): row pass (row
   // variant), column pass (column variant var_upd; var_div keeps the code a
@@ -277,6 +304,23 @@ int div_var_threads(const Geo& g, int cv);
 // variants in use by the loop (it >= 0), the column pass
 int use_rv(const Geo& g, bool f32, int it);
 int use_cv(const Geo& g, bool f32);
+// the small-grid team (nf_team.hpp): the split of a grid if it has one; reset of its
+// formation before a launch that no loop start precedes; what to launch
+bool team_shape(const Geo& g, TeamShape* ts);
+hipError_t launch_team_reset(const Geo& g, hipStream_t s);
+struct TeamGo {
+  enum { LOOP, ROW, COL, ROWS, COLS } what;  // the team; a pass as a launch, for one or `count` instances
+  TeamShape ts;
+  int it, nk, max_iter;
+  double tol2;
+  FluxArgs f;          // LOOP, ROW
+  IterArgs a;          // LOOP, COL
+  const FluxArgs* fb;  // ROWS
+  const IterArgs* ab;  // COLS
+  int count;
+};
+hipError_t launch_team(bool f32, const TeamGo& go, hipStream_t s);
+hipError_t launch_team_rr(const Geo& g, const TeamShape& ts, hipStream_t s);
 // whether an axis length has tuned variants; whether the grid has any
 bool tuned_length(int n);
 bool var_grid(const Geo& g);

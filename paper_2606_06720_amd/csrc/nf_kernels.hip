@@ -49,7 +49,15 @@ __device__ __forceinline__ void k_status_reset_one(DevStatus* st, int full) {
     st->converged = 0;
     st->iters = 0;
     st->flags = 0;
+    st->team = TEAM_NONE;
   }
+}
+// open the formation of the team a loop start may be followed by
+__device__ __forceinline__ void team_open(const Geo& g) {
+  if (g.team == nullptr) return;
+  ((TeamCtl*)g.team)->tickets = 0;
+  ((TeamCtl*)g.team)->state = TEAM_OPEN;
+  g.st->team = TEAM_NONE;
 }
 
 __global__ void k_status_reset(DevStatus* st, int full) {
@@ -728,6 +736,7 @@ __device__ __forceinline__ void col_start_body(Geo g, const cd* __restrict__ rh,
   const bool conv = !bad && (incompat || zero_x || rr <= tol2 * bb);
   if (bad) zero_x = false;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
+    team_open(g);
     st->rho[0] = rho;
     st->rr[0] = zero_x ? 0.0 : rr;
     st->rr0 = rr;
@@ -840,6 +849,7 @@ __device__ __forceinline__ void col_refine_start_body(Geo g, const cd* __restric
   double tin = 0.5 * sqrt(tol2 * bb / rr);
   tin = tin < floor_in ? floor_in : (tin > 0.5 ? 0.5 : tin);
   if (lead) {
+    team_open(g);
     st->orr = rr;
     st->obb = bb;
     st->rscale = sqrt(rr);

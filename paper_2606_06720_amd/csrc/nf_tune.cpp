@@ -362,6 +362,7 @@ int nf_set_tiles(nf_grid* g, int flux_var, int div_var, int update_var) {
     H->var_upd[k] = v[2];
   }
   g->tuned = 0;
+  g->team_on = g->team_loop = false;  // the caller asks for the tiled passes
   return NF_OK;
 }
 
