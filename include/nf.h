@@ -359,6 +359,11 @@ const char *nf_batch_last_error(const nf_batch *b);
  * of that shape use the same choice, so their results agree bit for bit.
  * The variants change the work split and the rounding of the transforms and
  * inner products only.
+ * Grids of 65537 to 524288 points whose tiles divide them (all powers of two with
+ * Nx from 128 to 2048 and Ny from 64 to 1024 among them) run the loop as one launch
+ * if no other solve is in progress on the device, and keep the tiles of that launch
+ * where its passes run as launches (concurrent solves, ensembles, timed handles);
+ * the record below then is that of the passes a handle uses after nf_set_tiles.
  * nf_set_autotune: 2 (the default) times each candidate's throughput with three
  *   concurrent launches on separate buffers on grids of 2^19 to 2^21 points
  *   (the choice for solves that share the GPU, as ensemble partitions and

@@ -15,7 +15,8 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libnf.so")
 
 SOURCES = ["nf_loop_row64.hip", "nf_loop_row32.hip", "nf_loop_col64.hip", "nf_loop_col32.hip", "nf_team.hip",
-           "nf_team64a.hip", "nf_team64b.hip", "nf_team32a.hip", "nf_team32b.hip", "nf_kernels.hip",
+           "nf_team64a.hip", "nf_team64b.hip", "nf_team32a.hip", "nf_team32b.hip", "nf_chip.hip", "nf_chip64a.hip",
+           "nf_chip64b.hip", "nf_chip64c.hip", "nf_chip32a.hip", "nf_chip32b.hip", "nf_chip32c.hip", "nf_kernels.hip",
            "nf_kernels3d.hip", "nf_api.cpp", "nf_batch.cpp", "nf_noalloc.hip", "nf_tune.cpp"]
 
 HIP_FLAGS = [

@@ -101,6 +101,28 @@ void team_init(nf_grid* g) {
   g->team_shape.xcc = (int)(next_xcc.fetch_add(1) % 8);
   g->team_shape.epoch = 0;
 }
+// The handle's team over the chip: its loop's passes, as launches or as one, take
+// the team's tiles, also where the device has too few compute units for one.
+void chip_init(nf_grid* g) {
+  int cus = 0;
+  g->geo.wide = g->geo32.wide = -1;
+  if (g->dim != 2 || g->team_on || !chip_shape(g->geo, &g->chip_shape)) return;
+  g->geo.wide = g->geo32.wide = g->chip_shape.wide;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess) cus = 0;
+  g->chip_loop = g->chip_shape.G <= cus;
+}
+
+// PCG loops in progress per device.  A team over the chip leaves no room for others,
+// so a loop runs as one only if it starts alone; loops on several streams run as
+// launches, which overlap (the results are the same either way).
+constexpr int MAX_DEV = 64;
+std::atomic<int> loops_on[MAX_DEV];
+struct LoopCount {
+  std::atomic<int>& n;
+  bool alone;
+  explicit LoopCount(int dev) : n(loops_on[dev >= 0 && dev < MAX_DEV ? dev : 0]), alone(n.fetch_add(1) == 0) {}
+  ~LoopCount() { n.fetch_sub(1); }
+};
 
 int check_launch(nf_grid* g, hipError_t e, const char* what) {
   if (e != hipSuccess) return fail(g, NF_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
@@ -222,7 +244,7 @@ TeamGo team_args(const nf_grid* g, bool f32, const double* m, const double* r, i
   return go;
 }
 
-// The loop as launches of the small-grid team.  *done: the solve has stopped and
+// The loop as launches of the grid's team.  *done: the solve has stopped and
 // *fin is its status; otherwise a team did not form and the loop of launches
 // goes on from iteration *it.
 int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_iter, double tol2, DevStatus* fin,
@@ -236,17 +258,17 @@ int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_it
     go.nk = max_iter - *it < TEAM_CHUNK ? max_iter - *it : TEAM_CHUNK;
     go.ts.epoch = g->team_shape.epoch;
     if (*it > 0) LCHK(g, launch_team_reset(go.a.g, s));
-    LCHK(g, launch_team(f32, go, s));
-    g->team_shape.epoch += 2 * (unsigned)go.nk + 2;
+    LCHK(g, g->chip_loop ? launch_chip(f32, go, s) : launch_team(f32, go, s));
+    g->team_shape.epoch += 2 * (unsigned)go.nk + 4;
     int rc = read_status(g, fin);
     if (rc) return rc;
     if (fin->conv_at != INT_MAX) {
       *done = true;
       return NF_OK;
     }
-    if (fin->team == TEAM_LOST) return fail(g, NF_EDEVICE, "a member of the small-grid team was lost");
+    if (fin->team == TEAM_LOST) return fail(g, NF_EDEVICE, "a member of the team was lost");
     if (fin->team != TEAM_MORE) {
-      if (++g->team_missed >= 2) g->team_loop = false;
+      if (++g->team_missed >= 2) g->team_loop = g->chip_loop = false;
       return NF_OK;
     }
     g->team_missed = 0;
@@ -271,7 +293,8 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
   int it = 0;
   TeamGo go{};
   if (g->team_on) go = team_args(g, f32, m, r, max_iter, tol2);
-  if (g->team_loop && g->timed < 0) {
+  LoopCount count(g->device);
+  if ((g->team_loop || (g->chip_loop && count.alone)) && g->timed < 0) {
     bool done = false;
     rc = team_loop(g, f32, m, r, max_iter, tol2, fin, &it, &done);
     if (rc || done) return rc;
@@ -846,6 +869,7 @@ int nf_create_grid(nf_grid** out, int ndim, const int64_t n[3], const double L[3
   g->geo32 = G;
   g->geo32.tw = g->tw32;
   team_init(g);
+  g->geo.wide = g->geo32.wide = -1;
   // tile variants of the PCG loop for this grid shape (tuned once per process)
   rc = nf::tune_handle(g);
   if (rc != NF_OK) {
@@ -853,6 +877,7 @@ int nf_create_grid(nf_grid** out, int ndim, const int64_t n[3], const double L[3
     nf_destroy_grid(g);
     return rc;
   }
+  chip_init(g);
   *out = g;
   return rc;
 }
@@ -1116,6 +1141,7 @@ int nf_pressure_solve_noalloc(const int64_t n[2], const double L[2], void* strea
     Gg.var_upd[k] = var[2];
   }
   team_init(g);
+  chip_init(g);
   // the array keeps the previous call's contents: clear the partial sums (a
   // fill kernel, no memset node) before the solve resets the status
   int rc = check_launch(g, launch_zero_doubles(g->part, part_doubles, g->stream), "clear workspace");

@@ -126,10 +126,13 @@ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n >> 1); }
 // Radices of a length-2^p transform: as many 8s as possible with a tail of 4,
 // 4,4 or a lone 2.  Plan 0 runs the 8s first, plan 1 the tail first (the two
 // differ when p is not a multiple of 3); the run-time tuner picks between them.
-constexpr int plan_nstages(int p) {
+// Plan 2 is 4s with a tail of 2.
+constexpr int plan_nstages(int p, int pl = 0) {
+  if (pl == 2) return p / 2 + p % 2;
   return p <= 2 ? 1 : (p % 3 == 0 ? p / 3 : (p % 3 == 2 ? p / 3 + 1 : p / 3 + 1));
 }
 constexpr int plan_radix(int p, int s, int pl = 0) {
+  if (pl == 2) return s < p / 2 ? 4 : 2;
   if (p == 1) return 2;
   if (p == 2) return 4;
   if (p % 3 == 0) return 8;
@@ -146,8 +149,8 @@ constexpr bool plan_has_alt(int p) { return p > 2 && p % 3 != 0; }
 // Lengths n = 5^k 2^p: k radix-5 stages first, then the power-of-two plan above.
 constexpr int f5(int n) { return n % 5 == 0 ? 1 + f5(n / 5) : 0; }
 constexpr int pow5(int k) { return k == 0 ? 1 : 5 * pow5(k - 1); }
-constexpr int mplan_nstages(int n) {
-  return f5(n) + (n / pow5(f5(n)) == 1 ? 0 : plan_nstages(ilog2(n / pow5(f5(n)))));
+constexpr int mplan_nstages(int n, int pl = 0) {
+  return f5(n) + (n / pow5(f5(n)) == 1 ? 0 : plan_nstages(ilog2(n / pow5(f5(n))), pl));
 }
 constexpr int mplan_radix(int n, int s, int pl = 0) {
   return s < f5(n) ? 5 : plan_radix(ilog2(n / pow5(f5(n))), s - f5(n), pl);
@@ -191,13 +194,12 @@ __device__ __forceinline__ void wave_sync() {
 // last stage (LAST) for the cross-wave phase that follows.
 template <typename T, int DIR, int L, int B, int LS, int NT, int R, int NS, bool PIN, bool POUT, bool WL = false,
           bool LAST = true>
-__device__ __forceinline__ void fft_stage(cx<T>* buf, const cx<T>* __restrict__ tw, int twn) {
+__device__ __forceinline__ void fft_stage(cx<T>* buf, const cx<T>* __restrict__ tw, int twn, int tid) {
   static_assert(!(PIN || POUT) || LS >= lpad_len(L), "line stride too small for the padded layout");
   constexpr int Q = L / R;          // butterflies per line
   constexpr int NBF = B * Q;        // butterflies in the batch
   constexpr int PER = (NBF + NT - 1) / NT;
   constexpr bool EXACT = (PER * NT == NBF);
-  const int tid = threadIdx.x;
   cx<T> v[PER][R];
   cx<T> w[PER][R];
   // the table has twn entries, this stage needs angles in units of
@@ -260,32 +262,32 @@ __device__ __forceinline__ void fft_stage(cx<T>* buf, const cx<T>* __restrict__ 
 // whole waves.
 template <int L, int NT, int PL>
 constexpr bool wave_local_ok() {
-  if (mplan_nstages(L) < 1 || NT % 64 != 0) return false;
+  if (mplan_nstages(L, PL) < 1 || NT % 64 != 0) return false;
   const int r0 = mplan_radix(L, 0, PL);
-  for (int s = 1; s < mplan_nstages(L); ++s)
+  for (int s = 1; s < mplan_nstages(L, PL); ++s)
     if (mplan_radix(L, s, PL) != r0) return false;
   const int q = L / r0;
   return q <= 64 && 64 % q == 0;
 }
 
 template <typename T, int DIR, int L, int B, int LS, int NT, int S, int PL>
-__device__ __forceinline__ void fft_stages(cx<T>* buf, const cx<T>* __restrict__ tw, int twn) {
+__device__ __forceinline__ void fft_stages(cx<T>* buf, const cx<T>* __restrict__ tw, int twn, int tid) {
   static_assert(plan_ok(L), "transform lengths are 5^k 2^p");
-  if constexpr (S < mplan_nstages(L)) {
+  if constexpr (S < mplan_nstages(L, PL)) {
     constexpr bool PAD = lpad_use(L) && LS >= lpad_len(L);
     constexpr bool WL = wave_local_ok<L, NT, PL>();
     fft_stage<T, DIR, L, B, LS, NT, mplan_radix(L, S, PL), mplan_ns(L, S, PL), PAD && (S > 0),
-              PAD && (S + 1 < mplan_nstages(L)), WL, S + 1 == mplan_nstages(L)>(buf, tw, twn);
-    fft_stages<T, DIR, L, B, LS, NT, S + 1, PL>(buf, tw, twn);
+              PAD && (S + 1 < mplan_nstages(L, PL)), WL, S + 1 == mplan_nstages(L, PL)>(buf, tw, twn, tid);
+    fft_stages<T, DIR, L, B, LS, NT, S + 1, PL>(buf, tw, twn, tid);
   }
 }
 
-// In-LDS FFT of B lines of length L (line stride LS), all NT threads taking part,
-// with radix plan PL (see plan_radix).
+// In-LDS FFT of B lines of length L (line stride LS), all NT threads taking part
+// (tid: their index), with radix plan PL (see plan_radix).
 // Caller must __syncthreads() before (data written) -- the routine ends with a barrier.
 template <typename T, int DIR, int L, int B, int LS, int NT, int PL = 0>
-__device__ __forceinline__ void lds_fft(cx<T>* buf, const cx<T>* __restrict__ tw, int twn) {
-  fft_stages<T, DIR, L, B, LS, NT, 0, PL>(buf, tw, twn);
+__device__ __forceinline__ void lds_fft(cx<T>* buf, const cx<T>* __restrict__ tw, int twn, int tid = threadIdx.x) {
+  fft_stages<T, DIR, L, B, LS, NT, 0, PL>(buf, tw, twn, tid);
 }
 
 // ------------------------------------------------- real <-> half-complex (x axis)

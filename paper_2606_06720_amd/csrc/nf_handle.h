@@ -68,6 +68,9 @@ struct nf_grid {
   nf::TeamShape team_shape{};
   bool team_on = false, team_loop = false;
   int team_missed = 0;
+  // team over the chip (nf_chip.hpp): whether the loop runs as one, and its split
+  bool chip_loop = false;
+  nf::ChipShape chip_shape{};
 };
 
 namespace nf {

@@ -55,13 +55,22 @@ struct TeamShape {
   int G, C, lr, nt, xcc;
   unsigned epoch;
 };
+// The team over the chip (nf_chip.hpp): members at most; its barrier's 16-byte
+// entries (two sets of two per member, two sets of eight published lines), which
+// lie in the arrays of SLOT_P3 that the 2D passes leave unused; the split of a grid:
+// members, the tiles' class (Geo::wide) with rows and columns per tile, row and
+// column tiles, row tiles whose elements a column tile's threads take at a time.
+enum { CHIP_MAX = 256, CHIP_SLOTS = 2 * CHIP_MAX * 2 + 2 * 64 };
+struct ChipShape {
+  int G, wide, R, C, nrow, ncol, step;
+};
 
 enum { FLAG_NONFINITE = 1, FLAG_INCOMPAT = 2 };
 
 // Slots of the partial-sum area; each slot holds up to SLOT_K arrays of
 // MAX_WG doubles.
 enum {
-  SLOT_P3 = 0,      // 2D: <z, A z> of z = M^-1 r; 3D: <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r>
+  SLOT_P3 = 0,      // 2D: <z, A z> of z = M^-1 r (and CHIP_SLOTS from its second array on); 3D: <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r>
   SLOT_P3INIT = 1,  // <r,M^-1 r>, <r,r>, <b,b>
   SLOT_KBAR = 2,    // sum mx^2, mx my, my^2, r
   SLOT_SCHK = 3,    // sum S, sum |S|
@@ -101,12 +110,16 @@ struct Geo {
   // caller set for the operator end, which is part of that pass).  Read by the
   // launchers only.
   int var_flux[2], var_div[2], var_upd[2];
+  // grids with a team over the chip: the loop's passes take that team's tiles, row
+  // variant RV_WIDE + wide and column variant CV_WIDE + wide, instead (-1: no team)
+  int wide;
 };
 
 enum { TCLK_CAP = 2048, TCLK_W = 64 };  // timed iterations per PCG loop, stamp slots per iteration
-// tile variants of the PCG-loop passes (codes 0 .. NVAR-1, see nf_tiles.hpp);
+// tile variants of the PCG-loop passes (see nf_tiles.hpp; the tuner times codes below NVAR);
 // VAR_DEFAULT is the untuned tile
-enum { VAR_DEFAULT = 1, RV_SMALL = 9, RV_SEQ = 12, NRV = 15, CV_SMALL = 12, CV_SEQ = 15, NCV = 17, NVAR = 17 };
+enum { VAR_DEFAULT = 1, RV_SMALL = 9, RV_SEQ = 12, RV_WIDE = 15, NRV = 17, CV_SMALL = 12, CV_SEQ = 15, CV_WIDE = 17,
+       NCV = 19, NVAR = 17 };
 
 __host__ __device__ inline double* slot_ptr(double* part, int slot) {
   return part + (size_t)slot * SLOT_K * MAX_WG;
@@ -321,6 +334,10 @@ struct TeamGo {
 };
 hipError_t launch_team(bool f32, const TeamGo& go, hipStream_t s);
 hipError_t launch_team_rr(const Geo& g, const TeamShape& ts, hipStream_t s);
+// the team over the chip (nf_chip.hpp): the split of a grid, if it has one; the launch
+// (go.a, go.f, go.ts.epoch)
+bool chip_shape(const Geo& g, ChipShape* cs);
+hipError_t launch_chip(bool f32, const TeamGo& go, hipStream_t s);
 // whether an axis length has tuned variants; whether the grid has any
 bool tuned_length(int n);
 bool var_grid(const Geo& g);

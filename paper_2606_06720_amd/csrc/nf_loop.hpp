@@ -22,6 +22,11 @@
 
 #include <climits>
 
+// Products are fused into sums within an expression only, not where the
+// optimiser happens to find them: these passes and the kernel that runs them as
+// one launch (nf_chip.hpp) have to round alike.
+#pragma clang fp contract(on)
+
 #include "nf_fft.hpp"
 #include "nf_internal.h"
 #include "nf_tiles.hpp"
@@ -178,7 +183,7 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
   tclk_end(g, 0, it);
 }
 // The loop's row pass with the two fields one after the other through one field's
-// LDS (row variants RV_SEQ and up, rows of 2048 and more): grad_x waits in
+// LDS (row variants from RV_SEQ to below RV_WIDE, rows of 2048 and more): grad_x waits in
 // registers while grad_y is transformed, F_x while F_y is.  For the same rows
 // the tile takes half the LDS and half the threads, so twice the workgroups
 // share a compute unit and one's transforms overlap the others' memory phases
@@ -294,13 +299,13 @@ template <int NX, typename T, int RV>
 __global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) k_row_flux(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
                                                   const T* __restrict__ r, int it, double* kslot, int nwg_col,
                                                   double tol2, float* lo) {
-  if constexpr (RV >= RV_SEQ) row_flux_seq_body<NX, T, RV>(g, G0, G1, m, r, it, nwg_col, tol2);
+  if constexpr (RV >= RV_SEQ && RV < RV_WIDE) row_flux_seq_body<NX, T, RV>(g, G0, G1, m, r, it, nwg_col, tol2);
   else row_flux_body<NX, T, RV>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo);
 }
 template <int NX, typename T, int RV>
 __global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) kb_row_flux(const FluxArgs* __restrict__ A, int it, int nwg_col, double tol2) {
   const FluxArgs& a = A[blockIdx.y];
-  if constexpr (RV >= RV_SEQ) row_flux_seq_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, nwg_col, tol2);
+  if constexpr (RV >= RV_SEQ && RV < RV_WIDE) row_flux_seq_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, nwg_col, tol2);
   else row_flux_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, (double*)a.kslot, nwg_col, tol2, (float*)a.lo);
 }
 
@@ -429,7 +434,7 @@ __device__ __forceinline__ void col_iter_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>
   tclk_end(g, 2, it + 1);
 }
 // The column pass with one field at a time through one field's LDS (column
-// variants CV_SEQ and up): w is summed up in registers, grad_x leaves before
+// variants from CV_SEQ to below CV_WIDE): w is summed up in registers, grad_x leaves before
 // grad_y is formed.  Half the LDS and, for the same elements per thread, half
 // the threads per workgroup, so twice the workgroups share a compute unit.
 template <int NY, typename T, int CV>
@@ -578,20 +583,20 @@ __device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, c
 template <int NY, typename T, int CV>
 __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) k_col_iter(Geo g, cx<T>* M0, cx<T>* M1, cx<T>* xh, cx<T>* rh,
                                                     cx<T>* dh, cx<T>* sh, int it, int max_iter, int nwg_row) {
-  if constexpr (CV >= CV_SEQ) col_iter_seq_body<NY, T, CV>(g, M0, M1, xh, rh, dh, sh, it, max_iter, nwg_row);
+  if constexpr (CV >= CV_SEQ && CV < CV_WIDE) col_iter_seq_body<NY, T, CV>(g, M0, M1, xh, rh, dh, sh, it, max_iter, nwg_row);
   else col_iter_body<NY, T, CV>(g, M0, M1, xh, rh, dh, sh, it, max_iter, nwg_row);
 }
 template <int NY, typename T, int CV>
 __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_iter(const IterArgs* __restrict__ A, int it, int max_iter, int nwg_row) {
   const IterArgs& a = A[blockIdx.y];
-  if constexpr (CV >= CV_SEQ) col_iter_seq_body<NY, T, CV>(a.g, (cx<T>*)a.M0, (cx<T>*)a.M1, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (cx<T>*)a.sh, it, max_iter, nwg_row);
+  if constexpr (CV >= CV_SEQ && CV < CV_WIDE) col_iter_seq_body<NY, T, CV>(a.g, (cx<T>*)a.M0, (cx<T>*)a.M1, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (cx<T>*)a.sh, it, max_iter, nwg_row);
   else col_iter_body<NY, T, CV>(a.g, (cx<T>*)a.M0, (cx<T>*)a.M1, (cx<T>*)a.xh, (cx<T>*)a.rh, (cx<T>*)a.dh, (cx<T>*)a.sh, it, max_iter, nwg_row);
 }
 
 // ---------------------------------------------------------------- dispatch
 // A switch over the variant code that instantiates only the variants that exist
 // for the size and real type.
-#define NF_VARIANTS(V_) V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11) V_(12) V_(13) V_(14) V_(15) V_(16)
+#define NF_VARIANTS(V_) V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11) V_(12) V_(13) V_(14) V_(15) V_(16) V_(17) V_(18)
 
 template <int NX, typename T, int RV>
 static hipError_t flux_go(const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const T* r, int it, double* kslot,

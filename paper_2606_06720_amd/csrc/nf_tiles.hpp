@@ -39,7 +39,7 @@ __host__ __device__ constexpr int row_tile(int nx, int nf) { return (nf <= 2 && 
 
 // threads rounded up to whole wavefronts
 __host__ __device__ constexpr int waves_of(int t) { return (t + 63) / 64 * 64; }
-template <int NX, int NF, int RT = TILE, int PL = 0, int TD = 1>
+template <int NX, int NF, int RT = TILE, int PL = 0, int TD = 1, int NTV = 0>
 struct RowCfg {
   static constexpr int H = NX / 2;
   static constexpr int R = tile_rows(H, RT);                    // rows per workgroup
@@ -48,7 +48,8 @@ struct RowCfg {
   // one radix-8 butterfly per thread, at most 1024 threads (wider tiles give
   // each thread several butterflies per stage); TD divides the thread count
   // (each thread then runs TD times the butterflies)
-  static constexpr int NT = ((RT / 8) * NF > 1024 ? 1024 : waves_of((RT / 8) * NF)) / TD;
+  // (NTV: thread count, if another)
+  static constexpr int NT = NTV > 0 ? NTV : ((RT / 8) * NF > 1024 ? 1024 : waves_of((RT / 8) * NF)) / TD;
   // LDS line stride: room for the FFT's padded layout, rounded so that the R
   // rows a group of 8 lanes touches in the row-interleaved phases (transposed
   // and paired loads and stores, consecutive lanes running over the rows of
@@ -108,6 +109,8 @@ struct ColCfg {
 // variants 9, 10, 11 hold RD/2, RD/4, RD/8 rows, column variants 12, 13, 14
 // CD/2, CD/4, CD/8 columns.  They exist for every size and are not part of the
 // public codes.
+// Wide tiles (wide_elems elements of a field, wide_threads threads, radix plan wide_plan),
+// the tiles of the team over the chip: row variants 15, 16, column variants 17, 18.
 // Sequential fields (one field of the tile in LDS at a time), for lengths from
 // 2048 on: row variants 12, 13, 14 hold 1, 2, 4 rows, column variants 15, 16 one
 // column with one and two radix-8 butterflies per thread and stage.
@@ -115,8 +118,18 @@ enum { LDS_LIMIT = 160 * 1024 };  // VAR_DEFAULT, NVAR, RV_SMALL, CV_SMALL: nf_i
 // threads of a small tile of `lines` lines of h elements over two fields
 __host__ __device__ constexpr int small_threads(int lines, int h) { return waves_of(lines * h / 8 * 2); }
 
+// Radix plan of a wide tile's transforms: a compute unit to themselves, they are
+// bound by LDS traffic and the barriers between stages, so radix 8 with half of the
+// threads idle beats radix 4 (512-point transforms of 1024 elements per field, FP64:
+// 3100 instead of 4800 cycles), except for 256 points, whose radix-4 stages need no
+// barriers.
+__host__ __device__ constexpr int wide_plan(int n) { return n == 256 ? 2 : 0; }
+// elements per field of wide class c
+__host__ __device__ constexpr int wide_elems(int c) { return 512 << c; }
+__host__ __device__ constexpr int wide_threads(int c) { return wide_elems(c) / 2; }
 __host__ __device__ constexpr int rv_rows(int nx, int rv) {
   const int rd = tile_rows(nx / 2, row_tile(nx, 2));
+  if (rv >= RV_WIDE) return wide_elems(rv - RV_WIDE) / (nx / 2);
   if (rv >= RV_SEQ) return 1 << (rv - RV_SEQ);
   if (rv >= RV_SMALL) return rd >> (rv - RV_SMALL + 1);
   return rv % 3 == 0 ? rd / 2 : (rv % 3 == 1 ? rd : 2 * rd);
@@ -125,6 +138,7 @@ __host__ __device__ constexpr int cv_cols_default(int ny) {
   return TILE / ny < 1 ? 1 : (TILE / ny > 64 ? 64 : TILE / ny);
 }
 __host__ __device__ constexpr int cv_cols(int ny, int cv) {
+  if (cv >= CV_WIDE) return wide_elems(cv - CV_WIDE) / ny;
   if (cv >= CV_SEQ) return 1;
   if (cv >= CV_SMALL) return cv_cols_default(ny) >> (cv - CV_SMALL + 1);
   return cv % 3 == 0 ? cv_cols_default(ny) / 2 : (cv % 3 == 1 ? cv_cols_default(ny) : 2 * cv_cols_default(ny));
@@ -141,15 +155,23 @@ __host__ __device__ constexpr int cv_tm(int cv) { return cv / 3 == 2 ? 2 : (cv /
 __host__ __device__ constexpr int rv_plan(int rv) { return rv / 3 == 1 ? 1 : 0; }
 __host__ __device__ constexpr int rv_td(int rv) { return rv / 3 == 2 ? 2 : 1; }
 // threads of the column variants beyond the public codes
-__host__ __device__ constexpr int wide_threads(int ny, int cv) {
+__host__ __device__ constexpr int cv_threads(int ny, int cv) {
+  if (cv >= CV_WIDE) return wide_threads(cv - CV_WIDE);
   return cv >= CV_SEQ ? ny / 8 / (cv - CV_SEQ + 1) : small_threads(cv_cols(ny, cv), ny);
 }
 // sequential fields: whether one field of the tile fits a workgroup's LDS
 __host__ __device__ constexpr bool rv_seq_ok(int nx, int rv, int es) {
-  return nx >= 2048 && rv < NRV && rv_rows(nx, rv) * (nx / 2 + 10) * es + 4096 <= LDS_LIMIT &&
+  return nx >= 2048 && rv < RV_WIDE && rv_rows(nx, rv) * (nx / 2 + 10) * es + 4096 <= LDS_LIMIT &&
          rv_rows(nx, rv) * (nx / 2) / 8 <= 1024;
 }
-__host__ __device__ constexpr bool cv_seq_ok(int ny, int cv) { return ny >= 2048 && cv < NCV; }
+__host__ __device__ constexpr bool cv_seq_ok(int ny, int cv) { return ny >= 2048 && cv < CV_WIDE; }
+// wide tiles: the lengths of grids with a team over the chip (nf_chip.hpp)
+__host__ __device__ constexpr bool wide_row_ok(int nx, int rv) {
+  return nx >= 128 && nx <= 2048 && rv < NRV && rv_rows(nx, rv) >= 1;
+}
+__host__ __device__ constexpr bool wide_col_ok(int ny, int cv) {
+  return ny >= 64 && ny <= 1024 && cv < NCV && cv_cols(ny, cv) >= 1;
+}
 // small tiles: at least one line, and at least half a wavefront of butterflies
 __host__ __device__ constexpr bool small_ok(int lines, int h) { return lines >= 1 && lines * h / 8 * 2 >= 32; }
 __host__ __device__ constexpr bool rv_ok(int nx, int ny, int rv, int es) {
@@ -169,24 +191,26 @@ __host__ __device__ constexpr bool var_size(int n) { return n >= 256 && n <= 409
 template <int NX, int RV>
 using FluxCfg = typename std::conditional<
     RV == VAR_DEFAULT, Row2D<NX, 2>,
-    typename std::conditional<(RV >= RV_SEQ), RowCfg<NX, 1, rv_rows(NX, RV) * (NX / 2)>,
-                              RowCfg<NX, 2, rv_rows(NX, RV) * (NX / 2), RV >= RV_SMALL ? 0 : rv_plan(RV),
-                                     RV >= RV_SMALL ? 1 : rv_td(RV)>>::type>::type;
+    typename std::conditional<(RV >= RV_SEQ && RV < RV_WIDE), RowCfg<NX, 1, rv_rows(NX, RV) * (NX / 2)>,
+                              RowCfg<NX, 2, rv_rows(NX, RV) * (NX / 2), RV >= RV_WIDE ? wide_plan(NX / 2) : (RV >= RV_SMALL ? 0 : rv_plan(RV)),
+                                     RV >= RV_SMALL ? 1 : rv_td(RV), RV >= RV_WIDE ? wide_threads(RV - RV_WIDE) : 0>>::type>::type;
 template <int NY, int CV>
 using DivCfg = typename std::conditional<
     CV == VAR_DEFAULT, ColCfg<NY, 2>,
     typename std::conditional<(CV >= CV_SMALL),
-                              ColCfg<NY, CV >= CV_SEQ ? 1 : 2, cv_cols(NY, CV) * NY, 0, 1, wide_threads(NY, CV)>,
+                              ColCfg<NY, CV >= CV_SEQ && CV < CV_WIDE ? 1 : 2, cv_cols(NY, CV) * NY, CV >= CV_WIDE ? wide_plan(NY) : 0, 1, cv_threads(NY, CV)>,
                               ColCfg<NY, 2, cv_cols(NY, CV) * NY, cv_plan(CV), cv_tm(CV)>>::type>::type;
 // variants that can be built for a size (the row count against Ny is checked at run time)
 template <int NX, int RV, int ES>
 constexpr bool flux_var_exists() {
+  if (RV >= RV_WIDE) return wide_row_ok(NX, RV);
   if (RV >= RV_SEQ) return rv_seq_ok(NX, RV, ES);
   return RV == VAR_DEFAULT || (RV >= RV_SMALL ? small_ok(rv_rows(NX, RV), NX / 2)
                                               : var_size(NX) && rv_ok(NX, 1 << 20, RV, ES));
 }
 template <int NY, int CV, int ES>
 constexpr bool div_var_exists() {
+  if (CV >= CV_WIDE) return wide_col_ok(NY, CV);
   if (CV >= CV_SEQ) return cv_seq_ok(NY, CV);
   return CV == VAR_DEFAULT || (CV >= CV_SMALL ? small_ok(cv_cols(NY, CV), NY)
                                               : var_size(NY) && cv_ok(NY, 1 << 20, CV, ES));
@@ -196,14 +220,14 @@ constexpr bool div_var_exists() {
 __device__ __forceinline__ double xi_tilde(int k, int n, double L) {
   if (2 * k == n) return 0.0;
   const int kk = (2 * k < n) ? k : k - n;
-  return TWO_PI * (double)kk / L;
+  return (double)kk * (TWO_PI / L);
 }
 __device__ __forceinline__ double xi_full(int k, int n, double L) {
   const int kk = (2 * k <= n) ? k : k - n;
-  return TWO_PI * (double)kk / L;
+  return (double)kk * (TWO_PI / L);
 }
 // x wavenumber of packed column kx (zero on the packed kx = 0 / Nx/2 column)
-__device__ __forceinline__ double xi_col(int kx, double lx) { return kx == 0 ? 0.0 : TWO_PI * kx / lx; }
+__device__ __forceinline__ double xi_col(int kx, double lx) { return (double)kx * (TWO_PI / lx); }
 
 // Workgroups are dealt round-robin over the 8 XCDs; map them so that
 // consecutive logical blocks (adjacent row blocks, which share cache lines of

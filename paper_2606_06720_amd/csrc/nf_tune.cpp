@@ -211,7 +211,7 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
     for (int v = 0; v < NVAR; ++v) best[v] = -1.0;
     int nc = 0;
     for (int round = 0; round < 2; ++round) {
-      for (int v = 0; v < NVAR; ++v) {
+      for (int v = 0; v < (pass == 0 ? RV_WIDE : CV_WIDE); ++v) {
         const bool ok = pass == 0 ? flux_var_valid(G, f32, v) : div_var_valid(G, f32, v);
         if (!ok) continue;
         if (round == 0) ++nc;
@@ -362,7 +362,8 @@ int nf_set_tiles(nf_grid* g, int flux_var, int div_var, int update_var) {
     H->var_upd[k] = v[2];
   }
   g->tuned = 0;
-  g->team_on = g->team_loop = false;  // the caller asks for the tiled passes
+  g->team_on = g->team_loop = g->chip_loop = false;  // the caller asks for the tiled passes
+  for (nf::Geo* H : {&g->geo, &g->geo32}) H->wide = -1;
   return NF_OK;
 }
 
