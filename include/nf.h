@@ -359,7 +359,7 @@ const char *nf_batch_last_error(const nf_batch *b);
  * of that shape use the same choice, so their results agree bit for bit.
  * The variants change the work split and the rounding of the transforms and
  * inner products only.
- * Grids of 65537 to 524288 points whose tiles divide them (all powers of two with
+ * Grids of 65537 to 1048576 points whose tiles divide them (all powers of two with
  * Nx from 128 to 2048 and Ny from 64 to 1024 among them) run the loop as one launch
  * if no other solve is in progress on the device, and keep the tiles of that launch
  * where its passes run as launches (concurrent solves, ensembles, timed handles);

@@ -1,25 +1,26 @@
-// The whole PCG loop of a mid-size 2D grid (65537 to 524288 points) in one launch over the chip, one workgroup per compute unit.
+// The whole PCG loop of a mid-size 2D grid (65537 points to about a million) in one launch over the chip, one workgroup per compute unit.
 //
 // As two launches per iteration such a grid's loop costs two kernel boundaries,
 // reads and writes x, r, d, s, m and r of every point, and forms the preconditioner
 // anew.  Here the tiles of the two passes of nf_loop.hpp stay with one workgroup for
 // the whole loop: r, d, s of its columns, symbols and twiddles in registers, x and m,
-// r of its rows in LDS, and only the two mixed fields move between the passes, 64
-// instead of 152 bytes per point and iteration.  The L2s of the XCDs meet in the Infinity Cache, so the fields are
+// r of its rows in LDS (tiles of 2048 elements leave x and r in the L2), and only the
+// two mixed fields move between the passes, 64 instead of 152 bytes per point and
+// iteration.  The L2s of the XCDs meet in the Infinity Cache, so the fields are
 // stored and loaded with sc1 (past the L2); invalidating the L2s instead and loading
 // through them measured 2 to 3 times slower.  A round of store, barrier and load over
-// 256 workgroups takes 3.7 us for 512^2 and 4.2 us for 1024x512, the barrier alone 1.7.
+// 256 workgroups takes 3.7 us for 512^2 and 6.3 us for 1024^2, the barrier alone 1.7.
 // Measured per solve, launches -> team (same box): 400^2 2.27 -> 1.58 ms, 512^2 2.26 ->
-// 1.40, 1024x512 3.44 -> 1.81, FP32-refined 512x1024 3.01 -> 1.87.  Of an iteration of
-// 512^2 (32000 cycles) the two waits take 14000, the transforms 9000, loads and stores
-// 6000: the loop is bound by the barrier's round trips.
+// 1.41, 1024x512 3.44 -> 1.81, 800^2 4.17 -> 3.34, 1024^2 4.40 -> 3.44; FP32-refined
+// 512x1024 3.01 -> 1.89, 1024^2 4.77 -> 2.94.  Of an iteration of 512^2 (32000 cycles)
+// the two waits take 14000, the transforms 9000, loads and stores 6000: the loop is
+// bound by the barrier's round trips and, on the larger tiles, by LDS traffic and the
+// few registers that are left.
 //
-// Larger grids have none: with 2048 elements per member alone a 1024^2 solve took
-// 3.25 instead of 4.40 ms and an 800^2 solve 3.48 instead of 4.17, but the launches
-// that have to round like it take the same large tiles, and three concurrent 1024^2
-// handles then reached 1.7-1.8 instead of 2.1e9 grid-point steps per second.  For the
-// same reason a loop is one launch only if no other loop is in progress on the device
-// (three concurrent 512^2 handles: 1.21e9, the tuned launches 1.16e9).
+// A team takes all compute units, so a loop is one launch only if no other loop is in
+// progress on the device; concurrent loops overlap better as launches (three 512^2
+// handles: 1.21e9 grid-point steps per second with this rule, 1.16e9 with the tuned
+// launches; three 1024^2 handles: 1.69e9 with teams, 2.1e9 as launches).
 //
 // Exchange layout: [row tile][kx][field][row] in the buffers of d and A d, which the
 // loop keeps in registers; kx below Nx/4 in the first, the others in the second, so
@@ -29,10 +30,13 @@
 // gradient, contiguous for the column pass, the waits grew from 14000 to 19000
 // cycles per iteration at 512^2, since the lines then were in the L2 of another XCD.
 //
-// A member does the work of the workgroup of the launched passes with the same index
-// (tile variants RV_WIDE and CV_WIDE), and the totals are added up in the order in
-// which those passes add them, so the results are bitwise those of the launches,
-// which ensembles, timed handles and handles whose team did not form run.
+// A member does the work of one or two workgroups of the launched passes, and the
+// totals are added up in the order in which those passes add them, so the results are
+// bitwise those of the launches, which ensembles, timed and concurrent handles and
+// handles whose team did not form run.  Tiles of 512 and 1024 elements are variants of
+// their own (RV_WIDE, CV_WIDE: with 128 and 256 threads and radix 8 the 512^2 solve
+// took 1.86 ms); tiles of 2048 elements are pairs of the launches' tuned tiles, since
+// launches of 2048-element tiles cost three concurrent 1024^2 handles 14%.
 //
 // Formation is that of nf_team.hpp: all members draw tickets; the last one turns
 // OPEN to GO, a member that waited CHIP_FORM_MS turns it to ABORT.  After GO all
@@ -86,30 +90,37 @@ constexpr int chip_tw_off(int S) {
   return o;
 }
 constexpr int CHIP_TW = 14;
+// whether stage S's twiddles are held (the last ones of 2048-element tiles are not)
+template <int L, int B, int NT>
+constexpr bool chip_held(int S) {
+  return chip_tw_off<L, B, NT>(S) + chip_per<L, B, NT>(S) * (mplan_radix(L, S, wide_plan(L)) - 1) <= CHIP_TW;
+}
 template <typename T, int L, int B, int NT, int S = 1>
 __device__ __forceinline__ void chip_tw_load(cx<T> (&wt)[CHIP_TW], const cx<T>* __restrict__ tw, int twn, int tid) {
   if constexpr (S < mplan_nstages(L, wide_plan(L))) {
     constexpr int R = mplan_radix(L, S, wide_plan(L)), NS = mplan_ns(L, S, wide_plan(L)), O = chip_tw_off<L, B, NT>(S);
-    static_assert(O + chip_per<L, B, NT>(S) * (R - 1) <= CHIP_TW, "twiddles exceed their registers");
-    const int mult = twn / (NS * R);
+    if constexpr (chip_held<L, B, NT>(S)) {
+      const int mult = twn / (NS * R);
 #pragma unroll
-    for (int b = 0; b < chip_per<L, B, NT>(S); ++b) {
-      const int k = (tid + b * NT) % (L / R) % NS;
+      for (int b = 0; b < chip_per<L, B, NT>(S); ++b) {
+        const int k = (tid + b * NT) % (L / R) % NS;
 #pragma unroll
-      for (int q = 1; q < R; ++q) wt[O + b * (R - 1) + q - 1] = tw[q * k * mult];
+        for (int q = 1; q < R; ++q) wt[O + b * (R - 1) + q - 1] = tw[q * k * mult];
+      }
     }
     chip_tw_load<T, L, B, NT, S + 1>(wt, tw, twn, tid);
   }
 }
 // The transform of lds_fft with the plan of the wide tiles and these twiddles.
 template <typename T, int DIR, int L, int B, int LS, int NT, int S = 0>
-__device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW], int tid) {
+__device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW], const cx<T>* __restrict__ tw, int twn,
+                                         int tid) {
   if constexpr (S < mplan_nstages(L, wide_plan(L))) {
     constexpr int R = mplan_radix(L, S, wide_plan(L)), NS = mplan_ns(L, S, wide_plan(L)), Q = L / R, NBF = B * Q;
     constexpr int PER = chip_per<L, B, NT>(S), O = chip_tw_off<L, B, NT>(S > 0 ? S : 1);
     constexpr bool EXACT = PER * NT == NBF, WL = wave_local_ok<L, NT, wide_plan(L)>(), POW2 = (L & (L - 1)) == 0;
-    constexpr bool PIN = S > 0, POUT = S + 1 < mplan_nstages(L, wide_plan(L));
-    cx<T> v[PER][R];
+    constexpr bool PIN = S > 0, POUT = S + 1 < mplan_nstages(L, wide_plan(L)), HELD = S == 0 || chip_held<L, B, NT>(S);
+    cx<T> v[PER][R], w[PER][R];
 #pragma unroll
     for (int b = 0; b < PER; ++b) {
       const int f = tid + b * NT, j = f % Q;
@@ -117,6 +128,10 @@ __device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW],
         const cx<T>* src = buf + f / Q * LS;
 #pragma unroll
         for (int q = 0; q < R; ++q) v[b][q] = src[PIN ? team_pad<POW2>(j, q * Q) : j + q * Q];
+        if constexpr (!HELD) {
+#pragma unroll
+          for (int q = 1; q < R; ++q) w[b][q] = tw[q * (j % NS) * (twn / (NS * R))];
+        }
       }
     }
     if constexpr (WL) wave_sync();
@@ -128,8 +143,8 @@ __device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW],
         if constexpr (S > 0) {
 #pragma unroll
           for (int q = 1; q < R; ++q) {
-            const cx<T> w = wt[O + b * (R - 1) + q - 1];
-            v[b][q] = mul(v[b][q], DIR > 0 ? conj(w) : w);
+            if constexpr (HELD) w[b][q] = wt[O + b * (R - 1) + q - 1];
+            v[b][q] = mul(v[b][q], DIR > 0 ? conj(w[b][q]) : w[b][q]);
           }
         }
         dft<R, DIR>(v[b]);
@@ -141,19 +156,18 @@ __device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW],
     }
     if constexpr (WL && POUT) wave_sync();
     else __syncthreads();
-    chip_fft<T, DIR, L, B, LS, NT, S + 1>(buf, wt, tid);
+    chip_fft<T, DIR, L, B, LS, NT, S + 1>(buf, wt, tw, twn, tid);
   }
 }
 
 // What a thread keeps for the whole loop (EP elements of a field): the vectors
 // and symbols of its spectral elements.  (x and, for its grid-point pairs, m and r
 // stay in LDS: in registers they made the members of 512 FP64 threads spill.)
-constexpr int CHIP_EP = 2;
-template <typename T>
+template <typename T, int EP>
 struct ChipState {
-  cx<T> r[CHIP_EP], d[CHIP_EP], s[CHIP_EP];
-  T sig[CHIP_EP];
-  cx<T> wr[CHIP_TW], wc[CHIP_TW], wp[CHIP_EP];  // twiddles of its row and column transforms and pairs
+  cx<T> r[EP], d[EP], s[EP];
+  T sig[EP];
+  cx<T> wr[CHIP_TW], wc[CHIP_TW], wp[EP];  // twiddles of its row and column transforms and pairs
   int go, li, t;  // place of its first column element in the exchange buffer and in LDS, that element's row tile
 };
 
@@ -164,26 +178,36 @@ __device__ __forceinline__ void chip_opaque(int& t) { asm volatile("" : "+v"(t))
 
 // The split of a grid.  A grid has a team over the chip if it has more than 65536
 // points (below, the team of one XCD has the cheaper barrier) and tiles of the
-// smaller class that holds it in at most 256 members, one per compute unit, divide
+// smallest class that holds it in at most 256 members, one per compute unit, divide
 // it, so that the exchange layouts have no ragged blocks, and are covered by their
 // threads; G is 0 otherwise.
 __host__ __device__ constexpr ChipShape chip_split(int nx, int ny) {
   ChipShape cs{0, 0, 0, 0, 0, 0, 0};
   const int h = nx / 2;
   if ((long long)nx * ny <= 65536) return cs;
-  for (int c = 0; c < 2; ++c) {
-    if (!wide_row_ok(nx, RV_WIDE + c) || !wide_col_ok(ny, CV_WIDE + c)) continue;
-    const int R = wide_elems(c) / h, C = wide_elems(c) / ny;
+  for (int c = 0; c < 3; ++c) {
+    if (!wide_row_ok(nx) || !wide_col_ok(ny) || wide_elems(c) < h || wide_elems(c) < ny) continue;
+    if (c == 2 && (h == 256 || ny == 256)) continue;  // (their launches would have another plan)
+    const int R = c < 2 ? wide_elems(c) / h : 2 * tile_rows(h, TILE), C = c < 2 ? wide_elems(c) / ny : 2 * cv_cols_default(ny);
     if (ny % R != 0 || h % 2 != 0 || h / 2 % C != 0) continue;
     const int nrow = ny / R, ncol = h / C, G = nrow > ncol ? nrow : ncol;
     const int step = wide_threads(c) / (2 * R * C);
-    if (G > CHIP_MAX || step * 2 * CHIP_EP < nrow) continue;
+    if (G > CHIP_MAX || step * 2 * wide_elems(c) < nrow * wide_threads(c)) continue;
     return ChipShape{G, c, R, C, nrow, ncol, step};
   }
   return cs;
 }
+// Launched tiles per member and pass, and the threads of those tiles: class 2 is two
+// tiles of TILE elements (256 threads), except that the rows of tuned lengths are
+// one tile of 512 threads, the tuner's choice there.
+__host__ __device__ constexpr int chip_sr(int nx, int c) { return c < 2 || var_size(nx) ? 1 : 2; }
+__host__ __device__ constexpr int chip_sc(int c) { return c < 2 ? 1 : 2; }
 __host__ __device__ constexpr int chip_threads(int nx, int ny) {
   return chip_split(nx, ny).G > 0 ? wide_threads(chip_split(nx, ny).wide) : 64;
+}
+
+__host__ __device__ constexpr int chip_ep(int nx, int ny) {
+  return wide_elems(chip_split(nx, ny).wide) / wide_threads(chip_split(nx, ny).wide);
 }
 
 // Line strides of the LDS tiles: the padded transform layout, on which the eight
@@ -193,66 +217,74 @@ __host__ __device__ constexpr int chip_ls(int len, int lines) {
   const int want = lines <= 1 ? 4 : (lines == 2 ? 2 : 1);
   return lpad_len(len) + ((want - lpad_len(len) % 8) + 8) % 8;
 }
-// tile variants of a team with NT threads per member
-__host__ __device__ constexpr int chip_rv(int nt) { return RV_WIDE + ilog2(nt / 256); }
-__host__ __device__ constexpr int chip_cv(int nt) { return CV_WIDE + ilog2(nt / 256); }
-// complex elements of a tile's LDS
-constexpr int chip_lds(int nt) { return 4 * nt + nt / 2 + 100; }
+// complex elements of a tile's LDS, class c
+constexpr int chip_lds(int c) { return 2 * wide_elems(c) + wide_elems(c) / 4 + 100; }
+// the largest class keeps in global memory (in the L2) what no longer fits
+constexpr bool chip_big(int c) { return wide_elems(c) > 1024; }
 
-template <typename T, int NX, int NT>
-__device__ __forceinline__ void chip_row_setup(ChipState<T>& st, cx<T>* ms, const Geo& g,
+// Element i of a thread in the pointwise phases: that of the launched tiles, SUB of
+// which share the N elements of the member; at least N if there is none.
+template <int NT, int SUB, int N>
+__device__ __forceinline__ int chip_elem(int tid, int i) {
+  constexpr int NS = NT / SUB, M = N / SUB;
+  const int p = tid % NS + i * NS;
+  return SUB == 1 ? p : (p < M ? tid / NS * M + p : N);
+}
+template <typename T, int NX, int CL, int R>
+__device__ __forceinline__ void chip_row_setup(ChipState<T, wide_elems(CL) / wide_threads(CL)>& st, cx<T>* ms, const Geo& g,
                                                const T* __restrict__ m, const T* __restrict__ r, int y0, int tid) {
-  using C = FluxCfg<NX, chip_rv(NT)>;
+  constexpr int NT = wide_threads(CL), E = wide_elems(CL), H = NX / 2, RH = R * H;
   const int ny = g.ny;
   const size_t n = (size_t)NX * ny;
   const cx<T>* tw = (const cx<T>*)g.tw;
-  chip_tw_load<T, C::H, 2 * C::R, NT>(st.wr, tw, g.twn, tid);
+  chip_tw_load<T, H, 2 * R, NT>(st.wr, tw, g.twn, tid);
 #pragma unroll
-  for (int i = 0; i < CHIP_EP; ++i) {
+  for (int i = 0; i < E / NT; ++i) {
     const int p = tid + i * NT;
-    st.wp[i] = tw[p < C::RH ? p / (2 * C::R) * (g.twn / NX) : 0];
-    const size_t o = (size_t)(y0 + p / C::H) * NX + 2 * (p % C::H);
-    const bool ok = p < C::RH && y0 < ny;
+    if (!chip_big(CL)) st.wp[i] = tw[p < RH ? p / (2 * R) * (g.twn / NX) : 0];
+    const size_t o = (size_t)(y0 + p / H) * NX + 2 * (p % H);
+    const bool ok = p < RH && y0 < ny;
     ms[p] = ok ? *(const cx<T>*)(m + o) : vzero<cx<T>>();
-    ms[NT * CHIP_EP + p] = ok ? *(const cx<T>*)(m + n + o) : vzero<cx<T>>();
-    ms[2 * NT * CHIP_EP + p] = ok ? *(const cx<T>*)(r + o) : vzero<cx<T>>();
+    ms[E + p] = ok ? *(const cx<T>*)(m + n + o) : vzero<cx<T>>();
+    if (!chip_big(CL)) ms[2 * E + p] = ok ? *(const cx<T>*)(r + o) : vzero<cx<T>>();
   }
 }
 template <typename T, int NX, int NY>
-__device__ __forceinline__ void chip_col_setup(ChipState<T>& st, const Geo& g, const double* K, int kx0, int tid) {
-  constexpr int NT = chip_threads(NX, NY), R = chip_split(NX, NY).R, H = NX / 2;
-  using C = DivCfg<NY, chip_cv(NT)>;
-  constexpr int LS = chip_ls(NY, C::C);
+__device__ __forceinline__ void chip_col_setup(ChipState<T, chip_ep(NX, NY)>& st, const Geo& g, const double* K, int kx0, int tid) {
+  constexpr int CL = chip_split(NX, NY).wide, NT = wide_threads(CL), R = chip_split(NX, NY).R, H = NX / 2;
+  constexpr int NC = chip_split(NX, NY).C;
+  constexpr int LS = chip_ls(NY, NC);
 #pragma unroll
-  for (int i = 0; i < CHIP_EP; ++i) {
-    const int p = tid + i * NT;
+  for (int i = 0; i < chip_ep(NX, NY); ++i) {
+    const int p = chip_elem<NT, chip_sc(CL), NC * NY>(tid, i);
     st.sig[i] = (T)precond_symbol_inv(K, xi_col(kx0 + p / NY, g.lx), xi_tilde(p % NY, NY, g.ly));
   }
-  chip_tw_load<T, NY, 2 * C::C, NT>(st.wc, (const cx<T>*)g.tw, g.twn, tid);
+  chip_tw_load<T, NY, 2 * NC, NT>(st.wc, (const cx<T>*)g.tw, g.twn, tid);
   // Exchange image of a column tile: the 2 C R elements of a row tile are
   // consecutive lanes (row, field, column), as many row tiles at a time as fit the
   // threads; later ones follow at a fixed stride.
-  constexpr int w = 2 * C::C * R, h2 = H / 2;
+  constexpr int w = 2 * NC * R, h2 = H / 2;
   const int rr = tid % R, f = tid / R & 1, c = tid % w / (2 * R);
   const int k0 = kx0 >= h2 ? kx0 - h2 : kx0;
   st.t = tid < NT / w * w && kx0 < H ? tid / w : INT_MAX / 2;
   st.go = tid / w * R * H + ((k0 + c) * 2 + f) * R + rr;
-  st.li = (f * C::C + c) * LS + tid / w * R + rr;
+  st.li = (f * NC + c) * LS + tid / w * R + rr;
 }
 
 // Row pass of the tile at row y0 (see row_flux_body): this thread's part of
 // sum g . K g.  lo, hi: the exchange buffers; G0, G1: the mixed fields in
 // their usual layout, which the first pass after a launch reads.
 template <typename T, int NX, int NY>
-__device__ __forceinline__ double chip_row(const ChipState<T>& st, cx<T>* buf, const cx<T>* ms, const Geo& g, const cx<T>* G0,
+__device__ __forceinline__ double chip_row(const ChipState<T, chip_ep(NX, NY)>& st, cx<T>* buf, const cx<T>* ms,
+                                           const T* __restrict__ rg, const Geo& g, const cx<T>* G0,
                                            const cx<T>* G1, __amdgpu_buffer_rsrc_t lo, __amdgpu_buffer_rsrc_t hi, int y0,
                                            bool first, int tid) {
-  constexpr int NT = chip_threads(NX, NY), ny = NY;
-  using C = FluxCfg<NX, chip_rv(NT)>;
+  constexpr int CL = chip_split(NX, NY).wide, NT = wide_threads(CL), E = wide_elems(CL), ny = NY;
   using V = cx<T>;
-  constexpr int H = C::H, R = C::R, NTK = R * H, LS = chip_ls(H, R), ETP = (NTK + NT - 1) / NT;
-  static_assert(2 * R * LS <= chip_lds(NT), "tile exceeds its LDS");
-  const int base = y0 * H;
+  constexpr int H = NX / 2, R = chip_split(NX, NY).R, EP = chip_ep(NX, NY), NTK = R * H, LS = chip_ls(H, R), ETP = (NTK + NT - 1) / NT;
+  static_assert(2 * R * LS <= chip_lds(CL), "tile exceeds its LDS");
+  const V* tw = (const V*)g.tw;
+  const int base = y0 * H, mult = g.twn / NX;
   const bool on = NY / R == chip_split(NX, NY).G || y0 < ny;
   V a[ETP], b[ETP];
 #pragma unroll
@@ -283,7 +315,7 @@ __device__ __forceinline__ double chip_row(const ChipState<T>& st, cx<T>* buf, c
       l[H / 2] = mk<T>(xh.x + xh.x, -(xh.y + xh.y));
     } else {
       const V xk = a[i], xm = b[i];
-      const V w = st.wp[i];
+      const V w = chip_big(CL) ? tw[k * mult] : st.wp[i];
       const V e1 = add(xk, conj(xm)), o1 = sub(xk, conj(xm));
       const V e2 = add(xm, conj(xk)), o2 = sub(xm, conj(xk));
       l[k] = add(e1, mul_i<+1>(mul(conj(w), o1)));
@@ -292,17 +324,18 @@ __device__ __forceinline__ double chip_row(const ChipState<T>& st, cx<T>* buf, c
   }
   __syncthreads();
   chip_opaque(tid);
-  chip_fft<T, +1, H, 2 * R, LS, NT>(buf, st.wr, tid);
+  chip_fft<T, +1, H, 2 * R, LS, NT>(buf, st.wr, tw, g.twn, tid);
   chip_opaque(tid);
   double de = 0.0;
 #pragma unroll
-  for (int i = 0; i < C::EP; ++i) {
-    const int p = tid + i * NT;
-    if (p < C::RH && on) {
+  for (int i = 0; i < EP; ++i) {
+    const int p = chip_elem<NT, chip_sr(NX, CL), R * H>(tid, i);
+    if (p < R * H && on) {
       V* px = buf + p / H * LS + p % H;
       V* py = px + R * LS;
       const V gx = *px, gy = *py;
-      const V mx = ms[p], my = ms[NT * CHIP_EP + p], rv = ms[2 * NT * CHIP_EP + p];
+      const V mx = ms[p], my = ms[E + p];
+      const V rv = chip_big(CL) ? *(const V*)(rg + (size_t)(y0 + p / H) * NX + 2 * (p % H)) : ms[2 * E + p];
       const T a0 = mx.x * gx.x + my.x * gy.x;
       const T a1 = mx.y * gx.y + my.y * gy.y;
       const V fx = mk<T>(fma(a0, mx.x, rv.x * gx.x), fma(a1, mx.y, rv.y * gx.y));
@@ -314,7 +347,7 @@ __device__ __forceinline__ double chip_row(const ChipState<T>& st, cx<T>* buf, c
   }
   __syncthreads();
   chip_opaque(tid);
-  chip_fft<T, -1, H, 2 * R, LS, NT>(buf, st.wr, tid);
+  chip_fft<T, -1, H, 2 * R, LS, NT>(buf, st.wr, tw, g.twn, tid);
   chip_opaque(tid);
 #pragma unroll
   for (int i = 0; i < ETP; ++i) {
@@ -329,7 +362,7 @@ __device__ __forceinline__ double chip_row(const ChipState<T>& st, cx<T>* buf, c
       chip_store(hi, oh, conj(l[H / 2]));
     } else {
       const V zk = l[k], zm = l[H - k];
-      const V w = st.wp[i];
+      const V w = chip_big(CL) ? tw[k * mult] : st.wp[i];
       const V e1 = add(zk, conj(zm)), o1 = sub(zk, conj(zm));
       const V e2 = add(zm, conj(zk)), o2 = sub(zm, conj(zk));
       const V t1 = mul_i<-1>(mul(w, o1));
@@ -345,32 +378,34 @@ __device__ __forceinline__ double chip_row(const ChipState<T>& st, cx<T>* buf, c
 // exchange buffer; ps: this thread's parts of ||r||^2 and <r, M^-1 r>.  The
 // gradient stays in buf as well.
 template <typename T, int NX, int NY>
-__device__ __forceinline__ void chip_col(ChipState<T>& st, cx<T>* buf, cx<T>* xs, const Geo& g, __amdgpu_buffer_rsrc_t ex, int kx0,
+__device__ __forceinline__ void chip_col(ChipState<T, chip_ep(NX, NY)>& st, cx<T>* buf, cx<T>* xs,
+                                         cx<T>* xh, const Geo& g, __amdgpu_buffer_rsrc_t ex, int kx0,
                                          T a, T bt, bool first, bool last, double (&ps)[2], int tid) {
   constexpr ChipShape cs = chip_split(NX, NY);
-  constexpr int NT = chip_threads(NX, NY), H = NX / 2;
-  using C = DivCfg<NY, chip_cv(NT)>;
+  constexpr int CL = cs.wide, NT = wide_threads(CL), EP = chip_ep(NX, NY), H = NX / 2;
+  constexpr int NC = cs.C, CN = NC * NY;
   using V = cx<T>;
-  constexpr int LS = chip_ls(NY, C::C);
-  static_assert(2 * C::C * LS <= chip_lds(NT), "tile exceeds its LDS");
+  constexpr int LS = chip_ls(NY, NC);
+  static_assert(2 * NC * LS <= chip_lds(CL), "tile exceeds its LDS");
+  const V* tw = (const V*)g.tw;
   const bool on = cs.ncol == cs.G || kx0 < H;
   constexpr int dt = cs.step, dg = dt * cs.R * H, dl = dt * cs.R;
-  V f[2 * CHIP_EP];
+  V f[2 * EP];
 #pragma unroll
-  for (int i = 0; i < 2 * CHIP_EP; ++i)
+  for (int i = 0; i < 2 * EP; ++i)
     if (st.t + i * dt < cs.nrow) f[i] = team_load(ex, st.go + i * dg, (V*)nullptr);
 #pragma unroll
-  for (int i = 0; i < 2 * CHIP_EP; ++i)
+  for (int i = 0; i < 2 * EP; ++i)
     if (st.t + i * dt < cs.nrow) buf[st.li + i * dl] = f[i];
   __syncthreads();
-  chip_fft<T, -1, NY, 2 * C::C, LS, NT>(buf, st.wc, tid);
+  chip_fft<T, -1, NY, 2 * NC, LS, NT>(buf, st.wc, tw, g.twn, tid);
   ps[0] = ps[1] = 0.0;
 #pragma unroll
-  for (int i = 0; i < C::EP; ++i) {
-    const int p = tid + i * NT;
-    if (p < C::CN && on) {
+  for (int i = 0; i < EP; ++i) {
+    const int p = chip_elem<NT, chip_sc(CL), CN>(tid, i);
+    if (p < CN && on) {
       V* px = buf + p / NY * LS + p % NY;
-      V* py = px + C::C * LS;
+      V* py = px + NC * LS;
       const double xx = xi_col(kx0 + p / NY, g.lx), yy = xi_tilde(p % NY, NY, g.ly);
       const V fx = *px, fy = *py;
       // w = -i (xx Fx + yy Fy)
@@ -381,7 +416,7 @@ __device__ __forceinline__ void chip_col(ChipState<T>& st, cx<T>* buf, cx<T>* xs
       const V zo = scl(rn, sig);
       const V d = first ? zo : add(zo, scl(st.d[i], bt));
       const V s = first ? w : add(w, scl(st.s[i], bt));
-      xs[p] = add(xs[p], scl(d, a));
+      if (!chip_big(CL)) xs[p] = add(xs[p], scl(d, a));
       rn = sub(rn, scl(s, a));
       st.r[i] = rn;
       st.d[i] = d;
@@ -396,21 +431,40 @@ __device__ __forceinline__ void chip_col(ChipState<T>& st, cx<T>* buf, cx<T>* xs
     }
   }
   __syncthreads();
-  if (last) return;
-  chip_opaque(tid);
-  chip_fft<T, +1, NY, 2 * C::C, LS, NT>(buf, st.wc, tid);
+  auto update_x = [&]() {
+    if constexpr (chip_big(CL)) {
+      cx<T>* xg = xh + (size_t)kx0 * NY;
+      V xv[EP];
 #pragma unroll
-  for (int i = 0; i < 2 * CHIP_EP; ++i)
+      for (int i = 0; i < EP; ++i) {
+        const int p = chip_elem<NT, chip_sc(CL), CN>(tid, i);
+        if (p < CN && on) xv[i] = xg[p];
+      }
+#pragma unroll
+      for (int i = 0; i < EP; ++i) {
+        const int p = chip_elem<NT, chip_sc(CL), CN>(tid, i);
+        if (p < CN && on) xg[p] = add(xv[i], scl(st.d[i], a));
+      }
+    }
+  };
+  if (last) {
+    update_x();
+    return;
+  }
+  chip_opaque(tid);
+  chip_fft<T, +1, NY, 2 * NC, LS, NT>(buf, st.wc, tw, g.twn, tid);
+#pragma unroll
+  for (int i = 0; i < 2 * EP; ++i)
     if (st.t + i * dt < cs.nrow) chip_store(ex, st.go + i * dg, buf[st.li + i * dl]);
+  update_x();
 }
-template <typename T, int NY, int NT>
+template <typename T, int NY, int NC, int NT>
 __device__ __forceinline__ void chip_col_out(const cx<T>* buf, cx<T>* M0, cx<T>* M1, int kx0, int h, int tid) {
-  using C = DivCfg<NY, chip_cv(NT)>;
-  constexpr int LS = chip_ls(NY, C::C);
+  constexpr int LS = chip_ls(NY, NC), CN = NC * NY;
   if (kx0 >= h) return;
-  for (int e = tid; e < 2 * C::CN; e += NT) {
-    const int f = e / C::CN, c = e % C::CN / NY, ky = e % NY;
-    (f ? M1 : M0)[(size_t)(kx0 + c) * NY + ky] = buf[(f * C::C + c) * LS + ky];
+  for (int e = tid; e < 2 * CN; e += NT) {
+    const int f = e / CN, c = e % CN / NY, ky = e % NY;
+    (f ? M1 : M0)[(size_t)(kx0 + c) * NY + ky] = buf[(f * NC + c) * LS + ky];
   }
 }
 
@@ -444,8 +498,10 @@ __device__ __forceinline__ bool chip_wait(__amdgpu_buffer_rsrc_t slots, int o, u
   }
   return false;
 }
-template <int NT, int K>
-__device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int member, int slot, int ntiles, unsigned epoch,
+// Q launched tiles per member, NTL threads of the launched pass that adds the sums up,
+// XCD whether the tiles' places are those of xcd_block.
+template <int NT, int K, int Q, int NTL, bool XCD>
+__device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int member, int ntiles, unsigned epoch,
                                           const double (&v)[K], double scale, double* sh, double& own, double (&tot)[K]) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63;
@@ -454,14 +510,16 @@ __device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int memb
   wave_sums<K>(v, sh);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  const int set = (int)(epoch & 1) * (CHIP_MAX * 2), pub = 2 * CHIP_MAX * 2 + (int)(epoch & 1) * 64;
+  const int set = (int)(epoch & 1) * (CHIP_TILES * 2), pub = 2 * CHIP_TILES * 2 + (int)(epoch & 1) * 64;
   ChipSlot w;
-  if (threadIdx.x < K) {
-    own = waves_total<NW>(sh + threadIdx.x * NW) * scale;
+  if (threadIdx.x < Q * K) {
+    const int q = threadIdx.x / K, k = threadIdx.x % K, t = member * Q + q;
+    const int slot = XCD && ntiles % 8 == 0 ? t % (ntiles / 8) * 8 + t / (ntiles / 8) : t;
+    own = waves_total<NW / Q>(sh + k * NW + q * (NW / Q)) * scale;
     w.d[0] = own;
     w.u.z = epoch;
     w.u.w = 0;
-    if (slot < ntiles) __builtin_amdgcn_raw_buffer_store_b128(w.u, slots, (set + slot * 2 + threadIdx.x) * 16, 0, TEAM_SC1);
+    if (t < ntiles) __builtin_amdgcn_raw_buffer_store_b128(w.u, slots, (set + slot * 2 + k) * 16, 0, TEAM_SC1);
   }
   double* okp = sh + 4 * NW;
   if (member == 0) {
@@ -469,18 +527,21 @@ __device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int memb
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < K; ++k) s[k] = 0.0;
-    if (threadIdx.x < CHIP_MAX) {
-      const bool has = (int)threadIdx.x < ntiles;
+    if (threadIdx.x < NTL) {
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        ok = chip_wait(slots, (set + (has ? (int)threadIdx.x : 0) * 2 + k) * 16, epoch, w) && ok;
-        if (has) s[k] = w.d[0];
+      for (int i = 0; i < (Q * CHIP_MAX + NTL - 1) / NTL; ++i) {
+        const int t = threadIdx.x + i * NTL;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          ok = chip_wait(slots, (set + (t < ntiles ? t : 0) * 2 + k) * 16, epoch, w) && ok;
+          if (t < ntiles) s[k] += w.d[0];
+        }
       }
     }
     wave_sums<K>(s, all);
     if (!__syncthreads_and(ok)) return false;
 #pragma unroll
-    for (int k = 0; k < K; ++k) tot[k] = waves_total<NW>(all + k * NW);
+    for (int k = 0; k < K; ++k) tot[k] = waves_total<NTL / 64>(all + k * NW);
     if (threadIdx.x < 8 * K) {
       w.d[0] = K == 2 && threadIdx.x % K == 1 ? tot[K - 1] : tot[0];
       w.u.z = epoch;
@@ -515,13 +576,14 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
                                                                int nk, int max_iter, double tol2) {
   using V = cx<T>;
   constexpr ChipShape cs = chip_split(NX, NY);
-  constexpr int NT = chip_threads(NX, NY);
+  constexpr int CL = cs.wide, NT = wide_threads(CL), E = wide_elems(CL), EP = E / NT;
+  constexpr int SR = chip_sr(NX, CL), SC = chip_sc(CL), CN = cs.C * NY;
   DevStatus* st = g.st;
   TeamCtl* ctl = (TeamCtl*)g.team;
   if (st->conv_at <= it0) return;
-  __shared__ V buf[chip_lds(NT)];
-  __shared__ V ms[3 * NT * CHIP_EP];  // pairs of m_x, m_y, r of the tile's rows
-  __shared__ V xs[NT * CHIP_EP];      // x of its columns
+  __shared__ V buf[chip_lds(CL)];
+  __shared__ V ms[(chip_big(CL) ? 2 : 3) * E];  // pairs of m_x, m_y, r of the tile's rows
+  __shared__ V xs[chip_big(CL) ? 1 : E];        // x of its columns
   __shared__ double red[chip_red(NT)];
   __shared__ int role_s, go_s;
   constexpr int G = cs.G;
@@ -558,24 +620,21 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
   const __amdgpu_buffer_rsrc_t slots = team_rsrc(slot_ptr(g.part, SLOT_P3) + MAX_WG, CHIP_SLOTS * 16);
   const int kx0 = member * cs.C, y0 = member * cs.R;
   const bool upper = kx0 >= h / 2;
-  // the place of the row tile's partial in the row pass's order (xcd_block)
-  const int rslot = cs.nrow % 8 == 0 && member < cs.nrow ? member % (cs.nrow / 8) * 8 + member / (cs.nrow / 8) : member;
-  ChipState<T> S;
+  ChipState<T, EP> S;
   {
-    const int cn = kx0 < h ? cs.C * ny : 0;
     const size_t base = (size_t)kx0 * ny;
 #pragma unroll
-    for (int i = 0; i < CHIP_EP; ++i) {
-      const int p = tid + i * NT;
-      const bool ok = p < cn;
-      xs[p] = ok ? xh[base + p] : vzero<V>();
+    for (int i = 0; i < EP; ++i) {
+      const int p = chip_elem<NT, SC, CN>(tid, i);
+      const bool ok = p < CN && kx0 < h;
+      if (!chip_big(CL)) xs[p] = ok ? xh[base + p] : vzero<V>();
       S.r[i] = ok ? rh[base + p] : vzero<V>();
       S.d[i] = ok && it0 > 0 ? dh[base + p] : vzero<V>();
       S.s[i] = ok && it0 > 0 ? sh[base + p] : vzero<V>();
     }
   }
   const double K[4] = {st->kbar[0], st->kbar[1], st->kbar[2], 0.0};
-  chip_row_setup<T, NX, NT>(S, ms, g, m, r, y0, tid);
+  chip_row_setup<T, NX, CL, cs.R>(S, ms, g, m, r, y0, tid);
   chip_col_setup<T, NX, NY>(S, g, K, kx0, tid);
   const double bb = st->bb;
   const int budget = st->budget;
@@ -590,24 +649,24 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
     // d and s are in registers everywhere before the first exchange store
     const double v0[1] = {0.0};
     double t0[1];
-    if (!chip_meet<NT, 1>(slots, member, member, cs.ncol, ++epoch, v0, 1.0, red, od, t0)) outcome = TEAM_LOST;
+    if (!chip_meet<NT, 1, SC, NT / SC, false>(slots, member, cs.ncol * SC, ++epoch, v0, 1.0, red, od, t0)) outcome = TEAM_LOST;
     ++epoch;
   }
   for (; outcome == TEAM_MORE && it < it0 + nk; ++it) {
     int t = tid;
     chip_opaque(t);
     double de[1] = {0.0}, det[1];
-    de[0] = chip_row<T, NX, NY>(S, buf, ms, g, M0, M1, lo, hi, y0, it == it0, t);
-    if (!chip_meet<NT, 1>(slots, member, rslot, cs.nrow, ++epoch, de, npts, red, od, det)) {
+    de[0] = chip_row<T, NX, NY>(S, buf, ms, r, g, M0, M1, lo, hi, y0, it == it0, t);
+    if (!chip_meet<NT, 1, SR, NT / SC, true>(slots, member, cs.nrow * SR, ++epoch, de, npts, red, od, det)) {
       outcome = TEAM_LOST;
       break;
     }
     const TeamStep q = team_step(ga, ga_prev, al_prev, det[0], it, max_iter, budget);
     bad = q.bad;
     double ps[2] = {0.0, 0.0}, pt[2];
-    chip_col<T, NX, NY>(S, buf, xs, g, upper ? hi : lo, kx0, (T)q.alpha, (T)q.beta, it == 0, q.stop,
+    chip_col<T, NX, NY>(S, buf, xs, xh, g, upper ? hi : lo, kx0, (T)q.alpha, (T)q.beta, it == 0, q.stop,
                         ps, t);
-    if (!chip_meet<NT, 2>(slots, member, member, cs.ncol, ++epoch, ps, 1.0, red, own, pt)) {
+    if (!chip_meet<NT, 2, SC, NT / SR, false>(slots, member, cs.ncol * SC, ++epoch, ps, 1.0, red, own, pt)) {
       outcome = TEAM_LOST;
       break;
     }
@@ -622,13 +681,12 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
     }
   }
   if (outcome != TEAM_LOST) {
-    const int cn = kx0 < h ? cs.C * ny : 0;
     const size_t base = (size_t)kx0 * ny;
 #pragma unroll
-    for (int i = 0; i < CHIP_EP; ++i) {
-      const int p = tid + i * NT;
-      if (p < cn) {
-        xh[base + p] = xs[p];
+    for (int i = 0; i < EP; ++i) {
+      const int p = chip_elem<NT, SC, CN>(tid, i);
+      if (p < CN && kx0 < h) {
+        if (!chip_big(CL)) xh[base + p] = xs[p];
         rh[base + p] = S.r[i];
         if (outcome == TEAM_MORE) {
           dh[base + p] = S.d[i];
@@ -637,8 +695,8 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
       }
     }
     if (outcome == TEAM_MORE) {
-      chip_col_out<T, NY, NT>(buf, M0, M1, kx0, h, tid);
-      if (tid < 2 && member < cs.ncol) slot_ptr(g.part, SLOT_RR)[tid * MAX_WG + member] = own;
+      chip_col_out<T, NY, cs.C, NT>(buf, M0, M1, kx0, h, tid);
+      if (tid < 2 * SC && member < cs.ncol) slot_ptr(g.part, SLOT_RR)[tid % 2 * MAX_WG + member * SC + tid / 2] = own;
     }
   }
   if (member == 0 && threadIdx.x == 0) {

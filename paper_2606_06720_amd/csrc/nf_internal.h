@@ -55,12 +55,12 @@ struct TeamShape {
   int G, C, lr, nt, xcc;
   unsigned epoch;
 };
-// The team over the chip (nf_chip.hpp): members at most; its barrier's 16-byte
-// entries (two sets of two per member, two sets of eight published lines), which
+// The team over the chip (nf_chip.hpp): members at most, launched tiles at most; its barrier's
+// 16-byte entries (two sets of two per tile, two sets of eight published lines), which
 // lie in the arrays of SLOT_P3 that the 2D passes leave unused; the split of a grid:
 // members, the tiles' class (Geo::wide) with rows and columns per tile, row and
 // column tiles, row tiles whose elements a column tile's threads take at a time.
-enum { CHIP_MAX = 256, CHIP_SLOTS = 2 * CHIP_MAX * 2 + 2 * 64 };
+enum { CHIP_MAX = 256, CHIP_TILES = 2 * CHIP_MAX, CHIP_SLOTS = 2 * CHIP_TILES * 2 + 2 * 64 };
 struct ChipShape {
   int G, wide, R, C, nrow, ncol, step;
 };
@@ -110,8 +110,9 @@ struct Geo {
   // caller set for the operator end, which is part of that pass).  Read by the
   // launchers only.
   int var_flux[2], var_div[2], var_upd[2];
-  // grids with a team over the chip: the loop's passes take that team's tiles, row
-  // variant RV_WIDE + wide and column variant CV_WIDE + wide, instead (-1: no team)
+  // grids with a team over the chip: the loop's passes take that team's tiles instead,
+  // row variant RV_WIDE + wide and column variant CV_WIDE + wide for wide = 0 and 1, row
+  // variant 2 (tuned lengths) or 1 and column variant 1 for wide = 2 (-1: no team)
   int wide;
 };
 

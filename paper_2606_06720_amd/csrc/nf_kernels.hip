@@ -1111,14 +1111,14 @@ int col_nwg_var(const Geo& g, int cv) {
 bool flux_var_valid(const Geo& g, bool f32, int rv) {
   if (rv == VAR_DEFAULT) return true;
   const int es = f32 ? 8 : 16;
-  if (rv >= RV_WIDE) return wide_row_ok(g.nx, rv) && g.nz == 1;
+  if (rv >= RV_WIDE) return wide_row_ok(g.nx) && rv < NRV && rv_rows(g.nx, rv) >= 1 && g.nz == 1;
   if (rv >= RV_SEQ) return rv_seq_ok(g.nx, rv, es) && rv_rows(g.nx, rv) <= g.ny && g.nz == 1;
   if (rv >= RV_SMALL) return small_ok(rv_rows(g.nx, rv), g.nx / 2) && g.nz == 1;
   return var_size(g.nx) && g.nz == 1 && rv_ok(g.nx, g.ny, rv, es);
 }
 bool div_var_valid(const Geo& g, bool f32, int cv) {
   if (cv == VAR_DEFAULT) return true;
-  if (cv >= CV_WIDE) return wide_col_ok(g.ny, cv) && g.nz == 1;
+  if (cv >= CV_WIDE) return wide_col_ok(g.ny) && cv < NCV && cv_cols(g.ny, cv) >= 1 && g.nz == 1;
   if (cv >= CV_SEQ) return cv_seq_ok(g.ny, cv) && g.nz == 1;
   if (cv >= CV_SMALL) return small_ok(cv_cols(g.ny, cv), g.ny) && g.nz == 1;
   const int es = f32 ? 8 : 16;
@@ -1135,11 +1135,11 @@ hipError_t launch_fill_doubles(double* p, size_t n, double v, hipStream_t s) {
 
 // variant codes in use (a variant that cannot run on this grid falls back to the default)
 int use_rv(const Geo& g, bool f32, int it) {
-  const int rv = it < 0 ? VAR_DEFAULT : (g.wide >= 0 ? RV_WIDE + g.wide : g.var_flux[f32 ? 1 : 0]);
+  const int rv = it < 0 ? VAR_DEFAULT : (g.wide == 2 ? (var_size(g.nx) ? 2 : VAR_DEFAULT) : (g.wide >= 0 ? RV_WIDE + g.wide : g.var_flux[f32 ? 1 : 0]));
   return flux_var_valid(g, f32, rv) ? rv : VAR_DEFAULT;
 }
 int use_cv(const Geo& g, bool f32) {
-  const int cv = g.wide >= 0 ? CV_WIDE + g.wide : g.var_upd[f32 ? 1 : 0];
+  const int cv = g.wide == 2 ? (int)VAR_DEFAULT : g.wide >= 0 ? CV_WIDE + g.wide : g.var_upd[f32 ? 1 : 0];
   return div_var_valid(g, f32, cv) ? cv : VAR_DEFAULT;
 }
 int rr_nwg(const Geo& g, bool f32) { return col_nwg_var(g, use_cv(g, f32)); }

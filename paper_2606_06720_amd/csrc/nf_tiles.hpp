@@ -126,7 +126,7 @@ __host__ __device__ constexpr int small_threads(int lines, int h) { return waves
 __host__ __device__ constexpr int wide_plan(int n) { return n == 256 ? 2 : 0; }
 // elements per field of wide class c
 __host__ __device__ constexpr int wide_elems(int c) { return 512 << c; }
-__host__ __device__ constexpr int wide_threads(int c) { return wide_elems(c) / 2; }
+__host__ __device__ constexpr int wide_threads(int c) { return c == 0 ? 256 : 512; }
 __host__ __device__ constexpr int rv_rows(int nx, int rv) {
   const int rd = tile_rows(nx / 2, row_tile(nx, 2));
   if (rv >= RV_WIDE) return wide_elems(rv - RV_WIDE) / (nx / 2);
@@ -166,12 +166,8 @@ __host__ __device__ constexpr bool rv_seq_ok(int nx, int rv, int es) {
 }
 __host__ __device__ constexpr bool cv_seq_ok(int ny, int cv) { return ny >= 2048 && cv < CV_WIDE; }
 // wide tiles: the lengths of grids with a team over the chip (nf_chip.hpp)
-__host__ __device__ constexpr bool wide_row_ok(int nx, int rv) {
-  return nx >= 128 && nx <= 2048 && rv < NRV && rv_rows(nx, rv) >= 1;
-}
-__host__ __device__ constexpr bool wide_col_ok(int ny, int cv) {
-  return ny >= 64 && ny <= 1024 && cv < NCV && cv_cols(ny, cv) >= 1;
-}
+__host__ __device__ constexpr bool wide_row_ok(int nx) { return nx >= 128 && nx <= 2048; }
+__host__ __device__ constexpr bool wide_col_ok(int ny) { return ny >= 64 && ny <= 1024; }
 // small tiles: at least one line, and at least half a wavefront of butterflies
 __host__ __device__ constexpr bool small_ok(int lines, int h) { return lines >= 1 && lines * h / 8 * 2 >= 32; }
 __host__ __device__ constexpr bool rv_ok(int nx, int ny, int rv, int es) {
@@ -203,14 +199,14 @@ using DivCfg = typename std::conditional<
 // variants that can be built for a size (the row count against Ny is checked at run time)
 template <int NX, int RV, int ES>
 constexpr bool flux_var_exists() {
-  if (RV >= RV_WIDE) return wide_row_ok(NX, RV);
+  if (RV >= RV_WIDE) return RV < NRV && wide_row_ok(NX) && rv_rows(NX, RV) >= 1;
   if (RV >= RV_SEQ) return rv_seq_ok(NX, RV, ES);
   return RV == VAR_DEFAULT || (RV >= RV_SMALL ? small_ok(rv_rows(NX, RV), NX / 2)
                                               : var_size(NX) && rv_ok(NX, 1 << 20, RV, ES));
 }
 template <int NY, int CV, int ES>
 constexpr bool div_var_exists() {
-  if (CV >= CV_WIDE) return wide_col_ok(NY, CV);
+  if (CV >= CV_WIDE) return CV < NCV && wide_col_ok(NY) && cv_cols(NY, CV) >= 1;
   if (CV >= CV_SEQ) return cv_seq_ok(NY, CV);
   return CV == VAR_DEFAULT || (CV >= CV_SMALL ? small_ok(cv_cols(NY, CV), NY)
                                               : var_size(NY) && cv_ok(NY, 1 << 20, CV, ES));
