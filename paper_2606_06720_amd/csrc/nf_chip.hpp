@@ -58,7 +58,7 @@
 namespace nf {
 
 constexpr double CHIP_FORM_MS = 5.0;
-constexpr unsigned CHIP_POLLS = 1u << 22;  // polls of about 0.7 us before a member counts as lost
+constexpr unsigned CHIP_POLLS = 1u << 22;  // polls (a second or more) before a member counts as lost
 
 __device__ __forceinline__ void chip_store(__amdgpu_buffer_rsrc_t b, int i, cx<double> v) {
   union {
