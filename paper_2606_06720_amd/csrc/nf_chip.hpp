@@ -28,7 +28,7 @@
 // pass reads and writes one contiguous block per buffer, a column pass runs of 2 C
 // rows.  Every pass writes where it has read: with a second layout for the
 // gradient, contiguous for the column pass, the waits grew from 14000 to 19000
-// cycles per iteration at 512^2, since the lines then were in the L2 of another XCD.
+// cycles per iteration at 512^2 (presumably since the lines then are in another XCD's L2).
 //
 // A member does the work of one or two workgroups of the launched passes, and the
 // totals are added up in the order in which those passes add them, so the results are

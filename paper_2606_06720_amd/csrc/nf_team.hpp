@@ -1,5 +1,5 @@
 // The whole PCG loop of a small 2D grid in one launch (FP64 and FP32
-// instantiations in nf_team64.hip and nf_team32.hip).
+// instantiations in nf_team64*.hip and nf_team32*.hip).
 //
 // On grids of up to 65536 points a loop pass is a chain of latencies: a launch,
 // the status and partial sums of the pass before, a tile of a few KB through a
@@ -12,8 +12,8 @@
 // the Infinity Cache); two kernel boundaries with their reloads cost most of the
 // 12 us of a 64^2 iteration.  Measured per iteration, launches -> team: 64^2 12
 // -> 5.6 us, 128^2 12 -> 8 us, 200^2 20 -> 13 us, 256^2 15.2 -> 14 us (there the
-// 1024 elements per field of each member fill a compute unit: larger grids have
-// no team).
+// 1024 elements per field of each member fill a compute unit: larger grids
+// use compute units of all XCDs, nf_chip.hpp).
 //
 // Visibility inside the team: stores go through the vector L1 to the L2 that
 // the team shares; every wave waits for its stores (vmcnt 0) before the

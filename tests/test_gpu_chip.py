@@ -2,8 +2,8 @@
 against the oracle and against the same passes as launches.
 
 Shapes: the smallest grids with such a team, one to sixteen rows or columns per
-tile, tiles that do not fill their threads, both tile sizes, more row than column
-tiles and the reverse, and shapes just outside its limits.  A handle
+tile, tiles that do not fill their threads, one and two launched tiles per member, more
+row than column tiles and the reverse, and shapes just outside its limits.  A handle
 that times a kernel runs the passes as launches, so the two can be compared on
 one handle: the tiles' work and the order of every sum are the same, so the
 results agree bit for bit.  Against the oracle: 1e-10 relative L2, the FP64 bound
