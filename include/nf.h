@@ -114,8 +114,9 @@ typedef struct {
  *   dtype   NF_F64 or NF_F32_REFINED;
  *   stream  hipStream_t to enqueue on (NULL = default stream).
  * Allocates the workspace (8 complex half-spectrum fields plus tables, 9 in
- * 3D; with NF_F32_REFINED also 6 (3D: 7) single-precision half-spectrum
- * fields and FP32 copies of m and r) on the current HIP device.
+ * 3D; with NF_F32_REFINED also 5 (3D: 6) single-precision half-spectrum
+ * fields, an FP32 gradient on the grid and FP32 copies of m and r) on the
+ * current HIP device.
  * Layouts of the caller's fields: 2D p, r, S [Ny][Nx], m [2][Ny][Nx]; 3D
  * p, r, S [Nz][Ny][Nx], m [3][Nz][Ny][Nx]; x fastest.
  * The first handle of a 2D shape and precision in a process also tunes the

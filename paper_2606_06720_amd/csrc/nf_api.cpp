@@ -218,7 +218,7 @@ int init_residual(nf_grid* g, const double* m, const double* r, float* lo = null
   const Geo& G = g->geo;
   hipStream_t s = g->stream;
   if (g->dim == 3) {
-    LCHK(g, launch3_row_flux(G, false, g->mix[0], g->mix[1], g->mix[2], m, r, -1, 1, lo, 0.0, s));
+    LCHK(g, launch3_row_flux(G, false, g->mix[0], g->mix[1], g->mix[2], m, r, -1, 1, lo, nullptr, 0.0, s));
     LCHK(g, launch3_ypass(G, false, 3, -1, g->mix[0], g->mix[1], g->mix[2], nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_zdiv(G, 1, g->mix[0], g->mix[1], g->mix[2], nullptr, g->rh, g->bh, s));
     return NF_OK;
@@ -235,10 +235,10 @@ TeamGo team_args(const nf_grid* g, bool f32, const double* m, const double* r, i
   go.max_iter = max_iter;
   go.tol2 = tol2;
   if (f32) {
-    go.f = FluxArgs{g->geo32, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, nullptr, nullptr};
-    go.a = IterArgs{g->geo32, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32};
+    go.f = FluxArgs{g->geo32, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, nullptr, nullptr, g->gd32};
+    go.a = IterArgs{g->geo32, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->gd32};
   } else {
-    go.f = FluxArgs{g->geo, g->mix[0], g->mix[1], m, r, nullptr, nullptr};
+    go.f = FluxArgs{g->geo, g->mix[0], g->mix[1], m, r, nullptr, nullptr, nullptr};
     go.a = IterArgs{g->geo, g->mix[0], g->mix[1], g->xh, g->rh, g->dh, g->qh};
   }
   return go;
@@ -314,10 +314,10 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
         void* const* F = f32 ? g->mix32 : g->mix;
         LCHK(g, launch3_ypass(G, f32, 3, +1, F[0], F[1], F[2], nullptr, it, it > 0 ? nwg3_ziter(G, f32) : 0, -1.0, s));
         LCHK(g, launch3_row_flux(G, f32, F[0], F[1], F[2], f32 ? (const void*)g->lo : (const void*)m,
-                                 f32 ? (const void*)(g->lo + 3 * n) : (const void*)r, it, 0, nullptr, tol2, s));
+                                 f32 ? (const void*)(g->lo + 3 * n) : (const void*)r, it, 0, nullptr, g->gd32, tol2, s));
         LCHK(g, launch3_ypass(G, f32, 3, -1, F[0], F[1], F[2], nullptr, it, nwg3_flux(G, f32), -1.0, s));
         LCHK(g, launch3_ziter(G, f32, F[0], F[1], F[2], f32 ? g->x32 : g->xh, f32 ? g->r32 : g->rh,
-                              f32 ? g->d32 : g->dh, f32 ? g->q32 : g->qh, it, max_iter, s));
+                              f32 ? g->d32 : g->dh, f32 ? nullptr : g->qh, it, max_iter, s));
         ++it;
         continue;
       }
@@ -328,8 +328,8 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
         go.what = TeamGo::COL;
         LCHK(g, launch_team(f32, go, s));
       } else if (f32) {
-        LCHK(g, launch_row_flux32(G, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, it, tol2, s));
-        LCHK(g, launch_col_iter32(G, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32, it, max_iter, s));
+        LCHK(g, launch_row_flux32(G, g->mix32[0], g->mix32[1], g->lo, g->lo + 2 * n, g->gd32, it, tol2, s));
+        LCHK(g, launch_col_iter32(G, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, it, max_iter, s));
       } else {
         LCHK(g, launch_row_flux(G, g->mix[0], g->mix[1], m, r, it, nullptr, tol2, s));
         LCHK(g, launch_col_iter64(G, g->mix[0], g->mix[1], g->xh, g->rh, g->dh, g->qh, it, max_iter, s));
@@ -835,9 +835,10 @@ int nf_create_grid(nf_grid** out, int ndim, const int64_t n[3], const double L[3
   CREATE_CHK(hipMemset(g->xh, 0, spec_bytes), NF_EDEVICE);
   if (dtype == NF_F32_REFINED) {
     const size_t spec32 = spec_bytes / 2;
-    void** b32[] = {&g->x32, &g->r32, &g->d32, &g->q32};
+    void** b32[] = {&g->x32, &g->r32, &g->d32};
     for (void** b : b32) CREATE_CHK(hipMalloc(b, spec32), NF_ENOMEM);
     for (int i = 0; i < ndim; ++i) CREATE_CHK(hipMalloc(&g->mix32[i], spec32), NF_ENOMEM);
+    CREATE_CHK(hipMalloc((void**)&g->gd32, (size_t)ndim * npts * sizeof(float)), NF_ENOMEM);
     CREATE_CHK(hipMalloc((void**)&g->lo, (size_t)(ndim + 1) * npts * sizeof(float)), NF_ENOMEM);
     CREATE_CHK(hipMalloc(&g->tw32, (size_t)twn * 2 * sizeof(float)), NF_ENOMEM);
     float* h = new float[2 * (size_t)twn];
@@ -930,7 +931,7 @@ int nf_destroy_grid(nf_grid* g) {
   if (g->stream) (void)hipStreamSynchronize(g->stream);
   else (void)hipDeviceSynchronize();
   void* bufs[] = {g->xh,     g->rh,     g->dh,   g->qh,  g->bh,  g->mix[0],  g->mix[1],  g->mix[2],
-                  g->mix[3], g->tw,     g->part, g->st_own, g->x32, g->r32, g->d32, g->q32,
+                  g->mix[3], g->tw,     g->part, g->st_own, g->x32, g->r32, g->d32, g->gd32,
                   g->mix32[0], g->mix32[1], g->mix32[2], g->lo, g->tw32};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -1009,7 +1010,7 @@ int nf_apply_operator(nf_grid* g, const double* m, const double* r, const double
     rc = prepare_iterate(g, X_FROM_P, p);
     if (rc) return rc;
     void* const* M = g->mix;
-    LCHK(g, launch3_row_flux(G, false, M[0], M[1], M[2], m, r, -1, 0, nullptr, 0.0, s));
+    LCHK(g, launch3_row_flux(G, false, M[0], M[1], M[2], m, r, -1, 0, nullptr, nullptr, 0.0, s));
     LCHK(g, launch3_ypass(G, false, 3, -1, M[0], M[1], M[2], nullptr, -1, 0, -1.0, s));
     LCHK(g, launch3_zdiv(G, 0, M[0], M[1], M[2], g->qh, nullptr, nullptr, s));
     LCHK(g, launch3_zinv(G, 1, g->qh, M[0], nullptr, nullptr, nullptr, s));

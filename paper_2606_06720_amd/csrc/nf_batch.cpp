@@ -177,13 +177,13 @@ int upload_tables(Part* b, Part::Group& G, const nf_params* prm, double dt, doub
     const size_t n = (size_t)g->nx * g->ny;
     const Geo& g64 = g->geo;
     const Geo& g32 = g->geo32;
-    H.t.flux_init[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], slot_ptr(g->part, SLOT_KBAR), nullptr};
-    H.t.flux_init_lo[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], slot_ptr(g->part, SLOT_KBAR), g->lo};
-    H.t.flux_loop[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], nullptr, nullptr};
-    H.t.flux32[j] = FluxArgs{g32, g->mix32[0], g->mix32[1], g->lo, g->lo ? g->lo + 2 * n : nullptr, nullptr, nullptr};
+    H.t.flux_init[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], slot_ptr(g->part, SLOT_KBAR), nullptr, nullptr};
+    H.t.flux_init_lo[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], slot_ptr(g->part, SLOT_KBAR), g->lo, nullptr};
+    H.t.flux_loop[j] = FluxArgs{g64, g->mix[0], g->mix[1], m[i], r[i], nullptr, nullptr, nullptr};
+    H.t.flux32[j] = FluxArgs{g32, g->mix32[0], g->mix32[1], g->lo, g->lo ? g->lo + 2 * n : nullptr, nullptr, nullptr, g->gd32};
     H.t.div_init[j] = DivArgs{g64, g->mix[0], g->mix[1], g->rh, g->bh};
     H.t.iter64[j] = IterArgs{g64, g->mix[0], g->mix[1], g->xh, g->rh, g->dh, g->qh};
-    H.t.iter32[j] = IterArgs{g32, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->q32};
+    H.t.iter32[j] = IterArgs{g32, g->mix32[0], g->mix32[1], g->x32, g->r32, g->d32, g->gd32};
     H.t.grad_x[j] = ColGradArgs{g64, g->xh, nullptr, g->mix[0], g->mix[1]};
     H.t.split_p[j] = ColGradArgs{g64, g->xh, g->mix[0], nullptr, nullptr};
     H.t.split_g[j] = ColGradArgs{g64, g->xh, nullptr, g->mix[1], g->mix[2]};

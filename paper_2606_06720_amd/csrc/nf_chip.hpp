@@ -161,11 +161,13 @@ __device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW],
 }
 
 // What a thread keeps for the whole loop (EP elements of a field): the vectors
-// and symbols of its spectral elements.  (x and, for its grid-point pairs, m and r
+// and symbols of its spectral elements; in FP32 the gradient of d at its grid-point
+// pairs instead of s (see grad_rec).  (x and, for its grid-point pairs, m and r
 // stay in LDS: in registers they made the members of 512 FP64 threads spill.)
 template <typename T, int EP>
 struct ChipState {
-  cx<T> r[EP], d[EP], s[EP];
+  cx<T> r[EP], d[EP], s[grad_rec<T>() ? 1 : EP];
+  cx<T> gx[grad_rec<T>() ? EP : 1], gy[grad_rec<T>() ? EP : 1];
   T sig[EP];
   cx<T> wr[CHIP_TW], wc[CHIP_TW], wp[EP];  // twiddles of its row and column transforms and pairs
   int go, li, t;  // place of its first column element in the exchange buffer and in LDS, that element's row tile
@@ -271,14 +273,38 @@ __device__ __forceinline__ void chip_col_setup(ChipState<T, chip_ep(NX, NY)>& st
   st.li = (f * NC + c) * LS + tid / w * R + rr;
 }
 
-// Row pass of the tile at row y0 (see row_flux_body): this thread's part of
-// sum g . K g.  lo, hi: the exchange buffers; G0, G1: the mixed fields in
+// The gradient of d at a thread's grid-point pairs (FP32), from and to its buffer
+// between launches, in units of pairs [2][Ny][Nx/2].
+template <typename T, int NX, int NY, bool STORE>
+__device__ __forceinline__ void chip_grad(ChipState<T, chip_ep(NX, NY)>& st, cx<T>* gd, int y0, int tid) {
+  if constexpr (grad_rec<T>()) {
+    constexpr int CL = chip_split(NX, NY).wide, H = NX / 2, RH = chip_split(NX, NY).R * H;
+#pragma unroll
+    for (int i = 0; i < chip_ep(NX, NY); ++i) {
+      const int p = chip_elem<wide_threads(CL), chip_sr(NX, CL), RH>(tid, i);
+      const bool ok = p < RH && y0 < NY;
+      const size_t o = (size_t)y0 * H + p, n2 = (size_t)H * NY;
+      if (STORE) {
+        if (ok) {
+          gd[o] = st.gx[i];
+          gd[n2 + o] = st.gy[i];
+        }
+      } else {
+        st.gx[i] = ok ? gd[o] : vzero<cx<T>>();
+        st.gy[i] = ok ? gd[n2 + o] : vzero<cx<T>>();
+      }
+    }
+  }
+}
+
+// Row pass of the tile at row y0 (see row_flux_body; bt: beta of the iteration, used
+// in FP32 beyond the first one, it0 of the loop): this thread's part of sum g . K g.  lo, hi: the exchange buffers; G0, G1: the mixed fields in
 // their usual layout, which the first pass after a launch reads.
 template <typename T, int NX, int NY>
-__device__ __forceinline__ double chip_row(const ChipState<T, chip_ep(NX, NY)>& st, cx<T>* buf, const cx<T>* ms,
+__device__ __forceinline__ double chip_row(ChipState<T, chip_ep(NX, NY)>& st, cx<T>* buf, const cx<T>* ms,
                                            const T* __restrict__ rg, const Geo& g, const cx<T>* G0,
                                            const cx<T>* G1, __amdgpu_buffer_rsrc_t lo, __amdgpu_buffer_rsrc_t hi, int y0,
-                                           bool first, int tid) {
+                                           bool first, T bt, bool start, int tid) {
   constexpr int CL = chip_split(NX, NY).wide, NT = wide_threads(CL), E = wide_elems(CL), ny = NY;
   using V = cx<T>;
   constexpr int H = NX / 2, R = chip_split(NX, NY).R, EP = chip_ep(NX, NY), NTK = R * H, LS = chip_ls(H, R), ETP = (NTK + NT - 1) / NT;
@@ -333,7 +359,15 @@ __device__ __forceinline__ double chip_row(const ChipState<T, chip_ep(NX, NY)>& 
     if (p < R * H && on) {
       V* px = buf + p / H * LS + p % H;
       V* py = px + R * LS;
-      const V gx = *px, gy = *py;
+      V gx = *px, gy = *py;
+      if constexpr (grad_rec<T>()) {
+        if (!start) {
+          gx = add(gx, scl(st.gx[i], bt));
+          gy = add(gy, scl(st.gy[i], bt));
+        }
+        st.gx[i] = gx;
+        st.gy[i] = gy;
+      }
       const V mx = ms[p], my = ms[E + p];
       const V rv = chip_big(CL) ? *(const V*)(rg + (size_t)(y0 + p / H) * NX + 2 * (p % H)) : ms[2 * E + p];
       const T a0 = mx.x * gx.x + my.x * gy.x;
@@ -415,12 +449,15 @@ __device__ __forceinline__ void chip_col(ChipState<T, chip_ep(NX, NY)>& st, cx<T
       V rn = st.r[i];
       const V zo = scl(rn, sig);
       const V d = first ? zo : add(zo, scl(st.d[i], bt));
-      const V s = first ? w : add(w, scl(st.s[i], bt));
+      V s = w;
+      if constexpr (!grad_rec<T>()) {
+        if (!first) s = add(w, scl(st.s[i], bt));
+        st.s[i] = s;
+      }
       if (!chip_big(CL)) xs[p] = add(xs[p], scl(d, a));
       rn = sub(rn, scl(s, a));
       st.r[i] = rn;
       st.d[i] = d;
-      st.s[i] = s;
       const double wr = (kx0 + p / NY == 0 ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
       ps[0] += wr;
       ps[1] += (double)sig * wr;
@@ -563,8 +600,8 @@ __device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int memb
 
 // Iterations it0 .. it0 + nk - 1 of the loop (fewer if it stops).  On entry the
 // mixed buffers hold the gradient of z and status.rho the scalar gamma of
-// iteration it0 (it0 > 0: status.alpha, d and s of the iteration before).  On exit
-// x, r (and, if iterations are left, d, s, the gradient and the partial sums) are
+// iteration it0 (it0 > 0: status.alpha, d and s of the iteration before; sh holds s
+// or, in FP32, the gradient of d, of which the exchange uses the first half).  On exit x, r (and, if iterations are left, d, s, the gradient and the partial sums) are
 // written back and the status records the outcome as the launches of nf_loop.hpp
 // do; status.team tells whether the team formed.
 // A kernel per grid shape: one that switches between the lengths inside the loop
@@ -630,8 +667,9 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
       if (!chip_big(CL)) xs[p] = ok ? xh[base + p] : vzero<V>();
       S.r[i] = ok ? rh[base + p] : vzero<V>();
       S.d[i] = ok && it0 > 0 ? dh[base + p] : vzero<V>();
-      S.s[i] = ok && it0 > 0 ? sh[base + p] : vzero<V>();
+      if constexpr (!grad_rec<T>()) S.s[i] = ok && it0 > 0 ? sh[base + p] : vzero<V>();
     }
+    if (it0 > 0) chip_grad<T, NX, NY, false>(S, sh, y0, tid);
   }
   const double K[4] = {st->kbar[0], st->kbar[1], st->kbar[2], 0.0};
   chip_row_setup<T, NX, CL, cs.R>(S, ms, g, m, r, y0, tid);
@@ -646,7 +684,7 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
   double own = 0.0, od;
   bool bad = false;
   if (it0 > 0) {
-    // d and s are in registers everywhere before the first exchange store
+    // d and s (or the gradient of d) are in registers everywhere before the first exchange store
     const double v0[1] = {0.0};
     double t0[1];
     if (!chip_meet<NT, 1, SC, NT / SC, false>(slots, member, cs.ncol * SC, ++epoch, v0, 1.0, red, od, t0)) outcome = TEAM_LOST;
@@ -656,12 +694,13 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
     int t = tid;
     chip_opaque(t);
     double de[1] = {0.0}, det[1];
-    de[0] = chip_row<T, NX, NY>(S, buf, ms, r, g, M0, M1, lo, hi, y0, it == it0, t);
+    const T bt = grad_rec<T>() ? (T)pcg_beta(ga, ga_prev, it == 0) : (T)0;
+    de[0] = chip_row<T, NX, NY>(S, buf, ms, r, g, M0, M1, lo, hi, y0, it == it0, bt, it == 0, t);
     if (!chip_meet<NT, 1, SR, NT / SC, true>(slots, member, cs.nrow * SR, ++epoch, de, npts, red, od, det)) {
       outcome = TEAM_LOST;
       break;
     }
-    const TeamStep q = team_step(ga, ga_prev, al_prev, det[0], it, max_iter, budget);
+    const TeamStep q = team_step<T>(ga, ga_prev, al_prev, det[0], it, max_iter, budget);
     bad = q.bad;
     double ps[2] = {0.0, 0.0}, pt[2];
     chip_col<T, NX, NY>(S, buf, xs, xh, g, upper ? hi : lo, kx0, (T)q.alpha, (T)q.beta, it == 0, q.stop,
@@ -690,11 +729,12 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
         rh[base + p] = S.r[i];
         if (outcome == TEAM_MORE) {
           dh[base + p] = S.d[i];
-          sh[base + p] = S.s[i];
+          if constexpr (!grad_rec<T>()) sh[base + p] = S.s[i];
         }
       }
     }
     if (outcome == TEAM_MORE) {
+      chip_grad<T, NX, NY, true>(S, sh, y0, tid);
       chip_col_out<T, NY, cs.C, NT>(buf, M0, M1, kx0, h, tid);
       if (tid < 2 * SC && member < cs.ncol) slot_ptr(g.part, SLOT_RR)[tid % 2 * MAX_WG + member * SC + tid / 2] = own;
     }

@@ -39,7 +39,7 @@ struct nf_grid {
   void* x32 = nullptr;  // inner iterate (correction e)
   void* r32 = nullptr;
   void* d32 = nullptr;
-  void* q32 = nullptr;
+  float* gd32 = nullptr;  // gradient of the search direction on the grid (d n)
   void* mix32[3] = {nullptr, nullptr, nullptr};  // 2D uses 2, 3D uses 3
   float* lo = nullptr;  // FP32 copies of m (d n) and r (n)
   double inner_floor = 1e-5;

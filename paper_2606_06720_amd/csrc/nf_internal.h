@@ -160,6 +160,7 @@ struct FluxArgs {
   const void* r;
   double* kslot;
   float* lo;
+  void* gd;  // FP32 loop: gradient of the search direction on the grid, [d][..][Ny][Nx]
 };
 struct DivArgs {
   Geo g;
@@ -175,7 +176,7 @@ struct IterArgs {
   void* xh;
   void* rh;
   void* dh;
-  void* sh;
+  void* sh;  // A d (FP64); in the FP32 loop the gradient of d on the grid (FluxArgs::gd)
 };
 struct SplitArgs {
   Geo g;
@@ -250,8 +251,9 @@ hipError_t launch3_row_r2c(const Geo& g, const double* f, void* out, int schk, h
 hipError_t launch3_row_c2r(const Geo& g, const void* in, double* f, hipStream_t s);
 // lo: FP32 copies of m (3n) then r (n), written when non-null; kbar: write the Kbar partials;
 // tol2: stopping test of the loop (it >= 1)
+// gd: gradient of the search direction on the grid (FP32 loop)
 hipError_t launch3_row_flux(const Geo& g, bool f32, void* G0, void* G1, void* G2, const void* m, const void* r, int it,
-                            int kbar, float* lo, double tol2, hipStream_t s);
+                            int kbar, float* lo, void* gd, double tol2, hipStream_t s);
 hipError_t launch3_row_split(const Geo& g, void* P, void* G0, void* G1, void* G2, const double* m, double* p_out,
                              double c2dt, double gamma, double dt, double relax1, double D2dt, hipStream_t s);
 hipError_t launch3_row_final(const Geo& g, const void* M0, const void* M1, const void* M2, double* m, hipStream_t s);
@@ -363,15 +365,16 @@ hipError_t launch_col_div(const Geo& g, int init, const void* Fx, const void* Fy
                           int nwg_row, hipStream_t s);
 hipError_t launch_col_start(const Geo& g, const void* rh, void* xh, void* Gx, void* Gy, int max_iter, double tol2,
                             hipStream_t s);
-// column pass of the PCG loop (M0, M1: fluxes in, gradient out; sh: A d)
+// column pass of the PCG loop (M0, M1: fluxes in, gradient out; sh: A d, FP64 only)
 hipError_t launch_col_iter64(const Geo& g, void* M0, void* M1, void* xh, void* rh, void* dh, void* sh, int it,
                              int max_iter, hipStream_t s);
 // FP32 instantiations of the PCG-loop passes (g.tw points at the FP32 table;
-// m32/r32 are the FP32 copies written by launch_row_flux)
-hipError_t launch_row_flux32(const Geo& g, void* G0, void* G1, const float* m32, const float* r32, int it,
+// m32/r32 are the FP32 copies written by launch_row_flux, gd the gradient of the
+// search direction on the grid)
+hipError_t launch_row_flux32(const Geo& g, void* G0, void* G1, const float* m32, const float* r32, float* gd, int it,
                              double tol2, hipStream_t s);
-hipError_t launch_col_iter32(const Geo& g, void* M0, void* M1, void* xh, void* rh, void* dh, void* sh, int it,
-                             int max_iter, hipStream_t s);
+hipError_t launch_col_iter32(const Geo& g, void* M0, void* M1, void* xh, void* rh, void* dh, int it, int max_iter,
+                             hipStream_t s);
 // mixed-precision correction start / accumulation (g32: FP32 twiddles)
 hipError_t launch_col_refine_start(const Geo& g32, const void* r64, void* x64, void* x32, void* r32,
                                    void* Gx32, void* Gy32, double tol2, double floor_in, int max_iter, hipStream_t s);

@@ -225,12 +225,14 @@ using Flux3Cfg = typename Flux3<NX, T>::C;
 // in place.  K = m m^T + r I.  In the PCG loop (it >= 0) the pass leaves the
 // partials of delta = n sum g . K g in SLOT_P3 and (it >= 1) takes the stopping
 // decision for the residual of the last z pass (its total was added up by the
-// inverse y pass).
+// inverse y pass).  FP32: the pass keeps the gradient of the search direction, gd
+// (see nf_loop.hpp).
 template <int NX, typename T>
 __global__ void __launch_bounds__((Flux3Cfg<NX, T>::NT)) k3_row_flux(Geo g, cx<T>* G0, cx<T>* G1, cx<T>* G2,
                                                      const T* __restrict__ m, const T* __restrict__ r, int it,
-                                                     int kbar, float* lo, double tol2) {
+                                                     int kbar, float* lo, T* gd, double tol2) {
   using C = Flux3Cfg<NX, T>;
+  constexpr bool GR = grad_rec<T>();
   using V = cx<T>;
   using P = typename vec2<T>::type;
   constexpr int NW = C::NT / 64;
@@ -260,6 +262,11 @@ __global__ void __launch_bounds__((Flux3Cfg<NX, T>::NT)) k3_row_flux(Geo g, cx<T
       return;
     }
   }
+  T bt = 0;
+  P dx[GR ? C::EP : 1], dy[GR ? C::EP : 1], dz[GR ? C::EP : 1];
+  if constexpr (GR) {
+    if (it >= 1) bt = (T)pcg_beta(g.st->rho[it & 1], g.st->rho[(it + 1) & 1], false);
+  }
   P mx[C::EP], my[C::EP], mz[C::EP], rv[C::EP];
   rowP_gload<C>(mx, m, y0, nrow);
   rowP_gload<C>(my, m + n, y0, nrow);
@@ -282,6 +289,14 @@ __global__ void __launch_bounds__((Flux3Cfg<NX, T>::NT)) k3_row_flux(Geo g, cx<T
   rowTP_put_pre<C>(buf, ta, tb, tw, g.twn);
   __syncthreads();
   lds_fft<T, +1, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
+  if constexpr (GR) {
+    // after the transform: held across it they would cost the pass 24 registers
+    if (it >= 1) {
+      rowP_gload<C>(dx, gd, y0, nrow);
+      rowP_gload<C>(dy, gd + n, y0, nrow);
+      rowP_gload<C>(dz, gd + 2 * n, y0, nrow);
+    }
+  }
   double ks[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   double de[1] = {0.0};
 #pragma unroll
@@ -292,7 +307,18 @@ __global__ void __launch_bounds__((Flux3Cfg<NX, T>::NT)) k3_row_flux(Geo g, cx<T
       V* px = buf + rr * C::LS + j;
       V* py = buf + (C::R + rr) * C::LS + j;
       V* pz = buf + (2 * C::R + rr) * C::LS + j;
-      const V gx = *px, gy = *py, gz = *pz;
+      V gx = *px, gy = *py, gz = *pz;
+      if constexpr (GR) {
+        if (it >= 1) {
+          gx = add(gx, scl(mk<T>(dx[i].x, dx[i].y), bt));
+          gy = add(gy, scl(mk<T>(dy[i].x, dy[i].y), bt));
+          gz = add(gz, scl(mk<T>(dz[i].x, dz[i].y), bt));
+        }
+        const size_t o = (size_t)(y0 + rr) * NX + 2 * j;
+        *(V*)(gd + o) = gx;
+        *(V*)(gd + n + o) = gy;
+        *(V*)(gd + 2 * n + o) = gz;
+      }
       const T a0 = mx[i].x * gx.x + my[i].x * gy.x + mz[i].x * gz.x;
       const T a1 = mx[i].y * gx.y + my[i].y * gy.y + mz[i].y * gz.y;
       const V fx = mk<T>(fma(a0, mx[i].x, rv[i].x * gx.x), fma(a1, mx[i].y, rv[i].y * gx.y));
@@ -786,6 +812,7 @@ __global__ void __launch_bounds__((ZIter<NZ, sizeof(cx<T>)>::NT))
   using C = ZIter<NZ, sizeof(cx<T>)>;
   using V = cx<T>;
   constexpr int NW = C::NT / 64;
+  constexpr bool GR = grad_rec<T>();
   DevStatus* st = g.st;
   if (st->conv_at <= it) return;
   tclk_start(g, 2, it + 1);
@@ -819,7 +846,7 @@ __global__ void __launch_bounds__((ZIter<NZ, sizeof(cx<T>)>::NT))
   __syncthreads();
   lds_fft<T, -1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
   // the vectors are loaded after the transform (fewer registers held across it)
-  V rv[C::EP], xv[C::EP], dv[C::EP], sv[C::EP];
+  V rv[C::EP], xv[C::EP], dv[C::EP], sv[GR ? 1 : C::EP];
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
@@ -828,15 +855,10 @@ __global__ void __launch_bounds__((ZIter<NZ, sizeof(cx<T>)>::NT))
     rv[i] = ok ? rh[idx] : vzero<V>();
     xv[i] = ok ? xh[idx] : vzero<V>();
     dv[i] = ok && !first ? dh[idx] : vzero<V>();
-    sv[i] = ok && !first ? sh[idx] : vzero<V>();
+    if constexpr (!GR) sv[i] = ok && !first ? sh[idx] : vzero<V>();
   }
-  double beta = first ? 0.0 : ga / ga_prev;
-  double den = first ? de : de - beta * (ga / al_prev);
-  if (!first && den <= 0.0) {
-    beta = 0.0;
-    den = de;
-  }
-  const double alpha = ga / den;
+  double beta = pcg_beta(ga, ga_prev, first);
+  const double alpha = pcg_alpha<T>(ga, de, al_prev, first, beta);
   const bool bad = !isfinite(ga) || !isfinite(alpha);
   const bool stop = bad || it + 1 >= max_iter || it + 1 >= budget;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -872,13 +894,16 @@ __global__ void __launch_bounds__((ZIter<NZ, sizeof(cx<T>)>::NT))
       V rn = rv[i];
       const V zo = scl(rn, sig);
       const V d = first ? zo : add(zo, scl(dv[i], bt));
-      const V s = first ? w : add(w, scl(sv[i], bt));
+      V s = w;
+      if constexpr (!GR) {
+        if (!first) s = add(w, scl(sv[i], bt));
+      }
       const size_t idx = (size_t)lam0 * NZ + p;
       xh[idx] = add(xv[i], scl(d, a));
       rn = sub(rn, scl(s, a));
       rh[idx] = rn;
       dh[idx] = d;
-      sh[idx] = s;
+      if constexpr (!GR) sh[idx] = s;
       const double wr = (lam < g.ny ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
       ps[0] += wr;
       ps[1] += (double)sig * wr;
@@ -1342,19 +1367,19 @@ hipError_t launch3_row_c2r(const Geo& g, const void* in, double* f, hipStream_t 
   return hipGetLastError();
 }
 hipError_t launch3_row_flux(const Geo& g, bool f32, void* G0, void* G1, void* G2, const void* m, const void* r, int it,
-                            int kbar, float* lo, double tol2, hipStream_t s) {
+                            int kbar, float* lo, void* gd, double tol2, hipStream_t s) {
   const dim3 grid(nwg3_flux(g, f32));
   if (f32) {
     typedef cx<float> cf;
 #define L_(N)                                                                                                     \
   hipLaunchKernelGGL((k3_row_flux<N, float>), grid, dim3(Flux3Cfg<N, float>::NT), 0, s, g, (cf*)G0, (cf*)G1,      \
-                     (cf*)G2, (const float*)m, (const float*)r, it, kbar, (float*)nullptr, tol2)
+                     (cf*)G2, (const float*)m, (const float*)r, it, kbar, (float*)nullptr, (float*)gd, tol2)
     NF3_DISPATCH(g.nx, L_)
 #undef L_
   } else {
 #define L_(N)                                                                                                     \
   hipLaunchKernelGGL((k3_row_flux<N, double>), grid, dim3(Flux3Cfg<N, double>::NT), 0, s, g, (cd*)G0, (cd*)G1,    \
-                     (cd*)G2, (const double*)m, (const double*)r, it, kbar, lo, tol2)
+                     (cd*)G2, (const double*)m, (const double*)r, it, kbar, lo, (double*)nullptr, tol2)
     NF3_DISPATCH(g.nx, L_)
 #undef L_
   }

@@ -13,7 +13,23 @@
 // (FP64) a row pass moves 56 bytes (two gradient fields in, two flux fields
 // out, m, r) and a column pass 96 (two fields in and out; x, r, d, s in and
 // out); the textbook recurrence moved 168 in three passes.  The iterates are
-// those of the textbook recurrence up to rounding.  Measured per iteration, one
+// those of the textbook recurrence up to rounding.
+//
+// The FP32 loop (corrections of the refined solve) does not carry s = A d: the
+// errors of the A z that s adds up, each relative to A z, stay in it, and where
+// |A d| is much smaller they leave a gap between r and b - A x that costs the
+// refinement more FP32 iterations (1024^2, m uniform in [-16, 16], r about 0.1,
+// rtol 1e-10: 1069, with the textbook recurrence 921; log-normal r of sigma 1.5:
+// 1098 and 930; the FP64 loop takes 838 and 807, textbook 839 and 802).  There
+// the row pass keeps the physical gradient of the search direction instead,
+// g_d = grad z + beta g_d, so that A d comes fresh from K g_d and delta =
+// sum g_d . K g_d is the curvature of d: 925 and 945 iterations.  This moves 84
+// instead of 76 bytes per point, which the loops in one launch, where g_d stays
+// on chip, do not notice (1024^2 solve of mild data 2.79 -> 2.78 ms); as launches
+// such a solve takes 60.3 instead of 55.8 ms at 4096^2 and 32.7 instead of 30.6 at
+// 256 x 256 x 128 (three textbook passes: 62.2 and 36.7).
+//
+// Measured per iteration, one
 // handle alone, three passes -> two (MI355X): 256^2 29.5 -> 20.6 us, 1024^2 55
 // -> 43.7 us, 4096^2 FP64 880 -> 770 us.
 #pragma once
@@ -49,7 +65,7 @@ namespace nf {
 template <int NX, typename T, int RV>
 __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
                                               const T* __restrict__ r, int it, double* kslot, int nwg_col,
-                                              double tol2, float* lo) {
+                                              double tol2, float* lo, T* gd) {
   using C = FluxCfg<NX, RV>;
   using V = cx<T>;
   using P = typename vec2<T>::type;
@@ -60,6 +76,7 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
   // and a workgroup with fewer registers shares a compute unit more easily
   // with the passes of concurrent solves.
   constexpr bool EARLY = NX <= 512;
+  constexpr bool GR = grad_rec<T>();
   if (it >= 0 ? g.st->conv_at <= it : g.st->outer_done != 0) return;
   tclk_start(g, 0, it);
   __shared__ V buf[C::NB * C::LS];
@@ -82,17 +99,31 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
   else
     rowT_gload<C>(ta, G0, G1, nullptr, g.ny, y0, nrow);
   P mx[C::EP], my[C::EP], rv[C::EP];
-  if constexpr (EARLY) {
+  // points whose old gradient of d is in registers at a time
+  constexpr int HE = C::EP > 8 ? 8 : C::EP;
+  P dx[GR ? HE : 1], dy[GR ? HE : 1];
+  auto load_grad = [&](int i0) {
+    if constexpr (GR) {
+      if (it >= 1) {
+        rowP_gload_part<C>(dx, gd, i0, y0, nrow);
+        rowP_gload_part<C>(dy, gd + n, i0, y0, nrow);
+      }
+    }
+  };
+  auto load_points = [&]() {
     rowP_gload<C>(mx, m, y0, nrow);
     rowP_gload<C>(my, m + n, y0, nrow);
     rowP_gload<C>(rv, r, y0, nrow);
-  }
+    load_grad(0);
+  };
+  if constexpr (EARLY) load_points();
+  T bt = 0;
   if (it >= 1) {
     const double* part = slot_ptr(g.part, SLOT_RR);
     double s[1] = {0.0};
     for (int i = threadIdx.x; i < nwg_col; i += C::NT) s[0] += part[i];
     wave_sums<1>(s, red);
-    if (blockIdx.x == 0) {
+    if (GR || blockIdx.x == 0) {
       double z[1] = {0.0};
       for (int i = threadIdx.x; i < nwg_col; i += C::NT) z[0] += part[MAX_WG + i];
       wave_sums<1>(z, red + NW);
@@ -117,14 +148,11 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
       return;
     }
     if (lead) g.st->rho[it & 1] = waves_total<NW>(red + NW);
+    if constexpr (GR) bt = (T)pcg_beta(waves_total<NW>(red + NW), g.st->rho[(it + 1) & 1], false);
   }
   if constexpr (!PAIRS) irfft_pre<T, C::H, C::NB, C::LS, C::NT>(buf, tw, g.twn);
   lds_fft<T, +1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
-  if constexpr (!EARLY) {
-    rowP_gload<C>(mx, m, y0, nrow);
-    rowP_gload<C>(my, m + n, y0, nrow);
-    rowP_gload<C>(rv, r, y0, nrow);
-  }
+  if constexpr (!EARLY) load_points();
   if (lo) {
 #pragma unroll
     for (int i = 0; i < C::EP; ++i) {
@@ -144,10 +172,20 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
     const int rr = p / C::H, j = p % C::H;
+    if (i > 0 && i % HE == 0) load_grad(i);
     if (p < C::RH && rr < nrow) {
       V* px = buf + rr * C::LS + j;
       V* py = buf + (C::R + rr) * C::LS + j;
-      const V gx = *px, gy = *py;
+      V gx = *px, gy = *py;
+      if constexpr (GR) {
+        if (it >= 1) {
+          gx = add(gx, scl(mk<T>(dx[i % HE].x, dx[i % HE].y), bt));
+          gy = add(gy, scl(mk<T>(dy[i % HE].x, dy[i % HE].y), bt));
+        }
+        const size_t o = (size_t)(y0 + rr) * NX + 2 * j;
+        *(V*)(gd + o) = gx;
+        *(V*)(gd + n + o) = gy;
+      }
       // K g = (m.g) m + r g at the two grid points packed in this element
       const T a0 = mx[i].x * gx.x + my[i].x * gy.x;
       const T a1 = mx[i].y * gx.y + my[i].y * gy.y;
@@ -191,11 +229,12 @@ __device__ __forceinline__ void row_flux_body(Geo g, cx<T>* G0, cx<T>* G1, const
 // 21% and HBM 50% busy, one phase after the other).
 template <int NX, typename T, int RV>
 __device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
-                                                  const T* __restrict__ r, int it, int nwg_col, double tol2) {
+                                                  const T* __restrict__ r, int it, int nwg_col, double tol2, T* gd) {
   using C = FluxCfg<NX, RV>;
   using V = cx<T>;
   using P = typename vec2<T>::type;
   constexpr int NW = C::NT / 64;
+  constexpr bool GR = grad_rec<T>();
   if (g.st->conv_at <= it) return;
   tclk_start(g, 0, it);
   __shared__ V buf[C::NB * C::LS];
@@ -207,12 +246,13 @@ __device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, c
   const size_t n = (size_t)g.nx * g.ny;
   V ta[RowPairs<C>::ETP], tb[RowPairs<C>::ETP];
   rowTP_gload<C>(ta, tb, G0, nullptr, nullptr, g.ny, y0, nrow);
+  T bt = 0;
   if (it >= 1) {
     const double* part = slot_ptr(g.part, SLOT_RR);
     double s[1] = {0.0};
     for (int i = threadIdx.x; i < nwg_col; i += C::NT) s[0] += part[i];
     wave_sums<1>(s, red);
-    if (blockIdx.x == 0) {
+    if (GR || blockIdx.x == 0) {
       double z[1] = {0.0};
       for (int i = threadIdx.x; i < nwg_col; i += C::NT) z[0] += part[MAX_WG + i];
       wave_sums<1>(z, red + NW);
@@ -234,6 +274,7 @@ __device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, c
       return;
     }
     if (lead) g.st->rho[it & 1] = waves_total<NW>(red + NW);
+    if constexpr (GR) bt = (T)pcg_beta(waves_total<NW>(red + NW), g.st->rho[(it + 1) & 1], false);
   }
   rowTP_gload<C>(ta, tb, G1, nullptr, nullptr, g.ny, y0, nrow);
   lds_fft<T, +1, C::H, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
@@ -253,7 +294,7 @@ __device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, c
   constexpr int HE = C::EP > 4 ? 4 : C::EP;
 #pragma unroll
   for (int i0 = 0; i0 < C::EP; i0 += HE) {
-    P mx[HE], my[HE], rv[HE];
+    P mx[HE], my[HE], rv[HE], dx[GR ? HE : 1], dy[GR ? HE : 1];
 #pragma unroll
     for (int q = 0; q < HE; ++q) {
       const int p = threadIdx.x + (i0 + q) * C::NT;
@@ -263,13 +304,28 @@ __device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, c
       mx[q] = ok ? *(const P*)(m + o) : vzero<P>();
       my[q] = ok ? *(const P*)(m + n + o) : vzero<P>();
       rv[q] = ok ? *(const P*)(r + o) : vzero<P>();
+      if constexpr (GR) {
+        dx[q] = ok && it >= 1 ? *(const P*)(gd + o) : vzero<P>();
+        dy[q] = ok && it >= 1 ? *(const P*)(gd + n + o) : vzero<P>();
+      }
     }
 #pragma unroll
     for (int q = 0; q < HE; ++q) {
       const int p = threadIdx.x + (i0 + q) * C::NT;
       if (p >= C::RH) continue;
       V* py = buf + (p / C::H) * C::LS + p % C::H;
-      const V gxv = gx[i0 + q], gyv = *py;
+      V gxv = gx[i0 + q], gyv = *py;
+      if constexpr (GR) {
+        if (it >= 1) {
+          gxv = add(gxv, scl(mk<T>(dx[q].x, dx[q].y), bt));
+          gyv = add(gyv, scl(mk<T>(dy[q].x, dy[q].y), bt));
+        }
+        const size_t o = (size_t)(y0 + p / C::H) * NX + 2 * (p % C::H);
+        if (p / C::H < nrow) {
+          *(V*)(gd + o) = gxv;
+          *(V*)(gd + n + o) = gyv;
+        }
+      }
       const T a0 = mx[q].x * gxv.x + my[q].x * gyv.x;
       const T a1 = mx[q].y * gxv.y + my[q].y * gyv.y;
       const V fx = mk<T>(fma(a0, mx[q].x, rv[q].x * gxv.x), fma(a1, mx[q].y, rv[q].y * gxv.y));
@@ -298,15 +354,15 @@ __device__ __forceinline__ void row_flux_seq_body(Geo g, cx<T>* G0, cx<T>* G1, c
 template <int NX, typename T, int RV>
 __global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) k_row_flux(Geo g, cx<T>* G0, cx<T>* G1, const T* __restrict__ m,
                                                   const T* __restrict__ r, int it, double* kslot, int nwg_col,
-                                                  double tol2, float* lo) {
-  if constexpr (RV >= RV_SEQ && RV < RV_WIDE) row_flux_seq_body<NX, T, RV>(g, G0, G1, m, r, it, nwg_col, tol2);
-  else row_flux_body<NX, T, RV>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo);
+                                                  double tol2, float* lo, T* gd) {
+  if constexpr (RV >= RV_SEQ && RV < RV_WIDE) row_flux_seq_body<NX, T, RV>(g, G0, G1, m, r, it, nwg_col, tol2, gd);
+  else row_flux_body<NX, T, RV>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo, gd);
 }
 template <int NX, typename T, int RV>
 __global__ void __launch_bounds__((FluxCfg<NX, RV>::NT)) kb_row_flux(const FluxArgs* __restrict__ A, int it, int nwg_col, double tol2) {
   const FluxArgs& a = A[blockIdx.y];
-  if constexpr (RV >= RV_SEQ && RV < RV_WIDE) row_flux_seq_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, nwg_col, tol2);
-  else row_flux_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, (double*)a.kslot, nwg_col, tol2, (float*)a.lo);
+  if constexpr (RV >= RV_SEQ && RV < RV_WIDE) row_flux_seq_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, nwg_col, tol2, (T*)a.gd);
+  else row_flux_body<NX, T, RV>(a.g, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, (double*)a.kslot, nwg_col, tol2, (float*)a.lo, (T*)a.gd);
 }
 
 // ---------------------------------------------------------------- column pass
@@ -330,6 +386,7 @@ __device__ __forceinline__ void col_iter_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>
   // chain of latencies); longer ones after the first transform, which saves
   // the registers they would hold across it.
   constexpr bool EARLY = NY <= 512;
+  constexpr bool GR = grad_rec<T>();
   DevStatus* st = g.st;
   if (st->conv_at <= it) return;
   tclk_start(g, 2, it + 1);
@@ -341,12 +398,12 @@ __device__ __forceinline__ void col_iter_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>
   const bool first = it == 0;
   V tv[C::ET];
   colT_gload<C, 2>(tv, M0, M1, kx0, g.h);
-  V rv[C::EP], xv[C::EP], dv[C::EP], sv[C::EP];
+  V rv[C::EP], xv[C::EP], dv[C::EP], sv[GR ? 1 : C::EP];
   auto load_vectors = [&]() {
     colP_gload<C>(rv, rh, kx0, g.h);
     if (!first) {
       colP_gload<C>(dv, dh, kx0, g.h);
-      colP_gload<C>(sv, sh, kx0, g.h);
+      if constexpr (!GR) colP_gload<C>(sv, sh, kx0, g.h);
     }
     colP_gload<C>(xv, xh, kx0, g.h);
   };
@@ -365,16 +422,8 @@ __device__ __forceinline__ void col_iter_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>
   __syncthreads();
   lds_fft<T, -1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
   if constexpr (!EARLY) load_vectors();
-  const double de = waves_total<NW>(red);
-  double beta = first ? 0.0 : ga / ga_prev;
-  double den = first ? de : de - beta * (ga / al_prev);
-  // rounding at the attainable accuracy can leave no positive curvature in the
-  // recurrence: restart from the steepest descent direction
-  if (!first && den <= 0.0) {
-    beta = 0.0;
-    den = de;
-  }
-  const double alpha = ga / den;
+  double beta = pcg_beta(ga, ga_prev, first);
+  const double alpha = pcg_alpha<T>(ga, waves_total<NW>(red), al_prev, first, beta);
   const bool bad = !isfinite(ga) || !isfinite(alpha);
   const bool stop = bad || it + 1 >= max_iter || it + 1 >= budget;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -407,13 +456,16 @@ __device__ __forceinline__ void col_iter_body(Geo g, cx<T>* M0, cx<T>* M1, cx<T>
       V rn = rv[i];
       const V zo = scl(rn, sig);
       const V d = first ? zo : add(zo, scl(dv[i], bt));
-      const V s = first ? w : add(w, scl(sv[i], bt));
+      V s = w;
+      if constexpr (!GR) {
+        if (!first) s = add(w, scl(sv[i], bt));
+      }
       const size_t idx = (size_t)kx * NY + ky;
       xh[idx] = add(xv[i], scl(d, a));
       rn = sub(rn, scl(s, a));
       rh[idx] = rn;
       dh[idx] = d;
-      sh[idx] = s;
+      if constexpr (!GR) sh[idx] = s;
       const double wr = (kx == 0 ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
       ps[0] += wr;
       ps[1] += (double)sig * wr;
@@ -444,6 +496,7 @@ __device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, c
   using C = DivCfg<NY, CV>;
   using V = cx<T>;
   constexpr int NW = C::NT / 64;
+  constexpr bool GR = grad_rec<T>();
   DevStatus* st = g.st;
   if (st->conv_at <= it) return;
   tclk_start(g, 2, it + 1);
@@ -487,14 +540,8 @@ __device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, c
   __syncthreads();
   put();
   lds_fft<T, -1, NY, C::NB, C::LS, C::NT, C::PLAN>(buf, tw, g.twn);
-  const double de = waves_total<NW>(red);
-  double beta = first ? 0.0 : ga / ga_prev;
-  double den = first ? de : de - beta * (ga / al_prev);
-  if (!first && den <= 0.0) {
-    beta = 0.0;
-    den = de;
-  }
-  const double alpha = ga / den;
+  double beta = pcg_beta(ga, ga_prev, first);
+  const double alpha = pcg_alpha<T>(ga, waves_total<NW>(red), al_prev, first, beta);
   const bool bad = !isfinite(ga) || !isfinite(alpha);
   const bool stop = bad || it + 1 >= max_iter || it + 1 >= budget;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -513,7 +560,7 @@ __device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, c
   constexpr int HE = C::EP > 4 ? 4 : C::EP;
 #pragma unroll
   for (int i0 = 0; i0 < C::EP; i0 += HE) {
-    V rv[HE], xv[HE], dv[HE], sv[HE];
+    V rv[HE], xv[HE], dv[HE], sv[GR ? 1 : HE];
 #pragma unroll
     for (int q = 0; q < HE; ++q) {
       const int p = threadIdx.x + (i0 + q) * C::NT;
@@ -521,7 +568,7 @@ __device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, c
       const size_t idx = (size_t)kx0 * NY + p;
       rv[q] = ok ? rh[idx] : vzero<V>();
       dv[q] = ok && !first ? dh[idx] : vzero<V>();
-      sv[q] = ok && !first ? sh[idx] : vzero<V>();
+      if constexpr (!GR) sv[q] = ok && !first ? sh[idx] : vzero<V>();
       xv[q] = ok ? xh[idx] : vzero<V>();
     }
 #pragma unroll
@@ -538,13 +585,16 @@ __device__ __forceinline__ void col_iter_seq_body(Geo g, cx<T>* M0, cx<T>* M1, c
         V rn = rv[q];
         const V zo = scl(rn, sig);
         const V d = first ? zo : add(zo, scl(dv[q], bt));
-        const V s = first ? wv : add(wv, scl(sv[q], bt));
+        V s = wv;
+        if constexpr (!GR) {
+          if (!first) s = add(wv, scl(sv[q], bt));
+        }
         const size_t idx = (size_t)kx0 * NY + p;
         xh[idx] = add(xv[q], scl(d, a));
         rn = sub(rn, scl(s, a));
         rh[idx] = rn;
         dh[idx] = d;
-        sh[idx] = s;
+        if constexpr (!GR) sh[idx] = s;
         const double wr = (kx == 0 ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
         ps[0] += wr;
         ps[1] += (double)sig * wr;
@@ -600,10 +650,10 @@ __global__ void __launch_bounds__((DivCfg<NY, CV>::NT)) kb_col_iter(const IterAr
 
 template <int NX, typename T, int RV>
 static hipError_t flux_go(const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const T* r, int it, double* kslot,
-                          int nwg_col, double tol2, float* lo, hipStream_t s) {
+                          int nwg_col, double tol2, float* lo, T* gd, hipStream_t s) {
   if constexpr (flux_var_exists<NX, RV, (int)sizeof(cx<T>)>()) {
     hipLaunchKernelGGL((k_row_flux<NX, T, RV>), dim3(row_nwg_var(g, RV)), dim3(FluxCfg<NX, RV>::NT), 0, s, g, G0, G1, m,
-                       r, it, kslot, nwg_col, tol2, lo);
+                       r, it, kslot, nwg_col, tol2, lo, gd);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -611,10 +661,10 @@ static hipError_t flux_go(const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const 
 }
 template <int NX, typename T>
 static hipError_t flux_var(int rv, const Geo& g, cx<T>* G0, cx<T>* G1, const T* m, const T* r, int it,
-                           double* kslot, int nwg_col, double tol2, float* lo, hipStream_t s) {
+                           double* kslot, int nwg_col, double tol2, float* lo, T* gd, hipStream_t s) {
   switch (rv) {
 #define V_(K) \
-  case K: return flux_go<NX, T, K>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo, s);
+  case K: return flux_go<NX, T, K>(g, G0, G1, m, r, it, kslot, nwg_col, tol2, lo, gd, s);
     NF_VARIANTS(V_)
 #undef V_
     default: return hipErrorInvalidValue;

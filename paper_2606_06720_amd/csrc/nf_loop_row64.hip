@@ -10,7 +10,7 @@ hipError_t launch_row_flux(const Geo& g, void* G0, void* G1, const double* m, co
                            double* kslot, double tol2, hipStream_t s, float* lo) {
   const int rv = use_rv(g, false, it);
   const int nwg_col = rr_nwg(g, false);
-#define L_(N) return flux_var<N, double>(rv, g, (cd*)G0, (cd*)G1, m, r, it, kslot, nwg_col, tol2, lo, s)
+#define L_(N) return flux_var<N, double>(rv, g, (cd*)G0, (cd*)G1, m, r, it, kslot, nwg_col, tol2, lo, (double*)nullptr, s)
   NF_DISPATCH(g.nx, L_)
 #undef L_
   return hipErrorInvalidValue;

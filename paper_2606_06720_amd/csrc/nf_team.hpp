@@ -5,7 +5,7 @@
 // the status and partial sums of the pass before, a tile of a few KB through a
 // handful of LDS stages.  Here a team of at most 32 workgroups on ONE XCD, a
 // workgroup per compute unit, runs the iterations of nf_loop.hpp with x, r, d,
-// s, m and r of its columns and rows in registers.  Only the two mixed fields
+// s (FP32: the gradient of d), m and r of its columns and rows on chip.  Only the two mixed fields
 // move between the passes, through that XCD's L2, and the passes meet at a
 // barrier that carries the partial sums.  A store-barrier-load round of 32
 // workgroups takes 0.84 us on one XCD (1.8 us over all XCDs, whose L2s meet in
@@ -192,12 +192,14 @@ __host__ __device__ constexpr int team_ls(int L) { return (lpad_len(L) + 7) / 8 
 
 // What a thread keeps of its workgroup's columns and rows for the whole loop: the
 // vectors, wavenumbers and inverse preconditioner symbol of its spectral
-// elements, and the twiddles of its butterflies and real-transform pairs.  (m
+// elements, in FP32 the gradient of d at its grid-point pairs (see grad_rec), and
+// the twiddles of its butterflies and real-transform pairs.  (m
 // and r of its grid points stay in LDS: in registers they made 512-thread
 // members spill.)
 template <typename T>
 struct TeamState {
-  cx<T> x[TEAM_EP], r[TEAM_EP], d[TEAM_EP], s[TEAM_EP];
+  cx<T> x[TEAM_EP], r[TEAM_EP], d[TEAM_EP], s[grad_rec<T>() ? 1 : TEAM_EP];
+  cx<T> gx[grad_rec<T>() ? TEAM_EP : 1], gy[grad_rec<T>() ? TEAM_EP : 1];
   double xx[TEAM_EP], yy[TEAM_EP], sig[TEAM_EP];
   cx<T> wc[TEAM_TW], wr[TEAM_TW], wp[TEAM_EP];
 };
@@ -226,12 +228,13 @@ __device__ __forceinline__ void team_col_setup(TeamState<T>& st, const Geo& g, c
   team_tw_load<T, NY, NT>(st.wc, (const cx<T>*)g.tw, g.twn, tid);
 }
 
-// Row pass on the R = 1 << lr rows from y0 (see row_flux_body): the return value
-// is this thread's part of sum g . K g.
+// Row pass on the R = 1 << lr rows from y0 (see row_flux_body; bt: beta of the
+// iteration, used in FP32 beyond the first): the return value is this thread's part
+// of sum g . K g.
 template <typename T, int NT, int NX>
 __device__ __forceinline__ double team_row(TeamState<T>& st, cx<T>* buf, const cx<T>* mr, const Geo& g, cx<T>* M0, cx<T>* M1,
                                            __amdgpu_buffer_rsrc_t b0, __amdgpu_buffer_rsrc_t b1, int y0, int lr,
-                                           int tid) {
+                                           T bt, bool first, int tid) {
   using V = cx<T>;
   constexpr int H = NX / 2, NP = (H + 1) / 2, LS = team_ls(H);
   const int R = 1 << lr, ntk = 2 * R * NP, ny = g.ny;
@@ -278,7 +281,15 @@ __device__ __forceinline__ double team_row(TeamState<T>& st, cx<T>* buf, const c
     if (p < R * H) {
       V* px = buf + (p / H) * LS + p % H;
       V* py = px + R * LS;
-      const V gx = *px, gy = *py;
+      V gx = *px, gy = *py;
+      if constexpr (grad_rec<T>()) {
+        if (!first) {
+          gx = add(gx, scl(st.gx[i], bt));
+          gy = add(gy, scl(st.gy[i], bt));
+        }
+        st.gx[i] = gx;
+        st.gy[i] = gy;
+      }
       const V m0 = mr[p], m1 = mr[NT * TEAM_EP + p], rr = mr[2 * NT * TEAM_EP + p];
       const T a0 = m0.x * gx.x + m1.x * gy.x;
       const T a1 = m0.y * gx.y + m1.y * gy.y;
@@ -363,9 +374,13 @@ __device__ __forceinline__ void team_col(TeamState<T>& st, cx<T>* buf, const Geo
       const T sig = (T)st.sig[i];
       const V zo = scl(st.r[i], sig);
       st.d[i] = first ? zo : add(zo, scl(st.d[i], bt));
-      st.s[i] = first ? w : add(w, scl(st.s[i], bt));
       st.x[i] = add(st.x[i], scl(st.d[i], a));
-      const V rn = sub(st.r[i], scl(st.s[i], a));
+      V s = w;
+      if constexpr (!grad_rec<T>()) {
+        if (!first) s = add(w, scl(st.s[i], bt));
+        st.s[i] = s;
+      }
+      const V rn = sub(st.r[i], scl(s, a));
       st.r[i] = rn;
       const double wr = (kx == 0 ? 1.0 : 2.0) * ((double)rn.x * rn.x + (double)rn.y * rn.y);
       ps[0] += wr;
@@ -544,23 +559,40 @@ __device__ __forceinline__ void team_load_mr(cx<T>* mr, const T* __restrict__ m,
     mr[2 * NT * TEAM_EP + p] = ok ? *(const V*)(r + o) : vzero<V>();
   }
 }
+// The gradient of d at a member's grid-point pairs (FP32), from and to its buffer
+// between launches: gd in units of pairs, [2][Ny][Nx/2].
+template <int NT, bool STORE, typename T>
+__device__ __forceinline__ void team_grad(TeamState<T>& st, cx<T>* gd, int h, int ny, int y0, int R) {
+  if constexpr (grad_rec<T>()) {
+#pragma unroll
+    for (int i = 0; i < TEAM_EP; ++i) {
+      const int p = threadIdx.x + i * NT;
+      const bool ok = p < R * h && y0 + p / h < ny;
+      const size_t o = (size_t)y0 * h + p, n2 = (size_t)h * ny;
+      if (STORE) {
+        if (ok) {
+          gd[o] = st.gx[i];
+          gd[n2 + o] = st.gy[i];
+        }
+      } else {
+        st.gx[i] = ok ? gd[o] : vzero<cx<T>>();
+        st.gy[i] = ok ? gd[n2 + o] : vzero<cx<T>>();
+      }
+    }
+  }
+}
 // The scalars of an iteration (see nf_loop.hpp).
 struct TeamStep {
   double alpha, beta;
   bool bad, stop;
 };
+template <typename T>
 __device__ __forceinline__ TeamStep team_step(double ga, double ga_prev, double al_prev, double de, int it, int max_iter,
                                               int budget) {
   TeamStep q;
   const bool first = it == 0;
-  q.beta = first ? 0.0 : ga / ga_prev;
-  double den = first ? de : de - q.beta * (ga / al_prev);
-  // no positive curvature left by rounding: restart from steepest descent
-  if (!first && den <= 0.0) {
-    q.beta = 0.0;
-    den = de;
-  }
-  q.alpha = ga / den;
+  q.beta = pcg_beta(ga, ga_prev, first);
+  q.alpha = pcg_alpha<T>(ga, de, al_prev, first, q.beta);
   q.bad = !isfinite(ga) || !isfinite(q.alpha);
   q.stop = q.bad || it + 1 >= max_iter || it + 1 >= budget;
   return q;
@@ -570,7 +602,8 @@ __device__ __forceinline__ TeamStep team_step(double ga, double ga_prev, double 
 // the residual the last column pass left.
 template <typename T, int NT>
 __device__ __forceinline__ void team_row_phase(const Geo& g, const TeamShape& ts, cx<T>* M0, cx<T>* M1,
-                                               const T* __restrict__ m, const T* __restrict__ r, int it, double tol2) {
+                                               const T* __restrict__ m, const T* __restrict__ r, cx<T>* gd, int it,
+                                               double tol2) {
   using V = cx<T>;
   DevStatus* st = g.st;
   TeamCtl* ctl = (TeamCtl*)g.team;
@@ -581,6 +614,7 @@ __device__ __forceinline__ void team_row_phase(const Geo& g, const TeamShape& ts
   __shared__ double red[2 * (NT / 64) + 4];
   const int role = blockIdx.x, y0 = role << ts.lr;
   const bool lead = role == 0 && threadIdx.x == 0;
+  T bt = 0;
   if (it >= 1) {
     double t[2];
     team_totals<NT, 2>(ctl, TEAM_SET_COL, ts.G, red, t);
@@ -595,6 +629,7 @@ __device__ __forceinline__ void team_row_phase(const Geo& g, const TeamShape& ts
       return;
     }
     if (lead) st->rho[it & 1] = t[1];
+    if constexpr (grad_rec<T>()) bt = (T)pcg_beta(t[1], st->rho[(it + 1) & 1], false);
   }
   double de[1] = {0.0};
   if (y0 < g.ny) {
@@ -602,11 +637,13 @@ __device__ __forceinline__ void team_row_phase(const Geo& g, const TeamShape& ts
     const __amdgpu_buffer_rsrc_t b0 = team_rsrc(M0, bytes), b1 = team_rsrc(M1, bytes);
     TeamState<T> S;
     team_load_mr<NT>(mr, m, r, g.nx, g.ny, y0, 1 << ts.lr);
+    if (it >= 1) team_grad<NT, false>(S, gd, g.h, g.ny, y0, 1 << ts.lr);
 #define M_(N)                                            \
   team_row_setup<T, NT, N>(S, g, ts.lr, threadIdx.x);    \
-  de[0] = team_row<T, NT, N>(S, buf, mr, g, M0, M1, b0, b1, y0, ts.lr, threadIdx.x)
+  de[0] = team_row<T, NT, N>(S, buf, mr, g, M0, M1, b0, b1, y0, ts.lr, bt, it == 0, threadIdx.x)
     NF_TEAM_NX(g.nx, M_)
 #undef M_
+    team_grad<NT, true>(S, gd, g.h, g.ny, y0, 1 << ts.lr);
   }
   de[0] *= (double)g.nx * g.ny;
   team_leave<NT, 1>(ctl, TEAM_SET_ROW, role, de, red);
@@ -636,13 +673,13 @@ __device__ __forceinline__ void team_col_phase(const Geo& g, const TeamShape& ts
     S.x[i] = ok ? xh[base + p] : vzero<V>();
     S.r[i] = ok ? rh[base + p] : vzero<V>();
     S.d[i] = ok && !first ? dh[base + p] : vzero<V>();
-    S.s[i] = ok && !first ? sh[base + p] : vzero<V>();
+    if constexpr (!grad_rec<T>()) S.s[i] = ok && !first ? sh[base + p] : vzero<V>();
   }
   const double K[4] = {st->kbar[0], st->kbar[1], st->kbar[2], 0.0};
   double det[1];
   team_totals<NT, 1>(ctl, TEAM_SET_ROW, ts.G, red, det);
-  const TeamStep q = team_step(st->rho[it & 1], st->rho[(it + 1) & 1], st->alpha[(it + 1) & 1], det[0], it, max_iter,
-                               st->budget);
+  const TeamStep q = team_step<T>(st->rho[it & 1], st->rho[(it + 1) & 1], st->alpha[(it + 1) & 1], det[0], it, max_iter,
+                                  st->budget);
   if (role == 0 && threadIdx.x == 0) {
     st->alpha[it & 1] = q.alpha;
     st->iters = it + 1;
@@ -669,7 +706,7 @@ __device__ __forceinline__ void team_col_phase(const Geo& g, const TeamShape& ts
       xh[base + p] = S.x[i];
       rh[base + p] = S.r[i];
       dh[base + p] = S.d[i];
-      sh[base + p] = S.s[i];
+      if constexpr (!grad_rec<T>()) sh[base + p] = S.s[i];
     }
   }
   team_leave<NT, 2>(ctl, TEAM_SET_COL, role, ps, red);
@@ -677,12 +714,12 @@ __device__ __forceinline__ void team_col_phase(const Geo& g, const TeamShape& ts
 }
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_team_row(FluxArgs a, TeamShape ts, int it, double tol2) {
-  team_row_phase<T, NT>(a.g, ts, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, tol2);
+  team_row_phase<T, NT>(a.g, ts, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, (cx<T>*)a.gd, it, tol2);
 }
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) kb_team_row(const FluxArgs* __restrict__ A, TeamShape ts, int it, double tol2) {
   const FluxArgs& a = A[blockIdx.y];
-  team_row_phase<T, NT>(a.g, ts, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, it, tol2);
+  team_row_phase<T, NT>(a.g, ts, (cx<T>*)a.G0, (cx<T>*)a.G1, (const T*)a.m, (const T*)a.r, (cx<T>*)a.gd, it, tol2);
 }
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_team_col(IterArgs a, TeamShape ts, int it, int max_iter) {
@@ -698,9 +735,10 @@ __global__ void __launch_bounds__(NT) kb_team_col(const IterArgs* __restrict__ A
 
 // Iterations it0 .. it0 + nk - 1 of the loop (fewer if it stops).  On entry the
 // mixed buffers hold the gradient of z and status.rho the scalar gamma of
-// iteration it0 (it0 > 0: status.alpha, d and s of the iteration before).  On
-// exit x, r, d, s are written back and the status records the outcome as the
-// launches of nf_loop.hpp do; status.team tells whether the team formed.
+// iteration it0 (it0 > 0: status.alpha, d and s of the iteration before; sh holds
+// s or, in FP32, the gradient of d).  On exit x, r (and, if iterations are left, d, s)
+// are written back and the status records the outcome as the launches of
+// nf_loop.hpp do; status.team tells whether the team formed.
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<T>* M1, const T* __restrict__ m,
                                              const T* __restrict__ r, cx<T>* xh, cx<T>* rh, cx<T>* dh, cx<T>* sh,
@@ -759,8 +797,9 @@ __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<
       S.x[i] = ok ? xh[base + p] : vzero<V>();
       S.r[i] = ok ? rh[base + p] : vzero<V>();
       S.d[i] = ok && it0 > 0 ? dh[base + p] : vzero<V>();
-      S.s[i] = ok && it0 > 0 ? sh[base + p] : vzero<V>();
+      if constexpr (!grad_rec<T>()) S.s[i] = ok && it0 > 0 ? sh[base + p] : vzero<V>();
     }
+    if (it0 > 0) team_grad<NT, false>(S, sh, h, ny, y0, R);
     team_load_mr<NT>(mr, m, r, nx, ny, y0, R);
   }
   const double K[4] = {st->kbar[0], st->kbar[1], st->kbar[2], 0.0};
@@ -786,8 +825,9 @@ __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<
     int t = tid;
     asm volatile("" : "+v"(t));
     double de[1] = {0.0}, det[1];
+    const T bt = grad_rec<T>() ? (T)pcg_beta(ga, ga_prev, it == 0) : (T)0;
     if (has_rows) {
-#define M_(N) de[0] = team_row<T, NT, N>(S, buf, mr, g, M0, M1, b0, b1, y0, ts.lr, t)
+#define M_(N) de[0] = team_row<T, NT, N>(S, buf, mr, g, M0, M1, b0, b1, y0, ts.lr, bt, it == 0, t)
       NF_TEAM_NX(nx, M_)
 #undef M_
     }
@@ -796,7 +836,7 @@ __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<
       outcome = TEAM_LOST;
       break;
     }
-    const TeamStep q = team_step(ga, ga_prev, al_prev, det[0], it, max_iter, budget);
+    const TeamStep q = team_step<T>(ga, ga_prev, al_prev, det[0], it, max_iter, budget);
     bad = q.bad;
     double ps[2] = {0.0, 0.0}, pt[2];
     if (nc > 0) {
@@ -835,10 +875,11 @@ __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<
         rh[base + p] = S.r[i];
         if (outcome == TEAM_MORE) {
           dh[base + p] = S.d[i];
-          sh[base + p] = S.s[i];
+          if constexpr (!grad_rec<T>()) sh[base + p] = S.s[i];
         }
       }
     }
+    if (outcome == TEAM_MORE) team_grad<NT, true>(S, sh, h, ny, y0, R);
   }
   if (role == 0 && tid == 0) {
     st->iters = it;

@@ -413,6 +413,18 @@ __device__ __forceinline__ void rowP_gload(P (&v)[(C::EP)], const S* __restrict_
   }
 }
 
+// N values of it from the i0-th on
+template <class C, int N, typename P, typename S>
+__device__ __forceinline__ void rowP_gload_part(P (&v)[N], const S* __restrict__ f, int i0, int y0, int nrow) {
+  constexpr int NX = 2 * C::H;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int p = threadIdx.x + (i0 + i) * C::NT;
+    const int rr = p / C::H, j = p % C::H;
+    v[i] = (i0 + i < C::EP && p < C::RH && rr < nrow) ? *(const P*)(f + (size_t)(y0 + rr) * NX + 2 * j) : vzero<P>();
+  }
+}
+
 // ---------------------------------------------------------------- column images
 // C is a ColCfg: C::NYv lines of C::C columns per field.
 template <class C, int NFL, typename V>
@@ -486,6 +498,26 @@ __device__ __forceinline__ void write_partials(double* slot, const double* v, in
 __device__ __forceinline__ double precond_symbol_inv(const double* K, double xx, double yy) {
   const double s = K[0] * xx * xx + 2.0 * K[1] * xx * yy + K[2] * yy * yy;
   return s > 0.0 ? 1.0 / s : 0.0;
+}
+
+// Scalars of an iteration of the PCG loop (nf_loop.hpp): beta from gamma of this
+// and the last iteration, alpha from gamma and delta.  Where the loop carries A d
+// (FP64), delta = <z, A z> and the curvature of d follows from it; rounding at the
+// attainable accuracy can leave none that is positive: the loop then restarts from
+// the steepest descent direction.  Where it carries the gradient of d (FP32),
+// delta is the curvature of d itself.
+template <typename T>
+constexpr bool grad_rec() { return sizeof(T) == 4; }
+__device__ __forceinline__ double pcg_beta(double ga, double ga_prev, bool first) { return first ? 0.0 : ga / ga_prev; }
+template <typename T>
+__device__ __forceinline__ double pcg_alpha(double ga, double de, double al_prev, bool first, double& beta) {
+  if constexpr (grad_rec<T>()) return ga / de;
+  double den = first ? de : de - beta * (ga / al_prev);
+  if (!first && den <= 0.0) {
+    beta = 0.0;
+    den = de;
+  }
+  return ga / den;
 }
 
 // Switch over the transform lengths of the 2D passes.

@@ -118,8 +118,9 @@ hipError_t time_pass(const std::vector<hipStream_t>& ss, hipEvent_t e0, hipEvent
   return hipSuccess;
 }
 
-// Buffers one stream of the tuning works on: two mixed fields, the four PCG
-// vectors and stand-ins for m and r (3 n values).
+// Buffers one stream of the tuning works on: two mixed fields, the PCG vectors
+// (Q: A d, or the gradient of d, 2 n values, in FP32) and stand-ins for m and r
+// (3 n values).
 struct TuneBufs {
   void* M0;
   void* M1;
@@ -166,7 +167,7 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
   // copies, so that concurrent launches touch distinct memory
   ss[0] = s;
   bufs[0] = {f32 ? g->mix32[0] : g->mix[0], f32 ? g->mix32[1] : g->mix[1], f32 ? g->x32 : g->xh,
-             f32 ? g->r32 : g->rh,          f32 ? g->d32 : g->dh,          f32 ? g->q32 : g->qh,
+             f32 ? g->r32 : g->rh,          f32 ? g->d32 : g->dh,          f32 ? (void*)g->gd32 : g->qh,
              f32 ? (void*)g->lo : nullptr};
   if (!f32) {
     void* q = nullptr;
@@ -187,10 +188,10 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
   }
   for (int k = 1; k < nstreams; ++k) {
     void* q = nullptr;
-    TCHK(hipMalloc(&q, 6 * spec + 3 * n * es));
+    TCHK(hipMalloc(&q, 7 * spec + 3 * n * es));
     owned.push_back(q);
     char* c = (char*)q;
-    bufs[k] = {c, c + spec, c + 2 * spec, c + 3 * spec, c + 4 * spec, c + 5 * spec, c + 6 * spec};
+    bufs[k] = {c, c + spec, c + 2 * spec, c + 3 * spec, c + 4 * spec, c + 5 * spec, c + 7 * spec};
     TCHK(hipStreamCreateWithFlags(&ss[k], hipStreamNonBlocking));
     TCHK(hipEventCreateWithFlags(&ej[k], hipEventDisableTiming));
   }
@@ -220,8 +221,8 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
           G.var_flux[k32] = v;
           TCHK(time_pass(ss, e0, e1, ej, [&](int k) {
             const TuneBufs& b = bufs[k];
-            return f32 ? launch_row_flux32(G, b.M0, b.M1, (const float*)b.mr, (const float*)b.mr + 2 * n, 0, 0.0,
-                                           ss[k])
+            return f32 ? launch_row_flux32(G, b.M0, b.M1, (const float*)b.mr, (const float*)b.mr + 2 * n,
+                                           (float*)b.Q, 0, 0.0, ss[k])
                        : launch_row_flux(G, b.M0, b.M1, (const double*)b.mr, (const double*)b.mr + 2 * n, 0,
                                          nullptr, 0.0, ss[k]);
           }, &ms, clear, nclear));
@@ -229,7 +230,7 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
           G.var_upd[k32] = v;
           TCHK(time_pass(ss, e0, e1, ej, [&](int k) {
             const TuneBufs& b = bufs[k];
-            return f32 ? launch_col_iter32(G, b.M0, b.M1, b.X, b.R, b.D, b.Q, 1, INT_MAX, ss[k])
+            return f32 ? launch_col_iter32(G, b.M0, b.M1, b.X, b.R, b.D, 1, INT_MAX, ss[k])
                        : launch_col_iter64(G, b.M0, b.M1, b.X, b.R, b.D, b.Q, 1, INT_MAX, ss[k]);
           }, &ms, clear, nclear));
         }
