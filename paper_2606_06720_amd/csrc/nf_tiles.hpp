@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <type_traits>
 
 #include "nf_fft.hpp"
@@ -505,12 +506,17 @@ __device__ __forceinline__ double precond_symbol_inv(const double* K, double xx,
 // (FP64), delta = <z, A z> and the curvature of d follows from it; rounding at the
 // attainable accuracy can leave none that is positive: the loop then restarts from
 // the steepest descent direction.  Where it carries the gradient of d (FP32),
-// delta is the curvature of d itself.
+// delta is the curvature of d itself.  Once gamma has left the normal range (an
+// rtol of 0 and thousands of iterations, or a tiny S) its ratios mean nothing: the
+// iterate stays as it is.
 template <typename T>
 constexpr bool grad_rec() { return sizeof(T) == 4; }
-__device__ __forceinline__ double pcg_beta(double ga, double ga_prev, bool first) { return first ? 0.0 : ga / ga_prev; }
+__device__ __forceinline__ double pcg_beta(double ga, double ga_prev, bool first) {
+  return first || ga < DBL_MIN ? 0.0 : ga / ga_prev;
+}
 template <typename T>
 __device__ __forceinline__ double pcg_alpha(double ga, double de, double al_prev, bool first, double& beta) {
+  if (ga < DBL_MIN) return 0.0;
   if constexpr (grad_rec<T>()) return ga / de;
   double den = first ? de : de - beta * (ga / al_prev);
   if (!first && den <= 0.0) {
