@@ -414,6 +414,30 @@ int nf_tuning(const nf_grid *g, nf_tuning_info *out);
 int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
 
 /*
+ * One-launch PCG loops.  2D grids of up to 65536 points with Nx <= 2048 and Ny <= 1024
+ * run the loop of a solve as one launch by a team of up to 32 workgroups on one XCD,
+ * larger ones as described at nf_tuning by a team of up to 256 workgroups over the
+ * chip.  A team whose workgroups do not all become resident within 5 ms gives up and
+ * the loop goes on as launches of the same passes: the results are bitwise the same.
+ * nf_team: how the loops of a handle have run (a refined solve runs one loop per
+ *   correction).  NF_EINVAL for NULL.
+ * nf_team_force: conditions for tests of the paths above, which ordinary use does
+ *   not reach at will.  NF_FORCE_MISS: of the handle's team launches from now on,
+ *   those with index at .. at + count - 1 (from 0) have too few workgroups, so that
+ *   they give up.  NF_EINVAL for another `what` or negative numbers.
+ */
+typedef struct {
+  int kind;            /* 0: no team, 1: on one XCD, 2: over the chip */
+  int members;         /* workgroups of the team */
+  int64_t formed;      /* team launches that formed */
+  int64_t missed;      /* team launches that gave up */
+  int64_t as_launches; /* loops that ran as launches without a try */
+} nf_team_info;
+enum { NF_FORCE_MISS = 0 };
+int nf_team(const nf_grid *g, nf_team_info *out);
+int nf_team_force(nf_grid *g, int what, int at, int count);
+
+/*
  * Kernel timing: nf_time_kernel(g, k) makes the PCG-loop kernel k (NF_KERNEL_*;
  * COL_DIV and COL_UPDATE are the same pass)
  * stamp, for every loop iteration, the start of its first and the end of its

@@ -258,16 +258,20 @@ int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_it
     go.nk = max_iter - *it < TEAM_CHUNK ? max_iter - *it : TEAM_CHUNK;
     go.ts.epoch = g->team_shape.epoch;
     if (*it > 0) LCHK(g, launch_team_reset(go.a.g, s));
+    go.miss = g->force_miss_count > 0 && g->force_miss_at-- <= 0;
+    if (go.miss) --g->force_miss_count;
     LCHK(g, g->chip_loop ? launch_chip(f32, go, s) : launch_team(f32, go, s));
     g->team_shape.epoch += 2 * (unsigned)go.nk + 4;
     int rc = read_status(g, fin);
     if (rc) return rc;
+    if (fin->team != TEAM_NONE) ++g->team_formed;
     if (fin->conv_at != INT_MAX) {
       *done = true;
       return NF_OK;
     }
     if (fin->team == TEAM_LOST) return fail(g, NF_EDEVICE, "a member of the team was lost");
     if (fin->team != TEAM_MORE) {
+      ++g->team_gave_up;
       if (++g->team_missed >= 2) g->team_loop = g->chip_loop = false;
       return NF_OK;
     }
@@ -298,6 +302,8 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
     bool done = false;
     rc = team_loop(g, f32, m, r, max_iter, tol2, fin, &it, &done);
     if (rc || done) return rc;
+  } else {
+    ++g->team_untried;
   }
   int slot = 0, pending = -1;
   bool first_chunk = true, stopped = false;
@@ -887,6 +893,25 @@ int nf_set_inner_tolerance(nf_grid* g, double floor_rtol) {
   if (!g) return NF_EINVAL;
   if (!(floor_rtol > 0.0 && floor_rtol < 0.5)) return fail(g, NF_EINVAL, "inner tolerance must lie in (0, 0.5)");
   g->inner_floor = floor_rtol;
+  return NF_OK;
+}
+
+int nf_team(const nf_grid* g, nf_team_info* out) {
+  if (!g || !out) return NF_EINVAL;
+  const bool chip = !g->team_on && g->geo.wide >= 0;
+  out->kind = g->team_on ? 1 : (chip ? 2 : 0);
+  out->members = g->team_on ? g->team_shape.G : (chip ? g->chip_shape.G : 0);
+  out->formed = g->team_formed;
+  out->missed = g->team_gave_up;
+  out->as_launches = g->team_untried;
+  return NF_OK;
+}
+
+int nf_team_force(nf_grid* g, int what, int at, int count) {
+  if (!g) return NF_EINVAL;
+  if (what != NF_FORCE_MISS || at < 0 || count < 0) return fail(g, NF_EINVAL, "unknown condition or negative number");
+  g->force_miss_at = at;
+  g->force_miss_count = count;
   return NF_OK;
 }
 

@@ -761,7 +761,7 @@ static hipError_t chip_pair(const TeamGo& go, hipStream_t s) {
     typedef cx<T> V;
     const FluxArgs& f = go.f;
     const IterArgs& a = go.a;
-    hipLaunchKernelGGL((k_chip<T, NX, NY>), dim3(chip_split(NX, NY).G), dim3(chip_threads(NX, NY)), 0, s, a.g, go.ts.epoch,
+    hipLaunchKernelGGL((k_chip<T, NX, NY>), dim3(chip_split(NX, NY).G - (go.miss ? 1 : 0)), dim3(chip_threads(NX, NY)), 0, s, a.g, go.ts.epoch,
                        (V*)a.M0, (V*)a.M1, (const T*)f.m, (const T*)f.r, (V*)a.xh, (V*)a.rh, (V*)a.dh, (V*)a.sh, go.it,
                        go.nk, go.max_iter, go.tol2);
     return hipGetLastError();

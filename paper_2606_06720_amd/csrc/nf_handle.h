@@ -68,6 +68,8 @@ struct nf_grid {
   nf::TeamShape team_shape{};
   bool team_on = false, team_loop = false;
   int team_missed = 0;
+  int64_t team_formed = 0, team_gave_up = 0, team_untried = 0;  // nf_team
+  int force_miss_at = 0, force_miss_count = 0;                  // nf_team_force: team launches from now on
   // team over the chip (nf_chip.hpp): whether the loop runs as one, and its split
   bool chip_loop = false;
   nf::ChipShape chip_shape{};

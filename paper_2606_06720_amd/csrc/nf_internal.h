@@ -326,6 +326,7 @@ bool team_shape(const Geo& g, TeamShape* ts);
 hipError_t launch_team_reset(const Geo& g, hipStream_t s);
 struct TeamGo {
   enum { LOOP, ROW, COL, ROWS, COLS } what;  // the team; a pass as a launch, for one or `count` instances
+  bool miss;                                 // LOOP: with too few workgroups to form (tests)
   TeamShape ts;
   int it, nk, max_iter;
   double tol2;

@@ -834,6 +834,7 @@ __device__ __forceinline__ void col_refine_start_body(Geo g, const cd* __restric
       st->converged = conv ? 1 : 0;
       st->iters = 0;
       st->outer_done = 1;
+      st->team = TEAM_NONE;
     }
     if (zero_b) {
 #pragma unroll

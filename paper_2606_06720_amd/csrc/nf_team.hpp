@@ -907,7 +907,7 @@ static hipError_t team_launch(const TeamGo& go, hipStream_t s) {
   const IterArgs& a = go.a;
   switch (go.what) {
     case TeamGo::LOOP:
-      hipLaunchKernelGGL((k_team<T, NT>), dim3(8 * (ts.G + 4)), dim3(NT), 0, s, a.g, ts, (V*)a.M0, (V*)a.M1,
+      hipLaunchKernelGGL((k_team<T, NT>), dim3(go.miss ? ts.G - 1 : 8 * (ts.G + 4)), dim3(NT), 0, s, a.g, ts, (V*)a.M0, (V*)a.M1,
                          (const T*)f.m, (const T*)f.r, (V*)a.xh, (V*)a.rh, (V*)a.dh, (V*)a.sh, go.it, go.nk, go.max_iter,
                          go.tol2);
       break;

@@ -35,6 +35,7 @@ NF_STOP_ERROR = 3
 NF_KERNEL_ROW_FLUX = 0
 NF_KERNEL_COL_DIV = 1
 NF_KERNEL_COL_UPDATE = 2
+NF_FORCE_MISS = 0
 
 _CODES = {
     NF_EINVAL: "NF_EINVAL",
@@ -80,6 +81,11 @@ class nf_tuning_info(ctypes.Structure):
                 ("us_default", ctypes.c_double * 3), ("flux_threads", ctypes.c_int)]
 
 
+class nf_team_info(ctypes.Structure):
+    _fields_ = [("kind", ctypes.c_int), ("members", ctypes.c_int), ("formed", ctypes.c_int64),
+                ("missed", ctypes.c_int64), ("as_launches", ctypes.c_int64)]
+
+
 def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError("libnf.so is not built (run __graft_entry__.build()): " + LIB_PATH)
@@ -112,6 +118,8 @@ def _load():
     lib.nf_set_autotune.argtypes = [ctypes.c_int]
     lib.nf_tuning.argtypes = [vp, ctypes.POINTER(nf_tuning_info)]
     lib.nf_set_tiles.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    lib.nf_team.argtypes = [vp, ctypes.POINTER(nf_team_info)]
+    lib.nf_team_force.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.nf_time_kernel.argtypes = [vp, ctypes.c_int]
     lib.nf_time_kernel_read.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]
     lib.nf_batch_create.argtypes = [ctypes.POINTER(vp), ctypes.c_int, i64p, ctypes.POINTER(ctypes.c_double),
@@ -134,7 +142,7 @@ def _load():
               "nf_energy", "nf_step_adjoint", "nf_transform_forward", "nf_transform_inverse", "nf_apply_operator",
               "nf_gradient", "nf_time_kernel",
               "nf_time_kernel_read", "nf_set_inner_tolerance", "nf_set_autotune", "nf_tuning", "nf_set_tiles",
-              "nf_batch_create", "nf_batch_destroy",
+              "nf_team", "nf_team_force", "nf_batch_create", "nf_batch_destroy",
               "nf_batch_set_stream", "nf_batch_run", "nf_batch_set_partitions", "nf_batch_partitions",
               "nf_batch_set_graphs"):
         getattr(lib, f).restype = ctypes.c_int
@@ -331,6 +339,16 @@ class Grid:
     def set_tiles(self, flux_var=-1, div_var=-1, update_var=-1):
         """nf_set_tiles: fix this handle's tile variants (operator middle 0..8, others 0..11; -1 keeps)."""
         self._check(_lib.nf_set_tiles(self._h, int(flux_var), int(div_var), int(update_var)))
+
+    def team(self):
+        """nf_team: how the PCG loops of this handle have run, as a dict."""
+        t = nf_team_info()
+        self._check(_lib.nf_team(self._h, ctypes.byref(t)))
+        return {k: int(getattr(t, k)) for k, _ in nf_team_info._fields_}
+
+    def team_force(self, what, at, count=1):
+        """nf_team_force: forced conditions of the one-launch loops (for tests)."""
+        self._check(_lib.nf_team_force(self._h, int(what), int(at), int(count)))
 
     def set_inner_tolerance(self, floor_rtol):
         self._check(_lib.nf_set_inner_tolerance(self._h, float(floor_rtol)))

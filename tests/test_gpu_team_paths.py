@@ -1,0 +1,117 @@
+"""Which form of the PCG loop runs, and the ways between the forms.
+
+The tests of the one-launch loops compare them bitwise with the same passes as launches;
+here it is the handle's own record that says that a team formed for the shapes that
+have one (and that none is tried for shapes outside the limits).  Formation that gives
+up is forced from the host by a launch with too few workgroups, at the start of a
+loop and where a loop of more than 4096 iterations goes on from one team launch to the
+next.  A handle that times a kernel runs launches only and gives the expected bits."""
+
+import numpy as np
+import pytest
+
+pytestmark = [pytest.mark.gpu, pytest.mark.filterwarnings("ignore::RuntimeWarning")]
+
+CHUNK = 4096  # iterations per team launch
+
+
+def fields(n, seed, a=1.0, r0=0.1):
+    import torch
+
+    rng = np.random.default_rng(seed)
+    shape = n[::-1]
+    m = rng.uniform(-a, a, (2,) + shape)
+    r = r0 * rng.uniform(0.5, 1.5, shape)
+    S = rng.standard_normal(shape)
+    S -= S.mean()
+    return tuple(torch.from_numpy(v).to("cuda:0") for v in (m, r, S))
+
+
+def box(n):
+    return tuple(v / min(n) for v in n)
+
+
+def solve(g, m, r, S, **kw):
+    import torch
+
+    p = torch.zeros_like(r)
+    rc, info = g.pressure_solve(m, r, S, p, allow_notconv=True, **kw)
+    return info, p
+
+
+XCD = [(8, 8), (50, 50), (64, 32), (200, 200), (256, 256), (2048, 32), (64, 1024)]
+CHIP = [(512, 256), (200, 400), (2048, 64), (128, 1024), (512, 512), (1600, 400), (800, 800), (1024, 1024),
+        (256, 400)]
+NONE = [(4096, 16), (32, 2048), (2048, 1024), (100, 800)]
+
+
+@pytest.mark.parametrize("n", XCD + CHIP + NONE)
+def test_form_of_the_loop(n):
+    from paper_2606_06720_amd import nf as NF
+
+    kind = 1 if n in XCD else (2 if n in CHIP else 0)
+    m, r, S = fields(n, 5)
+    for dtype in (NF.NF_F64, NF.NF_F32_REFINED):
+        with NF.Grid(n, box(n), dtype=dtype) as g:
+            assert g.team()["kind"] == kind and (g.team()["members"] > 0) == (kind > 0)
+            info, p = solve(g, m, r, S, rtol=1e-10)
+            assert info.converged
+            t = g.team()
+            assert t["missed"] == 0
+            if kind:
+                assert t["formed"] >= 1
+            else:
+                assert t["formed"] == 0 and t["as_launches"] >= 1
+            g.time_kernel(0)
+            solve(g, m, r, S, rtol=1e-10)
+            assert g.team()["formed"] == t["formed"]  # timed handles run launches
+
+
+@pytest.mark.parametrize("n", [(64, 64), (512, 256), (1024, 1024)])
+def test_formation_that_gives_up(n):
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    m, r, S = fields(n, 6)
+    for dtype in (NF.NF_F64, NF.NF_F32_REFINED):
+        with NF.Grid(n, box(n), dtype=dtype) as g:
+            _, want = solve(g, m, r, S, rtol=1e-10)
+            formed = g.team()["formed"]
+            g.team_force(NF.NF_FORCE_MISS, 0)
+            _, p = solve(g, m, r, S, rtol=1e-10)
+            assert g.team()["missed"] == 1
+            assert torch.equal(p, want)
+            _, p = solve(g, m, r, S, rtol=1e-10)
+            assert g.team()["missed"] == 1 and g.team()["formed"] > formed
+            assert torch.equal(p, want)
+            with pytest.raises(NF.NfError):
+                g.team_force(9, 0)
+
+
+@pytest.mark.parametrize("n", [(64, 64), (512, 256), (1024, 1024)])
+def test_loops_of_more_than_one_launch(n):
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    # ill-conditioned, so that the loop reaches its limit; in FP32 the first correction
+    # does if it is asked for a reduction that it cannot have by then
+    m, r, S = fields(n, 41, a=100.0, r0=1e-7)
+    kw = dict(rtol=1e-14, max_iter=CHUNK + 200)
+    for dtype in (NF.NF_F64, NF.NF_F32_REFINED):
+        with NF.Grid(n, box(n), dtype=dtype) as g:
+            if dtype == NF.NF_F32_REFINED:
+                g.set_inner_tolerance(1e-30)
+            g.time_kernel(0)
+            info, want = solve(g, m, r, S, **kw)
+            assert info.iters == kw["max_iter"] and g.team()["formed"] == 0
+            g.time_kernel(-1)
+            info, p = solve(g, m, r, S, **kw)
+            assert info.iters == kw["max_iter"] and g.team()["formed"] == 2
+            assert torch.equal(p, want)
+            # the second launch of the loop gives up: launches go on from its state
+            g.team_force(NF.NF_FORCE_MISS, 1)
+            info, p = solve(g, m, r, S, **kw)
+            assert info.iters == kw["max_iter"] and g.team()["formed"] == 3 and g.team()["missed"] == 1
+            assert torch.equal(p, want)
