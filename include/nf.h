@@ -419,6 +419,8 @@ int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
  * larger ones as described at nf_tuning by a team of up to 256 workgroups over the
  * chip.  A team whose workgroups do not all become resident within 5 ms gives up and
  * the loop goes on as launches of the same passes: the results are bitwise the same.
+ * After two such misses in a row the handle's next 64 loops run as launches before
+ * a team is tried again (twice as many after the next miss, up to 4096).
  * nf_team: how the loops of a handle have run (a refined solve runs one loop per
  *   correction).  NF_EINVAL for NULL.
  * nf_team_force: conditions for tests of the paths above, which ordinary use does
@@ -432,6 +434,7 @@ typedef struct {
   int64_t formed;      /* team launches that formed */
   int64_t missed;      /* team launches that gave up */
   int64_t as_launches; /* loops that ran as launches without a try */
+  int pause;           /* loops left before the next try, after misses */
 } nf_team_info;
 enum { NF_FORCE_MISS = 0 };
 int nf_team(const nf_grid *g, nf_team_info *out);

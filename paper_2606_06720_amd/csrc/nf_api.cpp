@@ -264,7 +264,11 @@ int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_it
     g->team_shape.epoch += 2 * (unsigned)go.nk + 4;
     int rc = read_status(g, fin);
     if (rc) return rc;
-    if (fin->team != TEAM_NONE) ++g->team_formed;
+    if (fin->team != TEAM_NONE) {
+      ++g->team_formed;
+      g->team_missed = 0;
+      if (g->team_pause > TEAM_PAUSE_MIN) --g->team_pause;
+    }
     if (fin->conv_at != INT_MAX) {
       *done = true;
       return NF_OK;
@@ -272,10 +276,12 @@ int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_it
     if (fin->team == TEAM_LOST) return fail(g, NF_EDEVICE, "a member of the team was lost");
     if (fin->team != TEAM_MORE) {
       ++g->team_gave_up;
-      if (++g->team_missed >= 2) g->team_loop = g->chip_loop = false;
+      if (++g->team_missed >= 2) {
+        g->team_skip = g->team_pause;
+        g->team_pause = 2 * g->team_pause < TEAM_PAUSE_MAX ? 2 * g->team_pause : TEAM_PAUSE_MAX;
+      }
       return NF_OK;
     }
-    g->team_missed = 0;
     *it += go.nk;
   }
   return NF_OK;
@@ -298,7 +304,12 @@ int pcg_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_ite
   TeamGo go{};
   if (g->team_on) go = team_args(g, f32, m, r, max_iter, tol2);
   LoopCount count(g->device);
-  if ((g->team_loop || (g->chip_loop && count.alone)) && g->timed < 0) {
+  bool team = (g->team_loop || (g->chip_loop && count.alone)) && g->timed < 0;
+  if (team && g->team_skip > 0) {
+    --g->team_skip;
+    team = false;
+  }
+  if (team) {
     bool done = false;
     rc = team_loop(g, f32, m, r, max_iter, tol2, fin, &it, &done);
     if (rc || done) return rc;
@@ -904,6 +915,7 @@ int nf_team(const nf_grid* g, nf_team_info* out) {
   out->formed = g->team_formed;
   out->missed = g->team_gave_up;
   out->as_launches = g->team_untried;
+  out->pause = g->team_skip;
   return NF_OK;
 }
 

@@ -64,10 +64,11 @@ struct nf_grid {
   double tune_us[3] = {0.0, 0.0, 0.0};
   double tune_us_default[3] = {0.0, 0.0, 0.0};
   // small-grid team (nf_team.hpp): its split, whether the grid uses its passes,
-  // whether as one launch (two launches that did not form switch to passes)
+  // whether as one launch; misses in a row, loops to run as launches before the
+  // next try, length of the next such pause
   nf::TeamShape team_shape{};
   bool team_on = false, team_loop = false;
-  int team_missed = 0;
+  int team_missed = 0, team_skip = 0, team_pause = nf::TEAM_PAUSE_MIN;
   int64_t team_formed = 0, team_gave_up = 0, team_untried = 0;  // nf_team
   int force_miss_at = 0, force_miss_count = 0;                  // nf_team_force: team launches from now on
   // team over the chip (nf_chip.hpp): whether the loop runs as one, and its split

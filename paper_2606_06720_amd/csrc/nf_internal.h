@@ -38,6 +38,11 @@ enum { TEAM_OPEN = 0, TEAM_GO = 1, TEAM_ABORT = 2 };
 enum {
   TEAM_MAX = 32,      // members at most: the compute units of an XCD
   TEAM_CHUNK = 4096,  // iterations per team launch at most
+  // Loops as launches after two misses in a row: a miss costs 5 ms, a team saves
+  // about a millisecond per loop, so that tries that keep failing cost a few
+  // per cent at first and next to nothing later
+  TEAM_PAUSE_MIN = 64,
+  TEAM_PAUSE_MAX = 4096,
 };
 // Device memory of a handle's team: formation and the barrier's slots, two sets
 // of two 16-byte entries (partial sum, epoch) per member.

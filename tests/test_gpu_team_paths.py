@@ -115,3 +115,39 @@ def test_loops_of_more_than_one_launch(n):
             info, p = solve(g, m, r, S, **kw)
             assert info.iters == kw["max_iter"] and g.team()["formed"] == 3 and g.team()["missed"] == 1
             assert torch.equal(p, want)
+
+
+@pytest.mark.parametrize("n", [(64, 64), (512, 256)])
+def test_misses_do_not_end_the_use_of_teams(n):
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    m, r, S = fields(n, 8)
+    with NF.Grid(n, box(n)) as g:
+
+        def go(miss=False):
+            if miss:
+                g.team_force(NF.NF_FORCE_MISS, 0)
+            before = g.team()
+            _, p = solve(g, m, r, S, rtol=1e-10)
+            return {k: v - before[k] for k, v in g.team().items()}, p
+
+        did, want = go()
+        assert did["formed"] == 1
+        # misses with a formed team between them: the next loop is tried again
+        for _ in range(3):
+            did, p = go(miss=True)
+            assert did["missed"] == 1 and torch.equal(p, want)
+            did, p = go()
+            assert did["formed"] == 1 and torch.equal(p, want)
+        # two in a row: 64 loops as launches, then teams again
+        go(miss=True)
+        go(miss=True)
+        assert g.team()["pause"] == 64
+        for _ in range(64):
+            did, p = go()
+            assert did["as_launches"] == 1 and did["formed"] == 0
+        assert torch.equal(p, want)
+        did, p = go()
+        assert did["formed"] == 1 and torch.equal(p, want)
