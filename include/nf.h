@@ -362,7 +362,7 @@ const char *nf_batch_last_error(const nf_batch *b);
  * inner products only.
  * Grids of 65537 to 1048576 points whose tiles divide them (all powers of two with
  * Nx from 128 to 2048 and Ny from 64 to 1024 among them) run the loop as one launch
- * if no other solve is in progress on the device, and keep the tiles of that launch
+ * if no other solve or ensemble run of the process is in progress on the device, and keep the tiles of that launch
  * where its passes run as launches (concurrent solves, ensembles, timed handles);
  * the record below then is that of the passes a handle uses after nf_set_tiles.
  * nf_set_autotune: 2 (the default) times each candidate's throughput with three

@@ -33,6 +33,9 @@ hipError_t poll_event(hipEvent_t e) {
   }
 }
 
+static std::atomic<int> loops_on[64];
+LoopCount::LoopCount(int dev) : n(loops_on[dev >= 0 && dev < 64 ? dev : 0]), alone(n.fetch_add(1) == 0) {}
+
 }  // namespace nf
 
 namespace {
@@ -111,18 +114,6 @@ void chip_init(nf_grid* g) {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess) cus = 0;
   g->chip_loop = g->chip_shape.G <= cus;
 }
-
-// PCG loops in progress per device.  A team over the chip leaves no room for others,
-// so a loop runs as one only if it starts alone; loops on several streams run as
-// launches, which overlap (the results are the same either way).
-constexpr int MAX_DEV = 64;
-std::atomic<int> loops_on[MAX_DEV];
-struct LoopCount {
-  std::atomic<int>& n;
-  bool alone;
-  explicit LoopCount(int dev) : n(loops_on[dev >= 0 && dev < MAX_DEV ? dev : 0]), alone(n.fetch_add(1) == 0) {}
-  ~LoopCount() { n.fetch_sub(1); }
-};
 
 int check_launch(nf_grid* g, hipError_t e, const char* what) {
   if (e != hipSuccess) return fail(g, NF_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));

@@ -875,6 +875,8 @@ int nf_batch_run(nf_batch* b, const nf_params* prm, double dt, int64_t steps, do
     if (!(prm[i].gamma > 0.0) || !(prm[i].c2 >= 0.0) || !(prm[i].D2 >= 0.0))
       return invalid("invalid params of instance " + std::to_string(i));
   }
+  // handles that solve meanwhile leave the compute units to launches
+  const LoopCount busy(b->inst[0]->device);
   if (b->nparts == 0) {
     const int rc = parts_tune(b, prm, dt, m, p, r, S, rtol, max_iter);
     if (rc != NF_OK) return rc;

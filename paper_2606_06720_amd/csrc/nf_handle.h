@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -77,6 +78,18 @@ struct nf_grid {
 };
 
 namespace nf {
+// PCG loops in progress per device, a running ensemble as one of them.  A team over the
+// chip leaves no room for others, so a loop runs as one only if it starts alone;
+// loops on several streams run as launches, which overlap (the results are the same
+// either way).
+struct LoopCount {
+  std::atomic<int>& n;
+  const bool alone;
+  explicit LoopCount(int dev);
+  ~LoopCount() { n.fetch_sub(1); }
+  LoopCount(const LoopCount&) = delete;
+  LoopCount& operator=(const LoopCount&) = delete;
+};
 // Wait for an event of a polling loop: query it, block after about a millisecond.
 hipError_t poll_event(hipEvent_t e);
 // Set the handle's tile variants for its grid shape and real type: from the

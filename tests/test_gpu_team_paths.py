@@ -7,6 +7,9 @@ up is forced from the host by a launch with too few workgroups, at the start of 
 loop and where a loop of more than 4096 iterations goes on from one team launch to the
 next.  A handle that times a kernel runs launches only and gives the expected bits."""
 
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -151,3 +154,39 @@ def test_misses_do_not_end_the_use_of_teams(n):
         assert torch.equal(p, want)
         did, p = go()
         assert did["formed"] == 1 and torch.equal(p, want)
+
+
+def test_no_team_over_the_chip_beside_an_ensemble():
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    m, r, S = fields((512, 256), 9)
+    shapes = [(64, 64), (128, 64)]
+    data = [fields(n, 20 + i) for i, n in enumerate(shapes)]
+    with NF.Grid((512, 256), (2.0, 1.0)) as g, NF.Batch(shapes) as b:
+        b.set_partitions(1)
+        _, want = solve(g, m, r, S, rtol=1e-10)
+        assert g.team()["formed"] == 1
+
+        def ensemble():
+            with torch.cuda.stream(torch.cuda.Stream()):
+                b.run([(25.0, 1e-3, 0.75)] * 2, 1e-3, 1500, [d[0].abs() for d in data],
+                      [torch.zeros_like(d[1]) for d in data], [d[1] for d in data], [d[2] for d in data])
+
+        torch.cuda.synchronize()
+        th = threading.Thread(target=ensemble)
+        th.start()
+        t0 = time.time()
+        while g.team()["as_launches"] == 0 and time.time() - t0 < 1.0:
+            _, p = solve(g, m, r, S, rtol=1e-10)
+        before = g.team()
+        for _ in range(10):
+            _, p = solve(g, m, r, S, rtol=1e-10)
+            assert torch.equal(p, want)
+        after, alive = g.team(), th.is_alive()
+        th.join()
+        assert alive, "the ensemble ended before the solves"
+        assert after["as_launches"] == before["as_launches"] + 10 and after["formed"] == before["formed"]
+        _, p = solve(g, m, r, S, rtol=1e-10)
+        assert torch.equal(p, want) and g.team()["formed"] == after["formed"] + 1
