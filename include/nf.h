@@ -426,7 +426,11 @@ int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
  * nf_team_force: conditions for tests of the paths above, which ordinary use does
  *   not reach at will.  NF_FORCE_MISS: of the handle's team launches from now on,
  *   those with index at .. at + count - 1 (from 0) have too few workgroups, so that
- *   they give up.  NF_EINVAL for another `what` or negative numbers.
+ *   they give up.  NF_FORCE_LOSE: in iteration `at` (from 0) of the next team launch's
+ *   loop the members but the first stop waiting for the others at the barrier after
+ *   the column pass, as after a wait of seconds (count is not used).  A member that
+ *   stops waiting makes the call NF_EDEVICE.  NF_EINVAL for another `what` or
+ *   negative numbers.
  */
 typedef struct {
   int kind;            /* 0: no team, 1: on one XCD, 2: over the chip */
@@ -436,7 +440,7 @@ typedef struct {
   int64_t as_launches; /* loops that ran as launches without a try */
   int pause;           /* loops left before the next try, after misses */
 } nf_team_info;
-enum { NF_FORCE_MISS = 0 };
+enum { NF_FORCE_MISS = 0, NF_FORCE_LOSE = 1 };
 int nf_team(const nf_grid *g, nf_team_info *out);
 int nf_team_force(nf_grid *g, int what, int at, int count);
 

@@ -251,10 +251,13 @@ int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_it
     if (*it > 0) LCHK(g, launch_team_reset(go.a.g, s));
     go.miss = g->force_miss_count > 0 && g->force_miss_at-- <= 0;
     if (go.miss) --g->force_miss_count;
+    go.ts.lose = g->force_lose;
+    g->force_lose = 0;
     LCHK(g, g->chip_loop ? launch_chip(f32, go, s) : launch_team(f32, go, s));
     g->team_shape.epoch += 2 * (unsigned)go.nk + 4;
     int rc = read_status(g, fin);
     if (rc) return rc;
+    if (fin->lost) return fail(g, NF_EDEVICE, "a member of the team was lost");
     if (fin->team != TEAM_NONE) {
       ++g->team_formed;
       g->team_missed = 0;
@@ -264,7 +267,6 @@ int team_loop(nf_grid* g, bool f32, const double* m, const double* r, int max_it
       *done = true;
       return NF_OK;
     }
-    if (fin->team == TEAM_LOST) return fail(g, NF_EDEVICE, "a member of the team was lost");
     if (fin->team != TEAM_MORE) {
       ++g->team_gave_up;
       if (++g->team_missed >= 2) {
@@ -912,7 +914,12 @@ int nf_team(const nf_grid* g, nf_team_info* out) {
 
 int nf_team_force(nf_grid* g, int what, int at, int count) {
   if (!g) return NF_EINVAL;
-  if (what != NF_FORCE_MISS || at < 0 || count < 0) return fail(g, NF_EINVAL, "unknown condition or negative number");
+  if ((what != NF_FORCE_MISS && what != NF_FORCE_LOSE) || at < 0 || count < 0)
+    return fail(g, NF_EINVAL, "unknown condition or negative number");
+  if (what == NF_FORCE_LOSE) {
+    g->force_lose = at + 1;
+    return NF_OK;
+  }
   g->force_miss_at = at;
   g->force_miss_count = count;
   return NF_OK;

@@ -536,10 +536,12 @@ __device__ __forceinline__ bool chip_wait(__amdgpu_buffer_rsrc_t slots, int o, u
   return false;
 }
 // Q launched tiles per member, NTL threads of the launched pass that adds the sums up,
-// XCD whether the tiles' places are those of xcd_block.
+// XCD whether the tiles' places are those of xcd_block, quit whether a member but the
+// first leaves without the totals.
 template <int NT, int K, int Q, int NTL, bool XCD>
 __device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int member, int ntiles, unsigned epoch,
-                                          const double (&v)[K], double scale, double* sh, double& own, double (&tot)[K]) {
+                                          const double (&v)[K], double scale, double* sh, double& own, double (&tot)[K],
+                                          bool quit = false) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63;
   sh += (epoch & 1) * (chip_red(NT) / 2);
@@ -588,7 +590,7 @@ __device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int memb
     return true;
   }
   if (threadIdx.x < 64) {
-    const bool ok = chip_wait(slots, (pub + (member & 7) * 8 + lane % K) * 16, epoch, w);
+    const bool ok = !quit && chip_wait(slots, (pub + (member & 7) * 8 + lane % K) * 16, epoch, w);
     if (lane < K) all[lane] = w.d[0];
     if (lane == 0) okp[0] = ok ? 1.0 : 0.0;
   }
@@ -607,7 +609,7 @@ __device__ __forceinline__ bool chip_meet(__amdgpu_buffer_rsrc_t slots, int memb
 // A kernel per grid shape: one that switches between the lengths inside the loop
 // keeps address and wavenumber terms of all of them and spills at 512 threads.
 template <typename T, int NX, int NY>
-__global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned epoch, cx<T>* M0, cx<T>* M1,
+__global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned epoch, int lose, cx<T>* M0, cx<T>* M1,
                                                                const T* __restrict__ m, const T* __restrict__ r,
                                                                cx<T>* xh, cx<T>* rh, cx<T>* dh, cx<T>* sh, int it0,
                                                                int nk, int max_iter, double tol2) {
@@ -705,7 +707,8 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
     double ps[2] = {0.0, 0.0}, pt[2];
     chip_col<T, NX, NY>(S, buf, xs, xh, g, upper ? hi : lo, kx0, (T)q.alpha, (T)q.beta, it == 0, q.stop,
                         ps, t);
-    if (!chip_meet<NT, 2, SC, NT / SR, false>(slots, member, cs.ncol * SC, ++epoch, ps, 1.0, red, own, pt)) {
+    if (!chip_meet<NT, 2, SC, NT / SR, false>(slots, member, cs.ncol * SC, ++epoch, ps, 1.0, red, own, pt,
+                                                   it + 1 == lose)) {
       outcome = TEAM_LOST;
       break;
     }
@@ -739,6 +742,7 @@ __global__ void __launch_bounds__(chip_threads(NX, NY)) k_chip(Geo g, unsigned e
       if (tid < 2 * SC && member < cs.ncol) slot_ptr(g.part, SLOT_RR)[tid % 2 * MAX_WG + member * SC + tid / 2] = own;
     }
   }
+  if (outcome == TEAM_LOST && threadIdx.x == 0) st->lost = 1;
   if (member == 0 && threadIdx.x == 0) {
     st->iters = it;
     st->rr[0] = rr;
@@ -761,7 +765,7 @@ static hipError_t chip_pair(const TeamGo& go, hipStream_t s) {
     typedef cx<T> V;
     const FluxArgs& f = go.f;
     const IterArgs& a = go.a;
-    hipLaunchKernelGGL((k_chip<T, NX, NY>), dim3(chip_split(NX, NY).G - (go.miss ? 1 : 0)), dim3(chip_threads(NX, NY)), 0, s, a.g, go.ts.epoch,
+    hipLaunchKernelGGL((k_chip<T, NX, NY>), dim3(chip_split(NX, NY).G - (go.miss ? 1 : 0)), dim3(chip_threads(NX, NY)), 0, s, a.g, go.ts.epoch, go.ts.lose,
                        (V*)a.M0, (V*)a.M1, (const T*)f.m, (const T*)f.r, (V*)a.xh, (V*)a.rh, (V*)a.dh, (V*)a.sh, go.it,
                        go.nk, go.max_iter, go.tol2);
     return hipGetLastError();

@@ -72,6 +72,7 @@ struct nf_grid {
   int team_missed = 0, team_skip = 0, team_pause = nf::TEAM_PAUSE_MIN;
   int64_t team_formed = 0, team_gave_up = 0, team_untried = 0;  // nf_team
   int force_miss_at = 0, force_miss_count = 0;                  // nf_team_force: team launches from now on
+  int force_lose = 0;                                           // iteration + 1, 0: none
   // team over the chip (nf_chip.hpp): whether the loop runs as one, and its split
   bool chip_loop = false;
   nf::ChipShape chip_shape{};

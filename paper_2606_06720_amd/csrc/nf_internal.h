@@ -28,10 +28,12 @@ struct DevStatus {
   int outer_done;   // mixed-precision solve: 1 once the FP64 residual test has ended it
   int itot;         // mixed-precision solve: FP32 iterations of the finished corrections
   int budget;       // iteration limit of the current (inner) PCG run, INT_MAX when unused
-  int team;         // outcome of the last team launch (TEAM_*), TEAM_NONE if no team ran
+  int team;         // outcome of the last team launch (TEAM_*) at its first member, TEAM_NONE if no team ran
+  int lost;         // 1 if any member of it stopped waiting at a barrier: its part of x is then missing,
+                    // whatever the others found
 };
 // what a team launch left (DevStatus::team): more iterations to do, stopped by
-// max_iter, stopped by the residual test, a member was lost
+// max_iter, stopped by the residual test, a wait given up
 enum { TEAM_NONE = 0, TEAM_MORE = 1, TEAM_STOP = 2, TEAM_CONV = 3, TEAM_LOST = 4 };
 // formation of a team (TeamCtl::state)
 enum { TEAM_OPEN = 0, TEAM_GO = 1, TEAM_ABORT = 2 };
@@ -59,6 +61,7 @@ constexpr int team_lds(int nt) { return nt == 64 ? 672 : (nt == 128 ? 1120 : (nt
 struct TeamShape {
   int G, C, lr, nt, xcc;
   unsigned epoch;
+  int lose;  // iteration + 1 in which the members but the first stop waiting (tests; 0: none)
 };
 // The team over the chip (nf_chip.hpp): members at most, launched tiles at most; its barrier's
 // 16-byte entries (two sets of two per tile, two sets of eight published lines), which

@@ -50,6 +50,7 @@ __device__ __forceinline__ void k_status_reset_one(DevStatus* st, int full) {
     st->iters = 0;
     st->flags = 0;
     st->team = TEAM_NONE;
+    st->lost = 0;
   }
 }
 // open the formation of the team a loop start may be followed by
@@ -58,6 +59,7 @@ __device__ __forceinline__ void team_open(const Geo& g) {
   ((TeamCtl*)g.team)->tickets = 0;
   ((TeamCtl*)g.team)->state = TEAM_OPEN;
   g.st->team = TEAM_NONE;
+  g.st->lost = 0;
 }
 
 __global__ void k_status_reset(DevStatus* st, int full) {

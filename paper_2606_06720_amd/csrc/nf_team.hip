@@ -39,6 +39,7 @@ bool team_shape(const Geo& g, TeamShape* ts) {
 __global__ void k_team_reset(DevStatus* st, TeamCtl* ctl) {
   if (threadIdx.x == 0) {
     st->team = TEAM_NONE;
+    st->lost = 0;
     ctl->tickets = 0;
     ctl->state = TEAM_OPEN;
   }

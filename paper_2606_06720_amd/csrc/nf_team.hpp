@@ -27,7 +27,8 @@
 // members see the same outcome.  After ABORT (workgroups of other kernels kept
 // members from becoming resident) nothing has been written.  After GO every
 // member is resident and runs the same control flow, so every later wait ends;
-// a wait of TEAM_WAIT_S seconds would end the kernel with an error all the same.
+// a wait of TEAM_WAIT_S seconds would end the kernel with an error all the same (any
+// member records it: the others may have passed the last barrier).
 //
 // The same passes also exist as launches of their own (team_row_phase,
 // team_col_phase, G workgroups per instance), which ensembles and handles whose
@@ -408,10 +409,11 @@ __device__ __forceinline__ void team_col(TeamState<T>& st, cx<T>* buf, const Geo
 // Barrier of the team with K partial sums (per-thread parts in v): every member
 // gets the totals, added in the same order, so their decisions agree.  Slots
 // alternate between two sets: a member overwrites a set only after the barrier
-// in between, which the slowest reader of that set has then passed.
+// in between, which the slowest reader of that set has then passed.  quit: announce
+// the arrival, but do not wait.
 template <int NT, int K>
 __device__ __forceinline__ bool team_barrier(__amdgpu_buffer_rsrc_t slots, int role, int G, unsigned epoch,
-                                             const double (&v)[K], double* sh, double (&tot)[K]) {
+                                             const double (&v)[K], double* sh, double (&tot)[K], bool quit = false) {
   constexpr int NW = NT / 64;
   wave_sums<K>(v, sh);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -435,7 +437,8 @@ __device__ __forceinline__ bool team_barrier(__amdgpu_buffer_rsrc_t slots, int r
     const int lane = threadIdx.x;
     const unsigned long long t0 = wall_clock64();
     bool ok = false;
-    double got[K];
+    double got[K] = {};
+    const unsigned want = quit ? ~epoch : epoch;
     for (unsigned q = 0;; ++q) {
       asm volatile("" ::: "memory");
       bool mine = true;
@@ -447,13 +450,13 @@ __device__ __forceinline__ bool team_barrier(__amdgpu_buffer_rsrc_t slots, int r
         } w;
         w.u = __builtin_amdgcn_raw_buffer_load_b128(slots, (set + (lane < G ? lane : 0) * 2 + k) * 16, 0, TEAM_SC1);
         got[k] = lane < G ? w.d[0] : 0.0;
-        mine = mine && w.u.z == epoch;
+        mine = mine && w.u.z == want;
       }
       if (__all(mine)) {
         ok = true;
         break;
       }
-      if ((q & 255) == 255 && wall_clock64() - t0 > (unsigned long long)(TEAM_WAIT_S * 1e8)) break;
+      if ((q & 255) == 255 && (quit || wall_clock64() - t0 > (unsigned long long)(TEAM_WAIT_S * 1e8))) break;
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) got[k] = wave_sum(got[k]);
@@ -844,7 +847,7 @@ __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<
       NF_TEAM_NY(ny, M_)
 #undef M_
     }
-    if (!team_barrier<NT, 2>(slots, role, G, ++epoch, ps, red, pt)) {
+    if (!team_barrier<NT, 2>(slots, role, G, ++epoch, ps, red, pt, it + 1 == ts.lose && role != 0)) {
       outcome = TEAM_LOST;
       break;
     }
@@ -881,6 +884,7 @@ __global__ void __launch_bounds__(NT) k_team(Geo g, TeamShape ts, cx<T>* M0, cx<
     }
     if (outcome == TEAM_MORE) team_grad<NT, true>(S, sh, h, ny, y0, R);
   }
+  if (outcome == TEAM_LOST && tid == 0) st->lost = 1;
   if (role == 0 && tid == 0) {
     st->iters = it;
     st->rr[0] = rr;

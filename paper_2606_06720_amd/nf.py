@@ -36,6 +36,7 @@ NF_KERNEL_ROW_FLUX = 0
 NF_KERNEL_COL_DIV = 1
 NF_KERNEL_COL_UPDATE = 2
 NF_FORCE_MISS = 0
+NF_FORCE_LOSE = 1
 
 _CODES = {
     NF_EINVAL: "NF_EINVAL",

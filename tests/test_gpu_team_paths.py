@@ -156,6 +156,27 @@ def test_misses_do_not_end_the_use_of_teams(n):
         assert did["formed"] == 1 and torch.equal(p, want)
 
 
+@pytest.mark.parametrize("n", [(8, 8), (64, 64), (256, 256), (512, 256), (1024, 1024)])
+def test_member_that_stops_waiting_at_the_last_barrier(n):
+    # the first member passes that barrier and finds the solve stopped; the others have
+    # left without their part of the solution
+    import torch
+
+    from paper_2606_06720_amd import nf as NF
+
+    m, r, S = fields(n, 10)
+    for dtype in (NF.NF_F64, NF.NF_F32_REFINED):
+        with NF.Grid(n, box(n), dtype=dtype) as g:
+            info, want = solve(g, m, r, S, rtol=1e-10, max_iter=5)
+            assert info.iters == 5
+            g.team_force(NF.NF_FORCE_LOSE, 4)
+            with pytest.raises(NF.NfError) as e:
+                solve(g, m, r, S, rtol=1e-10, max_iter=5)
+            assert e.value.code == NF.NF_EDEVICE
+            info, p = solve(g, m, r, S, rtol=1e-10, max_iter=5)
+            assert info.iters == 5 and torch.equal(p, want)
+
+
 def test_no_team_over_the_chip_beside_an_ensemble():
     import torch
 
