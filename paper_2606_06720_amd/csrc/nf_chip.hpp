@@ -160,19 +160,6 @@ __device__ __forceinline__ void chip_fft(cx<T>* buf, const cx<T> (&wt)[CHIP_TW],
   }
 }
 
-// What a thread keeps for the whole loop (EP elements of a field): the vectors
-// and symbols of its spectral elements; in FP32 the gradient of d at its grid-point
-// pairs instead of s (see grad_rec).  (x and, for its grid-point pairs, m and r
-// stay in LDS: in registers they made the members of 512 FP64 threads spill.)
-template <typename T, int EP>
-struct ChipState {
-  cx<T> r[EP], d[EP], s[grad_rec<T>() ? 1 : EP];
-  cx<T> gx[grad_rec<T>() ? EP : 1], gy[grad_rec<T>() ? EP : 1];
-  T sig[EP];
-  cx<T> wr[CHIP_TW], wc[CHIP_TW], wp[EP];  // twiddles of its row and column transforms and pairs
-  int go, li, t;  // place of its first column element in the exchange buffer and in LDS, that element's row tile
-};
-
 // The thread index as a value the compiler cannot follow: otherwise it hoists the
 // addresses of all the lengths out of the loop, keeps the twiddles of a forward
 // transform for the inverse one, and spills.
@@ -227,11 +214,48 @@ constexpr bool chip_big(int c) { return wide_elems(c) > 1024; }
 // Element i of a thread in the pointwise phases: that of the launched tiles, SUB of
 // which share the N elements of the member; at least N if there is none.
 template <int NT, int SUB, int N>
-__device__ __forceinline__ int chip_elem(int tid, int i) {
+__host__ __device__ constexpr int chip_elem(int tid, int i) {
   constexpr int NS = NT / SUB, M = N / SUB;
   const int p = tid % NS + i * NS;
   return SUB == 1 ? p : (p < M ? tid / NS * M + p : N);
 }
+// Task t of a row tile at element `base` (its first row times Nx/2) covers the entries k
+// and pair_mirror(k) of one line; the first is element base + t of the lower exchange
+// buffer, this is the other one's place in the upper.
+template <int H, int R>
+__host__ __device__ constexpr int chip_hi(int base, int t) {
+  return base + ((pair_mirror(t / (2 * R), H) - H / 2) * 2 + (t / R & 1)) * R + t % R;
+}
+// Exchange image of a column tile: the 2 C R elements of a row tile are
+// consecutive lanes (row, field, column), as many row tiles at a time as fit the
+// threads; later ones follow at a fixed stride.  Of thread tid: the row tile of its
+// first element (beyond all if it has none), that element's place in the exchange
+// buffer of the tile's half and in LDS.
+struct ChipPlace {
+  int t, go, li;
+};
+template <int NX, int NY>
+__host__ __device__ constexpr ChipPlace chip_place(int kx0, int tid) {
+  constexpr int NT = wide_threads(chip_split(NX, NY).wide), R = chip_split(NX, NY).R, NC = chip_split(NX, NY).C;
+  constexpr int H = NX / 2, LS = chip_ls(NY, NC), w = 2 * NC * R, h2 = H / 2;
+  const int rr = tid % R, f = tid / R & 1, c = tid % w / (2 * R);
+  const int k0 = kx0 >= h2 ? kx0 - h2 : kx0;
+  return ChipPlace{tid < NT / w * w && kx0 < H ? tid / w : INT_MAX / 2, tid / w * R * H + ((k0 + c) * 2 + f) * R + rr,
+                   (f * NC + c) * LS + tid / w * R + rr};
+}
+// What a thread keeps for the whole loop (EP elements of a field): the vectors
+// and symbols of its spectral elements; in FP32 the gradient of d at its grid-point
+// pairs instead of s (see grad_rec).  (x and, for its grid-point pairs, m and r
+// stay in LDS: in registers they made the members of 512 FP64 threads spill.)
+template <typename T, int EP>
+struct ChipState {
+  cx<T> r[EP], d[EP], s[grad_rec<T>() ? 1 : EP];
+  cx<T> gx[grad_rec<T>() ? EP : 1], gy[grad_rec<T>() ? EP : 1];
+  T sig[EP];
+  cx<T> wr[CHIP_TW], wc[CHIP_TW], wp[EP];  // twiddles of its row and column transforms and pairs
+  ChipPlace at;  // of its first element of the exchange image
+};
+
 template <typename T, int NX, int CL, int R>
 __device__ __forceinline__ void chip_row_setup(ChipState<T, wide_elems(CL) / wide_threads(CL)>& st, cx<T>* ms, const Geo& g,
                                                const T* __restrict__ m, const T* __restrict__ r, int y0, int tid) {
@@ -253,24 +277,14 @@ __device__ __forceinline__ void chip_row_setup(ChipState<T, wide_elems(CL) / wid
 }
 template <typename T, int NX, int NY>
 __device__ __forceinline__ void chip_col_setup(ChipState<T, chip_ep(NX, NY)>& st, const Geo& g, const double* K, int kx0, int tid) {
-  constexpr int CL = chip_split(NX, NY).wide, NT = wide_threads(CL), R = chip_split(NX, NY).R, H = NX / 2;
-  constexpr int NC = chip_split(NX, NY).C;
-  constexpr int LS = chip_ls(NY, NC);
+  constexpr int CL = chip_split(NX, NY).wide, NT = wide_threads(CL), NC = chip_split(NX, NY).C;
 #pragma unroll
   for (int i = 0; i < chip_ep(NX, NY); ++i) {
     const int p = chip_elem<NT, chip_sc(CL), NC * NY>(tid, i);
     st.sig[i] = (T)precond_symbol_inv(K, xi_col(kx0 + p / NY, g.lx), xi_tilde(p % NY, NY, g.ly));
   }
   chip_tw_load<T, NY, 2 * NC, NT>(st.wc, (const cx<T>*)g.tw, g.twn, tid);
-  // Exchange image of a column tile: the 2 C R elements of a row tile are
-  // consecutive lanes (row, field, column), as many row tiles at a time as fit the
-  // threads; later ones follow at a fixed stride.
-  constexpr int w = 2 * NC * R, h2 = H / 2;
-  const int rr = tid % R, f = tid / R & 1, c = tid % w / (2 * R);
-  const int k0 = kx0 >= h2 ? kx0 - h2 : kx0;
-  st.t = tid < NT / w * w && kx0 < H ? tid / w : INT_MAX / 2;
-  st.go = tid / w * R * H + ((k0 + c) * 2 + f) * R + rr;
-  st.li = (f * NC + c) * LS + tid / w * R + rr;
+  st.at = chip_place<NX, NY>(kx0, tid);
 }
 
 // The gradient of d at a thread's grid-point pairs (FP32), from and to its buffer
@@ -325,7 +339,7 @@ __device__ __forceinline__ double chip_row(ChipState<T, chip_ep(NX, NY)>& st, cx
         b[i] = src[(size_t)pair_mirror(k, H) * ny];
       } else {
         a[i] = team_load(lo, base + t, (V*)nullptr);
-        b[i] = team_load(hi, base + ((pair_mirror(k, H) - H / 2) * 2 + f) * R + rr, (V*)nullptr);
+        b[i] = team_load(hi, chip_hi<H, R>(base, t), (V*)nullptr);
       }
     }
   }
@@ -389,7 +403,7 @@ __device__ __forceinline__ double chip_row(ChipState<T, chip_ep(NX, NY)>& st, cx
     if (t >= NTK || !on) continue;
     const int rr = t % R, f = t / R & 1, k = t / (2 * R);
     const V* l = buf + (f * R + rr) * LS;
-    const int oh = base + ((pair_mirror(k, H) - H / 2) * 2 + f) * R + rr;
+    const int oh = chip_hi<H, R>(base, t);
     if (k == 0) {
       const V z0 = l[0];
       chip_store(lo, base + t, mk<T>(z0.x + z0.y, z0.x - z0.y));
@@ -427,10 +441,10 @@ __device__ __forceinline__ void chip_col(ChipState<T, chip_ep(NX, NY)>& st, cx<T
   V f[2 * EP];
 #pragma unroll
   for (int i = 0; i < 2 * EP; ++i)
-    if (st.t + i * dt < cs.nrow) f[i] = team_load(ex, st.go + i * dg, (V*)nullptr);
+    if (st.at.t + i * dt < cs.nrow) f[i] = team_load(ex, st.at.go + i * dg, (V*)nullptr);
 #pragma unroll
   for (int i = 0; i < 2 * EP; ++i)
-    if (st.t + i * dt < cs.nrow) buf[st.li + i * dl] = f[i];
+    if (st.at.t + i * dt < cs.nrow) buf[st.at.li + i * dl] = f[i];
   __syncthreads();
   chip_fft<T, -1, NY, 2 * NC, LS, NT>(buf, st.wc, tw, g.twn, tid);
   ps[0] = ps[1] = 0.0;
@@ -492,7 +506,7 @@ __device__ __forceinline__ void chip_col(ChipState<T, chip_ep(NX, NY)>& st, cx<T
   chip_fft<T, +1, NY, 2 * NC, LS, NT>(buf, st.wc, tw, g.twn, tid);
 #pragma unroll
   for (int i = 0; i < 2 * EP; ++i)
-    if (st.t + i * dt < cs.nrow) chip_store(ex, st.go + i * dg, buf[st.li + i * dl]);
+    if (st.at.t + i * dt < cs.nrow) chip_store(ex, st.at.go + i * dg, buf[st.at.li + i * dl]);
   update_x();
 }
 template <typename T, int NY, int NC, int NT>
