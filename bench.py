@@ -391,6 +391,12 @@ def precision_form(sizes, steps, warmup=3):
             "sizes": out}
 
 
+def tiles_in_use(g):
+    """Tiles of the passes a handle's PCG loop runs as launches (nf_team)."""
+    t = g.team()
+    return {k: t[k] for k in ("row_rows", "row_threads", "col_cols", "col_threads")}
+
+
 def ensemble_cost(steps, check_steps=20, mix=None):
     """The ensemble of independent instances (grid mix as given) advanced by one
     batch (nf_batch_run), FP64 and FP32-refined: `steps` timed steps from m0,
@@ -450,11 +456,13 @@ def ensemble_cost(steps, check_steps=20, mix=None):
         for g in gs:
             g.close()
         # the tile variants the tuner chose for each grid shape (a handle of an
-        # already tuned shape reads them from the process-wide choice)
-        variants = {}
+        # already tuned shape reads them from the process-wide choice), and the tiles
+        # that an ensemble's loop runs, which are other ones where the shape has a team
+        variants, in_use = {}, {}
         for N_, _ in (mix or W.ENSEMBLE_MIX):
             with NF.Grid((N_, N_), dtype=dt_) as gq:
                 variants["%d^2" % N_] = gq.tuning()
+                in_use["%d^2" % N_] = tiles_in_use(gq)
         progress("ensemble %s: batch %.3g grid-point-steps/s" % (name, npts * steps / tb))
         out[name] = {
             "batch_grid_point_steps_per_s": npts * steps / tb,
@@ -468,6 +476,7 @@ def ensemble_cost(steps, check_steps=20, mix=None):
             "partitions": parts,
             "tuning_ms_two_steps_by_partition_count": [round(t, 2) for t in tune_ms],
             "tile_variants": variants,
+            "tiles_in_use": in_use,
         }
         del mc, pc, ms2, ps2
         torch.cuda.empty_cache()
@@ -650,10 +659,12 @@ def main():
         "step_achieved": step_bytes / elapsed / 1e9,
         "step_frac": step_bytes / elapsed / 1e9 / HBM_PEAK_GBS,
     }
-    # context: the tuner's throughput of the chosen operator-middle tile, one launch per
-    # interval when three run concurrently on separate buffers (as the three streams do)
+    # context: the tuner's throughput of the operator-middle tile in use, if it is the one the
+    # tuner chose, one launch per interval when three run concurrently on separate buffers (as the three streams do)
     tun = inst[0]["g"].tuning()
-    if args.kernel == "row_flux" and tun.get("tuned") and tun["us"][0] > 0:
+    use = tiles_in_use(inst[0]["g"])
+    same = (tun["flux_rows"], tun["flux_threads"]) == (use["row_rows"], use["row_threads"])
+    if args.kernel == "row_flux" and tun.get("tuned") and tun["us"][0] > 0 and same:
         roofline["three_stream_throughput_us"] = tun["us"][0]
         roofline["frac_three_stream_throughput"] = alg_bytes / (tun["us"][0] * 1e-6) / 1e9 / HBM_PEAK_GBS
     finite = all(torch.isfinite(it["m"]).all().item() for it in inst)
@@ -700,6 +711,8 @@ def main():
         "single_instance": single,
         # tile variants of the PCG loop chosen by the tuner for the 1024^2 FP64 handles
         "tile_variants": inst[0]["g"].tuning(),
+        # the tiles their loop runs as launches
+        "tiles_in_use": use,
     }
     progress("headline done: %.4g grid-point-steps/s, %.3f ms per step" % (value, 1e3 * elapsed / args.steps))
     if args.adjoint_steps > 0:

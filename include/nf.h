@@ -360,11 +360,13 @@ const char *nf_batch_last_error(const nf_batch *b);
  * of that shape use the same choice, so their results agree bit for bit.
  * The variants change the work split and the rounding of the transforms and
  * inner products only.
- * Grids of 65537 to 1048576 points whose tiles divide them (all powers of two with
+ * The record is that of the tuned passes.  Handles of the grids with a team (see
+ * nf_team, which reports the tiles in use) run them only after nf_set_tiles:
+ * grids of up to 65536 points (Nx <= 2048, Ny <= 1024), and
+ * grids of 65537 to 1048576 points whose tiles divide them (all powers of two with
  * Nx from 128 to 2048 and Ny from 64 to 1024 among them) run the loop as one launch
  * if no other solve or ensemble run of the process is in progress on the device, and keep the tiles of that launch
- * where its passes run as launches (concurrent solves, ensembles, timed handles);
- * the record below then is that of the passes a handle uses after nf_set_tiles.
+ * where its passes run as launches (concurrent solves, ensembles, timed handles).
  * nf_set_autotune: 2 (the default) times each candidate's throughput with three
  *   concurrent launches on separate buffers on grids of 2^19 to 2^21 points
  *   (the choice for solves that share the GPU, as ensemble partitions and
@@ -422,7 +424,8 @@ int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
  * After two such misses in a row the handle's next 64 loops run as launches before
  * a team is tried again (twice as many after the next miss, up to 4096).
  * nf_team: how the loops of a handle have run (a refined solve runs one loop per
- *   correction).  NF_EINVAL for NULL.
+ *   correction), and the tiles of its passes as launches (2D; 0 in 3D).  NF_EINVAL
+ *   for NULL.
  * nf_team_force: conditions for tests of the paths above, which ordinary use does
  *   not reach at will.  NF_FORCE_MISS: of the handle's team launches from now on,
  *   those with index at .. at + count - 1 (from 0) have too few workgroups, so that
@@ -439,6 +442,8 @@ typedef struct {
   int64_t missed;      /* team launches that gave up */
   int64_t as_launches; /* loops that ran as launches without a try */
   int pause;           /* loops left before the next try, after misses */
+  int row_rows, row_threads;  /* row pass: grid rows and threads per workgroup */
+  int col_cols, col_threads;  /* column pass: spectral columns and threads per workgroup */
 } nf_team_info;
 enum { NF_FORCE_MISS = 0, NF_FORCE_LOSE = 1 };
 int nf_team(const nf_grid *g, nf_team_info *out);

@@ -909,6 +909,20 @@ int nf_team(const nf_grid* g, nf_team_info* out) {
   out->missed = g->team_gave_up;
   out->as_launches = g->team_untried;
   out->pause = g->team_skip;
+  out->row_rows = out->row_threads = out->col_cols = out->col_threads = 0;
+  if (g->team_on) {
+    out->row_rows = 1 << g->team_shape.lr;
+    out->col_cols = g->team_shape.C;
+    out->row_threads = out->col_threads = g->team_shape.nt;
+  } else if (g->dim == 2) {
+    const bool f32 = g->dtype == NF_F32_REFINED;
+    const Geo& G = f32 ? g->geo32 : g->geo;
+    const int rv = use_rv(G, f32, 0), cv = use_cv(G, f32);
+    out->row_rows = flux_var_rows(G, rv);
+    out->row_threads = flux_var_threads(G, rv);
+    out->col_cols = div_var_cols(G, cv);
+    out->col_threads = div_var_threads(G, cv);
+  }
   return NF_OK;
 }
 

@@ -1152,6 +1152,7 @@ int flux_var_rows(const Geo& g, int rv) {
 int flux_var_plan(int rv) { return rv >= RV_SMALL ? 0 : rv_plan(rv); }
 int flux_var_threads(const Geo& g, int rv) {
   const int rt = rv == VAR_DEFAULT ? row_tile(g.nx, 2) : rv_rows(g.nx, rv) * (g.nx / 2);
+  if (rv >= RV_WIDE) return wide_threads(rv - RV_WIDE);
   if (rv >= RV_SEQ) return rv_rows(g.nx, rv) * (g.nx / 2) / 8;
   if (rv >= RV_SMALL) return small_threads(rv_rows(g.nx, rv), g.nx / 2);
   const int nt = (rt / 8) * 2 > 1024 ? 1024 : (rt / 8) * 2;

@@ -84,7 +84,9 @@ class nf_tuning_info(ctypes.Structure):
 
 class nf_team_info(ctypes.Structure):
     _fields_ = [("kind", ctypes.c_int), ("members", ctypes.c_int), ("formed", ctypes.c_int64),
-                ("missed", ctypes.c_int64), ("as_launches", ctypes.c_int64), ("pause", ctypes.c_int)]
+                ("missed", ctypes.c_int64), ("as_launches", ctypes.c_int64), ("pause", ctypes.c_int),
+                ("row_rows", ctypes.c_int), ("row_threads", ctypes.c_int), ("col_cols", ctypes.c_int),
+                ("col_threads", ctypes.c_int)]
 
 
 def _load():

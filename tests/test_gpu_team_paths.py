@@ -70,6 +70,25 @@ def test_form_of_the_loop(n):
             assert g.team()["formed"] == t["formed"]  # timed handles run launches
 
 
+# row pass (rows, threads) and column pass (columns, threads) as launches, FP64
+TILES = [((64, 64), (2, 64, 1, 64)), ((256, 256), (8, 512, 4, 512)), ((512, 512), (2, 256, 1, 256)),
+         ((256, 512), (4, 256, 1, 256)), ((1024, 1024), (4, 512, 1, 256))]
+
+
+@pytest.mark.parametrize("n,want", TILES)
+def test_tiles_in_use(n, want):
+    from paper_2606_06720_amd import nf as NF
+
+    with NF.Grid(n) as g:
+        t = g.team()
+        assert tuple(t[k] for k in ("row_rows", "row_threads", "col_cols", "col_threads")) == want
+        g.set_tiles(1, 1, 1)  # the untuned passes from here on
+        t, tun = g.team(), g.tuning()
+        assert t["kind"] == 0
+        assert t["row_rows"] == tun["flux_rows"] and t["col_cols"] == tun["update_cols"]
+        assert t["row_threads"] == tun["flux_threads"] and t["col_threads"] == tun["update_threads"]
+
+
 @pytest.mark.parametrize("n", [(64, 64), (512, 256), (1024, 1024)])
 def test_formation_that_gives_up(n):
     import torch
