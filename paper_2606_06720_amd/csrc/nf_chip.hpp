@@ -1,15 +1,17 @@
-// The whole PCG loop of a mid-size 2D grid (65537 points to about a million) in one launch over the chip, one workgroup per compute unit.
+// The whole PCG loop of a mid-size 2D grid (65537 points to about a million) in one
+// launch over the chip, one workgroup per compute unit.
 //
-// As two launches per iteration such a grid's loop costs two kernel boundaries,
-// reads and writes x, r, d, s, m and r of every point, and forms the preconditioner
-// anew.  Here the tiles of the two passes of nf_loop.hpp stay with one workgroup for
-// the whole loop: r, d, s of its columns, symbols and twiddles in registers, x and m,
-// r of its rows in LDS (tiles of 2048 elements leave x and r in the L2), and only the
-// two mixed fields move between the passes, 64 instead of 152 bytes per point and
-// iteration.  The L2s of the XCDs meet in the Infinity Cache, so the fields are
-// stored and loaded with sc1 (past the L2); invalidating the L2s instead and loading
-// through them measured 2 to 3 times slower.  A round of store, barrier and load over
-// 256 workgroups takes 3.7 us for 512^2 and 6.3 us for 1024^2, the barrier alone 1.7.
+// As two launches per iteration such a grid's loop costs two kernel boundaries, reads
+// and writes x, r, d, s, m and r of every point, and forms the preconditioner anew.
+// Here the tiles of the two passes of nf_loop.hpp stay with one workgroup for the
+// whole loop: r, d, s of its columns (FP32: instead of s the gradient of d on its
+// rows), symbols and twiddles in registers, x and m, r of its rows in LDS (tiles of
+// 2048 elements leave x and r in the L2), and only the two mixed fields move between
+// the passes, 64 instead of 152 bytes per point and iteration.  The L2s of the XCDs
+// meet in the Infinity Cache, so the fields are stored and loaded with sc1 (past the
+// L2); invalidating the L2s instead and loading through them measured 2 to 3 times
+// slower.  A round of store, barrier and load over 256 workgroups takes 3.7 us for
+// 512^2 and 6.3 us for 1024^2, the barrier alone 1.7.
 // Measured per solve, launches -> team (same box): 400^2 2.27 -> 1.58 ms, 512^2 2.26 ->
 // 1.41, 1024x512 3.44 -> 1.81, 800^2 4.17 -> 3.34, 1024^2 4.40 -> 3.44; FP32-refined
 // 512x1024 3.01 -> 1.89, 1024^2 4.77 -> 2.94.  Of an iteration of 512^2 (32000 cycles)
@@ -17,13 +19,13 @@
 // bound by the barrier's round trips and, on the larger tiles, by LDS traffic and the
 // few registers that are left.
 //
-// A team takes all compute units, so a loop is one launch only if no other loop is in
-// progress on the device; concurrent loops overlap better as launches (three 512^2
-// handles: 1.21e9 grid-point steps per second with this rule, 1.16e9 with the tuned
-// launches; three 1024^2 handles: 1.69e9 with teams, 2.1e9 as launches).
+// A team takes all compute units, so a loop is one launch only if no other loop or
+// ensemble is in progress on the device; concurrent loops overlap better as launches
+// (three 512^2 handles: 1.21e9 grid-point steps per second with this rule, 1.16e9 with
+// the tuned launches; three 1024^2 handles: 1.69e9 with teams, 2.1e9 as launches).
 //
-// Exchange layout: [row tile][kx][field][row] in the buffers of d and A d, which the
-// loop keeps in registers; kx below Nx/4 in the first, the others in the second, so
+// Exchange layout: [row tile][kx][field][row] in the buffers of d and A d (FP32: the
+// first half of that of the gradient), which the loop keeps in registers; kx below Nx/4 in the first, the others in the second, so
 // that the two members of a real-transform pair come from one buffer each.  A row
 // pass reads and writes one contiguous block per buffer, a column pass runs of 2 C
 // rows.  Every pass writes where it has read: with a second layout for the
@@ -40,7 +42,8 @@
 //
 // Formation is that of nf_team.hpp: all members draw tickets; the last one turns
 // OPEN to GO, a member that waited CHIP_FORM_MS turns it to ABORT.  After GO all
-// members are running, so every wait below ends.
+// members are running, so every wait below ends; it is bounded all the same, and a
+// member that gives one up records that the loop is lost.
 #pragma once
 
 #include <hip/hip_runtime.h>

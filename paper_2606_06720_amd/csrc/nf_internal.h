@@ -78,14 +78,14 @@ enum { FLAG_NONFINITE = 1, FLAG_INCOMPAT = 2 };
 // Slots of the partial-sum area; each slot holds up to SLOT_K arrays of
 // MAX_WG doubles.
 enum {
-  SLOT_P3 = 0,      // 2D: <z, A z> of z = M^-1 r (and CHIP_SLOTS from its second array on); 3D: <d,q>, <q,M^-1 r>, <q,M^-1 q>, <r,M^-1 r>
+  SLOT_P3 = 0,      // delta of the PCG loop (nf_loop.hpp); 2D: also CHIP_SLOTS, from its second array on
   SLOT_P3INIT = 1,  // <r,M^-1 r>, <r,r>, <b,b>
   SLOT_KBAR = 2,    // sum mx^2, mx my, my^2, r
   SLOT_SCHK = 3,    // sum S, sum |S|
   SLOT_DM = 4,      // sum (m_new - m_old)^2, sum m_old^2
   SLOT_EPT = 5,     // sum r|g|^2, sum (m.g)^2, sum |m|^{2 gamma}
   SLOT_EGM = 6,     // sum w |xi|^2 |m_hat|^2 (both components)
-  SLOT_RR = 7,      // ||r||^2 of the residual written by the last PCG update (2D: and <r, M^-1 r>)
+  SLOT_RR = 7,      // ||r||^2 and <r, M^-1 r> of the residual that the last iteration of the loop left
   NSLOTS = 8,
   SLOT_K = 8,
   MAX_WG = 4096,

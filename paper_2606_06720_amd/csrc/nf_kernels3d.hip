@@ -16,9 +16,10 @@
 // factors of the separable heat kernel, whose x factor is applied in the row
 // pass before the planes are mixed.
 // Inner products use the weights of the 2D path (1 on slot 0, 2 elsewhere).
-// Reductions: every workgroup stores its block sums as partials and a
-// one-workgroup pass launched right after the producing pass adds them in
-// index order (deterministic) into the totals (see store_partials).
+// Reductions: every workgroup stores its block sums as partials, which are added
+// in index order (deterministic) into the totals: by block 0 of the y pass that
+// follows in the PCG loop (k3_ypass), elsewhere by a one-workgroup pass launched
+// right after the producing pass (see store_partials).
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -53,12 +54,11 @@ __device__ __forceinline__ double precond3_inv(const double* K, double a, double
 // ---------------------------------------------------------------- z tiles
 // A z tile holds 2 * TILE elements per field: at Nz = 256 that is 8 lines, so
 // the strided gathers and scatters move 128-byte runs (full cache lines).
-template <int NZ, int NF, int ES = 16, int TW = 1>
+template <int NZ, int NF, int TW = 1>
 struct ZCfg {
-  static constexpr int W = ES == 8 ? 2 : 1;
-  static constexpr int C0 = 2 * TILE * W / NZ;
+  static constexpr int C0 = 2 * TILE / NZ;
   static constexpr int C = C0 < 1 ? 1 : (C0 > 64 ? 64 : C0);  // lines (kx, ky) per workgroup
-  static constexpr int NT = TPF * NF * W * TW;  // TW: extra thread multiple (same lines)
+  static constexpr int NT = TPF * NF * TW;  // TW: extra thread multiple (same lines)
   static constexpr int LS = lpad_use(NZ) ? lpad_len(NZ) : NZ + 1;  // room for the FFT's padded layout
   static constexpr int CN = C * NZ;
   static constexpr int NB = NF * C;
@@ -77,10 +77,10 @@ __device__ __forceinline__ V* pick4w(int f, V* a, V* b, V* c, V* d) {
 
 // gathered image: element e -> field e / CN, line (e % CN) % C, z (e % CN) / C;
 // consecutive threads read consecutive ky of one z (coalesced runs of C)
-template <int NZ, int NF, int NFL, typename V, int ES = 16, int TW = 1>
-__device__ __forceinline__ void zT_gload(V (&v)[(ZCfg<NZ, NF, ES, TW>::ET)], const V* s0, const same<V>* s1,
+template <int NZ, int NF, int NFL, typename V, int TW = 1>
+__device__ __forceinline__ void zT_gload(V (&v)[(ZCfg<NZ, NF, TW>::ET)], const V* s0, const same<V>* s1,
                                          const same<V>* s2, const same<V>* s3, int lam0, int nlam, int ny) {
-  using C = ZCfg<NZ, NF, ES, TW>;
+  using C = ZCfg<NZ, NF, TW>;
 #pragma unroll
   for (int i = 0; i < C::ET; ++i) {
     const int e = threadIdx.x + i * C::NT;
@@ -95,9 +95,9 @@ __device__ __forceinline__ void zT_gload(V (&v)[(ZCfg<NZ, NF, ES, TW>::ET)], con
     v[i] = x;
   }
 }
-template <int NZ, int NF, int NFL, typename V, int ES = 16, int TW = 1>
-__device__ __forceinline__ void zT_put(V* buf, const V (&v)[(ZCfg<NZ, NF, ES, TW>::ET)]) {
-  using C = ZCfg<NZ, NF, ES, TW>;
+template <int NZ, int NF, int NFL, typename V, int TW = 1>
+__device__ __forceinline__ void zT_put(V* buf, const V (&v)[(ZCfg<NZ, NF, TW>::ET)]) {
+  using C = ZCfg<NZ, NF, TW>;
 #pragma unroll
   for (int i = 0; i < C::ET; ++i) {
     const int e = threadIdx.x + i * C::NT;
@@ -105,10 +105,10 @@ __device__ __forceinline__ void zT_put(V* buf, const V (&v)[(ZCfg<NZ, NF, ES, TW
     if (e < NFL * C::CN) buf[(f * C::C + ee % C::C) * C::LS + ee / C::C] = v[i];
   }
 }
-template <int NZ, int NF, int NFS, typename V, int ES = 16, int TW = 1>
+template <int NZ, int NF, int NFS, typename V, int TW = 1>
 __device__ __forceinline__ void zT_store(const V* buf, same<V>* d0, same<V>* d1, same<V>* d2, same<V>* d3, int lam0,
                                          int nlam, int ny) {
-  using C = ZCfg<NZ, NF, ES, TW>;
+  using C = ZCfg<NZ, NF, TW>;
   for (int e = threadIdx.x; e < NFS * C::CN; e += C::NT) {
     const int f = e / C::CN, ee = e % C::CN;
     const int c = ee % C::C, z = ee / C::C;
@@ -120,9 +120,9 @@ __device__ __forceinline__ void zT_store(const V* buf, same<V>* d0, same<V>* d1,
   }
 }
 // contiguous spectral image of one field: p -> line p / NZ, kz = p % NZ
-template <int NZ, int NF, typename V, int ES = 16, int TW = 1>
-__device__ __forceinline__ void zP_gload(V (&v)[(ZCfg<NZ, NF, ES, TW>::EP)], const V* __restrict__ src, int lam0, int nlam) {
-  using C = ZCfg<NZ, NF, ES, TW>;
+template <int NZ, int NF, typename V, int TW = 1>
+__device__ __forceinline__ void zP_gload(V (&v)[(ZCfg<NZ, NF, TW>::EP)], const V* __restrict__ src, int lam0, int nlam) {
+  using C = ZCfg<NZ, NF, TW>;
 #pragma unroll
   for (int i = 0; i < C::EP; ++i) {
     const int p = threadIdx.x + i * C::NT;
@@ -132,10 +132,10 @@ __device__ __forceinline__ void zP_gload(V (&v)[(ZCfg<NZ, NF, ES, TW>::EP)], con
 }
 
 // gradient multipliers i xi_c v / n of one spectral value into lines f0..f0+2
-template <int NZ, int NF, typename T, int ES = 16, int TW = 1>
+template <int NZ, int NF, typename T, int TW = 1>
 __device__ __forceinline__ void put_grad3(cx<T>* buf, int f0, int c, int kz, const cx<T> v, double xx, double yy,
                                           double zz, double inv_n) {
-  using C = ZCfg<NZ, NF, ES, TW>;
+  using C = ZCfg<NZ, NF, TW>;
   const T sx = (T)(xx * inv_n), sy = (T)(yy * inv_n), sz = (T)(zz * inv_n);
   buf[(f0 * C::C + c) * C::LS + kz] = mk<T>(-sx * v.y, sx * v.x);
   buf[((f0 + 1) * C::C + c) * C::LS + kz] = mk<T>(-sy * v.y, sy * v.x);
@@ -206,8 +206,8 @@ __global__ void __launch_bounds__(TPF) k3_row_c2r(Geo g, const cd* __restrict__ 
 // Tile of the operator middle: 128-byte runs through the mixed layout (8 rows of
 // FP64 values, 16 of FP32), with at least 512 and at most TILE (FP64) or
 // 2 TILE (FP32) elements per field, i.e. the same LDS in both precisions.  With
-// TILE elements in both, the FP32 pass moved 64-byte runs at Nx = 256 and took
-// 123 us at 256 x 256 x 128 instead of 113 us.
+// TILE elements in both, the FP32 pass moved 64-byte runs at Nx = 256 (256 x 256 x
+// 128: 123 instead of 113 us; 141 us since it also keeps the gradient of d).
 template <int NX, typename T>
 struct Flux3 {
   static constexpr int H = NX / 2;
@@ -651,10 +651,10 @@ __global__ void __launch_bounds__((MODE == 1 ? 1 : (MODE == 2 ? 3 : 4)) * TPF)
 // Twice the threads of the tile (its 111 KB of LDS at Nz = 256 admit one
 // workgroup per compute unit: 12 waves rather than 6).
 template <int NZ, bool INIT>
-__global__ void __launch_bounds__((ZCfg<NZ, 3, 16, 2>::NT))
+__global__ void __launch_bounds__((ZCfg<NZ, 3, 2>::NT))
     k3_zdiv(Geo g, const cd* F0, const cd* F1, const cd* F2, cd* __restrict__ qh, cd* rh, const cd* __restrict__ bh) {
-  constexpr int ES = 16, TW = 2;
-  using C = ZCfg<NZ, 3, ES, TW>;
+  constexpr int TW = 2;
+  using C = ZCfg<NZ, 3, TW>;
   using V = cd;
   if (INIT && g.st->outer_done != 0) return;
   __shared__ V buf[C::NB * C::LS];
@@ -664,9 +664,9 @@ __global__ void __launch_bounds__((ZCfg<NZ, 3, 16, 2>::NT))
   const int nlam = g.h * g.ny;
   const int lam0 = xcd_block() * C::C;
   V tv[C::ET], av[C::EP];
-  zT_gload<NZ, 3, 3, V, ES, TW>(tv, F0, F1, F2, nullptr, lam0, nlam, g.ny);
+  zT_gload<NZ, 3, 3, V, TW>(tv, F0, F1, F2, nullptr, lam0, nlam, g.ny);
   if (INIT) {
-    zP_gload<NZ, 3, V, ES, TW>(av, bh, lam0, nlam);
+    zP_gload<NZ, 3, V, TW>(av, bh, lam0, nlam);
     if (threadIdx.x == 0) {
       const double* kb = g.tot + SLOT_KBAR * SLOT_K;
       const double* sc = g.tot + SLOT_SCHK * SLOT_K;
@@ -683,7 +683,7 @@ __global__ void __launch_bounds__((ZCfg<NZ, 3, 16, 2>::NT))
       }
     }
   }
-  zT_put<NZ, 3, 3, V, ES, TW>(buf, tv);
+  zT_put<NZ, 3, 3, V, TW>(buf, tv);
   __syncthreads();
   lds_fft<double, -1, NZ, C::NB, C::LS, C::NT>(buf, tw, g.twn);
   double s[3] = {0.0, 0.0, 0.0};

@@ -5,9 +5,9 @@
 // the status and partial sums of the pass before, a tile of a few KB through a
 // handful of LDS stages.  Here a team of at most 32 workgroups on ONE XCD, a
 // workgroup per compute unit, runs the iterations of nf_loop.hpp with x, r, d,
-// s (FP32: the gradient of d), m and r of its columns and rows on chip.  Only the two mixed fields
-// move between the passes, through that XCD's L2, and the passes meet at a
-// barrier that carries the partial sums.  A store-barrier-load round of 32
+// s (FP32: the gradient of d), m and r of its columns and rows on chip.  Only the
+// two mixed fields move between the passes, through that XCD's L2, and the passes
+// meet at a barrier that carries the partial sums.  A store-barrier-load round of 32
 // workgroups takes 0.84 us on one XCD (1.8 us over all XCDs, whose L2s meet in
 // the Infinity Cache); two kernel boundaries with their reloads cost most of the
 // 12 us of a 64^2 iteration.  Measured per iteration, launches -> team: 64^2 12

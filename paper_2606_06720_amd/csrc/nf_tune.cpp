@@ -13,7 +13,8 @@
 // timed alone.  The choice is made once per process for
 // each (Nx, Ny, real type) and cached, so every handle, ensemble and
 // allocation-free solve of that shape runs the same kernels (their results then
-// agree bit for bit).
+// agree bit for bit).  Grids with a one-launch loop (nf_team.hpp, nf_chip.hpp) have
+// tiles of their own and run the choice only after nf_set_tiles.
 #include <hip/hip_runtime.h>
 
 #include <climits>
