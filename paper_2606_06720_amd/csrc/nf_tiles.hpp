@@ -508,22 +508,25 @@ __device__ __forceinline__ double precond_symbol_inv(const double* K, double xx,
 // the steepest descent direction.  Where it carries the gradient of d (FP32),
 // delta is the curvature of d itself.  Once gamma has left the normal range (an
 // rtol of 0 and thousands of iterations, or a tiny S) its ratios mean nothing: the
-// iterate stays as it is.
+// iterate stays as it is.  (All without branches, so that the loads of the pass that
+// waits for the scalars are not held back by the divisions.)
 template <typename T>
 constexpr bool grad_rec() { return sizeof(T) == 4; }
 __device__ __forceinline__ double pcg_beta(double ga, double ga_prev, bool first) {
-  return first || ga < DBL_MIN ? 0.0 : ga / ga_prev;
+  const double b = ga / ga_prev;
+  return first || ga < DBL_MIN ? 0.0 : b;
 }
 template <typename T>
 __device__ __forceinline__ double pcg_alpha(double ga, double de, double al_prev, bool first, double& beta) {
-  if (ga < DBL_MIN) return 0.0;
-  if constexpr (grad_rec<T>()) return ga / de;
-  double den = first ? de : de - beta * (ga / al_prev);
-  if (!first && den <= 0.0) {
-    beta = 0.0;
-    den = de;
+  double den = de;
+  if constexpr (!grad_rec<T>()) {
+    const double next = de - beta * (ga / al_prev);
+    const bool keep = !first && !(next <= 0.0);
+    den = keep ? next : de;
+    beta = keep ? beta : 0.0;
   }
-  return ga / den;
+  const double a = ga / den;
+  return ga < DBL_MIN ? 0.0 : a;
 }
 
 // Switch over the transform lengths of the 2D passes.
