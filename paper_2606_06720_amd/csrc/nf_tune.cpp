@@ -201,6 +201,11 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
   // a running solver state for the loop passes: no stop recorded
   TCHK(launch_status_reset(G, 1, s));
   TCHK(hipStreamSynchronize(s));
+  // the FP32 row pass is timed as iteration 1, which also reads the gradient of d (with
+  // beta = 0); its stopping test needs a residual
+  const int row_it = f32 ? 1 : 0;
+  if (f32) TCHK(launch_fill_doubles(slot_ptr(g->part, SLOT_RR), (size_t)MAX_WG, 1.0, s));
+  TCHK(hipStreamSynchronize(s));
   for (int pass = 0; pass < 2; ++pass) {
     if (pass == 1) {
       // totals that give the column pass finite, non-stopping PCG scalars
@@ -223,9 +228,9 @@ hipError_t run_tuning(nf_grid* g, bool f32, int nstreams, Choice* out) {
           TCHK(time_pass(ss, e0, e1, ej, [&](int k) {
             const TuneBufs& b = bufs[k];
             return f32 ? launch_row_flux32(G, b.M0, b.M1, (const float*)b.mr, (const float*)b.mr + 2 * n,
-                                           (float*)b.Q, 0, 0.0, ss[k])
-                       : launch_row_flux(G, b.M0, b.M1, (const double*)b.mr, (const double*)b.mr + 2 * n, 0,
-                                         nullptr, 0.0, ss[k]);
+                                           (float*)b.Q, row_it, 0.0, ss[k])
+                       : launch_row_flux(G, b.M0, b.M1, (const double*)b.mr, (const double*)b.mr + 2 * n,
+                                         row_it, nullptr, 0.0, ss[k]);
           }, &ms, clear, nclear));
         } else {
           G.var_upd[k32] = v;
