@@ -33,6 +33,9 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, public spec
 #   col_update: reads F_x, F_y (16), x, r, d, A d (32); writes x, r, d, A d (32)
 #               and grad_x, grad_y (16)
 KERNEL_BYTES_PER_POINT = {"row_flux": 56.0, "col_update": 96.0}
+# FP32 passes: row_flux also reads and writes the gradient of the search direction (2 x 4
+# each), col_update moves no A d
+KERNEL_BYTES_PER_POINT_F32 = {"row_flux": 28.0 + 16.0, "col_update": 48.0 - 8.0}
 KERNEL_IDS = {"row_flux": 0, "col_update": 2}
 # algorithmic bytes per grid point of the passes of one time step outside the
 # PCG loop: gradient of the warm start (24), initial operator apply (56 + 32),
@@ -305,10 +308,10 @@ def sampled_errors(gold, m, p):
     return out
 
 
-def loop_pass_spans(g, w, m, p, r, S, N, real_bytes, steps=10):
+def loop_pass_spans(g, w, m, p, r, S, N, per_point, steps=10):
     """Average execution span of each PCG-loop pass of handle g (stamped by the
     kernel on the device wall clock) over `steps` further time steps, with the
-    algorithmic bandwidth it gives (bytes per point scaled by real_bytes / 8)."""
+    algorithmic bandwidth it gives (bytes per point of each pass)."""
     out = {}
     for kname, kid in sorted(KERNEL_IDS.items(), key=lambda kv: kv[1]):
         g.time_kernel(kid)
@@ -318,7 +321,7 @@ def loop_pass_spans(g, w, m, p, r, S, N, real_bytes, steps=10):
         if not cnt:
             continue
         us = 1e3 * ms / cnt
-        gbs = KERNEL_BYTES_PER_POINT[kname] * real_bytes / 8.0 * N * N / (us * 1e-6) / 1e9
+        gbs = per_point[kname] * N * N / (us * 1e-6) / 1e9
         out[kname] = {"avg_launch_us": us, "launches": cnt, "achieved_GBs": gbs, "frac": gbs / HBM_PEAK_GBS}
     return out
 
@@ -363,8 +366,9 @@ def precision_form(sizes, steps, warmup=3):
                 if ndim == 2:
                     # the PCG-loop passes of this form, one at a time, over a few more steps:
                     # average execution span per launch (in-kernel stamps) against the
-                    # algorithmic bytes of the pass (half in the FP32 inner solve)
-                    res[name]["passes"] = loop_pass_spans(g, w, m, p, r, S, N, 8 if dt_ == NF.NF_F64 else 4)
+                    # algorithmic bytes of the pass
+                    per_point = KERNEL_BYTES_PER_POINT if dt_ == NF.NF_F64 else KERNEL_BYTES_PER_POINT_F32
+                    res[name]["passes"] = loop_pass_spans(g, w, m, p, r, S, N, per_point)
             progress("precision %d^%d %s: %.3f ms per step, vs oracle %s" % (N, ndim, name, 1e3 * t / steps, err))
             del m, r, S, p
             torch.cuda.empty_cache()
