@@ -360,13 +360,9 @@ const char *nf_batch_last_error(const nf_batch *b);
  * of that shape use the same choice, so their results agree bit for bit.
  * The variants change the work split and the rounding of the transforms and
  * inner products only.
- * The record is that of the tuned passes.  Handles of the grids with a team (see
- * nf_team, which reports the tiles in use) run them only after nf_set_tiles:
- * grids of up to 65536 points (Nx <= 2048, Ny <= 1024), and
- * grids of 65537 to 1048576 points whose tiles divide them (all powers of two with
- * Nx from 128 to 2048 and Ny from 64 to 1024 among them) run the loop as one launch
- * if no other solve or ensemble run of the process is in progress on the device, and keep the tiles of that launch
- * where its passes run as launches (concurrent solves, ensembles, timed handles).
+ * The record is that of the tuned passes.  Handles of grids with a team (see
+ * nf_team, which reports the tiles in use) have tiles of their own, also where
+ * their passes run as launches, and run the tuned ones only after nf_set_tiles.
  * nf_set_autotune: 2 (the default) times each candidate's throughput with three
  *   concurrent launches on separate buffers on grids of 2^19 to 2^21 points
  *   (the choice for solves that share the GPU, as ensemble partitions and
@@ -417,9 +413,12 @@ int nf_set_tiles(nf_grid *g, int flux_var, int div_var, int update_var);
 
 /*
  * One-launch PCG loops.  2D grids of up to 65536 points with Nx <= 2048 and Ny <= 1024
- * run the loop of a solve as one launch by a team of up to 32 workgroups on one XCD,
- * larger ones as described at nf_tuning by a team of up to 256 workgroups over the
- * chip.  A team whose workgroups do not all become resident within 5 ms gives up and
+ * run the loop of a solve as one launch by a team of up to 32 workgroups on one XCD.
+ * Grids of 65537 to 1048576 points whose tiles divide them (all powers of two with Nx
+ * from 128 to 2048 and Ny from 64 to 1024 among them) run it as one launch by a team
+ * of up to 256 workgroups over the chip, if no other solve or ensemble run of the
+ * process is in progress on the device.  Ensembles, timed handles (nf_time_kernel)
+ * and handles after nf_set_tiles run launches.  A team whose workgroups do not all become resident within 5 ms gives up and
  * the loop goes on as launches of the same passes: the results are bitwise the same.
  * After two such misses in a row the handle's next 64 loops run as launches before
  * a team is tried again (twice as many after the next miss, up to 4096).
