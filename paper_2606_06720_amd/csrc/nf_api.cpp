@@ -902,9 +902,8 @@ int nf_set_inner_tolerance(nf_grid* g, double floor_rtol) {
 
 int nf_team(const nf_grid* g, nf_team_info* out) {
   if (!g || !out) return NF_EINVAL;
-  const bool chip = !g->team_on && g->geo.wide >= 0;
-  out->kind = g->team_on ? 1 : (chip ? 2 : 0);
-  out->members = g->team_on ? g->team_shape.G : (chip ? g->chip_shape.G : 0);
+  out->kind = g->team_loop ? 1 : (g->chip_loop ? 2 : 0);
+  out->members = g->team_loop ? g->team_shape.G : (g->chip_loop ? g->chip_shape.G : 0);
   out->formed = g->team_formed;
   out->missed = g->team_gave_up;
   out->as_launches = g->team_untried;

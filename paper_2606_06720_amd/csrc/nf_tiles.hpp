@@ -508,20 +508,21 @@ __device__ __forceinline__ double precond_symbol_inv(const double* K, double xx,
 // the steepest descent direction.  Where it carries the gradient of d (FP32),
 // delta is the curvature of d itself.  Once gamma has left the normal range (an
 // rtol of 0 and thousands of iterations, or a tiny S) its ratios mean nothing: the
-// iterate stays as it is.  (All without branches, so that the loads of the pass that
+// iterate stays as it is (or, where a scaled FP32 residual starts there, the next
+// iteration starts anew).  (All without branches, so that the loads of the pass that
 // waits for the scalars are not held back by the divisions.)
 template <typename T>
 constexpr bool grad_rec() { return sizeof(T) == 4; }
 __device__ __forceinline__ double pcg_beta(double ga, double ga_prev, bool first) {
   const double b = ga / ga_prev;
-  return first || ga < DBL_MIN ? 0.0 : b;
+  return first || ga < DBL_MIN || ga_prev < DBL_MIN ? 0.0 : b;
 }
 template <typename T>
 __device__ __forceinline__ double pcg_alpha(double ga, double de, double al_prev, bool first, double& beta) {
   double den = de;
   if constexpr (!grad_rec<T>()) {
     const double next = de - beta * (ga / al_prev);
-    const bool keep = !first && !(next <= 0.0);
+    const bool keep = !first && beta > 0.0 && !(next <= 0.0);
     den = keep ? next : de;
     beta = keep ? beta : 0.0;
   }
