@@ -29,9 +29,8 @@
 // such a solve takes 60.3 instead of 55.8 ms at 4096^2 and 32.7 instead of 30.6 at
 // 256 x 256 x 128 (three textbook passes: 62.2 and 36.7).
 //
-// Measured per iteration, one
-// handle alone, three passes -> two (MI355X): 256^2 29.5 -> 20.6 us, 1024^2 55
-// -> 43.7 us, 4096^2 FP64 880 -> 770 us.
+// Measured per iteration, one handle alone, three passes -> two (MI355X): 256^2 29.5
+// -> 20.6 us, 1024^2 55 -> 43.7 us, 4096^2 FP64 880 -> 770 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
